@@ -163,8 +163,8 @@ int bca_plan_create(bca_plan** out, int device, uint32_t n_tensors, const uint64
 /* Attach the tensors.  Each argument is a HOST array of n_tensors DEVICE
  * pointers (grads[t] points to tensor_numel[t] values of the plan's gradient
  * type, the others to fp32).  Pointers of empty tensors may be NULL.  Pointers
- * must be aligned to their element size (BCA_ERR_ALIGN); 16-byte alignment
- * of all four arrays of a tensor lets the kernels use 128-bit accesses.  May
+ * must be aligned to their element size (BCA_ERR_ALIGN); the kernels use
+ * 128-bit accesses wherever the arrays start, so nothing more is needed.  May
  * be called again when the pointers change.  Synchronous (uploads the table). */
 int bca_plan_bind(bca_plan* plan, void* const* grads, float* const* params, float* const* exp_avg,
                   float* const* exp_avg_sq);

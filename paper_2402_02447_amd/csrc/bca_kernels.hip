@@ -16,9 +16,12 @@
 // Memory access: 128-bit loads/stores, lane-contiguous (a wavefront touches
 // 1 KiB per instruction per array), several independent loads in flight per
 // lane before first use, streaming (non-temporal) hints on data touched once.
-// A chunk whose arrays are not mutually 16-byte congruent falls back to
-// element-wise access.  No MFMA: nothing here is a contraction; the path is
-// bound by HBM bandwidth.
+// Arrays may start anywhere (gradients packed without padding next to aligned
+// parameters are common): vectors are accessed at element alignment.  With
+// gradients one element off their parameters' alignment the Adam sweep over 40 M
+// elements takes 178 us (element by element, as it was before: 254; aligned: 187)
+// and the fused step 196 us (243; 199).  No MFMA: nothing here is a contraction;
+// the path is bound by HBM bandwidth.
 //
 // Arithmetic follows the paper's definitions: clipping-by-norm (Sec. 2.3)
 // applied per bucket (Sec. 4.2, Alg. 1) and Adam (Alg. 1, last line; Kingma &
@@ -62,15 +65,42 @@ template <typename T>
 __device__ __forceinline__ BCA_GLOBAL T* as_global(T* p) {
   return (BCA_GLOBAL T*)p;
 }
+// A vector is accessed wherever its first element lies: gfx950 runs in unaligned access mode, so a 128-bit (64-bit)
+// access needs no more than its element's alignment, and telling the compiler so is all it takes to get the same
+// global_load_dwordx4 / dwordx2 as for aligned data.  A wavefront's access then touches one cache line more.
+template <typename T>
+struct Anywhere;
+template <>
+struct Anywhere<f32x4> {
+  typedef f32x4 type __attribute__((aligned(4)));
+};
+template <>
+struct Anywhere<f16x4> {
+  typedef f16x4 type __attribute__((aligned(2)));
+};
+template <>
+struct Anywhere<f16x8> {
+  typedef f16x8 type __attribute__((aligned(2)));
+};
+template <>
+struct Anywhere<u16x4> {
+  typedef u16x4 type __attribute__((aligned(2)));
+};
+template <>
+struct Anywhere<u16x8> {
+  typedef u16x8 type __attribute__((aligned(2)));
+};
 template <bool NT, typename T>
 __device__ __forceinline__ T ldv(const T* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(as_global(p));
-  else return *as_global(p);
+  typedef typename Anywhere<T>::type U;
+  if constexpr (NT) return __builtin_nontemporal_load((const BCA_GLOBAL U*)p);
+  else return *(const BCA_GLOBAL U*)p;
 }
 template <bool NT, typename T>
 __device__ __forceinline__ void stv(T* p, T x) {
-  if constexpr (NT) __builtin_nontemporal_store(x, as_global(p));
-  else *as_global(p) = x;
+  typedef typename Anywhere<T>::type U;
+  if constexpr (NT) __builtin_nontemporal_store(x, (BCA_GLOBAL U*)p);
+  else *(BCA_GLOBAL U*)p = x;
 }
 
 // ---- chunk table access -----------------------------------------------------------
@@ -250,18 +280,13 @@ struct Grad<BCA_GRAD_BF16> {
   }
 };
 
-// Number of leading elements to handle one by one so that what follows can be
-// accessed as aligned vectors (g in g_vec_bytes pieces, the fp32 arrays in 16-byte
-// pieces), or `len` if no such head exists (mutually incongruent addresses).
-__device__ __forceinline__ uint32_t vector_head(uint32_t len, uint64_t g_addr, uint32_t gsize, uint32_t g_vec_bytes,
-                                                bool with_state, uint64_t p, uint64_t m, uint64_t v) {
-  const uint32_t mis = (uint32_t)(g_addr & (g_vec_bytes - 1));
-  if (mis % gsize) return len;
-  const uint32_t h = ((g_vec_bytes - mis) & (g_vec_bytes - 1)) / gsize;
-  if (with_state) {
-    const uint64_t sh = (uint64_t)h * 4u;
-    if (((p + sh) | (m + sh) | (v + sh)) & 15u) return len;
-  }
+// LAMB's sweeps: elements to handle one by one so that the vectors that follow are 16-byte aligned in p, m and v
+// alike, where such a head exists (0 .. 3 elements).  Their cacheable moment stores suffer from lines written in two
+// parts: 40 M elements with all arrays one element off a 16-byte boundary take 275 us with the head and 290 without.
+// The Adam sweeps, whose stores stream, are better off without one (190 against 200 us on the same arrays).
+__device__ __forceinline__ uint32_t vector_head(uint32_t len, uint64_t p, uint64_t m, uint64_t v) {
+  if (((p ^ m) | (p ^ v)) & 15u) return 0;
+  const uint32_t h = (uint32_t)((16u - (p & 15u)) & 15u) / 4u;
   return h < len ? h : len;
 }
 
@@ -297,20 +322,17 @@ __device__ __forceinline__ void add_squares(const typename Grad<GDT>::wide& x, f
 template <int GDT, bool NT, uint32_t U = 8>  // U: 128-bit loads in flight per lane (the result does not depend on it)
 __device__ __forceinline__ double sqnorm_chunk(const Entry& en) {
   typedef Grad<GDT> G;
-  constexpr uint32_t gsize = sizeof(typename G::elem);
   constexpr uint32_t VE = G::VE;  // elements per 128-bit load: 4 (fp32) or 8 (fp16, bf16)
   const uint32_t tid = threadIdx.x;
   const uint64_t ga = en.g;
   const uint32_t len = en.len;
-  const uint32_t head = vector_head(len, ga, gsize, 16u, false, 0, 0, 0);
-  const uint32_t nvec = (len - head) / VE;
-  const uint32_t tail0 = head + nvec * VE;
+  const uint32_t nvec = len / VE;
+  const uint32_t tail0 = nvec * VE;
   const void* gbase = reinterpret_cast<const void*>(ga);
-  const void* gv = reinterpret_cast<const void*>(ga + (uint64_t)head * gsize);
   float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 
   typedef typename G::wide wide;
-  const wide* gw = reinterpret_cast<const wide*>(gv);
+  const wide* gw = reinterpret_cast<const wide*>(ga);
   // Lane t adds pieces t, t + 256, t + 512, ... in that order.  They are fetched U at a time; a slot past the end
   // of the chunk holds zeros, whose squares leave the (non-negative) accumulators as they are.
   for (uint32_t base = 0; base < nvec; base += kBlock * U) {
@@ -331,11 +353,7 @@ __device__ __forceinline__ double sqnorm_chunk(const Entry& en) {
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) add_squares<GDT>(x[u], a0, a1, a2, a3);
   }
-  // head and tail elements one by one (fewer than VE each unless the chunk is unaligned throughout)
-  for (uint32_t i = tid; i < head; i += kBlock) {
-    const float x = G::load1(gbase, i);
-    a0 = __fmaf_rn(x, x, a0);
-  }
+  // the last, fewer than VE, elements one by one
   for (uint32_t i = tail0 + tid; i < len; i += kBlock) {
     const float x = G::load1(gbase, i);
     a1 = __fmaf_rn(x, x, a1);
@@ -466,15 +484,11 @@ __global__ __launch_bounds__(kBlock) void k_coefs(uint32_t b0, uint32_t b1, cons
 template <int GDT, uint32_t U, bool NT>
 __device__ __forceinline__ void scale_chunk(const Entry& en, float coef) {
   typedef Grad<GDT> G;
-  constexpr uint32_t gsize = sizeof(typename G::elem);
   const uint32_t tid = threadIdx.x;
-  const uint64_t ga = en.g;
   const uint32_t len = en.len;
-  const uint32_t head = vector_head(len, ga, gsize, 4u * gsize, false, 0, 0, 0);
-  const uint32_t nvec = (len - head) / 4u;
-  const uint32_t tail0 = head + nvec * 4u;
-  void* gbase = reinterpret_cast<void*>(ga);
-  void* gv = reinterpret_cast<void*>(ga + (uint64_t)head * gsize);
+  const uint32_t nvec = len / 4u;
+  const uint32_t tail0 = nvec * 4u;
+  void* gv = reinterpret_cast<void*>(en.g);
   for (uint32_t base = 0; base < nvec; base += kBlock * U) {
     const uint32_t j0 = base + tid;
     if (base + kBlock * U <= nvec) {
@@ -491,8 +505,7 @@ __device__ __forceinline__ void scale_chunk(const Entry& en, float coef) {
       }
     }
   }
-  for (uint32_t i = tid; i < head; i += kBlock) G::store1(gbase, i, G::load1(gbase, i) * coef);
-  for (uint32_t i = tail0 + tid; i < len; i += kBlock) G::store1(gbase, i, G::load1(gbase, i) * coef);
+  for (uint32_t i = tail0 + tid; i < len; i += kBlock) G::store1(gv, i, G::load1(gv, i) * coef);
 }
 
 // Buckets with coef_b == 1 are not read at all.
@@ -573,20 +586,18 @@ __device__ __forceinline__ float chunk_wd(const Entry& en, const AdamK& k) {
 template <int GDT, bool FUSED, bool WB, uint32_t U, bool GNT>
 __device__ __forceinline__ void adam_chunk(const Entry& en, float coef, const AdamK& k) {
   typedef Grad<GDT> G;
-  constexpr uint32_t gsize = sizeof(typename G::elem);
   constexpr bool NT = true;
   const uint32_t tid = threadIdx.x;
   const uint64_t ga = en.g, pa = en.p, ma = en.m, va = en.v;
   const uint32_t len = en.len;
   const bool wb = WB && coef != 1.f;
   const float wd = chunk_wd(en, k);
-  const uint32_t head = vector_head(len, ga, gsize, 4u * gsize, true, pa, ma, va);
-  const uint32_t nvec = (len - head) / 4u;
-  const uint32_t tail0 = head + nvec * 4u;
-  void* gv = reinterpret_cast<void*>(ga + (uint64_t)head * gsize);
-  f32x4* pv = reinterpret_cast<f32x4*>(pa + (uint64_t)head * 4u);
-  f32x4* mv = reinterpret_cast<f32x4*>(ma + (uint64_t)head * 4u);
-  f32x4* vv = reinterpret_cast<f32x4*>(va + (uint64_t)head * 4u);
+  const uint32_t nvec = len / 4u;
+  const uint32_t tail0 = nvec * 4u;
+  void* gv = reinterpret_cast<void*>(ga);
+  f32x4* pv = reinterpret_cast<f32x4*>(pa);
+  f32x4* mv = reinterpret_cast<f32x4*>(ma);
+  f32x4* vv = reinterpret_cast<f32x4*>(va);
 
   for (uint32_t base = 0; base < nvec; base += kBlock * U) {
     const uint32_t j0 = base + tid;
@@ -622,18 +633,16 @@ __device__ __forceinline__ void adam_chunk(const Entry& en, float coef, const Ad
       }
     }
   }
-  // head and tail, element-wise
-  void* gbase = reinterpret_cast<void*>(ga);
+  // the last, fewer than four, elements
   BCA_GLOBAL float* p1 = as_global(reinterpret_cast<float*>(pa));
   BCA_GLOBAL float* m1 = as_global(reinterpret_cast<float*>(ma));
   BCA_GLOBAL float* v1 = as_global(reinterpret_cast<float*>(va));
-  for (uint32_t r = tid; r < head + (len - tail0); r += kBlock) {
-    const uint32_t i = r < head ? r : tail0 + (r - head);
-    float g = G::load1(gbase, i), p = p1[i], m = m1[i], v = v1[i];
+  for (uint32_t i = tail0 + tid; i < len; i += kBlock) {
+    float g = G::load1(gv, i), p = p1[i], m = m1[i], v = v1[i];
     if constexpr (FUSED) g = g * coef;
     adam1(g, p, m, v, k, wd);
     p1[i] = p, m1[i] = m, v1[i] = v;
-    if (wb) G::store1(gbase, i, g);
+    if (wb) G::store1(gv, i, g);
   }
 }
 
@@ -685,7 +694,7 @@ __device__ __forceinline__ void lamb_moments_chunk(const Entry& en, float coef, 
   const bool wb = WB && coef != 1.f;
   const float wd = chunk_wd(en, k);
   const uint32_t len = en.len;
-  const uint32_t head = vector_head(len, en.g, gsize, 4u * gsize, true, en.p, en.m, en.v);
+  const uint32_t head = vector_head(len, en.p, en.m, en.v);
   const uint32_t nvec = (len - head) / 4u;
   const uint32_t tail0 = head + nvec * 4u;
   void* gv = reinterpret_cast<void*>(en.g + (uint64_t)head * gsize);
@@ -783,7 +792,7 @@ __global__ __launch_bounds__(kBlock) void k_lamb_update(const Chunk* __restrict_
     const float sc = scale[en.tensor];
     const float wd = chunk_wd(en, k);
     const uint32_t len = en.len;
-    const uint32_t head = vector_head(len, en.p, 4u, 16u, true, en.p, en.m, en.v);
+    const uint32_t head = vector_head(len, en.p, en.m, en.v);
     const uint32_t nvec = (len - head) / 4u;
     const uint32_t tail0 = head + nvec * 4u;
     f32x4* pv = reinterpret_cast<f32x4*>(en.p + (uint64_t)head * 4u);
@@ -1064,7 +1073,7 @@ __global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* _
   }
 }
 
-// g <- coef * g over one chunk of the squared-norm cut.  A full, 16-byte aligned chunk of kDefaultChunkNorm
+// g <- coef * g over one chunk of the squared-norm cut.  A full chunk of kDefaultChunkNorm
 // elements is fetched whole (every load in flight before the first store); anything else goes through scale_chunk.
 // Element by element the stored value is the same either way.
 template <int GDT>
@@ -1072,7 +1081,7 @@ __device__ __forceinline__ void scale_norm_chunk(const Entry& en, float coef) {
   typedef Grad<GDT> G;
   typedef typename G::wide wide;
   constexpr uint32_t R = kDefaultChunkNorm / (G::VE * kBlock);  // 128-bit pieces per lane: 16 (fp32) or 8 (16-bit types)
-  if (en.len == kDefaultChunkNorm && (en.g & 15u) == 0) {
+  if (en.len == kDefaultChunkNorm) {
     wide* gw = reinterpret_cast<wide*>(en.g);
     const uint32_t tid = threadIdx.x;
     wide x[R];
@@ -1189,17 +1198,20 @@ constexpr uint32_t kFlatHeaderBytes = 256;  // one float: the coefficient of a l
 constexpr size_t kFlatScratchBytes = kFlatHeaderBytes + (size_t)(kFlatMaxElems / kFlatChunkNorm) * kWaves * sizeof(double);
 static __device__ __align__(256) unsigned char scratch[kFlatScratchBytes];
 
-__device__ __forceinline__ Entry flat_entry(uint64_t g, uint64_t n, uint32_t chunk_elems, uint32_t gsize, uint32_t i) {
-  const uint64_t first = (uint64_t)i * chunk_elems;
+// n <= kFlatMaxElems fits in 32 bits.  The length is a 32-bit minimum on purpose: written as a select on a 64-bit
+// comparison, the compiler has been seen to take the wrong arm where it also branches on the length (the scalar unit
+// has no 64-bit less-than; the select came out reading a condition code that nobody had set).
+__device__ __forceinline__ Entry flat_entry(uint64_t g, uint32_t n, uint32_t chunk_elems, uint32_t gsize, uint32_t i) {
+  const uint32_t first = i * chunk_elems;
   Entry e;
-  e.g = g + first * gsize, e.p = 0, e.m = 0, e.v = 0;
-  e.len = (uint32_t)(n - first < chunk_elems ? n - first : chunk_elems);
+  e.g = g + (uint64_t)first * gsize, e.p = 0, e.m = 0, e.v = 0;
+  e.len = min(n - first, chunk_elems);
   e.bucket = 0, e.tensor = 0, e.flags = 0;
   return e;
 }
 
 template <int GDT>
-__global__ __launch_bounds__(kBlock) void k_flat_sqnorm(uint64_t g, uint64_t n, double* __restrict__ partials) {
+__global__ __launch_bounds__(kBlock) void k_flat_sqnorm(uint64_t g, uint32_t n, double* __restrict__ partials) {
   const Entry en = flat_entry(g, n, kFlatChunkNorm, sizeof(typename Grad<GDT>::elem), blockIdx.x);
   const double ws = sqnorm_chunk<GDT, false, 16>(en);  // cacheable loads: the scale pass reads the bucket again at once
   if ((threadIdx.x & 63u) == 0) partials[(uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6)] = ws;
@@ -1241,7 +1253,7 @@ __global__ __launch_bounds__(kBlock) void k_flat_finalize(const double* __restri
 // every workgroup derives norm and coefficient from the partial sums itself, as in k_clip_scale, and workgroup 0
 // writes the outputs; else the coefficient is read from there.  Then the chunk is scaled.
 template <int GDT>
-__global__ __launch_bounds__(kBlock) void k_flat_scale(uint64_t g, uint64_t n, uint32_t n_chunks,
+__global__ __launch_bounds__(kBlock) void k_flat_scale(uint64_t g, uint32_t n, uint32_t n_chunks,
                                                         const double* __restrict__ partials,
                                                         const float* __restrict__ threshold, float* norm_out,
                                                         float* coef_out, int32_t* status,
@@ -1499,7 +1511,7 @@ hipError_t launch_clip_flat(int device, int gdt, void* g, uint64_t n, const floa
   // call reads is written by an earlier kernel of this same call.
   if (n_norm != 0) {
     pick_gdt(gdt, [&](auto gd) {
-      hipLaunchKernelGGL((k_flat_sqnorm<decltype(gd)::value>), dim3(n_norm), dim3(kBlock), 0, stream, ga, n, partials);
+      hipLaunchKernelGGL((k_flat_sqnorm<decltype(gd)::value>), dim3(n_norm), dim3(kBlock), 0, stream, ga, (uint32_t)n, partials);
     });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1509,7 +1521,7 @@ hipError_t launch_clip_flat(int device, int gdt, void* g, uint64_t n, const floa
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   pick_gdt(gdt, [&](auto gd) {
-    hipLaunchKernelGGL((k_flat_scale<decltype(gd)::value>), dim3(std::max(n_norm, 1u)), dim3(kBlock), 0, stream, ga, n, n_norm,
+    hipLaunchKernelGGL((k_flat_scale<decltype(gd)::value>), dim3(std::max(n_norm, 1u)), dim3(kBlock), 0, stream, ga, (uint32_t)n, n_norm,
                        partials, threshold, norm, coef, status, large ? coef_header : nullptr);
   });
   return hipGetLastError();
