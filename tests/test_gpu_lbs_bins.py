@@ -1,0 +1,63 @@
+"""Load-balancing simulation: guide tables with cells that have to be searched, and strata sorted in bins of 64 lanes,
+trial by trial against the oracle."""
+import numpy as np
+import pytest
+
+import workloads as W
+from paper_2402_02447_amd import lbs
+from test_gpu_lbs import check, check_all
+
+pytestmark = pytest.mark.gpu
+
+CUM, ENDS = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END
+LOCAL = (lbs.LBS_LOCAL_RASTER, lbs.LBS_LOCAL_SNAKE)
+
+
+def _cum(hist):
+    return np.concatenate([[0], np.cumsum(hist)]).astype(np.uint32)
+
+
+# (gpus per node, local batch, quota): what of 64 / gpus_per_node rows the strata fill
+@pytest.mark.parametrize("gpn,batch,quota", [
+    (8, 16, [6, 3, 2, 5]), (4, 32, [12, 6, 4, 10]), (2, 44, [20, 12, 12, 0]),       # two bins, full
+    (8, 12, [6, 3, 2, 1]), (16, 7, [3, 2, 1, 1]), (8, 9, [0, 8, 0, 1]),                       # two bins, padded
+    (4, 16, [5, 2, 3, 6]), (8, 8, [3, 2, 1, 2]), (16, 4, [1, 1, 1, 1]), (1, 64, [16, 16, 16, 16]),  # one bin, full
+    (8, 5, [2, 1, 1, 1]), (1, 3, [1, 0, 1, 1]), (16, 1, [0, 0, 1, 0]),                        # one bin, padded
+    (8, 16, [9, 3, 2, 2]), (16, 16, [6, 3, 2, 5]), (8, 21, [7, 7, 7, 0]),                     # do not fit
+])
+def test_quotas_that_fit_in_bins_and_quotas_that_do_not(gpn, batch, quota):
+    batch = sum(quota)
+    for n_nodes in (1, 9, 67):     # fewer nodes than a wavefront takes at a time, and numbers it does not divide
+        for method in LOCAL:
+            check(CUM, ENDS, method, batch, gpn, gpn * n_nodes, quota, seed=31 * gpn + n_nodes, n=7, first=3)
+        check_all(CUM, ENDS, batch, gpn, gpn * n_nodes, quota, seed=17 * gpn + n_nodes, n=7, first=11)
+
+
+@pytest.mark.parametrize("kind", ["gaps", "spike", "rare_tail", "wide_strata", "one_length"])
+def test_histograms_whose_cells_have_to_be_searched(kind):
+    rng = np.random.default_rng(5)
+    ends, quota = (100, 300, 700, 1000), [3, 2, 1, 2]
+    if kind == "gaps":          # most lengths do not occur
+        hist = np.where(rng.random(1000) < 0.1, rng.integers(1, 9, 1000), 0)
+        hist[[50, 200, 500, 999]] = 3
+    elif kind == "spike":       # one length holds nearly everything
+        hist = np.ones(1000, np.int64)
+        hist[411] = 4_000_000
+    elif kind == "rare_tail":
+        hist = (1e6 / (1 + np.arange(1000.0)) ** 2 + 1).astype(np.int64)
+    elif kind == "wide_strata":  # more than 256 lengths in a stratum
+        hist, ends, quota = np.full(1000, 977), (1000,), [8]
+    else:
+        hist, ends, quota = np.zeros(1000, np.int64), (1000,), [8]
+        hist[999] = 5
+    for method in range(5):
+        check(_cum(hist), ends, method, 8, 8, 8 * 5, quota, seed=3, n=20)
+    check_all(_cum(hist), ends, 8, 8, 8 * 5, quota, seed=4, n=20)
+
+
+def test_largest_token_counts_in_sixteen_bits_and_beyond_and_a_single_gpu():
+    for max_len in (1023, 1024):    # 64 x 1023 fits in half a register, 64 x 1024 does not
+        hist = np.zeros(max_len, np.int64)
+        hist[-1] = 7
+        check_all(_cum(hist), (max_len,), 64, 1, 5, [64], seed=1, n=4)
+        check(_cum(hist), (max_len,), lbs.LBS_GLOBAL, 64, 1, 1, [64], seed=1, n=4)
