@@ -136,8 +136,9 @@ typedef struct bca_tuning {
                             items in the work list (their gradients must stay cached that long); 0: default */
   uint64_t lamb_group_elems; /* lamb_step: the tensors are swept in runs of consecutive tensors of at most this many
                             elements (a larger tensor is a run of its own), both sweeps of a run before the next run, so
-                            that the second sweep reads the moments from cache; 0: default (32 Mi); results do not
-                            depend on it                                                                        */
+                            that the second sweep reads the moments from cache; 0: default (32 Mi where lamb_step goes by
+                            runs; plans of some size go in one pass instead, which any other value turns off); results do
+                            not depend on it                                                                    */
 } bca_tuning;
 
 /* which chunk table an introspection call looks at */
@@ -194,7 +195,7 @@ uint32_t bca_plan_num_chunks(const bca_plan* plan, int table);
 /* For chunk i: tensor index, first element, length, bucket.  Any out pointer may be NULL. */
 int bca_plan_chunk_info(const bca_plan* plan, int table, uint32_t i, uint32_t* tensor, uint64_t* begin,
                         uint32_t* len, uint32_t* bucket);
-/* The runs of tensors in which lamb_step sweeps the plan (bca_tuning.lamb_group_elems): their number, and the
+/* The runs of tensors in which lamb_step sweeps the plan when it goes by runs (bca_tuning.lamb_group_elems): their number, and the
  * tensors [*first_tensor, *end_tensor) of run i (either pointer may be NULL).  Runs are consecutive and cover all
  * tensors.  BCA_ERR_RANGE for i out of range. */
 uint32_t bca_plan_num_lamb_runs(const bca_plan* plan);
@@ -292,12 +293,13 @@ int bucket_clip_adam(bca_plan* plan, const float* thresholds /*DEVICE [B]*/, con
  * lamb_step reads the gradients as stored.  bucket_clip_lamb first clips bucket by bucket
  * exactly as bucket_clip_adam does (thresholds, norms, coefs, status as there) and feeds
  * LAMB the scaled gradient formed in registers; flags: BCA_WRITE_BACK_GRADS only.
- * trust (DEVICE [n_tensors], may be NULL) receives the ratios.  Two sweeps over p, m, v:
- * moments + per-tensor sums, then the parameter update; lamb_step carries them out run by
- * run of tensors (bca_tuning.lamb_group_elems; results do not depend on the runs);
- * bucket_clip_lamb runs the squared norms and the first sweep as one pipelined launch, as
- * bucket_clip_adam does with Adam (separate launches under BCA_TUNE_MULTI_LAUNCH; same
- * results bit for bit). */
+ * trust (DEVICE [n_tensors], may be NULL) receives the ratios.  Plans of some size go in one
+ * pass over p, m, v: a launch that keeps p and u of a tensor on the chip until its ratio is
+ * known, every wait bounded as in bucket_clip_adam, and a small one behind it (tensors too large
+ * for that are swept twice).  Others take two sweeps: moments + per-tensor sums, then the
+ * parameter update; lamb_step run by run of tensors (bca_tuning.lamb_group_elems),
+ * bucket_clip_lamb with the squared norms and the first sweep as one pipelined launch
+ * (separate launches under BCA_TUNE_MULTI_LAUNCH).  Same results bit for bit either way. */
 int lamb_step(bca_plan* plan, const bca_adam* hp /*HOST*/, uint64_t step, float* trust /*DEVICE or NULL*/,
               void* stream);
 int bucket_clip_lamb(bca_plan* plan, const float* thresholds /*DEVICE [B]*/, const bca_adam* hp /*HOST*/,

@@ -247,6 +247,90 @@ void build_work(bca_plan* p) {
   }
 }
 
+// Items and work lists of LAMB in one pass (see k_lamb), for tables cut at kDefaultChunkApply.  `slots`: workgroups of
+// that kernel that are resident on the GPU at a time.
+//   An item is up to kLambItemChunks full chunks, or one short chunk.  Items are made in the order of the apply table (bucket
+// by bucket, as the segments lie), which is also the order in which they are worked on, so that a tensor's items
+// follow one another.
+void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& apply_to_lamb) {
+  const Table& A = p->apply_tab;
+  const uint64_t most = (uint64_t)slots * kLambHeldNum / kLambHeldDen;  // items of a tensor, for it to be held
+  uint64_t large_elems = 0, all_elems = 0;
+  for (const uint64_t n : p->tensor_numel) {
+    all_elems += n;
+    if (n / (kLambItemChunks * kDefaultChunkApply) > most) large_elems += n;
+  }
+  if (all_elems < kLambOnePassElems || large_elems > all_elems / 2) return;
+  p->lamb_items_of.assign(p->n_tensors, 0);
+  std::vector<uint32_t> first_item(p->n_tensors, 0), last_item(p->n_tensors, 0), group_end;
+  for (const auto& g : p->groups) {
+    for (uint32_t c = A.bucket_off[g.first]; c < A.bucket_off[g.second];) {
+      const ChunkInfo& head = A.chunks[c];
+      uint32_t n = 1;
+      while (head.len == kDefaultChunkApply && n < kLambItemChunks && c + n < A.bucket_off[g.second]) {
+        const ChunkInfo& x = A.chunks[c + n];
+        if (x.tensor != head.tensor || x.bucket != head.bucket || x.len != kDefaultChunkApply ||
+            x.begin != head.begin + (uint64_t)n * kDefaultChunkApply)
+          break;
+        ++n;
+      }
+      LambItem it = {};
+      it.first = apply_to_lamb[c], it.count = n, it.tensor = head.tensor, it.bucket = head.bucket;
+      const uint32_t index = (uint32_t)p->lamb_items.size();
+      if (p->lamb_items_of[it.tensor]++ == 0) first_item[it.tensor] = index;
+      last_item[it.tensor] = index;
+      p->lamb_items.push_back(it);
+      c += n;
+    }
+    group_end.push_back((uint32_t)p->lamb_items.size());
+  }
+  // Held: all of the tensor's items, and those between them, fit on the GPU at once with room to spare.
+  large_elems = 0;
+  for (uint32_t t = 0; t < p->n_tensors; ++t)
+    if (p->lamb_items_of[t] != 0 && (uint64_t)last_item[t] - first_item[t] + 1u > most) large_elems += p->tensor_numel[t];
+  if (large_elems > all_elems / 2) {
+    p->lamb_items.clear();
+    return;
+  }
+  // held items first, the others behind them: the order in which lamb_step works on them
+  std::vector<LambItem> sorted;
+  std::vector<uint32_t> place(p->lamb_items.size());
+  for (const bool held : {true, false}) {
+    if (!held) p->lamb_first_large = (uint32_t)sorted.size();
+    for (uint32_t i = 0; i < p->lamb_items.size(); ++i) {
+      LambItem it = p->lamb_items[i];
+      if (((uint64_t)last_item[it.tensor] - first_item[it.tensor] + 1u <= most) != held) continue;
+      if (held) it.flags |= kLambHeld;
+      // read again by the tail kernel: worth keeping cached unless it is more than a cache holds
+      else if (large_elems <= kLambGroupElems) it.flags |= kLambKeep;
+      it.items = p->lamb_items_of[it.tensor], it.lo = p->tensor_off[it.tensor], it.hi = p->tensor_off[it.tensor + 1];
+      place[i] = (uint32_t)sorted.size();
+      sorted.push_back(it);
+    }
+  }
+  p->lamb_items = std::move(sorted);
+  p->lamb_clip_work.clear();
+  // bucket_clip_lamb: the fused step's list with its Adam items replaced, group by group
+  size_t g = 0;
+  uint32_t next = 0;
+  for (size_t w = 0; w < p->work.size();) {
+    if (p->work[w] >> 30 != kItemAdam) {
+      p->lamb_clip_work.push_back(p->work[w++]);
+      continue;
+    }
+    // a block of Adam items is whole groups; which ones, its first and last chunk say
+    uint32_t end_chunk = 0;
+    for (; w < p->work.size() && p->work[w] >> 30 == kItemAdam; ++w) end_chunk = (p->work[w] & 0x3fffffffu) + 1u;
+    while (g < p->groups.size() && A.bucket_off[p->groups[g].second] <= end_chunk) {
+      for (; next < group_end[g]; ++next) p->lamb_clip_work.push_back((kItemAdam << 30) | place[next]);
+      ++g;
+    }
+  }
+  p->lamb_clip_one_pass = true;
+  // lamb_step, unless the tensors that are not held are more than one run of its two sweeps would take
+  p->lamb_one_pass = large_elems <= kLambGroupElems;
+}
+
 void free_profile(bca_plan* p) {
   for (hipEvent_t e : p->prof_events) (void)hipEventDestroy(e);
   p->prof_events.clear();
@@ -279,6 +363,10 @@ void free_device(bca_plan* p) {
   if (p->d_trust) (void)hipFree(p->d_trust);
   if (p->d_lamb_scale) (void)hipFree(p->d_lamb_scale);
   p->d_tensor_off = nullptr, p->d_lamb_sums = nullptr, p->d_trust = nullptr, p->d_lamb_scale = nullptr;
+  for (void* q : {(void*)p->d_lamb_items, (void*)p->d_lamb_items_of, (void*)p->d_lamb_clip_work, (void*)p->d_lamb_late, (void*)p->d_lamb_arrived, (void*)p->d_lamb_ready})
+    if (q) (void)hipFree(q);
+  p->d_lamb_items = nullptr, p->d_lamb_items_of = nullptr;
+  p->d_lamb_clip_work = nullptr, p->d_lamb_late = nullptr, p->d_lamb_arrived = nullptr, p->d_lamb_ready = nullptr;
   if (p->d_adamk) (void)hipFree(p->d_adamk);
   p->d_adamk = nullptr;
   if (p->d_coefs) (void)hipFree(p->d_coefs);
@@ -315,12 +403,30 @@ hipError_t upload_table(const bca_plan* p, Table* t) {
   return hipMemcpy(t->d_chunks, table.data(), table.size() * sizeof(Chunk), hipMemcpyHostToDevice);
 }
 
+// The same for the items of LAMB in one pass.
+hipError_t upload_lamb_items(const bca_plan* p) {
+  if (p->lamb_items.empty()) return hipSuccess;
+  const uint64_t gsize = grad_bytes(p->grad_dtype);
+  std::vector<LambItem> items = p->lamb_items;
+  for (LambItem& it : items) {
+    const ChunkInfo& c = p->lamb_tab.chunks[it.first];
+    it.g = p->bound_g[c.tensor] + c.begin * gsize;
+    it.p = p->bound_p[c.tensor] + c.begin * 4, it.m = p->bound_m[c.tensor] + c.begin * 4, it.v = p->bound_v[c.tensor] + c.begin * 4;
+    if (!p->decay[c.tensor]) it.flags |= kChunkNoDecay;
+    // no vector head (see vector_head): p, m and v aligned alike, at 16 bytes, or not alike
+    const bool alike = (((it.p ^ it.m) | (it.p ^ it.v)) & 15u) == 0;
+    if (c.len == kDefaultChunkApply && (!alike || (it.p & 15u) == 0)) it.flags |= kLambRegular;
+  }
+  return hipMemcpy(p->d_lamb_items, items.data(), items.size() * sizeof(LambItem), hipMemcpyHostToDevice);
+}
+
 // Kernels enqueued earlier on any stream may still be reading the old tables, so
 // wait for them before the (host-synchronous) copies.
 hipError_t upload_all_tables(bca_plan* p) {
   hipError_t e = hipDeviceSynchronize();
   for (Table* t : {&p->norm_tab, &p->apply_tab, &p->lamb_tab})
     if (e == hipSuccess) e = upload_table(p, t);
+  if (e == hipSuccess) e = upload_lamb_items(p);
   return e;
 }
 
@@ -333,6 +439,14 @@ StepState step_state(const bca_plan* p) {
   ss.apply_to_lamb = p->d_apply_to_lamb, ss.lamb_sums = p->d_lamb_sums;
   ss.spin_limit = p->spin_limit;
   return ss;
+}
+
+LambState lamb_state(const bca_plan* p, float* trust) {
+  LambState ls;
+  ls.tab = p->lamb_tab.d_chunks, ls.items = p->d_lamb_items, ls.items_of = p->d_lamb_items_of;
+  ls.arrived = p->d_lamb_arrived, ls.ready = p->d_lamb_ready, ls.sums = p->d_lamb_sums, ls.trust = trust, ls.late = p->d_lamb_late;
+  ls.n_items = (uint32_t)p->lamb_items.size(), ls.first_large = p->lamb_first_large, ls.n_tensors = p->n_tensors;
+  return ls;
 }
 
 // For every chunk of the apply table, the index of the same chunk (same tensor, same first
@@ -530,6 +644,28 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
     const size_t nb = n_buckets;
     const size_t nl = std::max<size_t>(p->lamb_tab.chunks.size(), 1), nt = std::max<size_t>(n_tensors, 1);
     const std::vector<uint32_t> a2l = apply_to_lamb_map(p);
+    // LAMB in one pass for plans in the library's own cut; a caller who tunes the cut, the runs or the launches gets those
+    if (chunk_apply == kDefaultChunkApply && !(p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) {
+      build_lamb_items(p, (uint32_t)std::max(prop.multiProcessorCount, 1) * kLambResidentPerCu, a2l);
+      if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
+    }
+    const auto alloc_lamb = [&] {
+      const size_t n = p->lamb_items.size(), nw = p->lamb_clip_work.size();
+      hipError_t err = hipSuccess;
+      if (n == 0 ||  // the plan goes in two sweeps
+          (err = hipMalloc((void**)&p->d_lamb_items, n * sizeof(LambItem))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_late, n * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_clip_work, nw * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemcpy(p->d_lamb_clip_work, p->lamb_clip_work.data(), nw * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_items_of, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemcpy(p->d_lamb_items_of, p->lamb_items_of.data(), nt * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_arrived, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemset(p->d_lamb_arrived, 0, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_ready, nt * sizeof(unsigned long long))) != hipSuccess ||
+          (err = hipMemset(p->d_lamb_ready, 0, nt * sizeof(unsigned long long))) != hipSuccess)
+        return err;
+      return hipSuccess;
+    };
     const uint32_t first_epoch = 1;  // ready words start at zero: epoch 0 is never current
     if ((e = alloc_table(&p->norm_tab, n_buckets)) != hipSuccess ||
         (e = alloc_table(&p->apply_tab, n_buckets)) != hipSuccess ||
@@ -541,6 +677,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
         (e = hipMemcpy(p->d_apply_to_lamb, a2l.data(), a2l.size() * sizeof(uint32_t), hipMemcpyHostToDevice)) !=
             hipSuccess ||
         (e = hipMalloc((void**)&p->d_lamb_sums, nl * 2 * sizeof(double))) != hipSuccess ||
+        (e = alloc_lamb()) != hipSuccess ||
         (e = hipMalloc((void**)&p->d_trust, nt * sizeof(float))) != hipSuccess ||
         (e = hipMalloc((void**)&p->d_lamb_scale, nt * sizeof(float))) != hipSuccess ||
         (e = hipMalloc((void**)&p->d_work, std::max<size_t>(p->work.size(), 1) * sizeof(uint32_t))) != hipSuccess ||
@@ -1003,6 +1140,14 @@ static int lamb_impl(bca_plan* p, const float* thresholds, const bca_adam* hp, u
   const Table& TL = p->lamb_tab;
   const uint32_t nl = (uint32_t)TL.chunks.size();
   hipError_t e = hipSuccess;
+  if (thresholds ? p->lamb_clip_one_pass : p->lamb_one_pass) {
+    const size_t n_work = thresholds ? p->lamb_clip_work.size() : p->lamb_items.size();
+    e = launch_lamb(p->grad_dtype, step_state(p), lamb_state(p, trust ? trust : p->d_trust),
+                    p->d_lamb_clip_work, (uint32_t)n_work, thresholds != nullptr, thresholds,
+                    norms ? norms : p->d_norms, coefs ? coefs : p->d_coefs,
+                    thresholds ? (status ? status : p->d_status) : nullptr, (flags & BCA_WRITE_BACK_GRADS) != 0, k, s);
+    return e == hipSuccess ? (int)BCA_OK : fail_hip(e, "launching the LAMB kernels");
+  }
   if (thresholds) {
     float* nm = norms ? norms : p->d_norms;
     float* cw = coefs ? coefs : p->d_coefs;

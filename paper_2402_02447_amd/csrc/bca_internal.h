@@ -120,7 +120,12 @@ enum : uint32_t {
   // items that waited touch them, and spread over many lines so that they do not queue up behind one address.
   kCtlStats = 384,
   kStatSlots = 256,
-  kCtlWords = kCtlStats + 32 * kStatSlots
+  // LAMB in one pass: held items whose wait for their tensor's ratio expired (their indices are in LambState::late), the
+  // flag that such a wait has expired, and how many of the tail kernel's workers are done
+  kCtlLate = kCtlStats + 32 * kStatSlots,
+  kCtlLateAbort = kCtlLate + 32,
+  kCtlTailDone = kCtlLate + 64,
+  kCtlWords = kCtlLate + 96
 };
 // Work items of k_step: kind in bits 30..31; kItemAdam: apply-table chunk in bits 0..29; kItemNorm: first
 // norm-table chunk in bits 0..27 and the number of consecutive chunks minus one in bits 28..29; kItemEmpty: bucket.
@@ -138,6 +143,50 @@ struct StepState {
   double* lamb_sums;                // LAMB: two sums per chunk, in tensor-major order
   uint32_t skipped_cap;             // entries of `skipped`
   uint32_t spin_limit;              // polls of a ready word before a waiting item gives up
+};
+
+// LAMB in one pass (k_lamb).  An item is up to kLambItemChunks consecutive chunks of the tensor-major table, all of one
+// tensor and one bucket.  Addresses and the kLambRegular bit are filled in by bca_plan_bind.
+constexpr uint32_t kLambItemChunks = 12;
+struct alignas(16) LambItem {
+  uint64_t g, p, m, v;  // device byte addresses of the item's first element
+  uint32_t first;       // its first chunk in the tensor-major table
+  uint32_t count;       // chunks
+  uint32_t tensor, bucket;
+  uint32_t flags;       // kChunkNoDecay, kLamb*
+  uint32_t items;       // of the tensor
+  uint32_t lo, hi;      // the tensor's chunks
+};
+static_assert(sizeof(LambItem) == 64, "item table entries are 4 x 16 bytes");
+constexpr uint32_t kLambRegular = 2u;  // full chunks only, and 16-byte vectors from the first element on
+constexpr uint32_t kLambHeld = 4u;     // p and u stay on the chip until the tensor's ratio is known
+constexpr uint32_t kLambKeep = 8u;     // moments are stored cacheable: the tail kernel reads them again
+// Workgroups of k_lamb that are resident at a time on a compute unit: what __launch_bounds__ asks for (128 VGPRs), and four
+// times the 33 KiB of LDS fit in 160 KiB.
+constexpr uint32_t kLambResidentPerCu = 4;
+// A tensor is held if its items, with whatever lies between them in the work list, are at most this share of what is
+// resident on the whole GPU (3/4: a tensor's first workgroups hold their slots until its last one is through).
+constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
+// Plans go in one pass from this many elements on, and if at least half of them are in held tensors.  Below, the chain of
+// round trips to memory inside the launch costs more than it saves (two sweeps / one pass, lamb_step: 0.3 M elements
+// 12.3 / 18.5 us, 3.2 M 29.3 / 32.5, 7 M 50 / 45, 11 M 78 / 65; bucket_clip_lamb 3.2 M 42.4 / 45.6, 7 M 65 / 62);
+// with nothing held, two sweeps by items stream worse than chunk by chunk (four tensors of 16.8 M: 484 / 504 us).
+constexpr uint64_t kLambOnePassElems = 5ull << 20;
+// Polls of a tensor's ready word before a held item gives up: some milliseconds, fifty times what the largest tensors
+// take.  Short, because giving up costs little (the tail kernel reads the item again), and because two such launches on
+// one GPU at a time can hold the slots that each other's tensors are waiting for.
+constexpr uint32_t kTrustSpinLimit = 1u << 12;
+constexpr uint32_t kLambTailWorkers = 64;
+struct LambState {
+  const Chunk* tab;                 // tensor-major chunks
+  const LambItem* items;
+  const uint32_t* items_of;         // [n_tensors] items of each tensor
+  uint32_t* arrived;                // [n_tensors] items of the tensor whose sums are stored
+  unsigned long long* ready;        // [n_tensors] (epoch << 32) | bits of -lr * ratio
+  double* sums;                     // two per chunk
+  float* trust;                     // [n_tensors]
+  uint32_t* late;                   // [n_items] held items whose wait expired
+  uint32_t n_items, first_large, n_tensors;  // items from first_large on are of tensors that are not held
 };
 
 // Kernel launchers (bca_kernels.hip).  All enqueue on `stream` and return the
@@ -193,6 +242,11 @@ hipError_t launch_lamb_moments(int gdt, const Chunk* table, uint32_t n, const fl
 hipError_t launch_hyper(const bca_adam_device* dev, AdamK* out, hipStream_t stream);
 hipError_t launch_lamb_trust(const double* sums, const uint32_t* tensor_off, uint32_t n_tensors, const AdamK& k,
                              float* trust, float* scale, hipStream_t stream);
+// LAMB in one pass.  clip: squared-norm items and bucket coefficients as in launch_step, and a kernel for items that gave
+// up waiting for one; then the tail kernel, which also hands over the status bits and readies the state.
+hipError_t launch_lamb(int gdt, const StepState& st, const LambState& ls, const uint32_t* work, uint32_t n_work, bool clip,
+                       const float* thresholds, float* norms, float* coefs, int32_t* status, bool write_back, const AdamK& k,
+                       hipStream_t stream);
 hipError_t launch_lamb_update(const Chunk* table, uint32_t n, const float* scale, const AdamK& k,
                               hipStream_t stream);
 
@@ -225,6 +279,18 @@ struct bca_plan {
   double* d_lamb_sums = nullptr;   // 2 per chunk of lamb_tab: sum p^2, sum update^2
   float* d_trust = nullptr;        // n_tensors
   float* d_lamb_scale = nullptr;   // n_tensors: -lr * trust
+  // LAMB in one pass (tables cut at kDefaultChunkApply only): items in the order lamb_step works on them, and
+  // bucket_clip_lamb's work list
+  std::vector<bca::LambItem> lamb_items;  // addresses not filled in
+  std::vector<uint32_t> lamb_items_of, lamb_clip_work;
+  uint32_t lamb_first_large = 0;  // items from here on are of tensors that are not held
+  bool lamb_one_pass = false, lamb_clip_one_pass = false;  // which calls go that way
+  bca::LambItem* d_lamb_items = nullptr;
+  uint32_t* d_lamb_items_of = nullptr;
+  uint32_t* d_lamb_clip_work = nullptr;
+  uint32_t* d_lamb_late = nullptr;
+  uint32_t* d_lamb_arrived = nullptr;
+  unsigned long long* d_lamb_ready = nullptr;
   // what bca_plan_bind was given, kept so that the tables can be written again (decay mask)
   std::vector<uint64_t> bound_g, bound_p, bound_m, bound_v;
   std::vector<uint8_t> decay;      // per tensor: 1 = weight decay applies (default), 0 = exempt

@@ -681,13 +681,16 @@ __device__ __forceinline__ double block_sum(double x, double* s_w) {
 }
 
 // LAMB's first sweep over one chunk: moments updated and stored, the chunk's sums of
-// p^2 and u^2 written to out[0], out[1] (fp64; per lane 4 * chunk_elems / 1024 squares
+// p^2 and u^2 returned (fp64, valid in thread 0; per lane 4 * chunk_elems / 1024 squares
 // are added in fp32 first).  coef != 1 only behind clipping; WB: the scaled gradient,
 // rounded to its storage type, also replaces g.  GNT: whether g streams (it does not
 // when the squared-norm pass has just read it and it is still cached).
+struct ChunkSums {
+  double pp, uu;
+};
 template <int GDT, bool FUSED, bool WB, bool GNT, bool KEEP = false>
-__device__ __forceinline__ void lamb_moments_chunk(const Entry& en, float coef, const AdamK& k, double* s_pp,
-                                                   double* s_uu, double* __restrict__ out) {
+__device__ __forceinline__ ChunkSums lamb_moments_chunk(const Entry& en, float coef, const AdamK& k, double* s_pp,
+                                                        double* s_uu) {
   typedef Grad<GDT> G;
   constexpr uint32_t gsize = sizeof(typename G::elem);
   const uint32_t tid = threadIdx.x;
@@ -732,8 +735,9 @@ __device__ __forceinline__ void lamb_moments_chunk(const Entry& en, float coef, 
     m1[i] = m, v1[i] = v;
     if (wb) G::store1(gbase, i, g);
   }
-  const double tpp = block_sum((double)pp, s_pp), tuu = block_sum((double)uu, s_uu);
-  if (tid == 0) out[0] = tpp, out[1] = tuu;
+  ChunkSums r;
+  r.pp = block_sum((double)pp, s_pp), r.uu = block_sum((double)uu, s_uu);
+  return r;
 }
 
 template <int GDT, bool FUSED, bool WB, bool KEEP>
@@ -746,7 +750,8 @@ __global__ __launch_bounds__(kBlock) void k_lamb_moments(const Chunk* __restrict
     const Entry en = read_entry(&table[ci]);
     float coef = 1.f;
     if constexpr (FUSED) coef = coefs[en.bucket];
-    lamb_moments_chunk<GDT, FUSED, WB, true, KEEP>(en, coef, k, s_pp, s_uu, sums + (uint64_t)ci * 2u);
+    const ChunkSums r = lamb_moments_chunk<GDT, FUSED, WB, true, KEEP>(en, coef, k, s_pp, s_uu);
+    if (threadIdx.x == 0) sums[(uint64_t)ci * 2u] = r.pp, sums[(uint64_t)ci * 2u + 1u] = r.uu;
     __syncthreads();  // s_pp / s_uu are reused by the next chunk
   }
 }
@@ -783,36 +788,40 @@ __global__ __launch_bounds__(kTrustBlock) void k_lamb_trust(const double* __rest
   }
 }
 
+// The second sweep over one chunk: p + sc * u, u recomputed from the stored moments.
+__device__ __forceinline__ void lamb_update_chunk(const Entry& en, float sc, const AdamK& k) {
+  const uint32_t tid = threadIdx.x;
+  const float wd = chunk_wd(en, k);
+  const uint32_t len = en.len;
+  const uint32_t head = vector_head(len, en.p, en.m, en.v);
+  const uint32_t nvec = (len - head) / 4u;
+  const uint32_t tail0 = head + nvec * 4u;
+  f32x4* pv = reinterpret_cast<f32x4*>(en.p + (uint64_t)head * 4u);
+  const f32x4* mv = reinterpret_cast<const f32x4*>(en.m + (uint64_t)head * 4u);
+  const f32x4* vv = reinterpret_cast<const f32x4*>(en.v + (uint64_t)head * 4u);
+  for (uint32_t j = tid; j < nvec; j += kBlock) {
+    f32x4 p = ldv<true>(pv + j);
+    const f32x4 m = ldv<true>(mv + j), v = ldv<true>(vv + j);
+    loads_issued();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = __fmaf_rn(sc, adam_direction(p[i], m[i], v[i], k, wd), p[i]);
+    stv<true>(pv + j, p);
+  }
+  BCA_GLOBAL float* p1 = as_global(reinterpret_cast<float*>(en.p));
+  const BCA_GLOBAL float* m1 = as_global(reinterpret_cast<const float*>(en.m));
+  const BCA_GLOBAL float* v1 = as_global(reinterpret_cast<const float*>(en.v));
+  for (uint32_t r = tid; r < head + (len - tail0); r += kBlock) {
+    const uint32_t i = r < head ? r : tail0 + (r - head);
+    p1[i] = __fmaf_rn(sc, adam_direction(p1[i], m1[i], v1[i], k, wd), p1[i]);
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_lamb_update(const Chunk* __restrict__ table, uint32_t n,
                                                          const float* __restrict__ scale, const AdamK ka) {
-  const uint32_t tid = threadIdx.x;
   const AdamK k = resolve(ka);
   for (uint32_t ci = blockIdx.x; ci < n; ci += gridDim.x) {
     const Entry en = read_entry(&table[ci]);
-    const float sc = scale[en.tensor];
-    const float wd = chunk_wd(en, k);
-    const uint32_t len = en.len;
-    const uint32_t head = vector_head(len, en.p, en.m, en.v);
-    const uint32_t nvec = (len - head) / 4u;
-    const uint32_t tail0 = head + nvec * 4u;
-    f32x4* pv = reinterpret_cast<f32x4*>(en.p + (uint64_t)head * 4u);
-    const f32x4* mv = reinterpret_cast<const f32x4*>(en.m + (uint64_t)head * 4u);
-    const f32x4* vv = reinterpret_cast<const f32x4*>(en.v + (uint64_t)head * 4u);
-    for (uint32_t j = tid; j < nvec; j += kBlock) {
-      f32x4 p = ldv<true>(pv + j);
-      const f32x4 m = ldv<true>(mv + j), v = ldv<true>(vv + j);
-      loads_issued();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = __fmaf_rn(sc, adam_direction(p[i], m[i], v[i], k, wd), p[i]);
-      stv<true>(pv + j, p);
-    }
-    BCA_GLOBAL float* p1 = as_global(reinterpret_cast<float*>(en.p));
-    const BCA_GLOBAL float* m1 = as_global(reinterpret_cast<const float*>(en.m));
-    const BCA_GLOBAL float* v1 = as_global(reinterpret_cast<const float*>(en.v));
-    for (uint32_t r = tid; r < head + (len - tail0); r += kBlock) {
-      const uint32_t i = r < head ? r : tail0 + (r - head);
-      p1[i] = __fmaf_rn(sc, adam_direction(p1[i], m1[i], v1[i], k, wd), p1[i]);
-    }
+    lamb_update_chunk(en, scale[en.tensor], k);
   }
 }
 
@@ -1023,7 +1032,11 @@ __device__ __forceinline__ void apply_item(const StepState& st, const Entry& en,
   if constexpr (MODE == kModeLamb)
     // LAMB's first sweep in place of Adam: moments and the chunk's two sums, filed under the chunk's place in
     // the tensor-major order; the trust ratio and the parameter update follow as launches of their own.
-    lamb_moments_chunk<GDT, true, WB, false>(en, coef, k, sh.pp, sh.uu, st.lamb_sums + (uint64_t)st.apply_to_lamb[idx] * 2u);
+  {
+    double* out = st.lamb_sums + (uint64_t)st.apply_to_lamb[idx] * 2u;
+    const ChunkSums r = lamb_moments_chunk<GDT, true, WB, false>(en, coef, k, sh.pp, sh.uu);
+    if (threadIdx.x == 0) out[0] = r.pp, out[1] = r.uu;
+  }
   else
     adam_chunk<GDT, true, WB, U, false>(en, coef, k);
 }
@@ -1070,6 +1083,323 @@ __global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* _
   } else {
     // squared-norm items carry their chunk count (1 .. 4) in bits 28..29
     norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
+  }
+}
+
+// ---- LAMB in one pass over p, m, v -------------------------------------------------------
+//
+// LAMB's update needs its tensor's trust ratio, i.e. sums over the whole tensor, so that two sweeps read p, m and v
+// twice: 40 bytes per element instead of the 28 that have to move.  The path is bound by what crosses the
+// L2 / fabric boundary (about 6.9 TB/s whether HBM or the Infinity Cache answers), so a second read that hits the
+// Infinity Cache is still paid for.  Here a workgroup keeps p and u of its item (12 chunks of 1 024 elements) on the chip, p and a third
+// of u in registers, two thirds of u in LDS, stores the moments, and files the chunks' sums; the last workgroup of the tensor
+// to get there derives the ratio and publishes -lr * ratio; the others wait for it and then write p.  Four
+// workgroups per compute unit are resident (128 VGPRs, 33 KiB of LDS), 12.6 M elements in all.  A tensor's first
+// workgroups wait until its last one is through, so the slots of half a tensor idle on average: larger items
+// beat smaller ones although those stream better (335 M elements in tensors of 4 M: 8 chunks an item 1.83 ms, 12 with
+// part of u in LDS 1.67; in tensors of 1 M: 1.58 and 1.64; two sweeps in runs 2.05).
+//   BERT-Large, fp32: lamb_step 2085 -> 1875 us (two sweeps in runs before); with bf16 gradients 2017 -> 1743,
+// bucket_clip_lamb 2088 -> 1752; BERT-Base, fp16, behind clipping 695 -> 588.
+//
+// Sums are taken chunk by chunk and added in k_lamb_trust's order: results are those of the two sweeps bit for bit.
+//
+// Tensors too large to be held (kLambHeldNum / kLambHeldDen; BERT's word embedding) are last in the list of lamb_step: their items store the
+// moments cacheable and the tail kernel carries out their second sweep, most recent item first.
+//
+// Waiting.  Items wait for the rest of their own tensor, which the work list keeps together and which is resident at
+// once as a rule.  It need not be: another launch of this kind on the GPU may hold slots that it is waiting for, and
+// they for it.  Every wait is therefore bounded, and short: an item that gives up files itself, raises a flag that makes
+// other waiters give up at their next look, and ends; its moments and sums are stored, and the tail kernel, which
+// follows every such launch, reads it again and updates p with the same arithmetic.  Behind clipping, items first
+// wait for their bucket's coefficient, as in k_step; one that gives up there has done nothing, and is carried out (moments, sums,
+// and the ratio of a tensor that it completes) by k_lamb_late, between the launch and its tail.
+
+struct LambShared {
+  StepShared step;
+  double pp[kLambItemChunks][kWaves], uu[kLambItemChunks][kWaves];
+  double tp[kTrustBlock / 64], tu[kTrustBlock / 64];
+  uint32_t last;
+  float scale;
+  f32x4 u[2 * kLambItemChunks / 3][kBlock];
+};
+
+// k_lamb_trust for one tensor by a workgroup of 256 threads, each of whose wavefronts stands in for four of that kernel's
+// sixteen; the sums may just have been written by other workgroups (agent scope).  Publishes the result.
+__device__ __forceinline__ void tensor_ratio(const LambState& ls, uint32_t t, uint32_t lo, uint32_t hi, uint32_t epoch, double lr,
+                                             LambShared& sh) {
+  constexpr uint32_t Q = 2;  // of the four wavefronts that each one here stands in for, those handled at a time
+  const uint32_t lane = threadIdx.x & 63u;
+  // every workgroup of the tensor waits for this: a thread's loads are issued eight at a time
+#pragma unroll
+  for (uint32_t q0 = 0; q0 < kTrustBlock / kBlock; q0 += Q) {
+    double pp0[Q] = {}, uu0[Q] = {}, pp1[Q] = {}, uu1[Q] = {};
+    for (uint32_t base = lo + q0 * kBlock + threadIdx.x; base < hi; base += 2u * kTrustBlock) {
+      double x[Q][4];
+#pragma unroll
+      for (uint32_t q = 0; q < Q; ++q) {
+#pragma unroll
+        for (uint32_t r = 0; r < 4u; ++r) {  // r & 1: which sum; r >> 1: which of the two accumulators
+          const uint32_t c = base + q * kBlock + (r >> 1) * kTrustBlock;
+          x[q][r] = 0.0;  // adds nothing to sums of squares
+          if (c < hi) x[q][r] = __hip_atomic_load(&ls.sums[(uint64_t)c * 2u + (r & 1u)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < Q; ++q) pp0[q] += x[q][0], uu0[q] += x[q][1], pp1[q] += x[q][2], uu1[q] += x[q][3];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) {
+      const double pp = wave_sum(pp0[q] + pp1[q]), uu = wave_sum(uu0[q] + uu1[q]);
+      const uint32_t w = (q0 + q) * kWaves + (threadIdx.x >> 6);
+      if (lane == 0) sh.tp[w] = pp, sh.tu[w] = uu;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tpp = 0.0, tuu = 0.0;
+    for (uint32_t w = 0; w < kTrustBlock / 64; ++w) tpp += sh.tp[w], tuu += sh.tu[w];
+    const double pn = sqrt(tpp), un = sqrt(tuu);
+    const double r = (pn > 0.0 && un > 0.0) ? pn / un : 1.0;
+    const float scale = (float)(-lr * r);
+    const unsigned long long word = ((unsigned long long)epoch << 32) | (unsigned long long)__float_as_uint(scale);
+    __hip_atomic_store(&ls.ready[t], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ls.trust[t] = (float)r;
+    sh.scale = scale;
+  }
+}
+
+// Thread 0's bounded wait for tensor t's ready word; false after filing `self` as late.
+__device__ __forceinline__ bool wait_for_tensor(const StepState& st, const LambState& ls, uint32_t t, uint32_t epoch,
+                                                uint32_t self, float* scale) {
+  const uint32_t limit = min(st.spin_limit, kTrustSpinLimit);
+  uint32_t polls = 0;
+  for (;;) {
+    const unsigned long long r = __hip_atomic_load(&ls.ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)(r >> 32) == epoch) {
+      *scale = __uint_as_float((uint32_t)r);
+      return true;
+    }
+    if (++polls > limit) break;
+    if ((polls & 15u) == 0 && ctl_load(&st.ctl[kCtlLateAbort]) != 0u) break;
+    __builtin_amdgcn_s_sleep(16);
+  }
+  ctl_store(&st.ctl[kCtlLateAbort], 1u);
+  ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_TIMEOUT);
+  const uint32_t slot = atomicAdd(&st.ctl[kCtlLate], 1u);
+  if (slot < ls.n_items) ls.late[slot] = self;  // read by the tail kernel
+  else ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_INCOMPLETE);
+  return false;
+}
+
+// One item: moments, sums, arrival, ratio; HOLD: then the wait and the update of a held item.
+template <int GDT, bool CLIP, bool WB, bool HOLD>
+__device__ __forceinline__ void lamb_item(const StepState& st, const LambState& ls, const LambItem* __restrict__ ip, uint32_t self,
+                                          float coef, const AdamK& k, uint32_t epoch, LambShared& sh) {
+  typedef Grad<GDT> G;
+  constexpr uint32_t CH = kLambItemChunks, LD = 2 * CH / 3, B = 2;  // chunks; those whose u is in LDS; chunks loaded at a time
+  constexpr bool GNT = !CLIP;  // behind clipping the gradients are in cache
+  const uint32_t tid = threadIdx.x;
+  const uint32_t first = ip->first, count = ip->count, t = ip->tensor, flags = ip->flags;
+  const uint32_t items = ip->items, lo = ip->lo, hi = ip->hi;
+  const bool regular = HOLD && (flags & kLambRegular) != 0u;
+  const float wd = (flags & kChunkNoDecay) ? 0.f : k.wd;
+  f32x4 P[CH], U[CH - LD];
+  if (regular) {
+    const uint64_t ga = ip->g;
+    f32x4* pv = reinterpret_cast<f32x4*>(ip->p);
+    f32x4* mv = reinterpret_cast<f32x4*>(ip->m);
+    f32x4* vv = reinterpret_cast<f32x4*>(ip->v);
+    const bool keep = (flags & kLambKeep) != 0u, wb = WB && coef != 1.f;
+    const auto sweep = [&](auto full) {
+    constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+    for (uint32_t j = 0; j < CH; ++j)  // p stays in registers anyway: all of it is fetched at once
+      if (FULL || j < count) P[j] = ldv<true>(pv + j * kBlock + tid);
+    loads_issued();
+#pragma unroll
+    for (uint32_t j = 0; j < CH; j += B) {
+      if (FULL || j < count) {
+        f32x4 g[B], m[B], v[B];
+#pragma unroll
+        for (uint32_t q = 0; q < B; ++q) {
+          if (FULL || j + q < count) {
+            g[q] = G::template load4<GNT>(reinterpret_cast<const void*>(ga + (uint64_t)(j + q) * 1024u * sizeof(typename G::elem)), tid);
+            m[q] = ldv<true>(mv + (j + q) * kBlock + tid);
+            v[q] = ldv<true>(vv + (j + q) * kBlock + tid);
+          }
+        }
+        loads_issued();
+#pragma unroll
+        for (uint32_t q = 0; q < B; ++q) {
+          if (FULL || j + q < count) {
+            if constexpr (CLIP) g[q] = g[q] * coef;
+            float pp = 0.f, uu = 0.f;
+            f32x4 u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              float mi = m[q][i], vi = v[q][i];
+              adam_moments(g[q][i], mi, vi, k);
+              const float d = adam_direction(P[j + q][i], mi, vi, k, wd);
+              pp = __fmaf_rn(P[j + q][i], P[j + q][i], pp), uu = __fmaf_rn(d, d, uu);
+              m[q][i] = mi, v[q][i] = vi, u[i] = d;
+            }
+            if (keep) {
+              stv<false>(mv + (j + q) * kBlock + tid, m[q]), stv<false>(vv + (j + q) * kBlock + tid, v[q]);
+            } else {
+              stv<true>(mv + (j + q) * kBlock + tid, m[q]), stv<true>(vv + (j + q) * kBlock + tid, v[q]);
+            }
+            if (wb)
+              G::template store4<GNT>(reinterpret_cast<void*>(ga + (uint64_t)(j + q) * 1024u * sizeof(typename G::elem)), tid, g[q]);
+            if (j + q < LD) sh.u[j + q < LD ? j + q : 0][tid] = u;
+            else U[j + q < LD ? 0 : j + q - LD] = u;
+            const double wpp = wave_sum((double)pp), wuu = wave_sum((double)uu);
+            if ((tid & 63u) == 0) sh.pp[j + q][tid >> 6] = wpp, sh.uu[j + q][tid >> 6] = wuu;
+          }
+        }
+        loads_issued();
+      }
+    }
+    };
+    if (count == CH) sweep(std::true_type{});
+    else sweep(std::false_type{});
+    __syncthreads();
+    if (tid < 2u * count) {  // the four wavefronts' sums in index order; all in wavefront 0
+      const uint32_t j = tid >> 1;
+      const double* w = (tid & 1u) ? sh.uu[j] : sh.pp[j];
+      __hip_atomic_store(&ls.sums[(uint64_t)(first + j) * 2u + (tid & 1u)], ((w[0] + w[1]) + w[2]) + w[3], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  } else {
+    for (uint32_t j = 0; j < count; ++j) {
+      const ChunkSums r = lamb_moments_chunk<GDT, CLIP, WB, GNT>(read_entry(&ls.tab[first + j]), coef, k, sh.step.pp, sh.step.uu);
+      if (tid == 0) {
+        __hip_atomic_store(&ls.sums[(uint64_t)(first + j) * 2u], r.pp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ls.sums[(uint64_t)(first + j) * 2u + 1u], r.uu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();  // sh.step.pp / uu are reused by the next chunk
+    }
+  }
+  // Arrival: the sums were stored by wavefront 0, which waits for their acknowledgement before it counts (see norm_arrive).
+  if (tid < 64u) {
+    wait_vmem();
+    if (tid == 0) {
+      const bool last = atomicAdd(&ls.arrived[t], 1u) + 1u == items;
+      if (last) ctl_store(&ls.arrived[t], 0u);  // left at zero for the next call
+      sh.last = last ? 1u : 0u;
+    }
+  }
+  __syncthreads();
+  const bool last = sh.last != 0u;
+  if (last) tensor_ratio(ls, t, lo, hi, epoch, k.lr, sh);
+  if (!HOLD || !(flags & kLambHeld)) return;
+  if (!last && tid == 0) {
+    float scale = 0.f;
+    sh.step.flag = wait_for_tensor(st, ls, t, epoch, self, &scale) ? 1u : 0u;
+    sh.scale = scale;
+  }
+  __syncthreads();
+  if (!last && sh.step.flag == 0u) return;
+  const float sc = sh.scale;
+  if (regular) {
+    f32x4* pv = reinterpret_cast<f32x4*>(ip->p);
+#pragma unroll
+    for (uint32_t j = 0; j < CH; ++j) {
+      if (j < count) {
+        const f32x4 u = j < LD ? sh.u[j < LD ? j : 0][tid] : U[j < LD ? 0 : j - LD];
+        f32x4 x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = __fmaf_rn(sc, u[i], P[j][i]);
+        stv<true>(pv + j * kBlock + tid, x);
+      }
+    }
+  } else {
+    // every thread reads back the elements that it has stored itself
+    for (uint32_t j = 0; j < count; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j]), sc, k);
+  }
+}
+
+template <int GDT, bool CLIP, bool WB>
+__global__ __launch_bounds__(kBlock, kLambResidentPerCu) void k_lamb(StepState st, LambState ls, const uint32_t* __restrict__ work,
+                                                                     const float* __restrict__ thresholds, float* __restrict__ norms,
+                                                                     float* __restrict__ coefs, const AdamK ka) {
+  __shared__ LambShared sh;
+  const AdamK k = resolve(ka);
+  const uint32_t epoch = st.ctl[kCtlEpoch];  // left by the previous call, constant during this launch
+  uint32_t i = blockIdx.x;  // without clipping the items are worked on in their own order
+  float coef = 1.f;
+  if constexpr (CLIP) {
+    const uint32_t item = work[blockIdx.x], kind = item >> 30;
+    i = item & 0x3fffffffu;
+    if (kind != kItemAdam) {
+      norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh.step);
+      return;
+    }
+  }
+  if constexpr (CLIP) {
+    if (!wait_for_bucket(st, ls.items[i].bucket, epoch, i, sh.step)) return;
+    coef = sh.step.coef;
+  }
+  lamb_item<GDT, CLIP, WB, true>(st, ls, &ls.items[i], i, coef, k, epoch, sh);
+}
+
+// Behind a clipping launch: the items that gave up waiting for their bucket's coefficient (none, as a rule), which
+// exists by now.
+template <int GDT, bool WB>
+__global__ __launch_bounds__(kBlock) void k_lamb_late(StepState st, LambState ls, const AdamK ka) {
+  __shared__ LambShared sh;
+  const uint32_t n = min(ctl_load(&st.ctl[kCtlSkipped]), st.skipped_cap);
+  if (n == 0) return;
+  const AdamK k = resolve(ka);
+  const uint32_t epoch = ctl_load(&st.ctl[kCtlEpoch]);
+  for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
+    const uint32_t i = st.skipped[q];
+    const unsigned long long r = __hip_atomic_load(&st.ready[ls.items[i].bucket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)(r >> 32) != epoch) {  // cannot happen: squared-norm items never wait
+      if (threadIdx.x == 0) ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_INCOMPLETE);
+      continue;
+    }
+    lamb_item<GDT, true, WB, false>(st, ls, &ls.items[i], i, __uint_as_float((uint32_t)r), k, epoch, sh);
+    __syncthreads();
+  }
+}
+
+// Follows every k_lamb launch.  Workgroup w carries out the second sweep over the w-th chunk of the large tensors' items,
+// the most recent one first (its moments are the likeliest to be in cache; a workgroup per item, chunk after chunk,
+// takes 105 instead of 75 us over 31 M elements); the first kLambTailWorkers workgroups share the items
+// that gave up waiting, and the last of them to be done hands over the status bits and readies the state for the next
+// call.  Tensors without elements get ratio 1.
+// What it reads was written by earlier launches, so plain loads do; thousands of workgroups reading one word at agent scope
+// would queue up behind it (10 ns each).  Only workers look at the epoch: it moves on once they are all done, which
+// the other workgroups may still outlast.
+__global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls, int32_t* status, const AdamK ka) {
+  const uint32_t w = blockIdx.x, tid = threadIdx.x, workers = min(gridDim.x, kLambTailWorkers);
+  const AdamK k = resolve(ka);
+  const auto update = [&](uint32_t i, uint32_t from, uint32_t to) {  // chunks [from, to) of item i
+    const LambItem* ip = &ls.items[i];
+    const float sc = __uint_as_float((uint32_t)ls.ready[ip->tensor]);
+    const uint32_t first = ip->first, end = min(to, ip->count);
+    for (uint32_t j = from; j < end; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j]), sc, k);
+  };
+  const uint32_t back = w / kLambItemChunks, chunk = w % kLambItemChunks;
+  if (back < ls.n_items - ls.first_large) update(ls.n_items - 1u - back, chunk, chunk + 1u);
+  if (w >= workers) return;
+  const uint32_t epoch = st.ctl[kCtlEpoch];
+  const uint32_t n_late = min(st.ctl[kCtlLate], ls.n_items), n_skipped = min(st.ctl[kCtlSkipped], st.skipped_cap);
+  for (uint32_t q = w; q < n_late; q += workers) update(ls.late[q], 0u, kLambItemChunks);
+  for (uint32_t q = w; q < n_skipped; q += workers)
+    if (ls.items[st.skipped[q]].flags & kLambHeld) update(st.skipped[q], 0u, kLambItemChunks);
+  for (uint32_t t = w * kBlock + tid; t < ls.n_tensors; t += workers * kBlock) {
+    if (ls.items_of[t] == 0u) ls.trust[t] = 1.f;
+    // cannot happen: every item's sums have been counted by now
+    else if ((uint32_t)(ls.ready[t] >> 32) != epoch) ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_INCOMPLETE);
+  }
+  wait_vmem();  // a status bit raised above has arrived before this worker is counted
+  __syncthreads();
+  if (tid == 0 && atomicAdd(&st.ctl[kCtlTailDone], 1u) + 1u == workers) {
+    const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);
+    if (status != nullptr) *status = (int32_t)collected;
+    for (const uint32_t word : {kCtlStatus, kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort, kCtlTailDone}) ctl_store(&st.ctl[word], 0u);
+    ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
   }
 }
 
@@ -1469,6 +1799,31 @@ hipError_t launch_lamb_moments(int gdt, const Chunk* table, uint32_t n, const fl
         hipLaunchKernelGGL((k_lamb_moments<GDT, true, WB, KEEP>), dim3(n), dim3(kBlock), 0, stream, table, n, coefs, sums, k);
     });
   });
+  return hipGetLastError();
+}
+
+hipError_t launch_lamb(int gdt, const StepState& st, const LambState& ls, const uint32_t* work, uint32_t n_work, bool clip,
+                       const float* thresholds, float* norms, float* coefs, int32_t* status, bool write_back, const AdamK& k,
+                       hipStream_t stream) {
+  hipError_t e = hipSuccess;
+  pick_gdt(gdt, [&](auto gd) {
+    constexpr int GDT = decltype(gd)::value;
+    if (n_work != 0) {
+      if (!clip)
+        hipLaunchKernelGGL((k_lamb<GDT, false, false>), dim3(n_work), dim3(kBlock), 0, stream, st, ls, work, thresholds, norms, coefs, k);
+      else if (write_back)
+        hipLaunchKernelGGL((k_lamb<GDT, true, true>), dim3(n_work), dim3(kBlock), 0, stream, st, ls, work, thresholds, norms, coefs, k);
+      else
+        hipLaunchKernelGGL((k_lamb<GDT, true, false>), dim3(n_work), dim3(kBlock), 0, stream, st, ls, work, thresholds, norms, coefs, k);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess || !clip) return;
+    if (write_back) hipLaunchKernelGGL((k_lamb_late<GDT, true>), dim3(kLambTailWorkers), dim3(kBlock), 0, stream, st, ls, k);
+    else hipLaunchKernelGGL((k_lamb_late<GDT, false>), dim3(kLambTailWorkers), dim3(kBlock), 0, stream, st, ls, k);
+    e = hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_lamb_tail, dim3(std::max((ls.n_items - ls.first_large) * kLambItemChunks, kLambTailWorkers)), dim3(kBlock), 0, stream, st, ls, status, k);
   return hipGetLastError();
 }
 

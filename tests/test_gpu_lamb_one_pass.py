@@ -1,0 +1,132 @@
+"""LAMB in one pass over p, m, v (items held on the chip until their tensor's ratio is known) against the two sweeps, bit for
+bit: sizes around chunks, items and the limit up to which a tensor is held, and waits that expire."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_02447_amd as B
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+HP = B.AdamHyper(1e-3, 0.9, 0.999, 1e-6, 0.01)
+TYPES = [(torch.float32, B.BCA_GRAD_F32), (torch.float16, B.BCA_GRAD_F16), (torch.bfloat16, B.BCA_GRAD_BF16)]
+# edges of a chunk (1024), of an item (12 chunks), several items, an empty tensor, single elements
+SIZES = [1, 0, 1023, 1024, 1025, 12 * 1024, 12 * 1024 + 1, 13 * 1024, 24 * 1024, 100_003, 7, 300_000, 2]
+SIZES += [5 << 20]     # plans below this many elements go in two sweeps
+
+
+def _state(sizes, dtype, seed, offset=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+
+    def place(t):
+        buf = torch.zeros(t.numel() + offset + 8, dtype=t.dtype, device="cuda")
+        buf[offset:offset + t.numel()] = t
+        return buf[offset:offset + t.numel()]
+    g = [place((torch.randn(n, generator=gen, device="cuda") * 1e-3).to(dtype)) for n in sizes]
+    p = [place(torch.randn(n, generator=gen, device="cuda") * 0.02) for n in sizes]
+    m = [place(torch.randn(n, generator=gen, device="cuda") * 3e-4) for n in sizes]
+    v = [place((torch.rand(n, generator=gen, device="cuda") + 0.5) * 1e-6) for n in sizes]
+    return g, p, m, v
+
+
+class Run:
+    def __init__(self, lay, dtype, gdt, seed, offset=0, mask=None, **tuning):
+        self.lay, self.state = lay, _state([int(n) for n in lay.tensor_numel], dtype, seed, offset)
+        self.plan = B.Plan.from_layout(lay, gdt, **tuning)
+        if mask is not None:
+            self.plan.set_decay_mask(mask)
+        self.plan.bind(*self.state)
+        nb = lay.n_buckets
+        self.norms, self.coefs = (torch.zeros(nb, device="cuda") for _ in range(2))
+        self.trust = torch.full((lay.n_tensors,), -1.0, device="cuda")
+        self.status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        self.thr = torch.full((nb,), 0.05, device="cuda")
+
+    def go(self, clip, step, flags=0, stream=None):
+        if clip:
+            self.plan.bucket_clip_lamb(self.thr, HP, step, flags, self.norms, self.coefs, self.trust, self.status, stream=stream)
+        else:
+            self.plan.lamb_step(HP, step, self.trust, stream=stream)
+
+    def same(self, other):
+        for a, b in zip([x for ts in self.state for x in ts] + [self.trust, self.norms, self.coefs],
+                        [x for ts in other.state for x in ts] + [other.trust, other.norms, other.coefs]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+def _two_sweeps(clip):
+    return dict(tune_flags=B.BCA_TUNE_MULTI_LAUNCH) if clip else dict(lamb_group_elems=1 << 40)
+
+
+@pytest.mark.parametrize("dtype,gdt", TYPES)
+@pytest.mark.parametrize("clip,flags", [(False, 0), (True, 0), (True, B.BCA_WRITE_BACK_GRADS)])
+@pytest.mark.parametrize("cap,offset", [(1 << 30, 0), (20_000, 0), (70_001, 3)])
+def test_same_bits_as_two_sweeps(dtype, gdt, clip, flags, cap, offset):
+    lay = W.layout_flat_split(SIZES, cap)
+    mask = np.arange(len(SIZES)) % 2
+    one, two = Run(lay, dtype, gdt, 5, offset, mask), Run(lay, dtype, gdt, 5, offset, mask, **_two_sweeps(clip))
+    for step in (3, 4):
+        one.go(clip, step, flags)
+        two.go(clip, step, flags)
+        torch.cuda.synchronize()
+        one.same(two)
+        if clip:
+            assert int(one.status.item()) == int(two.status.item()) == 0
+    one.plan.close()
+    two.plan.close()
+
+
+@pytest.mark.parametrize("clip", [False, True])
+def test_tensors_too_large_to_be_held_beside_held_ones(clip):
+    slots = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    most = slots * 3 // 4 * 12 * 1024          # elements of the largest tensor that is held
+    for sizes in ([5000, most, 70_000, most + 1, 12], [most + 12 * 1024 + 7, most, 1 << 20], [most + 5, 40, most - 100, most // 2]):
+        lay = W.layout_flat_split(sizes, 6_553_600)
+        one, two = Run(lay, torch.float32, B.BCA_GRAD_F32, 9), Run(lay, torch.float32, B.BCA_GRAD_F32, 9, **_two_sweeps(clip))
+        for step in (3, 4):
+            one.go(clip, step)
+            two.go(clip, step)
+        torch.cuda.synchronize()
+        one.same(two)
+        one.plan.close()
+        two.plan.close()
+
+
+@pytest.mark.parametrize("clip", [False, True])
+def test_every_wait_expires_at_a_limit_of_one_poll(clip):
+    sizes = [400_000, 5, 1_000_000, 20_000, 4_000_000, 1024]
+    lay = W.layout_flat_split(sizes, 262_144)
+    one, two = Run(lay, torch.float32, B.BCA_GRAD_F32, 2, spin_limit=1), Run(lay, torch.float32, B.BCA_GRAD_F32, 2, **_two_sweeps(clip))
+    for step in (3, 4, 5):
+        one.go(clip, step)
+        two.go(clip, step)
+        torch.cuda.synchronize()
+        one.same(two)
+        if clip:
+            assert int(one.status.item()) == B.BCA_STATUS_TIMEOUT
+    one.plan.close()
+    two.plan.close()
+
+
+def test_two_plans_on_two_streams_at_once():
+    """Each may hold slots that the other's tensors wait for: waits are bounded and the results the same."""
+    lay = W.layout_flat_split([4_194_304] * 6 + [1_048_576] * 6, 6_553_600)
+    runs = [Run(lay, torch.float32, B.BCA_GRAD_F32, 20 + i) for i in range(2)]
+    ref = [Run(lay, torch.float32, B.BCA_GRAD_F32, 20 + i) for i in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for step in range(3, 13):
+        for clip in (False, True):
+            for r, s in zip(runs, streams):
+                r.go(clip, step, stream=s)
+    torch.cuda.synchronize()
+    for step in range(3, 13):
+        for clip in (False, True):
+            for r in ref:
+                r.go(clip, step)
+                torch.cuda.synchronize()
+    for a, b in zip(runs, ref):
+        a.same(b)
+        a.plan.close()
+        b.plan.close()
