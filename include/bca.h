@@ -314,7 +314,8 @@ int bucket_clip_lamb(bca_plan* plan, const float* thresholds /*DEVICE [B]*/, con
  * are not recorded.  bca_plan_profile_read waits for the recorded events and
  * returns the summed duration of each kernel in milliseconds in ms[0..2] and the
  * number of calls summed in *n_calls, then starts a new series.  The single pipelined
- * launch (the default) reports its step kernel in ms[2] and its finish kernel in ms[0]. */
+ * launch (the default) reports its step kernel in ms[2] and its finish kernel in ms[0]
+ * (small plans, which do without a finish kernel, have one while they are profiled). */
 int bca_plan_profile(bca_plan* plan, uint32_t max_calls);
 int bca_plan_profile_read(bca_plan* plan, double* ms /*HOST [3]*/, uint32_t* n_calls /*HOST*/);
 

@@ -863,6 +863,9 @@ __global__ __launch_bounds__(kBlock) void k_lamb_update(const Chunk* __restrict_
 // bucket zeroes that bucket's arrival counter, and the finish kernel hands the collected
 // status bits to the caller, clears the abort word, the skipped count and the tickets and
 // moves the epoch on, so that the state is ready for the next call on the plan.
+//
+// Small plans do without the finish kernel (SELF): the workgroup whose item is decided last
+// carries out the skipped items and readies the state.
 
 // Waits until this wavefront's outstanding vector-memory operations have completed (stores
 // included: gfx9-family stores are counted by vmcnt until they are acknowledged).
@@ -917,7 +920,7 @@ __device__ __forceinline__ bool wait_for_bucket(const StepState& st, uint32_t b,
       // every item is filed at most once, so the list cannot overflow unless an earlier call on the plan was
       // cut short between its two launches; then the item is reported lost rather than written out of bounds
       const uint32_t slot = atomicAdd(&st.ctl[kCtlSkipped], 1u);
-      if (slot < st.skipped_cap) st.skipped[slot] = self;  // read by the finish kernel, after this launch has ended
+      if (slot < st.skipped_cap) ctl_store(&st.skipped[slot], self);  // read by whoever finishes the call
       else ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_INCOMPLETE);
     }
   }
@@ -1041,11 +1044,66 @@ __device__ __forceinline__ void apply_item(const StepState& st, const Entry& en,
     adam_chunk<GDT, true, WB, U, false>(en, coef, k);
 }
 
-template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB>
+// Carries out the items whose wait expired (none, as a rule; one after the other if there are any -- an expired wait has
+// cost about a second already), with the coefficient their bucket's ready word holds by now.  Returns status bits.
+template <int GDT, bool WB, uint32_t U, int MODE>
+__device__ __forceinline__ uint32_t finish_items(const StepState& st, uint32_t epoch, const AdamK& ka, StepShared& sh) {
+  const uint32_t n_skipped = min(ctl_load(&st.ctl[kCtlSkipped]), st.skipped_cap);
+  uint32_t bits = 0;
+  if (n_skipped != 0) {
+    const AdamK k = resolve(ka);
+    for (uint32_t i = 0; i < n_skipped; ++i) {
+      const uint32_t idx = ctl_load(&st.skipped[i]);
+      const Entry en = read_entry(&st.apply_tab[idx]);
+      const unsigned long long r = __hip_atomic_load(&st.ready[en.bucket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((uint32_t)(r >> 32) != epoch) {  // cannot happen: squared-norm items never wait
+        bits |= BCA_STATUS_INCOMPLETE;
+        continue;
+      }
+      apply_item<GDT, WB, U, MODE>(st, en, idx, __uint_as_float((uint32_t)r), k, sh);
+      __syncthreads();  // LAMB: sh.pp / sh.uu are reused by the next item
+    }
+  }
+  return bits;
+}
+
+// Hands the status bits collected during the call to the caller and resets the per-call state, epoch included (thread 0).
+__device__ __forceinline__ void finish_state(const StepState& st, uint32_t epoch, uint32_t bits, int32_t* status) {
+  if (status != nullptr) *status = (int32_t)(ctl_load(&st.ctl[kCtlStatus]) | bits);
+  ctl_store(&st.ctl[kCtlStatus], 0u);
+  ctl_store(&st.ctl[kCtlSkipped], 0u);
+  ctl_store(&st.ctl[kCtlAbort], 0u);
+  for (uint32_t y = 0; y < 8u; ++y) ctl_store(&st.ctl[kCtlTicket + 32u * y], 0u);
+  ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
+}
+
+// SELF: a workgroup whose item is decided (its squared norms are published, or its wait has ended, one way or the other, with
+// everything it has filed in place) counts itself in one of kDoneSlots words, so that no word sees more than a share of
+// the increments (about 8 ns each, one after the other); those that complete a word count it in one more.  Thread 0 only.
+__device__ __forceinline__ uint32_t count_done(const StepState& st) {
+  return atomicAdd(&st.ctl[kCtlDone + 32u * (blockIdx.x % kDoneSlots)], 1u);
+}
+// Whether the workgroup that `count_done` gave `before` is the last of the launch.
+__device__ __forceinline__ bool last_done(const StepState& st, uint32_t n_work, uint32_t before) {
+  const uint32_t slot = blockIdx.x % kDoneSlots;
+  if (before + 1u != n_work / kDoneSlots + (slot < n_work % kDoneSlots ? 1u : 0u)) return false;
+  ctl_store(&st.ctl[kCtlDone + 32u * slot], 0u);  // left at zero for the next call
+  const uint32_t slots = n_work < kDoneSlots ? n_work : (uint32_t)kDoneSlots;
+  if (atomicAdd(&st.ctl[kCtlDone + 32u * kDoneSlots], 1u) + 1u != slots) return false;
+  ctl_store(&st.ctl[kCtlDone + 32u * kDoneSlots], 0u);
+  return true;
+}
+
+// SELF: the launch needs no k_finish behind it.  Every workgroup is counted once its item is decided, and the one that
+// completes the count does what k_finish would.  Adam items are counted when their wait has ended, before they load
+// anything, so that the round trip is hidden behind the item itself.
+template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB, bool SELF = false>
 __global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,
                                                   const float* __restrict__ thresholds, float* __restrict__ norms,
-                                                  float* __restrict__ coefs, const AdamK ka) {
+                                                  float* __restrict__ coefs, const AdamK ka, int32_t* status) {
   __shared__ StepShared sh;
+  constexpr int MODE = LAMB ? kModeLamb : kModeAdam;
+  uint32_t before = 0;  // SELF, thread 0: what count_done returned
   const AdamK k = resolve(ka);
   uint32_t ticket;
   if constexpr (TICKETS) {
@@ -1078,11 +1136,30 @@ __global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* _
   if (kind == kItemAdam) {
     const uint32_t idx = item & 0x3fffffffu;
     const Entry en = read_entry(&st.apply_tab[idx]);
-    if (wait_for_bucket(st, en.bucket, epoch, idx, sh))
-      apply_item<GDT, WB, U, LAMB ? kModeLamb : kModeAdam>(st, en, idx, sh.coef, k, sh);
+    const bool ready = wait_for_bucket(st, en.bucket, epoch, idx, sh);
+    if constexpr (SELF) {
+      if (threadIdx.x == 0) {
+        if (!ready) wait_vmem();  // what the wait has filed has arrived
+        before = count_done(st);  // not looked at before the item is done
+      }
+    }
+    if (ready) apply_item<GDT, WB, U, MODE>(st, en, idx, sh.coef, k, sh);
   } else {
     // squared-norm items carry their chunk count (1 .. 4) in bits 28..29
     norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
+    if constexpr (SELF) {
+      if (threadIdx.x == 0) {
+        wait_vmem();  // status bits and ready word have arrived
+        before = count_done(st);
+      }
+    }
+  }
+  if constexpr (SELF) {
+    if (threadIdx.x == 0) sh.item = last_done(st, n_work, before) ? 1u : 0u;
+    __syncthreads();
+    if (sh.item == 0u) return;
+    const uint32_t bits = finish_items<GDT, WB, U, MODE>(st, epoch, ka, sh);
+    if (threadIdx.x == 0) finish_state(st, epoch, bits, status);
   }
 }
 
@@ -1477,41 +1554,14 @@ __global__ __launch_bounds__(kBlock) void k_clip_scale(const Chunk* __restrict__
   if (coef != 1.f) scale_norm_chunk<GDT>(en, coef);
 }
 
-// Follows every k_step launch on the stream; ONE workgroup, so that it costs a launch and one round trip to
-// memory when there is nothing to do.  (1) Carries out the items whose wait expired (none, as a rule; one after
-// the other if there are any -- an expired wait has cost about a second already), with the coefficient their
-// bucket's ready word holds by now.  (2) Hands the status bits collected during the call to the caller and
-// resets the per-call state, epoch included.
+// Follows every k_step launch that does not finish itself; ONE workgroup, so that it costs a launch and one round trip to
+// memory when there is nothing to do.
 template <int GDT, bool WB, uint32_t U, int MODE>
 __global__ __launch_bounds__(kBlock) void k_finish(StepState st, int32_t* status, const AdamK ka) {
   __shared__ StepShared sh;
-  const uint32_t tid = threadIdx.x;
   const uint32_t epoch = ctl_load(&st.ctl[kCtlEpoch]);
-  const uint32_t n_skipped = min(ctl_load(&st.ctl[kCtlSkipped]), st.skipped_cap);
-  const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);  // complete: the launch that ORed into it has ended
-  uint32_t bits = 0;
-  if (n_skipped != 0) {
-    const AdamK k = resolve(ka);
-    for (uint32_t i = 0; i < n_skipped; ++i) {
-      const uint32_t idx = st.skipped[i];
-      const Entry en = read_entry(&st.apply_tab[idx]);
-      const unsigned long long r = __hip_atomic_load(&st.ready[en.bucket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((uint32_t)(r >> 32) != epoch) {  // cannot happen: squared-norm items never wait
-        bits |= BCA_STATUS_INCOMPLETE;
-        continue;
-      }
-      apply_item<GDT, WB, U, MODE>(st, en, idx, __uint_as_float((uint32_t)r), k, sh);
-      __syncthreads();  // LAMB: sh.pp / sh.uu are reused by the next item
-    }
-  }
-  if (tid == 0) {
-    if (status != nullptr) *status = (int32_t)(collected | bits);
-    ctl_store(&st.ctl[kCtlStatus], 0u);
-    ctl_store(&st.ctl[kCtlSkipped], 0u);
-    ctl_store(&st.ctl[kCtlAbort], 0u);
-    for (uint32_t y = 0; y < 8u; ++y) ctl_store(&st.ctl[kCtlTicket + 32u * y], 0u);
-    ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
-  }
+  const uint32_t bits = finish_items<GDT, WB, U, MODE>(st, epoch, ka, sh);
+  if (threadIdx.x == 0) finish_state(st, epoch, bits, status);
 }
 
 // ---- clipping one contiguous bucket without a plan and without allocating ---------------
@@ -1677,16 +1727,30 @@ hipError_t launch_clip_scale(int gdt, const Chunk* norm_tab, uint32_t cn0, uint3
 hipError_t launch_step(int gdt, const StepState& st, const uint32_t* work, uint32_t n_work, const float* thresholds,
                        float* norms, float* coefs, int32_t* status, bool write_back, const AdamK& k, uint32_t unroll,
                        bool tickets, bool lamb, hipEvent_t between, hipStream_t stream) {
+  // Plans of few items finish themselves (kSelfFinishItems); with events to be recorded in between there are two launches.
+  const bool self = !lamb && !tickets && unroll == 1 && between == nullptr && n_work <= kSelfFinishItems;
   if (n_work != 0) {
+    if (self) {
+      pick_gdt(gdt, [&](auto gd) {
+        constexpr int GDT = decltype(gd)::value;
+        if (write_back)
+          hipLaunchKernelGGL((k_step<GDT, true, 1, false, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
+                             thresholds, norms, coefs, k, status);
+        else
+          hipLaunchKernelGGL((k_step<GDT, false, 1, false, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
+                             thresholds, norms, coefs, k, status);
+      });
+      return hipGetLastError();
+    }
     if (lamb) {  // one variant per gradient type and write-back setting: items by workgroup index, no unrolling
       pick_gdt(gdt, [&](auto gd) {
         constexpr int GDT = decltype(gd)::value;
         if (write_back)
           hipLaunchKernelGGL((k_step<GDT, true, 1, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
-                             thresholds, norms, coefs, k);
+                             thresholds, norms, coefs, k, status);
         else
           hipLaunchKernelGGL((k_step<GDT, false, 1, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
-                             thresholds, norms, coefs, k);
+                             thresholds, norms, coefs, k, status);
       });
     } else {
       pick_unroll(unroll, [&](auto uu) {
@@ -1696,7 +1760,7 @@ hipError_t launch_step(int gdt, const StepState& st, const uint32_t* work, uint3
           pick_gdt(gdt, [&](auto gd) {
             constexpr int GDT = decltype(gd)::value;
             hipLaunchKernelGGL((k_step<GDT, WB, U, TK, false>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
-                               thresholds, norms, coefs, k);
+                               thresholds, norms, coefs, k, status);
           });
         });
       });
