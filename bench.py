@@ -38,7 +38,7 @@ MEASURED_TRAFFIC_BYTES = {      # from profiles/k_step_<workload>.txt; a combina
     (5, "f32", True): 10805399362, (3, "bf16", True): 9463045573}
 # The same for the other entry points (all kernels of one call summed), config 3, fp32 gradients
 # (profiles/other_entry_points_bert_large_fp32_50MiB.txt).
-MEASURED_TRAFFIC_OTHER_OPS = {"adam": 9446939648, "norms": 1346181120, "lamb": 13547380736, "clip_lamb": 14914948096}
+MEASURED_TRAFFIC_OTHER_OPS = {"adam": 9446939648, "norms": 1346181120}
 
 def parse():
     ap = argparse.ArgumentParser()
@@ -114,16 +114,20 @@ def other_ops(a, w, plan, g, p, m, v, dev):
         for b in range(lay.n_buckets):
             plan.bucket_clip(b, b + 1, thr_now, norms, coefs, status, stream)
         plan.adam_step(hp, step[0], stream)
-    # algorithmic bytes per element: every sweep's reads and writes, nothing assumed cached
+    # algorithmic bytes per element: every sweep's reads and writes, nothing assumed cached.  LAMB goes once over p, m, v for
+    # tensors of up to 9.4 M elements (3/4 of the 1 024 resident workgroups of 12 288 elements each), and reads p, m, v
+    # again for larger ones; in runs (--lamb-group-mi) for all.
+    swept_twice = 1.0 if a.lamb_group_mi else sum(int(n) for n in lay.tensor_numel if n > 768 * 12288) / lay.n_elements
     ops = {
         "adam": (lambda: plan.adam_step(hp, step[0], stream), 24 + gb,
                  "adam_step: k_adam, g p m v read, p m v written"),
         "norms": (lambda: plan.bucket_clip_norms(0, lay.n_buckets, norms, stream), gb,
                   "bucket_clip_norms: k_sqnorm + k_finalize, g read"),
-        "lamb": (lambda: plan.lamb_step(hp, step[0], trust, stream), (gb + 12 + 8) + (12 + 4),
-                 "lamb_step: k_lamb_moments (g p m v read, m v written), k_lamb_trust, k_lamb_update (p m v read, p written)"),
+        "lamb": (lambda: plan.lamb_step(hp, step[0], trust, stream), gb + 24 + 12 * swept_twice,
+                 "lamb_step: k_lamb (g p m v read, p m v written), k_lamb_tail (p m v of the largest tensors read again)"),
         "clip_lamb": (lambda: plan.bucket_clip_lamb(thr, hp, step[0], 0, norms, coefs, trust, status, stream),
-                      gb + (gb + 12 + 8) + (12 + 4), "bucket_clip_lamb: k_sqnorm + k_finalize, then the three LAMB kernels"),
+                      gb + gb + 24 + 12 * swept_twice,
+                      "bucket_clip_lamb: k_lamb (g read twice, p m v read and written), k_lamb_late, k_lamb_tail"),
         # the paper's two baselines (Sec. 3.2): one coefficient from the whole gradient's norm, so every norm
         # comes before any update and g crosses HBM twice
         "whole_clip_adam": (lambda: plan.bucket_clip_adam(thr_whole, hp, step[0], B.BCA_CLIP_WHOLE_GRADIENT, norms_whole,
