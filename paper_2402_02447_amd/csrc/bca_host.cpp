@@ -363,7 +363,8 @@ void free_device(bca_plan* p) {
   if (p->d_trust) (void)hipFree(p->d_trust);
   if (p->d_lamb_scale) (void)hipFree(p->d_lamb_scale);
   p->d_tensor_off = nullptr, p->d_lamb_sums = nullptr, p->d_trust = nullptr, p->d_lamb_scale = nullptr;
-  if (p->d_lamb_ready) (void)hipFree(p->d_lamb_ready);  // the block that all of these are in
+  for (void* q : {(void*)p->d_lamb_items, (void*)p->d_lamb_items_of, (void*)p->d_lamb_clip_work, (void*)p->d_lamb_late, (void*)p->d_lamb_arrived, (void*)p->d_lamb_ready})
+    if (q) (void)hipFree(q);
   p->d_lamb_items = nullptr, p->d_lamb_items_of = nullptr;
   p->d_lamb_clip_work = nullptr, p->d_lamb_late = nullptr, p->d_lamb_arrived = nullptr, p->d_lamb_ready = nullptr;
   if (p->d_adamk) (void)hipFree(p->d_adamk);
@@ -648,27 +649,22 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
       build_lamb_items(p, (uint32_t)std::max(prop.multiProcessorCount, 1) * kLambResidentPerCu, a2l);
       if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
     }
-    // One block: ready words, arrival counters (both start at zero), bucket_clip_lamb's work list, items of each tensor (one
-    // copy), items, late items.
     const auto alloc_lamb = [&] {
       const size_t n = p->lamb_items.size(), nw = p->lamb_clip_work.size();
-      if (n == 0) return hipSuccess;  // the plan goes in two sweeps
-      const size_t words = (nt + nw + nt + 3) / 4 * 4;  // a multiple of 16 bytes in front of the items
-      const size_t zero = nt * sizeof(unsigned long long) + nt * sizeof(uint32_t);
-      const size_t head = (nt * sizeof(unsigned long long) + words * sizeof(uint32_t) + 15) / 16 * 16;
-      char* base = nullptr;
-      hipError_t err = hipMalloc((void**)&base, head + n * sizeof(LambItem) + n * sizeof(uint32_t));
-      if (err != hipSuccess) return err;
-      p->d_lamb_ready = reinterpret_cast<unsigned long long*>(base);  // the block's address, which is what gets freed
-      p->d_lamb_arrived = reinterpret_cast<uint32_t*>(base + nt * sizeof(unsigned long long));
-      p->d_lamb_clip_work = p->d_lamb_arrived + nt;
-      p->d_lamb_items_of = p->d_lamb_clip_work + nw;
-      p->d_lamb_items = reinterpret_cast<LambItem*>(base + head);
-      p->d_lamb_late = reinterpret_cast<uint32_t*>(p->d_lamb_items + n);
-      std::vector<uint32_t> init(p->lamb_clip_work);
-      init.insert(init.end(), p->lamb_items_of.begin(), p->lamb_items_of.end());
-      if ((err = hipMemset(base, 0, zero)) != hipSuccess) return err;
-      return hipMemcpy(p->d_lamb_clip_work, init.data(), init.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+      hipError_t err = hipSuccess;
+      if (n == 0 ||  // the plan goes in two sweeps
+          (err = hipMalloc((void**)&p->d_lamb_items, n * sizeof(LambItem))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_late, n * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_clip_work, nw * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemcpy(p->d_lamb_clip_work, p->lamb_clip_work.data(), nw * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_items_of, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemcpy(p->d_lamb_items_of, p->lamb_items_of.data(), nt * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_arrived, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMemset(p->d_lamb_arrived, 0, nt * sizeof(uint32_t))) != hipSuccess ||
+          (err = hipMalloc((void**)&p->d_lamb_ready, nt * sizeof(unsigned long long))) != hipSuccess ||
+          (err = hipMemset(p->d_lamb_ready, 0, nt * sizeof(unsigned long long))) != hipSuccess)
+        return err;
+      return hipSuccess;
     };
     const uint32_t first_epoch = 1;  // ready words start at zero: epoch 0 is never current
     if ((e = alloc_table(&p->norm_tab, n_buckets)) != hipSuccess ||
