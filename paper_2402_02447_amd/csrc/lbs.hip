@@ -90,6 +90,17 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 
+// No C++ exception crosses the C boundary.
+template <typename F>
+int no_throw(F&& body) {
+  try {
+    return body();
+  } catch (...) {
+    g_error.clear();  // out of host memory: nothing is allocated to say so
+    return LBS_ERR_HIP;
+  }
+}
+
 struct Params {  // by-value kernel argument
   uint32_t max_len, local_batch, gpus_per_node, n_gpus, snake, stratified;
   uint32_t total;                             // dataset size
@@ -1180,13 +1191,7 @@ void lbs_dataset_destroy(lbs_dataset* ds) {
 
 int lbs_dataset_create(lbs_dataset** out, int device, uint32_t max_len, const uint32_t* cum, uint32_t n_strata,
                        const uint32_t* stratum_end) {
-  int rc;
-  try {  // no C++ exception crosses the C boundary
-    rc = dataset_create(out, device, max_len, cum, n_strata, stratum_end);
-  } catch (...) {
-    rc = LBS_ERR_HIP;
-    g_error.clear();  // out of host memory: nothing is allocated to say so
-  }
+  const int rc = no_throw([&] { return dataset_create(out, device, max_len, cum, n_strata, stratum_end); });
   if (rc != 0 && out && *out) {
     lbs_dataset_destroy(*out);
     *out = nullptr;
@@ -1221,11 +1226,14 @@ static Bins pack_bins(const lbs_dataset* ds, const lbs_run* run) {
   const uint32_t rows = 64u / gpn;
   uint32_t used[2] = {0, 0};
   int bin_of[LBS_MAX_STRATA];
-  std::vector<uint32_t> order(ds->n_strata);
-  for (uint32_t s = 0; s < ds->n_strata; ++s) order[s] = s;
-  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return run->quota[a] > run->quota[b]; });
-  for (const uint32_t s : order) {
-    const uint32_t q = run->quota[s];
+  uint32_t order[LBS_MAX_STRATA];  // by falling quota, equal ones in their order; on the stack: a call allocates nothing
+  for (uint32_t s = 0; s < ds->n_strata; ++s) {
+    uint32_t i = s;
+    for (; i > 0 && run->quota[order[i - 1]] < run->quota[s]; --i) order[i] = order[i - 1];
+    order[i] = s;
+  }
+  for (uint32_t i = 0; i < ds->n_strata; ++i) {
+    const uint32_t s = order[i], q = run->quota[s];
     bin_of[s] = used[0] + q <= rows ? 0 : used[1] + q <= rows ? 1 : -1;
     if (bin_of[s] < 0) return L;
     used[bin_of[s]] += q;
@@ -1315,12 +1323,14 @@ static int simulate_one(const lbs_dataset* ds, const lbs_run* run, uint32_t meth
 
 int lbs_simulate(const lbs_dataset* ds, const lbs_run* run, uint32_t* trial_min, uint32_t* trial_max, uint64_t* sums,
                  void* stream) {
-  if (!ds || !run) return fail(LBS_ERR_NULL, "dataset or run is NULL");
-  return simulate_one(ds, run, run->method, trial_min, trial_max, sums, stream);
+  return no_throw([&] {
+    if (!ds || !run) return fail(LBS_ERR_NULL, "dataset or run is NULL");
+    return simulate_one(ds, run, run->method, trial_min, trial_max, sums, stream);
+  });
 }
 
-int lbs_simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* trial_min, uint32_t* trial_max, uint64_t* sums,
-                     void* stream) {
+static int simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* trial_min, uint32_t* trial_max, uint64_t* sums,
+                        void* stream) {
   if (!ds || !run) return fail(LBS_ERR_NULL, "dataset or run is NULL");
   if (!sums) return fail(LBS_ERR_NULL, "sums is NULL");
   const uint32_t gpn = run->gpus_per_node, lb = run->local_batch, G = run->n_gpus;
@@ -1367,6 +1377,11 @@ int lbs_simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* trial_
   if (prev >= 0 && prev != ds->device) (void)hipSetDevice(prev);
   if (e != hipSuccess) return fail(LBS_ERR_HIP, std::string("launching the simulation: ") + hipGetErrorString(e));
   return 0;
+}
+
+int lbs_simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* trial_min, uint32_t* trial_max, uint64_t* sums,
+                     void* stream) {
+  return no_throw([&] { return simulate_all(ds, run, trial_min, trial_max, sums, stream); });
 }
 
 }  // extern "C"
