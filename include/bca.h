@@ -207,6 +207,14 @@ int bca_plan_lamb_run(const bca_plan* plan, uint32_t i, uint32_t* first_tensor, 
  * squared-norm item of a bucket comes before every Adam item of that bucket. */
 uint32_t bca_plan_num_work_items(const bca_plan* plan);
 int bca_plan_work_item(const bca_plan* plan, uint32_t i, uint32_t* kind, uint32_t* first, uint32_t* count);
+/* The work list of LAMB in one pass (see lamb_step), in the order its workgroups take it: of lamb_step (clip = 0) or of
+ * bucket_clip_lamb (clip = 1).  bca_plan_num_lamb_items is 0 where that call goes in two sweeps, which also depends on
+ * where the bound tensors lie.  Item i is kind 0 or 2 as above, or kind 1 = LAMB on `count` consecutive chunks of
+ * BCA_TABLE_LAMB from `first` on, all of `tensor`; *held: 1 if they wait on the chip for that tensor's ratio, 0 if the
+ * tensor is swept twice.  Any out pointer may be NULL.  BCA_ERR_RANGE for i out of range. */
+uint32_t bca_plan_num_lamb_items(const bca_plan* plan, int clip);
+int bca_plan_lamb_item(const bca_plan* plan, int clip, uint32_t i, uint32_t* kind, uint32_t* first, uint32_t* count,
+                       uint32_t* tensor, uint32_t* held);
 /* Chunks of bucket b are [first, first + count); for BCA_TABLE_LAMB b is a tensor index. */
 int bca_plan_bucket_chunks(const bca_plan* plan, int table, uint32_t b, uint32_t* first, uint32_t* count);
 

@@ -25,7 +25,7 @@ _ERR_NAMES = {-1: "BCA_ERR_NULL", -2: "BCA_ERR_LAYOUT", -3: "BCA_ERR_RANGE", -4:
               -5: "BCA_ERR_UNBOUND", -6: "BCA_ERR_HIP", -7: "BCA_ERR_DTYPE", -8: "BCA_ERR_ALIGN", -9: "BCA_ERR_NOMEM"}
 
 EXPORTS = ["bca_alg1_thresholds", "bucket_clip_flat", "bca_plan_create", "bca_plan_bind", "bca_plan_set_decay_mask", "bca_plan_set_device_hyper", "bca_plan_destroy", "bca_plan_num_buckets",
-           "bca_plan_num_groups", "bca_plan_norm_item_chunks", "bca_plan_num_work_items", "bca_plan_work_item", "bca_plan_num_lamb_runs", "bca_plan_lamb_run", "bca_plan_num_chunks", "bca_plan_chunk_info", "bca_plan_bucket_chunks",
+           "bca_plan_num_groups", "bca_plan_norm_item_chunks", "bca_plan_num_work_items", "bca_plan_work_item", "bca_plan_num_lamb_runs", "bca_plan_lamb_run", "bca_plan_num_lamb_items", "bca_plan_lamb_item", "bca_plan_num_chunks", "bca_plan_chunk_info", "bca_plan_bucket_chunks",
            "bucket_clip_norms", "bucket_clip_apply", "bucket_clip", "adam_step", "bucket_clip_adam", "lamb_step",
            "bucket_clip_lamb", "bca_plan_profile", "bca_plan_profile_read", "bca_plan_wait_stats", "bca_copy_bytes", "bca_last_error",
            "bca_version"]
@@ -120,6 +120,9 @@ def load_library():
     L.bca_plan_num_lamb_runs.argtypes = [vp]
     L.bca_plan_num_lamb_runs.restype = u32
     L.bca_plan_lamb_run.argtypes = [vp, u32, C.POINTER(u32), C.POINTER(u32)]
+    L.bca_plan_num_lamb_items.argtypes = [vp, i32]
+    L.bca_plan_num_lamb_items.restype = u32
+    L.bca_plan_lamb_item.argtypes = [vp, i32, u32, C.POINTER(u32), C.POINTER(u32), C.POINTER(u32), C.POINTER(u32), C.POINTER(u32)]
     L.bca_plan_num_chunks.argtypes = [vp, i32]
     L.bca_plan_num_chunks.restype = u32
     L.bca_plan_chunk_info.argtypes = [vp, i32, u32, C.POINTER(u32), C.POINTER(u64), C.POINTER(u32), C.POINTER(u32)]
@@ -264,6 +267,18 @@ class Plan:
         for i in range(int(self._L.bca_plan_num_work_items(self._h))):
             _check(self._L.bca_plan_work_item(self._h, i, C.byref(k), C.byref(f), C.byref(c)))
             out.append((k.value, f.value, c.value))
+        return out
+
+    def n_lamb_items(self, clip: bool) -> int:
+        """Work items of lamb_step / bucket_clip_lamb in one pass; 0 where that call goes in two sweeps."""
+        return int(self._L.bca_plan_num_lamb_items(self._h, int(clip)))
+
+    def lamb_items(self, clip: bool):
+        """That work list as (kind, first, count, tensor, held) tuples (bca_plan_lamb_item)."""
+        out, x = [], [C.c_uint32() for _ in range(5)]
+        for i in range(self.n_lamb_items(clip)):
+            _check(self._L.bca_plan_lamb_item(self._h, int(clip), i, *(C.byref(y) for y in x)))
+            out.append(tuple(y.value for y in x))
         return out
 
     def n_chunks(self, table: int = BCA_TABLE_APPLY) -> int:

@@ -403,6 +403,21 @@ hipError_t upload_table(const bca_plan* p, Table* t) {
   return hipMemcpy(t->d_chunks, table.data(), table.size() * sizeof(Chunk), hipMemcpyHostToDevice);
 }
 
+// Where a tensor's p, m and v start has no say in the order of LAMB's sums, with one exception: elements in front of the
+// vectors that are 16-byte aligned in all three (see vector_head).
+bool has_vector_head(uint64_t p, uint64_t m, uint64_t v) { return (((p ^ m) | (p ^ v)) & 15u) == 0 && (p & 15u) != 0; }
+
+// Whether too much of the plan lies so that LAMB in one pass is the slower way (see kLambIrregularShare).
+bool lamb_irregular(const bca_plan* p) {
+  uint64_t irregular = 0, all = 0;
+  for (uint32_t t = 0; t < p->n_tensors; ++t) {
+    all += p->tensor_numel[t];
+    // full chunks start at multiples of 1024 elements, so that a tensor's lie alike
+    if (has_vector_head(p->bound_p[t], p->bound_m[t], p->bound_v[t])) irregular += p->tensor_numel[t];
+  }
+  return irregular > all / kLambIrregularShare;
+}
+
 // The same for the items of LAMB in one pass.
 hipError_t upload_lamb_items(const bca_plan* p) {
   if (p->lamb_items.empty()) return hipSuccess;
@@ -413,9 +428,7 @@ hipError_t upload_lamb_items(const bca_plan* p) {
     it.g = p->bound_g[c.tensor] + c.begin * gsize;
     it.p = p->bound_p[c.tensor] + c.begin * 4, it.m = p->bound_m[c.tensor] + c.begin * 4, it.v = p->bound_v[c.tensor] + c.begin * 4;
     if (!p->decay[c.tensor]) it.flags |= kChunkNoDecay;
-    // no vector head (see vector_head): p, m and v aligned alike, at 16 bytes, or not alike
-    const bool alike = (((it.p ^ it.m) | (it.p ^ it.v)) & 15u) == 0;
-    if (c.len == kDefaultChunkApply && (!alike || (it.p & 15u) == 0)) it.flags |= kLambRegular;
+    if (c.len == kDefaultChunkApply && !has_vector_head(it.p, it.m, it.v)) it.flags |= kLambRegular;
   }
   return hipMemcpy(p->d_lamb_items, items.data(), items.size() * sizeof(LambItem), hipMemcpyHostToDevice);
 }
@@ -628,6 +641,13 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
   if (p->work.size() >= (1ull << 24))
     return fail(BCA_ERR_RANGE, "too many chunks for one launch; raise chunk_norm / chunk_apply");
 
+  // LAMB in one pass for plans in the library's own cut; a caller who tunes the cut, the runs or the launches gets those
+  const auto lamb_items = [&](int n_cus, const std::vector<uint32_t>& a2l) {
+    if (chunk_apply != kDefaultChunkApply || (p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) return;
+    build_lamb_items(p, (uint32_t)std::max(n_cus, 1) * kLambResidentPerCu, a2l);
+    if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
+  };
+  if (device < 0) lamb_items(kHostPlanCus, apply_to_lamb_map(p));
   if (device >= 0) {
     int n_dev = 0;
     hipError_t e = hipGetDeviceCount(&n_dev);
@@ -644,11 +664,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
     const size_t nb = n_buckets;
     const size_t nl = std::max<size_t>(p->lamb_tab.chunks.size(), 1), nt = std::max<size_t>(n_tensors, 1);
     const std::vector<uint32_t> a2l = apply_to_lamb_map(p);
-    // LAMB in one pass for plans in the library's own cut; a caller who tunes the cut, the runs or the launches gets those
-    if (chunk_apply == kDefaultChunkApply && !(p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) {
-      build_lamb_items(p, (uint32_t)std::max(prop.multiProcessorCount, 1) * kLambResidentPerCu, a2l);
-      if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
-    }
+    lamb_items(prop.multiProcessorCount, a2l);
     const auto alloc_lamb = [&] {
       const size_t n = p->lamb_items.size(), nw = p->lamb_clip_work.size();
       hipError_t err = hipSuccess;
@@ -742,6 +758,7 @@ static int plan_bind(bca_plan* p, void* const* grads, float* const* params, floa
   }
   hipError_t e = upload_all_tables(p);
   if (e != hipSuccess) return fail_hip(e, "uploading the chunk tables");
+  p->lamb_irregular = !p->lamb_items.empty() && lamb_irregular(p);
   p->bound = true;
   return BCA_OK;
 }
@@ -814,6 +831,36 @@ int bca_plan_lamb_run(const bca_plan* p, uint32_t i, uint32_t* first_tensor, uin
   if (i >= p->lamb_groups.size()) return fail(BCA_ERR_RANGE, "run index out of range");
   if (first_tensor) *first_tensor = p->lamb_groups[i].first;
   if (end_tensor) *end_tensor = p->lamb_groups[i].second;
+  return BCA_OK;
+}
+
+static bool lamb_in_one_pass(const bca_plan* p, bool clip) {
+  return (clip ? p->lamb_clip_one_pass : p->lamb_one_pass) && !p->lamb_irregular;
+}
+
+uint32_t bca_plan_num_lamb_items(const bca_plan* p, int clip) {
+  if (!p || !lamb_in_one_pass(p, clip != 0)) return 0;
+  return (uint32_t)(clip ? p->lamb_clip_work.size() : p->lamb_items.size());
+}
+
+int bca_plan_lamb_item(const bca_plan* p, int clip, uint32_t i, uint32_t* kind, uint32_t* first, uint32_t* count,
+                       uint32_t* tensor, uint32_t* held) {
+  if (!p) return fail(BCA_ERR_NULL, "plan is NULL");
+  if (i >= bca_plan_num_lamb_items(p, clip)) return fail(BCA_ERR_RANGE, "LAMB item index out of range");
+  const uint32_t item = clip ? p->lamb_clip_work[i] : (kItemAdam << 30) | i, k = item >> 30;
+  if (kind) *kind = k;
+  if (k == kItemAdam) {
+    const LambItem& it = p->lamb_items[item & 0x3fffffffu];
+    if (first) *first = it.first;
+    if (count) *count = it.count;
+    if (tensor) *tensor = it.tensor;
+    if (held) *held = (it.flags & kLambHeld) ? 1u : 0u;
+    return BCA_OK;
+  }
+  if (first) *first = item & 0x0fffffffu;
+  if (count) *count = k == kItemNorm ? ((item >> 28) & 3u) + 1u : 0u;
+  if (tensor) *tensor = 0;
+  if (held) *held = 0;
   return BCA_OK;
 }
 
@@ -1140,7 +1187,7 @@ static int lamb_impl(bca_plan* p, const float* thresholds, const bca_adam* hp, u
   const Table& TL = p->lamb_tab;
   const uint32_t nl = (uint32_t)TL.chunks.size();
   hipError_t e = hipSuccess;
-  if (thresholds ? p->lamb_clip_one_pass : p->lamb_one_pass) {
+  if (lamb_in_one_pass(p, thresholds != nullptr)) {
     const size_t n_work = thresholds ? p->lamb_clip_work.size() : p->lamb_items.size();
     e = launch_lamb(p->grad_dtype, step_state(p), lamb_state(p, trust ? trust : p->d_trust),
                     p->d_lamb_clip_work, (uint32_t)n_work, thresholds != nullptr, thresholds,

@@ -170,6 +170,7 @@ constexpr uint32_t kLambKeep = 8u;     // moments are stored cacheable: the tail
 // Workgroups of k_lamb that are resident at a time on a compute unit: what __launch_bounds__ asks for (128 VGPRs), and four
 // times the 33 KiB of LDS fit in 160 KiB.
 constexpr uint32_t kLambResidentPerCu = 4;
+constexpr int kHostPlanCus = 256;  // compute units that a host-only plan (device -1) is made for: one MI355X
 // A tensor is held if its items, with whatever lies between them in the work list, are at most this share of what is
 // resident on the whole GPU (3/4: a tensor's first workgroups hold their slots until its last one is through).
 constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
@@ -178,6 +179,12 @@ constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
 // 12.3 / 18.5 us, 3.2 M 29.3 / 32.5, 7 M 50 / 45, 11 M 78 / 65; bucket_clip_lamb 3.2 M 42.4 / 45.6, 7 M 65 / 62);
 // with nothing held, two sweeps by items stream worse than chunk by chunk (four tensors of 16.8 M: 484 / 504 us).
 constexpr uint64_t kLambOnePassElems = 5ull << 20;
+// Bound plans go in one pass if at most this share of their elements (1/8) is in tensors whose p, m and v start alike but off
+// 16 bytes (parameters packed into one buffer without padding).  Those are swept chunk by chunk, and read again for the
+// update while the workgroup holds its slot.  Sixteen tensors of 4 M of which k are one element off, two sweeps / one pass,
+// lamb_step: k = 0 418 / 365 us, 1 419 / 403, 2 409 / 404, 3 416 / 437, 4 412 / 435, 8 425 / 462; bucket_clip_lamb: 454 / 383,
+// 456 / 422, 448 / 427, 454 / 461, 451 / 461, 459 / 536; sixty tensors of 300 001 packed: 124 / 172 and 145 / 184.
+constexpr uint64_t kLambIrregularShare = 8;
 // Polls of a tensor's ready word before a held item gives up: some milliseconds, fifty times what the largest tensors
 // take.  Short, because giving up costs little (the tail kernel reads the item again), and because two such launches on
 // one GPU at a time can hold the slots that each other's tensors are waiting for.
@@ -290,7 +297,8 @@ struct bca_plan {
   std::vector<bca::LambItem> lamb_items;  // addresses not filled in
   std::vector<uint32_t> lamb_items_of, lamb_clip_work;
   uint32_t lamb_first_large = 0;  // items from here on are of tensors that are not held
-  bool lamb_one_pass = false, lamb_clip_one_pass = false;  // which calls go that way
+  bool lamb_one_pass = false, lamb_clip_one_pass = false;  // which calls go that way ...
+  bool lamb_irregular = false;  // ... unless the bound tensors are not placed for it
   bca::LambItem* d_lamb_items = nullptr;
   uint32_t* d_lamb_items_of = nullptr;
   uint32_t* d_lamb_clip_work = nullptr;

@@ -43,3 +43,41 @@ with lbs.Dataset(cum, ends, device=0) as ds:
 print("went through")
 """)
     assert "went through" in out
+
+
+def test_lamb_goes_in_two_sweeps_where_the_parameters_do_not_lie_for_one_pass(device):
+    """Which kernels lamb_step and bucket_clip_lamb enqueue: by the share of the elements in tensors whose p, m and v start
+    alike but off 16 bytes, and after a second bind that mends or spoils the placement."""
+    fake_device.run(device, """
+MI, hp = 1 << 20, B.AdamHyper()
+def bind(plan, sizes, off):                     # off: per tensor, the element offsets of g, p, m, v
+    base = [[(1 << 40) + (k << 36) + (t << 26) + 4 * o[k] for t, o in enumerate(off)] for k in range(4)]
+    plan.bind(*base)
+def forms(plan):
+    plan.lamb_step(hp, 1, 64)
+    a = [k for k, _ in kernels()]
+    plan.bucket_clip_lamb(64, hp, 1, 0, 64, 64, 64, 64)
+    b = [k for k, _ in kernels()]
+    one = (a == ["k_lamb", "k_lamb_tail"], b == ["k_lamb", "k_lamb_late", "k_lamb_tail"])
+    two = (a == ["k_lamb_moments", "k_lamb_trust", "k_lamb_update"] * len(plan.lamb_runs()),
+           b == ["k_step", "k_finish", "k_lamb_trust", "k_lamb_update"])
+    assert one[0] != two[0] and one[1] != two[1], (a, b)
+    assert (plan.n_lamb_items(False) > 0, plan.n_lamb_items(True) > 0) == one
+    return one
+
+aligned, packed, grads, mutual = (0, 0, 0, 0), (1, 1, 1, 1), (1, 0, 0, 0), (0, 1, 2, 3)
+sizes = [MI] * 16
+plan = B.Plan.from_layout(W.layout_flat_split(sizes, 2 * MI), B.BCA_GRAD_F32)
+for n_off in (0, 1, 2, 3, 16):                  # an eighth of the elements is the limit
+    bind(plan, sizes, [packed] * n_off + [aligned] * (16 - n_off))
+    assert forms(plan) == ((n_off <= 2,) * 2), n_off
+for off in (aligned, grads, mutual, (3, 2, 2, 1)):      # these are no obstacle
+    bind(plan, sizes, [off] * 16)
+    assert forms(plan) == (True, True), off
+for off in (packed, (0, 3, 3, 3), (0, 2, 2, 2), (1, 5, 1, 9)):
+    bind(plan, sizes, [off] * 16)
+    assert forms(plan) == (False, False), off
+bind(plan, sizes, [aligned] * 16)
+assert forms(plan) == (True, True)
+plan.close()
+""")
