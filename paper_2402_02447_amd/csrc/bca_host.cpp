@@ -284,6 +284,12 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     }
     group_end.push_back((uint32_t)p->lamb_items.size());
   }
+  // Tensors cut into many small items (buckets that end inside them, or sizes just above a chunk or two)
+  p->lamb_badly_cut.assign(p->n_tensors, 0);
+  for (uint32_t t = 0; t < p->n_tensors; ++t) {
+    const uint64_t k = p->lamb_items_of[t];
+    p->lamb_badly_cut[t] = k > 1 && p->tensor_numel[t] < k * std::min<uint64_t>(kLambItemElemsMany, k * kLambItemElemsFew);
+  }
   // Held: all of the tensor's items, and those between them, fit on the GPU at once with room to spare.
   large_elems = 0;
   for (uint32_t t = 0; t < p->n_tensors; ++t)
@@ -292,6 +298,7 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     p->lamb_items.clear();
     return;
   }
+  const bool small = all_elems < kLambSmallElems && all_elems < p->lamb_items.size() * kLambItemElemsMany;
   // held items first, the others behind them: the order in which lamb_step works on them
   std::vector<LambItem> sorted;
   std::vector<uint32_t> place(p->lamb_items.size());
@@ -328,7 +335,7 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
   }
   p->lamb_clip_one_pass = true;
   // lamb_step, unless the tensors that are not held are more than one run of its two sweeps would take
-  p->lamb_one_pass = large_elems <= kLambGroupElems;
+  p->lamb_one_pass = large_elems <= kLambGroupElems && !small;
 }
 
 void free_profile(bca_plan* p) {
@@ -413,7 +420,8 @@ bool lamb_irregular(const bca_plan* p) {
   for (uint32_t t = 0; t < p->n_tensors; ++t) {
     all += p->tensor_numel[t];
     // full chunks start at multiples of 1024 elements, so that a tensor's lie alike
-    if (has_vector_head(p->bound_p[t], p->bound_m[t], p->bound_v[t])) irregular += p->tensor_numel[t];
+    const bool head = !p->bound_p.empty() && has_vector_head(p->bound_p[t], p->bound_m[t], p->bound_v[t]);
+    if (head || p->lamb_badly_cut[t]) irregular += p->tensor_numel[t];
   }
   return irregular > all / kLambIrregularShare;
 }
@@ -646,6 +654,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
     if (chunk_apply != kDefaultChunkApply || (p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) return;
     build_lamb_items(p, (uint32_t)std::max(n_cus, 1) * kLambResidentPerCu, a2l);
     if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
+    p->lamb_irregular = !p->lamb_items.empty() && lamb_irregular(p);
   };
   if (device < 0) lamb_items(kHostPlanCus, apply_to_lamb_map(p));
   if (device >= 0) {

@@ -184,7 +184,20 @@ constexpr uint64_t kLambOnePassElems = 5ull << 20;
 // update while the workgroup holds its slot.  Sixteen tensors of 4 M of which k are one element off, two sweeps / one pass,
 // lamb_step: k = 0 418 / 365 us, 1 419 / 403, 2 409 / 404, 3 416 / 437, 4 412 / 435, 8 425 / 462; bucket_clip_lamb: 454 / 383,
 // 456 / 422, 448 / 427, 454 / 461, 451 / 461, 459 / 536; sixty tensors of 300 001 packed: 124 / 172 and 145 / 184.
+// The same goes for tensors that are badly cut: of k > 1 items, with fewer elements an item than kLambItemElemsFew * k, at most
+// kLambItemElemsMany (full ones have 12 288).  Every item of a tensor holds a slot until the last one is through, however
+// few elements it has; a tensor of two or three items has little to wait for and pays for its arrivals only.  Two sweeps /
+// one pass, lamb_step and bucket_clip_lamb: 64 tensors of 1 M in buckets of 5 000 elements (1 700 an item) 412 / 955 us and
+// 467 / 1 144, of 10 000 (3 300) 406 / 530 and 446 / 637, of 20 000 (5 000) 403 / 452 and 442 / 511, of 50 000 (8 300)
+// 404 / 377 and 446 / 425; 64 M elements in tensors of 1 500 (two items of 750) 638 / 756 and 878 / 1 119, of 2 000 (1 000)
+// 568 / 610 and 746 / 882, of 3 000 (1 500) 541 / 466 and 640 / 639.
 constexpr uint64_t kLambIrregularShare = 8;
+constexpr uint64_t kLambItemElemsFew = 640, kLambItemElemsMany = 8192;
+// lamb_step takes plans below this size in one pass only if their items have kLambItemElemsMany elements on average: they
+// are little more than the items resident at a time, and short items then push full ones into a second round.  6 M and 8 M
+// elements in tensors of 9 000 (4 500 an item) 46.6 / 51.2 and 60.7 / 64.4, of 12 300 (6 150) 45.4 / 49.2 and 59.8 / 67.2,
+// of 100 000 (10 000) 45.1 / 42.6 and 57 / 53; 16 M in tensors of 9 000 118 / 111.
+constexpr uint64_t kLambSmallElems = 12ull << 20;
 // Polls of a tensor's ready word before a held item gives up: some milliseconds, fifty times what the largest tensors
 // take.  Short, because giving up costs little (the tail kernel reads the item again), and because two such launches on
 // one GPU at a time can hold the slots that each other's tensors are waiting for.
@@ -296,6 +309,7 @@ struct bca_plan {
   // bucket_clip_lamb's work list
   std::vector<bca::LambItem> lamb_items;  // addresses not filled in
   std::vector<uint32_t> lamb_items_of, lamb_clip_work;
+  std::vector<uint8_t> lamb_badly_cut;    // per tensor, see kLambItemElemsFew
   uint32_t lamb_first_large = 0;  // items from here on are of tensors that are not held
   bool lamb_one_pass = false, lamb_clip_one_pass = false;  // which calls go that way ...
   bool lamb_irregular = false;  // ... unless the bound tensors are not placed for it
