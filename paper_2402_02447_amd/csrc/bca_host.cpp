@@ -292,9 +292,14 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
   }
   // Held: all of the tensor's items, and those between them, fit on the GPU at once with room to spare.
   large_elems = 0;
-  for (uint32_t t = 0; t < p->n_tensors; ++t)
-    if (p->lamb_items_of[t] != 0 && (uint64_t)last_item[t] - first_item[t] + 1u > most) large_elems += p->tensor_numel[t];
-  if (large_elems > all_elems / 2) {
+  uint64_t wide_elems = 0;  // in tensors of which no two fit
+  for (uint32_t t = 0; t < p->n_tensors; ++t) {
+    if (p->lamb_items_of[t] == 0) continue;
+    const uint64_t span = (uint64_t)last_item[t] - first_item[t] + 1u;
+    if (span > most) large_elems += p->tensor_numel[t];
+    if (span > slots / 2) wide_elems += p->tensor_numel[t];
+  }
+  if (large_elems > all_elems / 2 || wide_elems > all_elems - all_elems / kLambNarrowShare) {
     p->lamb_items.clear();
     return;
   }

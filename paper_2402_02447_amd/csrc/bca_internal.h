@@ -179,6 +179,13 @@ constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
 // 12.3 / 18.5 us, 3.2 M 29.3 / 32.5, 7 M 50 / 45, 11 M 78 / 65; bucket_clip_lamb 3.2 M 42.4 / 45.6, 7 M 65 / 62);
 // with nothing held, two sweeps by items stream worse than chunk by chunk (four tensors of 16.8 M: 484 / 504 us).
 constexpr uint64_t kLambOnePassElems = 5ull << 20;
+// ... and if at least this share of them (1/4) is in tensors that fill no more than half the slots.  Of tensors beyond that no
+// two are resident at a time, so that the chip idles while one waits for its ratio, unless smaller ones fill in.  Two sweeps / one
+// pass, all tensors of k items, lamb_step and bucket_clip_lamb: k = 500 374 / 352 us and 416 / 379, 512 381 / 376 and 419 / 397,
+// 520 389 / 410 and 428 / 421, 534 399 / 436 and 442 / 444, 576 401 / 421 and 434 / 433, 640 394 / 406 and 427 / 415; layers of
+// width 1280, two thirds of whose elements are in tensors of 534 items, 850 / 820 and 927 / 869, of width 1536 (768 items)
+// 869 / 868 and 946 / 902.
+constexpr uint64_t kLambNarrowShare = 4;
 // Bound plans go in one pass if at most this share of their elements (1/8) is in tensors whose p, m and v start alike but off
 // 16 bytes (parameters packed into one buffer without padding).  Those are swept chunk by chunk, and read again for the
 // update while the workgroup holds its slot.  Sixteen tensors of 4 M of which k are one element off, two sweeps / one pass,

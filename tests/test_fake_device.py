@@ -86,15 +86,17 @@ plan.close()
 """)
 
 
-def test_lamb_goes_in_two_sweeps_where_short_items_hold_the_slots():
-    """Tensors cut into items of few elements, by buckets that end inside them or by their own size: the form of a host-only
+def test_lamb_goes_in_two_sweeps_where_slots_would_idle():
+    """Tensors cut into items of few elements, by buckets that end inside them or by their own size, and tensors that take more
+    than half the slots with too little beside them: the form of a host-only
     plan (which lies as one whose tensors start on 16 bytes)."""
     MI = 1 << 20
     for sizes, cap, want in [
             ([MI] * 16, 1 << 40, (1, 1)), ([MI] * 16, 50_000, (1, 1)), ([MI] * 16, 20_000, (0, 0)), ([MI] * 16, 5_000, (0, 0)), ([MI] * 16, 1_000, (0, 0)),
             ([1_000] * 16_000, 4 * MI, (1, 1)), ([1_500] * 11_000, 4 * MI, (0, 0)), ([2_000] * 8_000, 4 * MI, (0, 0)), ([3_000] * 6_000, 4 * MI, (1, 1)),
             ([9_000] * 2_000, 4 * MI, (1, 1)), ([9_000] * 700, 4 * MI, (0, 1)), ([12_300] * 600, 4 * MI, (0, 1)), ([12_300] * 1_400, 4 * MI, (1, 1)),
-            ([100_000] * 63, 4 * MI, (1, 1)), ([MI] * 14 + [1_500] * 1_200, 1 << 40, (1, 1)), ([MI] * 14 + [1_500] * 1_500, 1 << 40, (0, 0))]:
+            ([100_000] * 63, 4 * MI, (1, 1)), ([512 * 12_288] * 6, 1 << 40, (1, 1)), ([513 * 12_288] * 6, 1 << 40, (0, 0)),
+            ([8 * MI] * 3 + [MI] * 8, 1 << 40, (1, 1)), ([8 * MI] * 3 + [MI] * 7, 1 << 40, (0, 0)), ([MI] * 14 + [1_500] * 1_200, 1 << 40, (1, 1)), ([MI] * 14 + [1_500] * 1_500, 1 << 40, (0, 0))]:
         lay = W.layout_flat_split(sizes, cap)
         with B.Plan.from_layout(lay, B.BCA_GRAD_F32, device=-1) as plan:
             got = tuple(int(plan.n_lamb_items(clip) > 0) for clip in (False, True))
