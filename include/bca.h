@@ -307,8 +307,7 @@ int bucket_clip_adam(bca_plan* plan, const float* thresholds /*DEVICE [B]*/, con
  * for that are swept twice).  Others take two sweeps: moments + per-tensor sums, then the
  * parameter update; lamb_step run by run of tensors (bca_tuning.lamb_group_elems),
  * bucket_clip_lamb with the squared norms and the first sweep as one pipelined launch
- * (separate launches under BCA_TUNE_MULTI_LAUNCH).  Same results bit for bit either way (up to
- * the grouping of fp32 terms in the ratio's sums where gradients are not aligned as p is). */
+ * (separate launches under BCA_TUNE_MULTI_LAUNCH).  Same results bit for bit either way. */
 int lamb_step(bca_plan* plan, const bca_adam* hp /*HOST*/, uint64_t step, float* trust /*DEVICE or NULL*/,
               void* stream);
 int bucket_clip_lamb(bca_plan* plan, const float* thresholds /*DEVICE [B]*/, const bca_adam* hp /*HOST*/,

@@ -396,11 +396,38 @@ hipError_t alloc_table(Table* t, uint32_t n_buckets) {
   return e;
 }
 
+// Where a tensor's p, m and v start has no say in the order of LAMB's sums, with one exception: elements in front of the
+// vectors that are 16-byte aligned in all three (see vector_head).
+bool has_vector_head(uint64_t p, uint64_t m, uint64_t v) { return (((p ^ m) | (p ^ v)) & 15u) == 0 && (p & 15u) != 0; }
+
+// Whether too much of the plan lies so that LAMB in one pass is the slower way (see kLambIrregularShare).
+bool lamb_irregular(const bca_plan* p) {
+  if (!p->lamb_layout_one_pass && !p->lamb_layout_clip_one_pass) return false;
+  uint64_t irregular = 0, all = 0;
+  for (uint32_t t = 0; t < p->n_tensors; ++t) {
+    all += p->tensor_numel[t];
+    // full chunks start at multiples of 1024 elements, so that a tensor's lie alike
+    const bool head = !p->bound_p.empty() && has_vector_head(p->bound_p[t], p->bound_m[t], p->bound_v[t]);
+    if (head || p->lamb_badly_cut[t]) irregular += p->tensor_numel[t];
+  }
+  return irregular > all / kLambIrregularShare;
+}
+
+// Whether p, m and v have a common alignment (which a few leading elements bring to 16 bytes) that the gradients do not share.
+bool gradients_off(const Chunk& c, uint64_t gsize) {
+  if (((c.p ^ c.m) | (c.p ^ c.v)) & 15u) return false;
+  const uint64_t head = ((16u - (c.p & 15u)) & 15u) / 4u;
+  return ((c.g + head * gsize) & (4u * gsize - 1u)) != 0;
+}
+
 // Writes a table's device copy from the bound pointers and the decay mask.
 hipError_t upload_table(const bca_plan* p, Table* t) {
   const uint64_t gsize = grad_bytes(p->grad_dtype);
   std::vector<Chunk> table(std::max<size_t>(t->chunks.size(), 1));
   memset(table.data(), 0, table.size() * sizeof(Chunk));
+  const bool irregular = p->lamb_irregular;
+  const uint32_t lamb_by_element = (p->lamb_layout_one_pass && !irregular ? 0u : kChunkLambByElement) |
+                                   (p->lamb_layout_clip_one_pass && !irregular ? 0u : kChunkClipLambByElement);
   for (size_t i = 0; i < t->chunks.size(); ++i) {
     const ChunkInfo& c = t->chunks[i];
     table[i].g = p->bound_g[c.tensor] + c.begin * gsize;
@@ -411,24 +438,9 @@ hipError_t upload_table(const bca_plan* p, Table* t) {
     table[i].bucket = c.bucket;
     table[i].tensor = c.tensor;
     table[i].flags = p->decay[c.tensor] ? 0u : kChunkNoDecay;
+    if (lamb_by_element != 0u && gradients_off(table[i], gsize)) table[i].flags |= lamb_by_element;
   }
   return hipMemcpy(t->d_chunks, table.data(), table.size() * sizeof(Chunk), hipMemcpyHostToDevice);
-}
-
-// Where a tensor's p, m and v start has no say in the order of LAMB's sums, with one exception: elements in front of the
-// vectors that are 16-byte aligned in all three (see vector_head).
-bool has_vector_head(uint64_t p, uint64_t m, uint64_t v) { return (((p ^ m) | (p ^ v)) & 15u) == 0 && (p & 15u) != 0; }
-
-// Whether too much of the plan lies so that LAMB in one pass is the slower way (see kLambIrregularShare).
-bool lamb_irregular(const bca_plan* p) {
-  uint64_t irregular = 0, all = 0;
-  for (uint32_t t = 0; t < p->n_tensors; ++t) {
-    all += p->tensor_numel[t];
-    // full chunks start at multiples of 1024 elements, so that a tensor's lie alike
-    const bool head = !p->bound_p.empty() && has_vector_head(p->bound_p[t], p->bound_m[t], p->bound_v[t]);
-    if (head || p->lamb_badly_cut[t]) irregular += p->tensor_numel[t];
-  }
-  return irregular > all / kLambIrregularShare;
 }
 
 // The same for the items of LAMB in one pass.
@@ -656,10 +668,15 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
 
   // LAMB in one pass for plans in the library's own cut; a caller who tunes the cut, the runs or the launches gets those
   const auto lamb_items = [&](int n_cus, const std::vector<uint32_t>& a2l) {
-    if (chunk_apply != kDefaultChunkApply || (p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) return;
+    if (chunk_apply != kDefaultChunkApply) return;
     build_lamb_items(p, (uint32_t)std::max(n_cus, 1) * kLambResidentPerCu, a2l);
+    p->lamb_layout_one_pass = p->lamb_one_pass, p->lamb_layout_clip_one_pass = p->lamb_clip_one_pass;
+    p->lamb_irregular = lamb_irregular(p);
     if (tuning && tuning->lamb_group_elems) p->lamb_one_pass = false;
-    p->lamb_irregular = !p->lamb_items.empty() && lamb_irregular(p);
+    if (p->tune_flags & BCA_TUNE_MULTI_LAUNCH) {
+      p->lamb_one_pass = p->lamb_clip_one_pass = false;
+      p->lamb_items.clear(), p->lamb_clip_work.clear();
+    }
   };
   if (device < 0) lamb_items(kHostPlanCus, apply_to_lamb_map(p));
   if (device >= 0) {
@@ -770,9 +787,9 @@ static int plan_bind(bca_plan* p, void* const* grads, float* const* params, floa
     p->bound_g[t] = (uint64_t)(uintptr_t)grads[t], p->bound_p[t] = (uint64_t)(uintptr_t)params[t];
     p->bound_m[t] = (uint64_t)(uintptr_t)exp_avg[t], p->bound_v[t] = (uint64_t)(uintptr_t)exp_avg_sq[t];
   }
+  p->lamb_irregular = lamb_irregular(p);
   hipError_t e = upload_all_tables(p);
   if (e != hipSuccess) return fail_hip(e, "uploading the chunk tables");
-  p->lamb_irregular = !p->lamb_items.empty() && lamb_irregular(p);
   p->bound = true;
   return BCA_OK;
 }

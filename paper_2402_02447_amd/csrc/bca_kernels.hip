@@ -695,11 +695,8 @@ __device__ __forceinline__ void lamb_moments_chunk(const Entry& en, float coef, 
   const float wd = chunk_wd(en, k);
   const uint32_t len = en.len;
   uint32_t head = vector_head(len, en.p, en.m, en.v);
-  // Gradients that do not lie at the parameters' alignment: this sweep is then faster element by element (40 M elements,
-  // gradients one element off, both sweeps: 259 us against 266; 1.3 M elements, bf16: 14.5 against 15.6), unlike the Adam
-  // sweep and k_lamb, and unlike arrays whose p, m and v differ among themselves (302 against 280).
   if constexpr (!AGENT)
-    if ((((en.p ^ en.m) | (en.p ^ en.v)) & 15u) == 0 && ((en.g + (uint64_t)head * gsize) & (4u * gsize - 1u)) != 0) head = len;
+    if (en.flags & (FUSED ? kChunkClipLambByElement : kChunkLambByElement)) head = len;
   const uint32_t nvec = (len - head) / 4u;
   const uint32_t tail0 = head + nvec * 4u;
   void* gv = reinterpret_cast<void*>(en.g + (uint64_t)head * gsize);

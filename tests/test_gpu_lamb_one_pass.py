@@ -14,20 +14,30 @@ TYPES = [(torch.float32, B.BCA_GRAD_F32), (torch.float16, B.BCA_GRAD_F16), (torc
 # edges of a chunk (1024), of an item (12 chunks), several items, an empty tensor, single elements
 SIZES = [1, 0, 1023, 1024, 1025, 12 * 1024, 12 * 1024 + 1, 13 * 1024, 24 * 1024, 100_003, 7, 300_000, 2]
 SIZES += [5 << 20]     # plans below this many elements go in two sweeps
+PATTERN = 7.0          # around the tensors
 
 
 def _state(sizes, dtype, seed, offset=0):
+    """g, p, m, v; `offset`: elements by which they (or, as four numbers, each of them) start off an allocation."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
+    og, op, om, ov = (offset,) * 4 if isinstance(offset, int) else offset
 
-    def place(t):
-        buf = torch.zeros(t.numel() + offset + 8, dtype=t.dtype, device="cuda")
-        buf[offset:offset + t.numel()] = t
-        return buf[offset:offset + t.numel()]
-    g = [place((torch.randn(n, generator=gen, device="cuda") * 1e-3).to(dtype)) for n in sizes]
-    p = [place(torch.randn(n, generator=gen, device="cuda") * 0.02) for n in sizes]
-    m = [place(torch.randn(n, generator=gen, device="cuda") * 3e-4) for n in sizes]
-    v = [place((torch.rand(n, generator=gen, device="cuda") + 0.5) * 1e-6) for n in sizes]
+    def place(t, o):
+        buf = torch.full((t.numel() + o + 16,), PATTERN, dtype=t.dtype, device="cuda")
+        buf[o:o + t.numel()] = t
+        return buf[o:o + t.numel()]
+    g = [place((torch.randn(n, generator=gen, device="cuda") * 1e-3).to(dtype), og) for n in sizes]
+    p = [place(torch.randn(n, generator=gen, device="cuda") * 0.02, op) for n in sizes]
+    m = [place(torch.randn(n, generator=gen, device="cuda") * 3e-4, om) for n in sizes]
+    v = [place((torch.rand(n, generator=gen, device="cuda") + 0.5) * 1e-6, ov) for n in sizes]
     return g, p, m, v
+
+
+def _nothing_outside_touched(state):
+    for t in (t for ts in state for t in ts):
+        o, n = t.storage_offset(), t.numel()
+        buf = torch.empty(0, dtype=t.dtype, device="cuda").set_(t.untyped_storage())
+        assert bool((buf[:o] == PATTERN).all()) and bool((buf[o + n:] == PATTERN).all())
 
 
 class Run:
@@ -130,3 +140,27 @@ def test_two_plans_on_two_streams_at_once():
         a.same(b)
         a.plan.close()
         b.plan.close()
+
+
+# gradients off the parameters' alignment (packed views), everything off, p, m and v that differ among themselves: the last
+# column says whether that can go in one pass
+PLACEMENTS = [((0, 0, 0, 0), True), ((1, 0, 0, 0), True), ((2, 0, 0, 0), True), ((3, 1, 1, 1), False), ((1, 2, 3, 0), True), ((0, 1, 0, 0), True), ((1, 1, 1, 1), False)]
+
+
+@pytest.mark.parametrize("dtype,gdt", TYPES)
+@pytest.mark.parametrize("offset,one_pass", PLACEMENTS)
+@pytest.mark.parametrize("clip,flags", [(False, 0), (True, 0), (True, B.BCA_WRITE_BACK_GRADS)])
+def test_same_bits_by_every_form_wherever_the_arrays_start(dtype, gdt, offset, one_pass, clip, flags):
+    lay = W.layout_flat_split(SIZES, 2 << 20)
+    mask = np.arange(len(SIZES)) % 3
+    forms = [dict(), dict(spin_limit=1), dict(tune_flags=B.BCA_TUNE_MULTI_LAUNCH), dict(lamb_group_elems=1 << 20)]
+    runs = [Run(lay, dtype, gdt, 6, offset, mask, **tuning) for tuning in forms]
+    assert [r.plan.n_lamb_items(clip) > 0 for r in runs] == [one_pass, one_pass, False, one_pass and clip]
+    for r in runs:
+        for step in (3, 4):
+            r.go(clip, step, flags)
+        torch.cuda.synchronize()
+        r.same(runs[0])
+        _nothing_outside_touched(r.state)
+    for r in runs:
+        r.plan.close()
