@@ -1250,19 +1250,22 @@ __device__ __forceinline__ void tensor_ratio(const LambState& ls, uint32_t t, ui
 __device__ __forceinline__ bool wait_for_tensor(const StepState& st, const LambState& ls, uint32_t t, uint32_t epoch,
                                                 uint32_t self, float* scale) {
   const uint32_t limit = min(st.spin_limit, kTrustSpinLimit);
-  uint32_t polls = 0;
+  uint32_t polls = 0, aborted = 0;
   for (;;) {
     const unsigned long long r = __hip_atomic_load(&ls.ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // once one wait has expired nobody waits any more: items that start after that do not hold their slots at all
+    if ((polls & 15u) == 0) aborted = ctl_load(&st.ctl[kCtlLateAbort]);
     if ((uint32_t)(r >> 32) == epoch) {
       *scale = __uint_as_float((uint32_t)r);
       return true;
     }
-    if (++polls > limit) break;
-    if ((polls & 15u) == 0 && ctl_load(&st.ctl[kCtlLateAbort]) != 0u) break;
+    if (aborted != 0u || ++polls > limit) break;
     __builtin_amdgcn_s_sleep(16);
   }
-  ctl_store(&st.ctl[kCtlLateAbort], 1u);
-  ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_TIMEOUT);
+  if (aborted == 0u) {  // the others have nothing to add
+    ctl_store(&st.ctl[kCtlLateAbort], 1u);
+    ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_TIMEOUT);
+  }
   const uint32_t slot = atomicAdd(&st.ctl[kCtlLate], 1u);
   if (slot < ls.n_items) ls.late[slot] = self;  // read by the tail kernel
   else ctl_or(&st.ctl[kCtlStatus], BCA_STATUS_INCOMPLETE);
@@ -1422,10 +1425,11 @@ __global__ __launch_bounds__(kBlock, kLambResidentPerCu) void k_lamb(StepState s
 template <int GDT, bool WB>
 __global__ __launch_bounds__(kBlock) void k_lamb_late(StepState st, LambState ls, const AdamK ka) {
   __shared__ LambShared sh;
-  const uint32_t n = min(ctl_load(&st.ctl[kCtlSkipped]), st.skipped_cap);
+  // written by the launch before this one, so plain loads do (see k_lamb_tail)
+  const uint32_t n = min(st.ctl[kCtlSkipped], st.skipped_cap);
   if (n == 0) return;
   const AdamK k = resolve(ka);
-  const uint32_t epoch = ctl_load(&st.ctl[kCtlEpoch]);
+  const uint32_t epoch = st.ctl[kCtlEpoch];
   for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
     const uint32_t i = st.skipped[q];
     const unsigned long long r = __hip_atomic_load(&st.ready[ls.items[i].bucket], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1440,7 +1444,7 @@ __global__ __launch_bounds__(kBlock) void k_lamb_late(StepState st, LambState ls
 
 // Follows every k_lamb launch.  Workgroup w carries out the second sweep over the w-th chunk of the large tensors' items,
 // the most recent one first (its moments are the likeliest to be in cache; a workgroup per item, chunk after chunk,
-// takes 105 instead of 75 us over 31 M elements); the first kLambTailWorkers workgroups share the items
+// takes 105 instead of 75 us over 31 M elements); the first kLambTailWorkers workgroups share the chunks of the items
 // that gave up waiting, and the last of them to be done hands over the status bits and readies the state for the next
 // call.  Tensors without elements get ratio 1.
 // What it reads was written by earlier launches, so plain loads do; thousands of workgroups reading one word at agent scope
@@ -1460,9 +1464,12 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   if (w >= workers) return;
   const uint32_t epoch = st.ctl[kCtlEpoch];
   const uint32_t n_late = min(st.ctl[kCtlLate], ls.n_items), n_skipped = min(st.ctl[kCtlSkipped], st.skipped_cap);
-  for (uint32_t q = w; q < n_late; q += workers) update(ls.late[q], 0u, kLambItemChunks);
-  for (uint32_t q = w; q < n_skipped; q += workers)
-    if (ls.items[st.skipped[q]].flags & kLambHeld) update(st.skipped[q], 0u, kLambItemChunks);
+  for (uint32_t q = w; q < n_late * kLambItemChunks; q += workers)
+    update(ls.late[q / kLambItemChunks], q % kLambItemChunks, q % kLambItemChunks + 1u);
+  for (uint32_t q = w; q < n_skipped * kLambItemChunks; q += workers) {
+    const uint32_t i = st.skipped[q / kLambItemChunks];
+    if (ls.items[i].flags & kLambHeld) update(i, q % kLambItemChunks, q % kLambItemChunks + 1u);
+  }
   for (uint32_t t = w * kBlock + tid; t < ls.n_tensors; t += workers * kBlock) {
     if (ls.items_of[t] == 0u) ls.trust[t] = 1.f;
     // cannot happen: every item's sums have been counted by now
@@ -1470,10 +1477,10 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   }
   wait_vmem();  // a status bit raised above has arrived before this worker is counted
   __syncthreads();
-  if (tid == 0 && atomicAdd(&st.ctl[kCtlTailDone], 1u) + 1u == workers) {
+  if (tid == 0 && last_done(st, workers, count_done(st))) {
     const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);
     if (status != nullptr) *status = (int32_t)collected;
-    for (const uint32_t word : {kCtlStatus, kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort, kCtlTailDone}) ctl_store(&st.ctl[word], 0u);
+    for (const uint32_t word : {kCtlStatus, kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort}) ctl_store(&st.ctl[word], 0u);
     ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
   }
 }
@@ -1880,8 +1887,8 @@ hipError_t launch_lamb(int gdt, const StepState& st, const LambState& ls, const 
       e = hipGetLastError();
     }
     if (e != hipSuccess || !clip) return;
-    if (write_back) hipLaunchKernelGGL((k_lamb_late<GDT, true>), dim3(kLambTailWorkers), dim3(kBlock), 0, stream, st, ls, k);
-    else hipLaunchKernelGGL((k_lamb_late<GDT, false>), dim3(kLambTailWorkers), dim3(kBlock), 0, stream, st, ls, k);
+    if (write_back) hipLaunchKernelGGL((k_lamb_late<GDT, true>), dim3(kLambLateWorkers), dim3(kBlock), 0, stream, st, ls, k);
+    else hipLaunchKernelGGL((k_lamb_late<GDT, false>), dim3(kLambLateWorkers), dim3(kBlock), 0, stream, st, ls, k);
     e = hipGetLastError();
   });
   if (e != hipSuccess) return e;
