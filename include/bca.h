@@ -53,12 +53,16 @@ typedef struct bca_plan bca_plan; /* opaque */
 /* bits of the device status word written by the clip calls */
 #define BCA_STATUS_NONFINITE 1     /* some bucket's sum of squares is Inf or NaN          */
 #define BCA_STATUS_BAD_THRESHOLD 2 /* some threshold is <= 0 or NaN: that bucket not clipped */
-#define BCA_STATUS_TIMEOUT 4       /* a bounded wait inside a pipelined launch expired; the work it
-                                      held back was carried out by the call's finish kernel: the
-                                      result is complete and the same bits, the call was only slow */
+#define BCA_STATUS_TIMEOUT 4       /* a bounded wait inside a pipelined launch expired (after about a second for a bucket's
+                                      coefficient, about a millisecond for a tensor's LAMB ratio, which another kernel
+                                      that holds compute units for that long is enough to cause); the work it held back
+                                      was carried out at the end of the call: the result is complete and the same
+                                      bits, the call was only slow.  lamb_step has no status word and does not say so */
 #define BCA_STATUS_INCOMPLETE 8    /* a work item could not be carried out at all: p, m, v (or g) are
                                       partly updated.  Cannot happen by construction; reported
-                                      rather than assumed                                       */
+                                      rather than assumed.  Raised in a call without a status word (lamb_step has
+                                      none), it is reported by the plan's next bucket_clip_adam or bucket_clip_lamb
+                                      that is one pipelined launch and has one                                     */
 
 /* flags of bucket_clip_adam */
 #define BCA_WRITE_BACK_GRADS 1u       /* also store the scaled gradient into g (what Alg. 1
@@ -125,10 +129,11 @@ typedef struct bca_tuning {
                             per compute unit (160 KiB each) -- the sweep streams fastest with few
                             wavefronts in flight.  0: default (48 KiB); 1: none; at most 65536       */
   uint32_t spin_limit;   /* pipelined calls (bucket_clip_adam, bucket_clip_lamb): polls of a bucket's
-                            ready word after which a waiting work item gives up, is handed to the call's finish
-                            kernel and BCA_STATUS_TIMEOUT is reported; 0: default (2^18, about a second).  Small
-                            values exist for tests of that path: every kernel still ends normally and the
-                            result is the same                                                            */
+                            ready word after which a waiting work item gives up, is carried out at the end of the
+                            call and BCA_STATUS_TIMEOUT is reported; 0: default (2^18, about a second).  LAMB in one
+                            pass, lamb_step included, waits for a tensor's ratio too: for at most this many polls and at
+                            most 512 (about 0.7 ms), whatever is given here.  Small values exist for tests of that
+                            path: every kernel still ends normally and the result is the same                  */
   uint32_t norm_item_chunks; /* fused calls: consecutive squared-norm chunks one work item reads, 1 .. 4;
                             0: chosen from the bucket sizes so that an item reads 16 Ki .. 64 Ki elements
                             (1 when chunk_norm is given)                                               */

@@ -1163,7 +1163,7 @@ int bucket_clip_adam(bca_plan* p, const float* thresholds, const bca_adam* hp, u
     const StepState ss = step_state(p);
     if (ev) (void)hipEventRecord(ev[0], s);
     hipError_t e = launch_step(p->grad_dtype, ss, p->d_work, (uint32_t)p->work.size(), thresholds, nm, cf,
-                               st, (flags & BCA_WRITE_BACK_GRADS) != 0, k, p->unroll_apply,
+                               status, (flags & BCA_WRITE_BACK_GRADS) != 0, k, p->unroll_apply,
                                (p->tune_flags & BCA_TUNE_TICKETS) != 0, false, ev ? ev[1] : nullptr, s);
     if (e != hipSuccess) return fail_hip(e, "launching the fused step kernel");
     if (ev) (void)hipEventRecord(ev[2], s);
@@ -1223,7 +1223,7 @@ static int lamb_impl(bca_plan* p, const float* thresholds, const bca_adam* hp, u
     e = launch_lamb(p->grad_dtype, step_state(p), lamb_state(p, trust ? trust : p->d_trust),
                     p->d_lamb_clip_work, (uint32_t)n_work, thresholds != nullptr, thresholds,
                     norms ? norms : p->d_norms, coefs ? coefs : p->d_coefs,
-                    thresholds ? (status ? status : p->d_status) : nullptr, (flags & BCA_WRITE_BACK_GRADS) != 0, k, s);
+                    status, (flags & BCA_WRITE_BACK_GRADS) != 0, k, s);
     return e == hipSuccess ? (int)BCA_OK : fail_hip(e, "launching the LAMB kernels");
   }
   if (thresholds) {
@@ -1234,7 +1234,7 @@ static int lamb_impl(bca_plan* p, const float* thresholds, const bca_adam* hp, u
       // squared norms, coefficients and LAMB's first sweep as one pipelined launch (the fused Adam step's
       // work list and waiting scheme; the first sweep's second read of the gradients is served from cache)
       e = launch_step(p->grad_dtype, step_state(p), p->d_work, (uint32_t)p->work.size(), thresholds, nm, cw,
-                      st, (flags & BCA_WRITE_BACK_GRADS) != 0, k, 1, false, true, nullptr, s);
+                      status, (flags & BCA_WRITE_BACK_GRADS) != 0, k, 1, false, true, nullptr, s);
       if (e != hipSuccess) return fail_hip(e, "launching the fused clip + LAMB moments kernel");
     } else {
       const Table& TN = p->norm_tab;

@@ -1069,8 +1069,10 @@ __device__ __forceinline__ uint32_t finish_items(const StepState& st, uint32_t e
 
 // Hands the status bits collected during the call to the caller and resets the per-call state, epoch included (thread 0).
 __device__ __forceinline__ void finish_state(const StepState& st, uint32_t epoch, uint32_t bits, int32_t* status) {
-  if (status != nullptr) *status = (int32_t)(ctl_load(&st.ctl[kCtlStatus]) | bits);
-  ctl_store(&st.ctl[kCtlStatus], 0u);
+  const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]) | bits;
+  if (status != nullptr) *status = (int32_t)collected;
+  // without a status word a lost item is reported by the plan's next pipelined call that has one
+  ctl_store(&st.ctl[kCtlStatus], status != nullptr ? 0u : collected & (uint32_t)BCA_STATUS_INCOMPLETE);
   ctl_store(&st.ctl[kCtlSkipped], 0u);
   ctl_store(&st.ctl[kCtlAbort], 0u);
   for (uint32_t y = 0; y < 8u; ++y) ctl_store(&st.ctl[kCtlTicket + 32u * y], 0u);
@@ -1480,7 +1482,9 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   if (tid == 0 && last_done(st, workers, count_done(st))) {
     const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);
     if (status != nullptr) *status = (int32_t)collected;
-    for (const uint32_t word : {kCtlStatus, kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort}) ctl_store(&st.ctl[word], 0u);
+    // as in finish_state; lamb_step has no status word
+    ctl_store(&st.ctl[kCtlStatus], status != nullptr ? 0u : collected & (uint32_t)BCA_STATUS_INCOMPLETE);
+    for (const uint32_t word : {kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort}) ctl_store(&st.ctl[word], 0u);
     ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
   }
 }
