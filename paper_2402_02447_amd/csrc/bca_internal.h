@@ -28,7 +28,9 @@ struct alignas(16) Chunk {
 constexpr uint32_t kChunkNoDecay = 1u;  // the chunk's tensor is exempt from weight decay
 // LAMB's first sweep takes the chunk element by element: in lamb_step, behind clipping.  For gradients that do not lie at the
 // parameters' alignment where p, m and v do lie alike: 40 M elements, gradients one element off, both sweeps 259 us against 266
-// with vectors; 1.3 M elements, bf16, 14.5 against 15.6 (p, m and v that differ among themselves: 302 against 280).  Only in plans
+// with vectors; 1.3 M elements, bf16, 14.5 against 15.6 (p, m and v that differ among themselves: 302 against 280).  That is call
+// after call on the same arrays; with them out of the caches vectors are the faster way (1 M 19.9 against 18.0, 4 M 47.6 / 39.7,
+// 40 M behind clipping 351 / 335).  Only in plans
 // which that call never takes in one pass, whatever the tuning: k_lamb has vectors throughout, and so its sums' order.
 constexpr uint32_t kChunkLambByElement = 2u, kChunkClipLambByElement = 4u;
 static_assert(sizeof(Chunk) == 48, "chunk table entries are 3 x 16 bytes");
@@ -208,8 +210,9 @@ constexpr uint64_t kLambItemElemsFew = 640, kLambItemElemsMany = 8192;
 // lamb_step takes plans below this size in one pass only if their items have kLambItemElemsMany elements on average: they
 // are little more than the items resident at a time, and short items then push full ones into a second round.  6 M and 8 M
 // elements in tensors of 9 000 (4 500 an item) 46.6 / 51.2 and 60.7 / 64.4, of 12 300 (6 150) 45.4 / 49.2 and 59.8 / 67.2,
-// of 100 000 (10 000) 45.1 / 42.6 and 57 / 53; 16 M in tensors of 9 000 118 / 111.
-constexpr uint64_t kLambSmallElems = 12ull << 20;
+// of 100 000 (10 000) 45.1 / 42.6 and 57 / 53; 16 M in tensors of 9 000 118 / 111.  With the data out of the caches the two are
+// within 4 % of each other at 6 M and 8 M, and one pass is 1 to 8 % faster at 10 M, hence the line below that.
+constexpr uint64_t kLambSmallElems = 9ull << 20;
 // Polls of a tensor's ready word before a held item gives up: about 0.7 ms, ten times what the largest tensors take.
 // Short, because the slots may be held by what does not go away soon (another launch of this kind whose tensors wait for the
 // slots that this one holds, any long kernel), and because giving up costs little: the rest of the launch then holds nothing and goes as
