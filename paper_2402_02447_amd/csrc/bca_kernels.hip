@@ -90,6 +90,11 @@ template <>
 struct Anywhere<u16x8> {
   typedef u16x8 type __attribute__((aligned(2)));
 };
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <>
+struct Anywhere<u32x4> {
+  typedef u32x4 type __attribute__((aligned(4)));
+};
 template <bool NT, typename T>
 __device__ __forceinline__ T ldv(const T* p) {
   typedef typename Anywhere<T>::type U;
@@ -101,6 +106,38 @@ __device__ __forceinline__ void stv(T* p, T x) {
   typedef typename Anywhere<T>::type U;
   if constexpr (NT) __builtin_nontemporal_store(x, (BCA_GLOBAL U*)p);
   else *(BCA_GLOBAL U*)p = x;
+}
+
+// Pieces of eight 16-bit elements that start in the middle of a 32-bit word: p (piece 0 of this lane), p + stride, ...; lane
+// l + 1 has the pieces behind those of lane l.  128-bit loads that start on words of 32 bits cost what aligned ones do; from the middle of
+// one they are 10 to 20 % slower (squared norms of 128 M bf16 one element off 45.5 us before any of this, with loads from
+// where the pieces start 53.7, like this 45.1; out of the caches 53.0 / 59.4 / 48.3; clip of 16 M 16.9 / 19.9 / 17.1).  So a lane loads
+// the words from the one that holds its first element on, takes the word behind them from the next lane (lane 63 loads it), and
+// shifts them into place.  Every word that is read holds an element of the piece.
+template <bool NT, uint32_t U, typename W>
+__device__ __forceinline__ void ld_odd(W (&x)[U], const W* p, uint32_t stride) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p) - 2u;
+  u32x4 w[U];
+  uint32_t next[U] = {};
+#pragma unroll
+  for (uint32_t u = 0; u < U; ++u) w[u] = ldv<NT>(reinterpret_cast<const u32x4*>(a) + u * stride);
+  if ((threadIdx.x & 63u) == 63u) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const BCA_GLOBAL uint32_t* q = (const BCA_GLOBAL uint32_t*)(a + 16u) + u * stride * 4u;
+      if constexpr (NT) next[u] = __builtin_nontemporal_load(q);
+      else next[u] = *q;
+    }
+  }
+  loads_issued();
+#pragma unroll
+  for (uint32_t u = 0; u < U; ++u) {
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)next[u], (int)w[u].x, 0x130, 0xf, 0xf, false);  // wave_shl:1
+    u32x4 r;
+    r.x = __builtin_amdgcn_alignbit(w[u].y, w[u].x, 16u), r.y = __builtin_amdgcn_alignbit(w[u].z, w[u].y, 16u);
+    r.z = __builtin_amdgcn_alignbit(w[u].w, w[u].z, 16u), r.w = __builtin_amdgcn_alignbit(y, w[u].w, 16u);
+    x[u] = __builtin_bit_cast(W, r);
+  }
 }
 
 // ---- chunk table access -----------------------------------------------------------
@@ -319,10 +356,13 @@ __device__ __forceinline__ void add_squares(const typename Grad<GDT>::wide& x, f
 // in every lane).  Per lane the squares are accumulated in fp32 (four independent
 // accumulators, at most chunk_elems/1024 terms each), then the lanes are combined
 // in fp64 by butterfly shuffles.  Wavefronts never wait for each other.
-template <int GDT, bool NT, uint32_t U = 8>  // U: 128-bit loads in flight per lane (the result does not depend on it)
+// LOADS: 128-bit loads in flight per lane, ODD: whether 16-bit elements off 32-bit words go by ld_odd (the result depends on
+// neither).
+template <int GDT, bool NT, uint32_t LOADS = 8, bool ODD = true>
 __device__ __forceinline__ double sqnorm_chunk(const Entry& en) {
   typedef Grad<GDT> G;
   constexpr uint32_t VE = G::VE;  // elements per 128-bit load: 4 (fp32) or 8 (fp16, bf16)
+  constexpr uint32_t whole = kDefaultChunkNorm / (VE * kBlock), U = LOADS < whole ? LOADS : whole;  // no more than a chunk has
   const uint32_t tid = threadIdx.x;
   const uint64_t ga = en.g;
   const uint32_t len = en.len;
@@ -339,8 +379,15 @@ __device__ __forceinline__ double sqnorm_chunk(const Entry& en) {
     const uint32_t j0 = base + tid;
     wide x[U];
     if (base + kBlock * U <= nvec) {
+      bool odd = false;
+      if constexpr (ODD && VE == 8) {
+        odd = (ga & 2u) != 0;
+        if (odd) ld_odd<NT>(x, gw + j0, kBlock);
+      }
+      if (!odd) {
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) x[u] = ldv<NT>(gw + j0 + u * kBlock);
+        for (uint32_t u = 0; u < U; ++u) x[u] = ldv<NT>(gw + j0 + u * kBlock);
+      }
     } else {
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
@@ -1025,7 +1072,8 @@ __device__ __forceinline__ void norm_item(const StepState& st, uint32_t kind, ui
   for (uint32_t c = idx; c < idx + count; ++c) {
     const Entry en = read_entry(&st.norm_tab[c]);
     b = en.bucket;
-    store_partial(st, c, sqnorm_chunk<GDT, false>(en));
+    // not ODD: k_step would need 70 registers instead of 55, and lose an eighth of its wavefronts wherever the gradients lie
+    store_partial(st, c, sqnorm_chunk<GDT, false, 8, false>(en));
   }
   norm_arrive(st, b, count, epoch, thresholds, norms, coefs, sh);
 }
@@ -1501,8 +1549,12 @@ __device__ __forceinline__ void scale_norm_chunk(const Entry& en, float coef) {
     wide* gw = reinterpret_cast<wide*>(en.g);
     const uint32_t tid = threadIdx.x;
     wide x[R];
+    if (G::VE == 8 && (en.g & 2u) != 0) {
+      if constexpr (G::VE == 8) ld_odd<false>(x, gw + tid, kBlock);
+    } else {
 #pragma unroll
-    for (uint32_t u = 0; u < R; ++u) x[u] = ldv<false>(gw + tid + u * kBlock);
+      for (uint32_t u = 0; u < R; ++u) x[u] = ldv<false>(gw + tid + u * kBlock);
+    }
     loads_issued();
 #pragma unroll
     for (uint32_t u = 0; u < R; ++u) {

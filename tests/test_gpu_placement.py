@@ -73,3 +73,14 @@ def test_offsets_do_not_change_results(op, dtype, gdt):
                 np.testing.assert_allclose(a.float().numpy(), b.float().numpy(), rtol=1e-5, atol=1e-9)
             else:                 # a chunk's elements go to the same lanes wherever it starts
                 assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), (op, offsets)
+
+
+@pytest.mark.parametrize("dtype,gdt", [(torch.float16, B.BCA_GRAD_F16), (torch.bfloat16, B.BCA_GRAD_BF16), (torch.float32, B.BCA_GRAD_F32)])
+@pytest.mark.parametrize("op", ["clip", "two_calls", "step"])
+def test_whole_squared_norm_chunks_wherever_they_start(op, dtype, gdt):
+    """Buckets that leave chunks of 16 384 elements whole: 16-bit ones off 32-bit words go by a path of their own."""
+    want = _run(op, dtype, gdt, (0, 0, 0, 0), cap=1 << 20)
+    for o in (1, 2, 3, 5, 7, 9, 15):
+        got = _run(op, dtype, gdt, (o, 0, 0, 0), cap=1 << 20)
+        for a, b in zip(got, want):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), o
