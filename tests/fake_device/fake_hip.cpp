@@ -24,7 +24,7 @@ std::vector<Launch>& launches() {
   return v;
 }
 bool g_fail = false;
-unsigned long long g_mallocs = 0;
+unsigned long long g_mallocs = 0, g_frees = 0;
 int g_cus = 256;
 struct Config {
   dim3 grid, block;
@@ -49,6 +49,7 @@ extern "C" {
 // ---- for the tests
 void fake_fail_host_allocations(int on) { g_fail = on != 0; }
 unsigned long long fake_device_allocations() { return g_mallocs; }
+unsigned long long fake_device_frees() { return g_frees; }
 void fake_set_cus(int n) { g_cus = n; }
 unsigned fake_num_launches() { return (unsigned)launches().size(); }
 const char* fake_launch_name(unsigned i) { return names()[launches()[i].kernel].c_str(); }
@@ -86,6 +87,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void* p) {
+  g_frees += p != nullptr;
   free(p);
   return hipSuccess;
 }

@@ -108,3 +108,18 @@ def test_lamb_goes_in_two_sweeps_where_slots_would_idle():
                         if kind == 1:
                             seen[first:first + count] += 1
                     assert (seen == 1).all()
+
+
+def test_lamb_in_one_pass_costs_a_plan_one_allocation(device):
+    """Every plan of some size has its tables, also where only Adam is called: they are one block, given back with the plan."""
+    fake_device.run(device, """
+def allocations(n, **tuning):
+    before = fake.fake_device_allocations()
+    with B.Plan.from_layout(W.layout_flat_split([1 << 20] * n, 1 << 21), B.BCA_GRAD_F32, **tuning) as plan:
+        one = plan.n_lamb_items(True) > 0
+    assert fake.fake_device_allocations() - fake.fake_device_frees() == 0
+    return fake.fake_device_allocations() - before, one
+(small, a), (large, b), (multi, c) = allocations(2), allocations(16), allocations(16, tune_flags=B.BCA_TUNE_MULTI_LAUNCH)
+assert (a, b, c) == (False, True, False)
+assert large == small + 1 == multi + 1, (small, large, multi)
+""")
