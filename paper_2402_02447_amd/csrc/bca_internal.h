@@ -127,13 +127,13 @@ enum : uint32_t {
   // items that waited touch them, and spread over many lines so that they do not queue up behind one address.
   kCtlStats = 384,
   kStatSlots = 256,
-  // LAMB in one pass: held items whose wait for their tensor's ratio expired (their indices are in LambState::late), and the
-  // flag that such a wait has expired
+  // LAMB in one pass: held items whose wait for their tensor's ratio expired (their indices are in LambState::late), the
+  // flag that such a wait has expired, and how many of the tail kernel's workers are done
   kCtlLate = kCtlStats + 32 * kStatSlots,
   kCtlLateAbort = kCtlLate + 32,
-  // k_step that finishes itself: workgroups whose item is decided; k_lamb_tail: workers that are done.  In kDoneSlots words and
-  // one that counts the full ones
-  kCtlDone = kCtlLate + 64,
+  kCtlTailDone = kCtlLate + 64,
+  // k_step that finishes itself: workgroups whose item is decided, in kDoneSlots words and one that counts the full ones
+  kCtlDone = kCtlLate + 96,
   kDoneSlots = 64,
   kCtlWords = kCtlDone + 32 * (kDoneSlots + 1)
 };
@@ -218,14 +218,14 @@ constexpr uint64_t kLambSmallElems = 9ull << 20;
 // slots that this one holds, any long kernel), and because giving up costs little: the rest of the launch then holds nothing and goes as
 // a first sweep, and the tail kernel carries out the second.  Everything given up (a limit of one poll) against two sweeps in a
 // plan of its own, lamb_step: BERT-Large 2.55 / 2.04 ms, BERT-Base 0.79 / 0.68, 59 M elements in tensors of 1 and 4 M
-// 0.42 / 0.36 (in one pass 1.84, 0.61, 0.32); bucket_clip_lamb 3.82 / 2.40, 1.25 / 0.79, 0.67 / 0.42.  With 64 workers and a share
+// 0.42 / 0.36 (in one pass 1.84, 0.61, 0.32); bucket_clip_lamb 4.97 / 2.40, 1.63 / 0.79, 0.87 / 0.42.  With 64 workers and a share
 // of whole items each it was 7.46, 2.17, 1.35 and 17.8, 5.7, 3.1 ms.  Beside a kernel that holds all but one slot of every compute
 // unit for 75 ms, a limit of 4 096 polls cost 6 ms.
 constexpr uint32_t kTrustSpinLimit = 512;
-// Workgroups that share the late items' chunks: enough to stream (512: 3.03 ms, 1 024: 2.64, 2 048: 2.55 on BERT-Large); without late
-// items they cost nothing that can be measured.  Those that carry out whole items behind a clipping launch stay fewer: 2 048 of
-// them add 1 us to a call that needs none.
-constexpr uint32_t kLambTailWorkers = 2048, kLambLateWorkers = 512;
+// Workgroups that share the late items' chunks: enough to stream (512: 3.03 ms, 1 024: 2.64, 2 048: 2.55 on BERT-Large).  Without
+// late items kLambTailFew do what there is.  Those that carry out whole items behind a clipping launch stay fewer: 2 048 of them
+// add 1 us to a call that needs none.
+constexpr uint32_t kLambTailWorkers = 2048, kLambTailFew = 64, kLambLateWorkers = 256;
 struct LambState {
   const Chunk* tab;                 // tensor-major chunks
   const LambItem* items;

@@ -1303,8 +1303,8 @@ __device__ __forceinline__ bool wait_for_tensor(const StepState& st, const LambS
   uint32_t polls = 0, aborted = 0;
   for (;;) {
     const unsigned long long r = __hip_atomic_load(&ls.ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // once one wait has expired nobody waits any more: items that start after that do not hold their slots at all
-    if ((polls & 15u) == 0) aborted = ctl_load(&st.ctl[kCtlLateAbort]);
+    // once one wait has expired nobody waits any more: items that start after that hardly hold their slots
+    if (polls == 1u || (polls & 15u) == 15u) aborted = ctl_load(&st.ctl[kCtlLateAbort]);
     if ((uint32_t)(r >> 32) == epoch) {
       *scale = __uint_as_float((uint32_t)r);
       return true;
@@ -1501,7 +1501,7 @@ __global__ __launch_bounds__(kBlock) void k_lamb_late(StepState st, LambState ls
 // would queue up behind it (10 ns each).  Only workers look at the epoch: it moves on once they are all done, which
 // the other workgroups may still outlast.
 __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls, int32_t* status, const AdamK ka) {
-  const uint32_t w = blockIdx.x, tid = threadIdx.x, workers = min(gridDim.x, kLambTailWorkers);
+  const uint32_t w = blockIdx.x, tid = threadIdx.x;
   const AdamK k = resolve(ka);
   const auto update = [&](uint32_t i, uint32_t from, uint32_t to) {  // chunks [from, to) of item i
     const LambItem* ip = &ls.items[i];
@@ -1511,9 +1511,13 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   };
   const uint32_t back = w / kLambItemChunks, chunk = w % kLambItemChunks;
   if (back < ls.n_items - ls.first_large) update(ls.n_items - 1u - back, chunk, chunk + 1u);
+  if (w >= kLambTailWorkers) return;
+  const uint32_t n_late = min(st.ctl[kCtlLate], ls.n_items), n_skipped = min(st.ctl[kCtlSkipped], st.skipped_cap);
+  // Without late items a few workers do.  The others find zeros here whether they look before the reset below or after it;
+  // with late items there is no reset before all of them have been counted.
+  const uint32_t workers = min(gridDim.x, n_late + n_skipped != 0u ? kLambTailWorkers : kLambTailFew);
   if (w >= workers) return;
   const uint32_t epoch = st.ctl[kCtlEpoch];
-  const uint32_t n_late = min(st.ctl[kCtlLate], ls.n_items), n_skipped = min(st.ctl[kCtlSkipped], st.skipped_cap);
   for (uint32_t q = w; q < n_late * kLambItemChunks; q += workers)
     update(ls.late[q / kLambItemChunks], q % kLambItemChunks, q % kLambItemChunks + 1u);
   for (uint32_t q = w; q < n_skipped * kLambItemChunks; q += workers) {
@@ -1527,12 +1531,12 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   }
   wait_vmem();  // a status bit raised above has arrived before this worker is counted
   __syncthreads();
-  if (tid == 0 && last_done(st, workers, count_done(st))) {
+  if (tid == 0 && atomicAdd(&st.ctl[kCtlTailDone], 1u) + 1u == workers) {
     const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);
     if (status != nullptr) *status = (int32_t)collected;
     // as in finish_state; lamb_step has no status word
     ctl_store(&st.ctl[kCtlStatus], status != nullptr ? 0u : collected & (uint32_t)BCA_STATUS_INCOMPLETE);
-    for (const uint32_t word : {kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort}) ctl_store(&st.ctl[word], 0u);
+    for (const uint32_t word : {kCtlSkipped, kCtlAbort, kCtlLate, kCtlLateAbort, kCtlTailDone}) ctl_store(&st.ctl[word], 0u);
     ctl_store(&st.ctl[kCtlEpoch], epoch + 1u == 0u ? 1u : epoch + 1u);
   }
 }
