@@ -303,7 +303,11 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     p->lamb_items.clear();
     return;
   }
-  const bool small = all_elems < kLambSmallElems && all_elems < p->lamb_items.size() * kLambItemElemsMany;
+  uint64_t shared_elems = 0, shared_items = 0;  // tensors of one item wait for nobody
+  for (uint32_t t = 0; t < p->n_tensors; ++t)
+    if (p->lamb_items_of[t] > 1) shared_elems += p->tensor_numel[t], shared_items += p->lamb_items_of[t];
+  const bool small = p->lamb_items.size() <= 2u * slots && shared_elems > all_elems / kLambIrregularShare &&
+                     shared_elems < shared_items * kLambItemElemsMany;
   // held items first, the others behind them: the order in which lamb_step works on them
   std::vector<LambItem> sorted;
   std::vector<uint32_t> place(p->lamb_items.size());

@@ -207,12 +207,11 @@ constexpr uint64_t kLambNarrowShare = 4;
 // 568 / 610 and 746 / 882, of 3 000 (1 500) 541 / 466 and 640 / 639.
 constexpr uint64_t kLambIrregularShare = 8;
 constexpr uint64_t kLambItemElemsFew = 640, kLambItemElemsMany = 8192;
-// lamb_step takes plans below this size in one pass only if their items have kLambItemElemsMany elements on average: they
-// are little more than the items resident at a time, and short items then push full ones into a second round.  6 M and 8 M
-// elements in tensors of 9 000 (4 500 an item) 46.6 / 51.2 and 60.7 / 64.4, of 12 300 (6 150) 45.4 / 49.2 and 59.8 / 67.2,
-// of 100 000 (10 000) 45.1 / 42.6 and 57 / 53; 16 M in tensors of 9 000 118 / 111.  With the data out of the caches the two are
-// within 4 % of each other at 6 M and 8 M, and one pass is 1 to 8 % faster at 10 M, hence the line below that.
-constexpr uint64_t kLambSmallElems = 9ull << 20;
+//   lamb_step takes plans of at most twice as many items as are resident at a time in one pass only if the items of tensors that
+// have several have kLambItemElemsMany elements on average: short items then push full ones into a second round.  6 M and 8 M
+// elements in tensors of 9 000 (4 500 an item; 1 398 and 1 864 items) 46.6 / 51.2 and 60.7 / 64.4, of 12 300 (6 150; 1 022 and
+// 1 364) 45.4 / 49.2 and 59.8 / 67.2; but of 5 000 (2 500; 2 516 and 3 356) 52.0 / 52.7 and 66.9 / 63.1, of 100 000 (10 000)
+// 45.1 / 42.6 and 57 / 53, and 16 M in tensors of 9 000 118 / 111.
 // Polls of a tensor's ready word before a held item gives up: about 0.7 ms, ten times what the largest tensors take.
 // Short, because the slots may be held by what does not go away soon (another launch of this kind whose tensors wait for the
 // slots that this one holds, any long kernel), and because giving up costs little: the rest of the launch then holds nothing and goes as

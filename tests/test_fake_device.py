@@ -93,8 +93,8 @@ def test_lamb_goes_in_two_sweeps_where_slots_would_idle():
     MI = 1 << 20
     for sizes, cap, want in [
             ([MI] * 16, 1 << 40, (1, 1)), ([MI] * 16, 50_000, (1, 1)), ([MI] * 16, 20_000, (0, 0)), ([MI] * 16, 5_000, (0, 0)), ([MI] * 16, 1_000, (0, 0)),
-            ([1_000] * 16_000, 4 * MI, (1, 1)), ([1_500] * 11_000, 4 * MI, (0, 0)), ([2_000] * 8_000, 4 * MI, (0, 0)), ([3_000] * 6_000, 4 * MI, (1, 1)),
-            ([9_000] * 2_000, 4 * MI, (1, 1)), ([9_000] * 700, 4 * MI, (0, 1)), ([12_300] * 600, 4 * MI, (0, 1)), ([12_300] * 900, 4 * MI, (1, 1)),
+            ([1_000] * 16_000, 4 * MI, (1, 1)), ([1_000] * 8_000, 4 * MI, (1, 1)), ([1_500] * 11_000, 4 * MI, (0, 0)), ([2_000] * 8_000, 4 * MI, (0, 0)), ([3_000] * 6_000, 4 * MI, (1, 1)),
+            ([9_000] * 2_000, 4 * MI, (1, 1)), ([9_000] * 700, 4 * MI, (0, 1)), ([12_300] * 600, 4 * MI, (0, 1)), ([12_300] * 1_100, 4 * MI, (1, 1)), ([5_000] * 1_100, 4 * MI, (1, 1)),
             ([100_000] * 63, 4 * MI, (1, 1)), ([512 * 12_288] * 6, 1 << 40, (1, 1)), ([513 * 12_288] * 6, 1 << 40, (0, 0)),
             ([8 * MI] * 3 + [MI] * 8, 1 << 40, (1, 1)), ([8 * MI] * 3 + [MI] * 7, 1 << 40, (0, 0)), ([MI] * 14 + [1_500] * 1_200, 1 << 40, (1, 1)), ([MI] * 14 + [1_500] * 1_500, 1 << 40, (0, 0))]:
         lay = W.layout_flat_split(sizes, cap)
