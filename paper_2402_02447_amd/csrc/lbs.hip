@@ -764,6 +764,11 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
 //   Measured (100 000 trials of 1 024 GPUs x 16, nodes of 8, five methods at once): 3.11 ms; one node at a time (LG == 0)
 // with thresholds compared 3.90; k_lbs_all<2>, whose draws were all searched, 5.31.  20 000 trials: snake alone 420 us
 // (k_lbs_local 637), nodes of 4: 688 (1168), 8 sequences a GPU: 351 (596), 64 GPUs: 158 (187).
+// A run of many short trials (one node a wavefront at most, and its strata fit in one bin) is better off with k_lbs_local, of
+// which eight workgroups are resident instead of six, once a workgroup runs this many of them; up to there its longer start
+// decides.  One node of 8, batch 8: 20 000 trials 110 us (k_lbs_local 207), 200 000 165 (243), 1 500 000 928 (826); four nodes of
+// 2, batch 4: 110 (207), 181 (265), 1 160 (1 106).
+constexpr uint32_t kBinsMostShortTrials = 60;
 struct Bins {
   uint8_t slot[2][64];  // slot (draw number j of a GPU) whose stratum row r of the bin belongs to, or kNoSlot: padding
   uint32_t count;       // bins used: 1 or 2; 0: the strata do not fit
@@ -1021,7 +1026,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
   if (tid < 2u * kMethods && (WHOLE || (tid >> 1) == method)) atomicAdd(&sums[WHOLE ? tid : (tid & 1u)], s_sum[tid]);
 }
 
-// k_lbs_bins for a run whose strata fit in L.count bins.
+// k_lbs_bins for a run whose strata fit in L.count bins.  Columns in registers for nodes of 4 and 8: with two columns only 6 of the
+// 21 stages would stay within a lane (11 with four, 15 with eight), and sixteen are more columns than a group has lanes.
 template <bool WHOLE>
 auto pick_bins(const Bins& L, uint32_t gpus_per_node, uint32_t n_nodes) {
   const bool two = L.count == 2;
@@ -1295,7 +1301,9 @@ static int simulate_one(const lbs_dataset* ds, const lbs_run* run, uint32_t meth
     const dim3 grid(trial_grid(run->n_trials, run->n_gpus, ds->n_cus)), block(kBlock);
     P.first_trial = run->first_trial, P.n_trials = (uint32_t)run->n_trials;
     const Bins L = local ? pack_bins(ds, run) : Bins{};
-    if (local && L.count != 0) {
+    const bool many_short = local && L.count == 1 && run->n_gpus / run->gpus_per_node <= kWaves &&
+                            run->n_trials > (uint64_t)kBinsMostShortTrials * grid.x;
+    if (local && L.count != 0 && !many_short) {
       hipLaunchKernelGGL(pick_bins<false>(L, run->gpus_per_node, run->n_gpus / run->gpus_per_node), grid, block, sizeof(uint32_t) * tables, s, P, L,
                          method, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);
     } else if (local) {

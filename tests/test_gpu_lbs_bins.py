@@ -61,3 +61,12 @@ def test_largest_token_counts_in_sixteen_bits_and_beyond_and_a_single_gpu():
         hist[-1] = 7
         check_all(_cum(hist), (max_len,), 64, 1, 5, [64], seed=1, n=4)
         check(_cum(hist), (max_len,), lbs.LBS_GLOBAL, 64, 1, 1, [64], seed=1, n=4)
+
+
+@pytest.mark.parametrize("gpn,n_nodes,batch,quota", [(1, 1, 3, [1, 0, 1, 1]), (2, 4, 2, [1, 0, 0, 1]), (4, 3, 3, [1, 1, 1, 0])])
+def test_many_short_trials_on_both_sides_of_the_line(gpn, n_nodes, batch, quota):
+    """Few nodes and small pools: beyond sixty trials a workgroup the sorted pools take over from the bins."""
+    import torch
+    line = 60 * 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    for n in (line, line + 1):
+        check(CUM, ENDS, lbs.LBS_LOCAL_SNAKE, batch, gpn, gpn * n_nodes, quota, seed=n, n=n)
