@@ -71,11 +71,12 @@ def _two_sweeps(clip):
 
 @pytest.mark.parametrize("dtype,gdt", TYPES)
 @pytest.mark.parametrize("clip,flags", [(False, 0), (True, 0), (True, B.BCA_WRITE_BACK_GRADS)])
-@pytest.mark.parametrize("cap,offset", [(1 << 30, 0), (20_000, 0), (70_001, 3)])
+@pytest.mark.parametrize("cap,offset", [(1 << 30, 0), (262_144, 0), (300_001, (3, 0, 0, 0))])
 def test_same_bits_as_two_sweeps(dtype, gdt, clip, flags, cap, offset):
     lay = W.layout_flat_split(SIZES, cap)
     mask = np.arange(len(SIZES)) % 2
     one, two = Run(lay, dtype, gdt, 5, offset, mask), Run(lay, dtype, gdt, 5, offset, mask, **_two_sweeps(clip))
+    assert one.plan.n_lamb_items(clip) > 0 and two.plan.n_lamb_items(clip) == 0
     for step in (3, 4):
         one.go(clip, step, flags)
         two.go(clip, step, flags)
@@ -88,12 +89,21 @@ def test_same_bits_as_two_sweeps(dtype, gdt, clip, flags, cap, offset):
 
 
 @pytest.mark.parametrize("clip", [False, True])
-def test_tensors_too_large_to_be_held_beside_held_ones(clip):
-    slots = 4 * torch.cuda.get_device_properties(0).multi_processor_count
-    most = slots * 3 // 4 * 12 * 1024          # elements of the largest tensor that is held
-    for sizes in ([5000, most, 70_000, most + 1, 12], [most + 12 * 1024 + 7, most, 1 << 20], [most + 5, 40, most - 100, most // 2]):
-        lay = W.layout_flat_split(sizes, 6_553_600)
-        one, two = Run(lay, torch.float32, B.BCA_GRAD_F32, 9), Run(lay, torch.float32, B.BCA_GRAD_F32, 9, **_two_sweeps(clip))
+@pytest.mark.parametrize("spin_limit", [0, 1])
+def test_tensors_too_large_to_be_held_beside_held_ones(clip, spin_limit):
+    """A tensor is held up to three quarters of the resident items.  Whole tensors in a bucket: exactly that many and one more;
+    buckets that end inside them, which adds an item or two at every end."""
+    most = 4 * torch.cuda.get_device_properties(0).multi_processor_count * 3 // 4          # items
+    item = 12 * 1024
+    for sizes, cap, held in [([most * item, 5000, 3 << 20, most * item + 1, 70_000, 4 << 20, 12], 1 << 40, [1, 1, 1, 0, 1, 1, 1]),
+                             ([5000, most * item + 1, 5 << 20, 5 << 20], 1 << 40, [1, 0, 1, 1]),
+                             ([(most - 9) * item, 4 << 20, (most + 1) * item, 40, 4 << 20], 6_553_600, [1, 1, 0, 1, 1])]:
+        lay = W.layout_flat_split(sizes, cap)
+        one = Run(lay, torch.float32, B.BCA_GRAD_F32, 9, spin_limit=spin_limit)
+        two = Run(lay, torch.float32, B.BCA_GRAD_F32, 9, **_two_sweeps(clip))
+        items = [i for i in one.plan.lamb_items(clip) if i[0] == 1]
+        assert [max((h for _, _, _, t, h in items if t == k)) for k in range(len(sizes))] == held and two.plan.n_lamb_items(clip) == 0
+        assert [min((h for _, _, _, t, h in items if t == k)) for k in range(len(sizes))] == held
         for step in (3, 4):
             one.go(clip, step)
             two.go(clip, step)
@@ -108,6 +118,7 @@ def test_every_wait_expires_at_a_limit_of_one_poll(clip):
     sizes = [400_000, 5, 1_000_000, 20_000, 4_000_000, 1024]
     lay = W.layout_flat_split(sizes, 262_144)
     one, two = Run(lay, torch.float32, B.BCA_GRAD_F32, 2, spin_limit=1), Run(lay, torch.float32, B.BCA_GRAD_F32, 2, **_two_sweeps(clip))
+    assert one.plan.n_lamb_items(clip) > 0 and two.plan.n_lamb_items(clip) == 0
     for step in (3, 4, 5):
         one.go(clip, step)
         two.go(clip, step)
@@ -124,6 +135,7 @@ def test_two_plans_on_two_streams_at_once():
     lay = W.layout_flat_split([4_194_304] * 6 + [1_048_576] * 6, 6_553_600)
     runs = [Run(lay, torch.float32, B.BCA_GRAD_F32, 20 + i) for i in range(2)]
     ref = [Run(lay, torch.float32, B.BCA_GRAD_F32, 20 + i) for i in range(2)]
+    assert all(r.plan.n_lamb_items(clip) > 0 for r in runs for clip in (False, True))
     streams = [torch.cuda.Stream() for _ in range(2)]
     torch.cuda.synchronize()
     for step in range(3, 13):
@@ -191,3 +203,30 @@ def test_giving_up_every_wait_costs_little_more_than_two_sweeps():
     assert a < 1.8 * b, (a, b)
     late.plan.close()
     two.plan.close()
+
+
+@pytest.mark.parametrize("clip", [False, True])
+def test_in_a_hip_graph_replays_like_eager_calls(clip):
+    """The whole sequence of launches captured, replayed several times with eager work and new gradients in between."""
+    sizes = [3_000_000, 70_001, 0, 1024, 2_000_000, 513 * 1024]
+    lay = W.layout_flat_split(sizes, 1 << 20)
+    graph, eager = Run(lay, torch.bfloat16, B.BCA_GRAD_BF16, 12), Run(lay, torch.bfloat16, B.BCA_GRAD_BF16, 12)
+    assert graph.plan.n_lamb_items(clip) > 0
+    torch.cuda.synchronize()
+    cg, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(cg, stream=s):
+        graph.go(clip, 7, stream=torch.cuda.current_stream())
+    for k in range(5):
+        gen = torch.Generator(device="cuda").manual_seed(100 + k)
+        for a, b in zip(graph.state[0], eager.state[0]):
+            a.copy_((torch.randn(a.numel(), generator=gen, device="cuda") * 10.0 ** (k - 4)).to(a.dtype))
+            b.copy_(a)
+        cg.replay()
+        torch.cuda.synchronize()
+        eager.go(clip, 7)
+        torch.cuda.synchronize()
+        graph.same(eager)
+        if clip:
+            assert int(graph.status.item()) == int(eager.status.item()) == 0
+    graph.plan.close()
+    eager.plan.close()

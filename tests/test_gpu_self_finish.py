@@ -32,8 +32,6 @@ def test_same_bits_as_separate_launches(sizes, cap, flags, spin_limit):
     if sizes[0] > 1_000_000:
         n = len(plan.work_items())
         assert (n <= 8192) == (sizes[0] < 8_000_000)
-        if spin_limit:                   # the items that gave up are carried out one after the other
-            pytest.skip("covered by the smaller sizes")
     for step in range(1, 6):
         plan.bucket_clip_adam(thr, HP, step, flags, *out)
         ref.bucket_clip_adam(thr, HP, step, flags, *rout)
