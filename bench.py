@@ -38,7 +38,7 @@ MEASURED_TRAFFIC_BYTES = {      # from profiles/k_step_<workload>.txt; a combina
     (5, "f32", True): 10805399362, (3, "bf16", True): 9463045573}
 # The same for the other entry points (all kernels of one call summed), config 3, fp32 gradients
 # (profiles/other_entry_points_bert_large_fp32_50MiB.txt).
-MEASURED_TRAFFIC_OTHER_OPS = {"adam": 9446939648, "norms": 1346181120}
+MEASURED_TRAFFIC_OTHER_OPS = {"adam": 9446939648, "norms": 1346181120, "lamb": 9790156800, "clip_lamb": 11137740800}
 
 def parse():
     ap = argparse.ArgumentParser()
