@@ -416,13 +416,6 @@ bool lamb_irregular(const bca_plan* p) {
   return irregular > all / kLambIrregularShare;
 }
 
-// Whether p, m and v have a common alignment (which a few leading elements bring to 16 bytes) that the gradients do not share.
-bool gradients_off(const Chunk& c, uint64_t gsize) {
-  if (((c.p ^ c.m) | (c.p ^ c.v)) & 15u) return false;
-  const uint64_t head = ((16u - (c.p & 15u)) & 15u) / 4u;
-  return ((c.g + head * gsize) & (4u * gsize - 1u)) != 0;
-}
-
 // Writes a table's device copy from the bound pointers and the decay mask.
 hipError_t upload_table(const bca_plan* p, Table* t) {
   const uint64_t gsize = grad_bytes(p->grad_dtype);
@@ -440,8 +433,7 @@ hipError_t upload_table(const bca_plan* p, Table* t) {
     table[i].len = c.len;
     table[i].bucket = c.bucket;
     table[i].tensor = c.tensor;
-    table[i].flags = p->decay[c.tensor] ? 0u : kChunkNoDecay;
-    if (lamb_by_element != 0u && gradients_off(table[i], gsize)) table[i].flags |= lamb_by_element;
+    table[i].flags = (p->decay[c.tensor] ? 0u : kChunkNoDecay) | lamb_by_element;
   }
   return hipMemcpy(t->d_chunks, table.data(), table.size() * sizeof(Chunk), hipMemcpyHostToDevice);
 }

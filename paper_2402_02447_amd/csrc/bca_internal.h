@@ -26,8 +26,8 @@ struct alignas(16) Chunk {
   uint32_t flags;       // kChunk* bits
 };
 constexpr uint32_t kChunkNoDecay = 1u;  // the chunk's tensor is exempt from weight decay
-// LAMB's first sweep takes the chunk element by element: in lamb_step, behind clipping.  For gradients that do not lie at the
-// parameters' alignment where p, m and v do lie alike: 40 M elements, gradients one element off, both sweeps 259 us against 266
+// LAMB's first sweep may take the chunk element by element: in lamb_step, behind clipping.  It does so for gradients that do not
+// lie at the parameters' alignment where p, m and v do lie alike: 40 M elements, gradients one element off, both sweeps 259 us against 266
 // with vectors; 1.3 M elements, bf16, 14.5 against 15.6 (p, m and v that differ among themselves: 302 against 280).  That is call
 // after call on the same arrays; with them out of the caches vectors are the faster way (1 M 19.9 against 18.0, 4 M 47.6 / 39.7,
 // 40 M behind clipping 351 / 335).  Only in plans

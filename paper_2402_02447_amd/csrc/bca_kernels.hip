@@ -742,7 +742,11 @@ __device__ __forceinline__ void lamb_moments_chunk(const Entry& en, float coef, 
   const float wd = chunk_wd(en, k);
   const uint32_t len = en.len;
   uint32_t head = vector_head(len, en.p, en.m, en.v);
-  if constexpr (!AGENT) head = (en.flags & (FUSED ? kChunkClipLambByElement : kChunkLambByElement)) != 0u ? len : head;
+  // gradients that do not lie at the parameters' alignment, in plans that allow it (see kChunkLambByElement)
+  if constexpr (!AGENT)
+    if ((((en.p ^ en.m) | (en.p ^ en.v)) & 15u) == 0 && ((en.g + (uint64_t)head * gsize) & (4u * gsize - 1u)) != 0 &&
+        (en.flags & (FUSED ? kChunkClipLambByElement : kChunkLambByElement)) != 0u)
+      head = len;
   const uint32_t nvec = (len - head) / 4u;
   const uint32_t tail0 = head + nvec * 4u;
   void* gv = reinterpret_cast<void*>(en.g + (uint64_t)head * gsize);
@@ -1146,10 +1150,8 @@ __device__ __forceinline__ bool last_done(const StepState& st, uint32_t n_work, 
 // SELF: the launch needs no k_finish behind it.  Every workgroup is counted once its item is decided, and the one that
 // completes the count does what k_finish would.  Adam items are counted when their wait has ended, before they load
 // anything, so that the round trip is hidden behind the item itself.
-// LAMB: eight workgroups per compute unit, i.e. 64 registers (two more and an eighth of the wavefronts is lost: 8 M elements in
-// buckets of 1 000, bucket_clip_lamb 89 -> 95 us).
 template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB, bool SELF = false>
-__global__ __launch_bounds__(kBlock, LAMB ? 8 : 1) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,
+__global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,
                                                   const float* __restrict__ thresholds, float* __restrict__ norms,
                                                   float* __restrict__ coefs, const AdamK ka, int32_t* status) {
   __shared__ StepShared sh;
