@@ -14,9 +14,9 @@
 // read and one addition give the length, with no search and no look at the histogram.  The other cells (flagged)
 // hold the interval of lengths that they can select, which is searched.
 //   NONE / STRATIFIED : a thread owns whole GPUs; local_batch draws, one sum each.
-//   LOCAL_*           : (k_lbs_bins, node sizes and quotas that fit) a wavefront owns a node; its strata, which
-//                       are disjoint ranges of lengths and take whole rows of the sorted pool, are packed into
-//                       bins of 64 lanes, two bins to a register as 16-bit halves, and sorted there;
+//   LOCAL_*           : (k_lbs_bins, k_lbs_nodes, node sizes and quotas that fit) a wavefront owns a node or several;
+//                       their strata, which are disjoint ranges of lengths and take whole rows of the sorted pool,
+//                       are packed into bins of 64 entries, two bins to a register as 16-bit halves, and sorted there;
 //                       (k_lbs_local, everything else) a wavefront owns a node.  Its lanes draw the node's pool into
 //                       registers (entry i of the pool in register i / 64 of lane
 //                       i % 64, padded to a multiple of 64 with a sentinel above every
@@ -135,23 +135,49 @@ __device__ __forceinline__ uint32_t first_above(const uint32_t* counts, uint32_t
   return lo;
 }
 
-// Guide entries.  A draw's upper BITS bits select the cell, its other bits are added to the entry, and the sum's upper
-// BITS bits are the length (counted from the length below the range's first one): an entry is l * 2^(32 - BITS) for a
-// cell that selects l only, and 2^(32 - BITS) - from more for one that selects l + 1 from the lower bits `from` on.
-// Entries of kFlagged and above belong to cells that have to be searched: bits 0 .. 9 hold the smallest length minus
-// one, bits 10 .. 19 how far the largest one lies above it.  (A mask, an addition and a shift, which issue in two cycles
-// each here; comparing with a threshold instead takes three instructions of four cycles.)
+// Guide entries.  A draw's upper BITS bits select the cell, the draw is added to the entry (modulo 2^32), and the sum's
+// upper BITS bits are the length (counted from the length below the range's first one): an entry is (l - cell) * 2^(32 - BITS)
+// for a cell that selects l only, and 2^(32 - BITS) - from more for one that selects l + 1 from the lower bits `from` on.
+// Cells that have to be searched have kFlagged and more where the others have l * 2^(32 - BITS): bits 0 .. 9 hold the
+// smallest length minus one, bits 10 .. 19 how far the largest one lies above it.  (An addition and a shift, which issue in
+// two cycles each here; comparing with a threshold instead takes three instructions of four cycles.)
 template <uint32_t BITS>
 constexpr uint32_t kFlagged = ((1u << BITS) - 1u) << (32u - BITS);
 
-// Length selected by the draw with generator state z; `guide` is its range's table, `base` the length below the range's
-// first one.  FLAGGED: some entry may be flagged; `range` then says which dataset entries the draw is from.
+// The draw with generator state z: the upper half of the generator's output.
+__device__ __forceinline__ uint32_t drawn(uint64_t z) { return (uint32_t)(mix(z) >> 32); }
+
+// The same in fewer, longer instructions: a * b + c on 64 bits costs what a 32-bit multiplication does, but the compiler takes it
+// apart where only the sum's lower half is used.  61 instead of 66 cycles of issue a draw, for kernels that are bound by that (five methods at
+// 1 024 GPUs 463 -> 453 us, snake 370 -> 343); those that wait rather than issue lose by the longer chain (one node of 8, batch 8:
+// 1827 -> 2100).
+__device__ __forceinline__ uint64_t mad64(uint32_t a, uint32_t b, uint64_t c) {
+  uint64_t d, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(d), "=s"(carry) : "v"(a), "s"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ uint32_t drawn_dense(uint64_t z) {
+  constexpr uint32_t A = 0xBF58476Du, B = 0x1CE4E5B9u, C = 0x94D049BBu, D = 0x133111EBu;  // mix's multipliers, halves
+  z ^= z >> 30;
+  const uint64_t y = (uint64_t)(uint32_t)z * B;
+  const uint64_t cross = mad64((uint32_t)(z >> 32), B, (uint64_t)(uint32_t)z * A);
+  z = ((uint64_t)((uint32_t)(y >> 32) + (uint32_t)cross) << 32) | (uint32_t)y;
+  z ^= z >> 27;
+  uint32_t any;
+  asm("" : "=v"(any));  // of the sums that follow only the lower words are used
+  const uint64_t carried = (uint64_t)any << 32 | __umulhi((uint32_t)z, D);
+  const uint32_t u = (uint32_t)mad64((uint32_t)(z >> 32), D, mad64((uint32_t)z, C, carried));
+  return u ^ (u >> 31);
+}
+
+// Length selected by draw u; `guide` is its range's table, `base` the length below the range's first one.  FLAGGED: some
+// entry may be flagged; `range` then says which dataset entries the draw is from.
 template <uint32_t BITS, bool FLAGGED, typename F>
-__device__ __forceinline__ uint32_t draw(const uint32_t* s_cum, const uint32_t* guide, uint64_t z, uint32_t base, F range) {
-  const uint32_t u = (uint32_t)(mix(z) >> 32);
-  const uint32_t e = guide[u >> (32u - BITS)];
-  uint32_t l = base + ((e + (u & ((1u << (32u - BITS)) - 1u))) >> (32u - BITS));
+__device__ __forceinline__ uint32_t length_of(const uint32_t* s_cum, const uint32_t* guide, uint32_t u, uint32_t base, F range) {
+  const uint32_t at = guide[u >> (32u - BITS)];
+  uint32_t l = base + ((at + u) >> (32u - BITS));
   if constexpr (FLAGGED) {
+    const uint32_t e = at + (u & ~((1u << (32u - BITS)) - 1u));
     if (e >= kFlagged<BITS>) {
       const uint32_t lo = (e & 1023u) + 1u;
       uint32_t before, size;
@@ -296,8 +322,8 @@ __global__ __launch_bounds__(kBlock) void k_lbs_keep(const Params P, const uint3
         uint32_t tokens = 0;
 #pragma unroll 4
         for (uint32_t j = 0; j < P.local_batch; ++j, z += kGamma)
-          tokens += draw<BITS, decltype(fl)::value>(
-              s_dyn, s_guide + P.slot_guide[j], z, P.slot_base[j],
+          tokens += length_of<BITS, decltype(fl)::value>(
+              s_dyn, s_guide + P.slot_guide[j], drawn(z), P.slot_base[j],
               [&](uint32_t& before, uint32_t& size) { before = P.slot_lo[j], size = P.slot_size[j]; });
         lo = min(lo, tokens), hi = max(hi, tokens);
       }
@@ -393,8 +419,8 @@ __global__ __launch_bounds__(kBlock) void k_lbs_local(const Params P, const uint
 #pragma unroll
           for (int e = 0; e < E; ++e) {
             const uint32_t i = (uint32_t)e * 64u + lane;
-            v[e] = i < pool ? draw<kGuideBits, decltype(fl)::value>(
-                                  s_dyn, s_guide + goff[e], z_node + i * kGamma, base_len[e],
+            v[e] = i < pool ? length_of<kGuideBits, decltype(fl)::value>(
+                                  s_dyn, s_guide + goff[e], drawn(z_node + i * kGamma), base_len[e],
                                   [&](uint32_t& before, uint32_t& size) {
                                     before = P.slot_lo[i % P.local_batch], size = P.slot_size[i % P.local_batch];
                                   })
@@ -505,8 +531,8 @@ __global__ __launch_bounds__(kBlock) void k_lbs_global(const Params P, const uin
     const auto draws = [&](auto fl) {
 #pragma unroll 4
       for (uint32_t i = tid; i < pool; i += kBlock, z += kBlock * kGamma)
-        atomicAdd(&s_cnt[draw<kWholeGuideBits, decltype(fl)::value>(
-                      s_dyn, s_guide, z, 0u, [&](uint32_t& before, uint32_t& size) { before = 0u, size = P.total; })],
+        atomicAdd(&s_cnt[length_of<kWholeGuideBits, decltype(fl)::value>(
+                      s_dyn, s_guide, drawn(z), 0u, [&](uint32_t& before, uint32_t& size) { before = 0u, size = P.total; })],
                   1u);
     };
     if (P.flagged != 0u) draws(std::true_type{});
@@ -563,84 +589,110 @@ __global__ __launch_bounds__(kBlock) void k_lbs_global(const Params P, const uin
 }
 
 // ---- all five methods on one set of draws ----------------------------------------
-// NONE and GLOBAL use the same draws from the whole dataset, STRATIFIED and the two LOCAL methods the same
-// stratified draws (draw number k of a run does not depend on the method), so one pass makes each set once:
-// first a thread per GPU draws from the whole dataset, sums its GPU's tokens (NONE) and counts the lengths
-// for the counting sort (GLOBAL, as in k_lbs_global<true>); then a wavefront per node draws the stratified
-// pool into registers, adds up each GPU's own draws (STRATIFIED: local_batch consecutive pool entries, a
-// butterfly over the low lane bits), sorts and deals twice (LOCAL_RASTER, LOCAL_SNAKE, as in
-// k_lbs_local<E, true>).  Needs gpus_per_node and local_batch to be powers of two (<= 32 and <= 64).
+// Draw number k of a run does not depend on the method, and it belongs to the same GPU and the same one of its local_batch
+// sequences in all of them: NONE and GLOBAL look it up in the whole dataset, STRATIFIED and the LOCAL methods in the
+// sequence's stratum.  So one generator output (most of what a draw costs: two 64-bit multiplications) serves both.
+// A wavefront takes a node (or several), makes its draws, counts the lengths from the whole dataset for the counting
+// sort (GLOBAL, as in k_lbs_global<true>), adds up each GPU's own lengths of either kind (NONE, STRATIFIED), sorts the
+// stratified ones and deals twice (LOCAL_RASTER, LOCAL_SNAKE).
 constexpr uint32_t kMethods = 5;
 
-// One trial's draws from the whole dataset: NONE (a thread per GPU sums its draws) and GLOBAL (the lengths are counted,
-// then as in k_lbs_global<true>).  All threads of the workgroup call it; s_cnt, s_gpu, *s_base and s_scan are its own until
-// the next barrier of the caller.
-__device__ __forceinline__ void whole_draws(const Params& P, const uint32_t* s_cum, const uint32_t* s_whole, uint32_t* s_cnt,
-                                            uint32_t* s_gpu, uint32_t* s_base, uint32_t (*s_scan)[kWaves], uint64_t k_trial,
-                                            uint32_t& none_lo, uint32_t& none_hi, uint32_t& glob_lo, uint32_t& glob_hi) {
+// A trial's draws from the whole dataset are counted in s_cnt between these two.  All threads of the workgroup call both, with
+// a barrier after the first and one before the second; s_cnt, s_gpu, *s_base and s_scan are theirs until the next barrier
+// of the caller.
+__device__ __forceinline__ void whole_clear(const Params& P, uint32_t* s_cnt, uint32_t* s_gpu, uint32_t* s_base) {
+  for (uint32_t i = threadIdx.x; i <= P.max_len; i += kBlock) s_cnt[i] = 0u;
+  for (uint32_t i = threadIdx.x; i < P.n_gpus; i += kBlock) s_gpu[i] = 0u;
+  if (threadIdx.x == 0) *s_base = 0u;
+}
+
+// GLOBAL: the counted lengths dealt over all GPUs as in k_lbs_global<true>; smallest and largest sum of this thread's GPUs.
+__device__ __forceinline__ void whole_deal(const Params& P, const uint32_t* s_cnt, uint32_t* s_gpu, uint32_t* s_base,
+                                           uint32_t (*s_scan)[kWaves], uint32_t& glob_lo, uint32_t& glob_hi) {
   const uint32_t tid = threadIdx.x;
   const uint32_t per = (P.max_len + 1u + kBlock - 1u) / kBlock;
   const uint32_t a = tid * per, b = min(a + per, P.max_len + 1u);
   const uint32_t per_gpu = (P.n_gpus + kBlock - 1u) / kBlock;
   const uint32_t ga = min(tid * per_gpu, P.n_gpus), gb = min(ga + per_gpu, P.n_gpus);
-  for (uint32_t i = tid; i <= P.max_len; i += kBlock) s_cnt[i] = 0u;
-  for (uint32_t i = tid; i < P.n_gpus; i += kBlock) s_gpu[i] = 0u;
-  if (tid == 0) *s_base = 0u;
-  __syncthreads();
-  const auto draws = [&](auto fl) {
-    for (uint32_t g = tid; g < P.n_gpus; g += kBlock) {
-      uint64_t z = state(P.seed, k_trial + (uint64_t)g * P.local_batch);
-      uint32_t tokens = 0;
-#pragma unroll 4
-      for (uint32_t j = 0; j < P.local_batch; ++j, z += kGamma) {
-        const uint32_t l = draw<kWholeGuideBits, decltype(fl)::value>(
-            s_cum, s_whole, z, 0u, [&](uint32_t& before, uint32_t& size) { before = 0u, size = P.total; });
-        tokens += l;
-        atomicAdd(&s_cnt[l], 1u);
+  uint32_t piece = 0;
+  for (uint32_t i = a; i < b; ++i) piece += s_cnt[i];
+  uint32_t run = block_running_sum(s_scan[0], piece) - piece;
+  uint32_t whole_turns = 0;
+  for (uint32_t l = a; l < b; ++l) {
+    const uint32_t n = s_cnt[l];
+    if (n != 0u) {
+      const uint32_t turns = turns_of(n, P), rest = n - turns * P.n_gpus, first = run - turns_of(run, P) * P.n_gpus;
+      whole_turns += turns * l;
+      if (rest != 0u) {
+        const uint32_t end = first + rest;
+        atomicAdd(&s_gpu[first], l);
+        if (end < P.n_gpus) atomicAdd(&s_gpu[end], 0u - l);
+        if (end > P.n_gpus) atomicAdd(&s_gpu[0], l), atomicAdd(&s_gpu[end - P.n_gpus], 0u - l);
       }
-      none_lo = min(none_lo, tokens), none_hi = max(none_hi, tokens);
     }
-  };
-  if (P.flagged != 0u) draws(std::true_type{});
-  else draws(std::false_type{});
+    run += n;
+  }
+  if (whole_turns != 0u) atomicAdd(s_base, whole_turns);
   __syncthreads();
-  {
-    uint32_t piece = 0;
-    for (uint32_t i = a; i < b; ++i) piece += s_cnt[i];
-    uint32_t run = block_running_sum(s_scan[0], piece) - piece;
-    uint32_t whole_turns = 0;
-    for (uint32_t l = a; l < b; ++l) {
-      const uint32_t n = s_cnt[l];
-      if (n != 0u) {
-        const uint32_t turns = turns_of(n, P), rest = n - turns * P.n_gpus, first = run - turns_of(run, P) * P.n_gpus;
-        whole_turns += turns * l;
-        if (rest != 0u) {
-          const uint32_t end = first + rest;
-          atomicAdd(&s_gpu[first], l);
-          if (end < P.n_gpus) atomicAdd(&s_gpu[end], 0u - l);
-          if (end > P.n_gpus) atomicAdd(&s_gpu[0], l), atomicAdd(&s_gpu[end - P.n_gpus], 0u - l);
-        }
-      }
-      run += n;
-    }
-    if (whole_turns != 0u) atomicAdd(s_base, whole_turns);
-    __syncthreads();
-    uint32_t mine = 0;
-    for (uint32_t g = ga; g < gb; ++g) mine += s_gpu[g];
-    uint32_t tokens = block_running_sum(s_scan[1], mine) - mine + *s_base;
-    for (uint32_t g = ga; g < gb; ++g) {
-      tokens += s_gpu[g];
-      glob_lo = min(glob_lo, tokens), glob_hi = max(glob_hi, tokens);
-    }
+  uint32_t mine = 0;
+  for (uint32_t g = ga; g < gb; ++g) mine += s_gpu[g];
+  uint32_t tokens = block_running_sum(s_scan[1], mine) - mine + *s_base;
+  for (uint32_t g = ga; g < gb; ++g) {
+    tokens += s_gpu[g];
+    glob_lo = min(glob_lo, tokens), glob_hi = max(glob_hi, tokens);
   }
 }
 
+// Minima and maxima of a trial, one for every row of 16 lanes, double-buffered by the parity of the workgroup's trial count.
+constexpr uint32_t kRows = 4u * kWaves;
 struct FinishAll {
-  uint32_t lo[2][kMethods][kWaves], hi[2][kMethods][kWaves];
+  uint32_t lo[2][kMethods][kRows], hi[2][kMethods][kRows];
 };
 
+// Minimum and maximum over each row of 16 lanes, in all of its lanes.
+__device__ __forceinline__ void row_min_max(uint32_t& lo, uint32_t& hi) {
+  const auto step = [&](auto rotate) {
+    lo = min(lo, (uint32_t)__builtin_amdgcn_mov_dpp((int)lo, decltype(rotate)::value, 0xf, 0xf, true));
+    hi = max(hi, (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, decltype(rotate)::value, 0xf, 0xf, true));
+  };
+  step(std::integral_constant<int, 0x128>{}), step(std::integral_constant<int, 0x124>{});
+  step(std::integral_constant<int, 0x122>{}), step(std::integral_constant<int, 0x121>{});
+}
+
+// Files the minimum and maximum that the wavefront's lanes have seen of method q.
+__device__ __forceinline__ void file_min_max(FinishAll& fin, uint32_t buf, uint32_t q, uint32_t lo, uint32_t hi) {
+  row_min_max(lo, hi);
+  const uint32_t tid = threadIdx.x;
+  if ((tid & 15u) == 0) fin.lo[buf][q][tid >> 4] = lo, fin.hi[buf][q][tid >> 4] = hi;
+}
+
+// A trial's results from what has been filed: thread 2 q stores method q's minimum, thread 2 q + 1 its maximum,
+// and adds it to the workgroup's sums.  all: the five methods, else `method` alone.
+__device__ __forceinline__ void finish_methods(const Params& P, const FinishAll& fin, unsigned long long* s_sum, uint32_t buf, uint32_t t,
+                                               bool all, uint32_t method, uint32_t* trial_min, uint32_t* trial_max) {
+  const uint32_t tid = threadIdx.x, m = tid >> 1;
+  if (tid >= 2u * kMethods || (!all && m != method)) return;
+  const size_t at = all ? (size_t)m * P.n_trials + t : t;
+  uint32_t x;
+  if (tid & 1u) {
+    x = 0u;
+#pragma unroll
+    for (uint32_t r = 0; r < kRows; ++r) x = max(x, fin.hi[buf][m][r]);
+    if (trial_max) trial_max[at] = x;
+  } else {
+    x = 0xffffffffu;
+#pragma unroll
+    for (uint32_t r = 0; r < kRows; ++r) x = min(x, fin.lo[buf][m][r]);
+    if (trial_min) trial_min[at] = x;
+  }
+  s_sum[tid] += x;
+}
+
+// A wavefront per node, whose pool lies in registers (entry i in register i / 64 of lane i % 64) and is sorted as in
+// k_lbs_local<E, true>; a GPU's own draws are local_batch consecutive entries, added up by a butterfly over the low lane
+// bits.  Needs gpus_per_node and local_batch to be powers of two (<= 32 and <= 64).
 template <int E>
-__global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) void k_lbs_all(const Params P, const uint32_t* __restrict__ cum,
+__global__ __launch_bounds__(kBlock, E <= 1 ? 6 : E == 2 ? 5 : E == 4 ? 4 : E == 8 ? 3 : 2) void k_lbs_all(const Params P, const uint32_t* __restrict__ cum,
                                                      const uint32_t* __restrict__ guide, uint32_t* trial_min,
                                                      uint32_t* trial_max, unsigned long long* sums) {
   extern __shared__ uint32_t s_dyn[];  // histogram, all guide tables, the trial's own histogram, one word per GPU
@@ -673,6 +725,7 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
   for (int q = 0; q < 6; ++q) bit[q] = 0u - ((lane >> q) & 1u);
   const bool odd_row = ((lane / P.gpus_per_node) & 1u) != 0u;
   const uint32_t gpn_bit = (uint32_t)__ffs((int)P.gpus_per_node) - 1u, batch_bit = (uint32_t)__ffs((int)P.local_batch) - 1u;
+  const bool halves = P.local_batch * P.max_len < 65536u;
 
   for (uint32_t t = blockIdx.x, round = 0; t < P.n_trials; t += gridDim.x, ++round) {
     const uint32_t buf = round & 1u;
@@ -680,16 +733,8 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
 #pragma unroll
     for (uint32_t q = 0; q < kMethods; ++q) lo[q] = 0xffffffffu, hi[q] = 0u;
     const uint64_t k_trial = (P.first_trial + t) * (uint64_t)pool_all;  // the trial's first draw
-    whole_draws(P, s_dyn, s_whole, s_cnt, s_gpu, &s_base, s_scan, k_trial, lo[LBS_NONE], hi[LBS_NONE], lo[LBS_GLOBAL],
-                hi[LBS_GLOBAL]);
-    // these two are filed now, so that they need no registers during the sort
-    wave_min_max(lo[LBS_NONE], hi[LBS_NONE]);
-    wave_min_max(lo[LBS_GLOBAL], hi[LBS_GLOBAL]);
-    if (lane == 0) {
-      s_fin.lo[buf][LBS_NONE][wave] = lo[LBS_NONE], s_fin.hi[buf][LBS_NONE][wave] = hi[LBS_NONE];
-      s_fin.lo[buf][LBS_GLOBAL][wave] = lo[LBS_GLOBAL], s_fin.hi[buf][LBS_GLOBAL][wave] = hi[LBS_GLOBAL];
-    }
-    // ---- stratified draws, a wavefront per node: STRATIFIED, LOCAL_RASTER, LOCAL_SNAKE (no LDS writes, no barriers)
+    whole_clear(P, s_cnt, s_gpu, &s_base);
+    __syncthreads();
     for (uint32_t node = wave; node < n_nodes; node += kWaves) {
       const uint64_t z_node = state(P.seed, k_trial + (uint64_t)node * pool);
       uint32_t v[E];
@@ -697,22 +742,34 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const uint32_t i = (uint32_t)e * 64u + lane;
-          v[e] = i < pool ? draw<kGuideBits, decltype(fl)::value>(
-                                s_dyn, s_strata + goff[e], z_node + i * kGamma, base_len[e],
-                                [&](uint32_t& before, uint32_t& size) {
-                                  before = P.slot_lo[i % P.local_batch], size = P.slot_size[i % P.local_batch];
-                                })
-                          : 0xffffffffu;
+          const bool real = i < pool;
+          uint32_t w = 0u;
+          v[e] = 0xffffffffu;
+          if (real) {
+            const uint32_t u = drawn(z_node + i * kGamma);
+            v[e] = length_of<kGuideBits, decltype(fl)::value>(s_dyn, s_strata + goff[e], u, base_len[e],
+                                                              [&](uint32_t& before, uint32_t& size) {
+                                                                before = P.slot_lo[i % P.local_batch], size = P.slot_size[i % P.local_batch];
+                                                              });
+            w = length_of<kWholeGuideBits, decltype(fl)::value>(
+                s_dyn, s_whole, u, 0u, [&](uint32_t& before, uint32_t& size) { before = 0u, size = P.total; });
+            atomicAdd(&s_cnt[w], 1u);
+          }
+          // a GPU's own draws; both kinds in one word where the sums fit in 16 bits
+          const auto own = [&](uint32_t q, uint32_t tokens) {
+            if (real) lo[q] = min(lo[q], tokens), hi[q] = max(hi[q], tokens);
+          };
+          if (halves) {
+            const uint32_t both = butterfly_sum(real ? v[e] | w << 16 : 0u, 0u, batch_bit);
+            own(LBS_STRATIFIED, both & 0xffffu), own(LBS_NONE, both >> 16);
+          } else {
+            own(LBS_STRATIFIED, butterfly_sum(real ? v[e] : 0u, 0u, batch_bit));
+            own(LBS_NONE, butterfly_sum(w, 0u, batch_bit));
+          }
         }
       };
       if (P.flagged != 0u) draws(std::true_type{});
       else draws(std::false_type{});
-#pragma unroll
-      for (int e = 0; e < E; ++e) {  // a GPU's own draws are local_batch consecutive pool entries
-        const bool real = (uint32_t)e * 64u + lane < pool;
-        const uint32_t own = butterfly_sum(real ? v[e] : 0u, 0u, batch_bit);
-        if (real) lo[LBS_STRATIFIED] = min(lo[LBS_STRATIFIED], own), hi[LBS_STRATIFIED] = max(hi[LBS_STRATIFIED], own);
-      }
       bitonic_sort<E>(v, bit);
       uint32_t column = 0;
 #pragma unroll
@@ -723,25 +780,13 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
       lo[LBS_LOCAL_RASTER] = min(lo[LBS_LOCAL_RASTER], raster), hi[LBS_LOCAL_RASTER] = max(hi[LBS_LOCAL_RASTER], raster);
       lo[LBS_LOCAL_SNAKE] = min(lo[LBS_LOCAL_SNAKE], snake), hi[LBS_LOCAL_SNAKE] = max(hi[LBS_LOCAL_SNAKE], snake);
     }
+    __syncthreads();
+    whole_deal(P, s_cnt, s_gpu, &s_base, s_scan, lo[LBS_GLOBAL], hi[LBS_GLOBAL]);
     // ---- the trial's five results
 #pragma unroll
-    for (uint32_t q = LBS_STRATIFIED; q <= LBS_LOCAL_SNAKE; ++q) {
-      wave_min_max(lo[q], hi[q]);
-      if (lane == 0) s_fin.lo[buf][q][wave] = lo[q], s_fin.hi[buf][q][wave] = hi[q];
-    }
+    for (uint32_t q = 0; q < kMethods; ++q) file_min_max(s_fin, buf, q, lo[q], hi[q]);
     __syncthreads();  // also: this trial's last reads of s_cnt and s_gpu lie before the next trial's clearing
-    if (tid < 2u * kMethods) {  // thread 2 q: method q's minimum; thread 2 q + 1: its maximum
-      const uint32_t q = tid >> 1;
-      uint32_t r;
-      if (tid & 1u) {
-        r = max(max(s_fin.hi[buf][q][0], s_fin.hi[buf][q][1]), max(s_fin.hi[buf][q][2], s_fin.hi[buf][q][3]));
-        if (trial_max) trial_max[(size_t)q * P.n_trials + t] = r;
-      } else {
-        r = min(min(s_fin.lo[buf][q][0], s_fin.lo[buf][q][1]), min(s_fin.lo[buf][q][2], s_fin.lo[buf][q][3]));
-        if (trial_min) trial_min[(size_t)q * P.n_trials + t] = r;
-      }
-      s_sum[tid] += r;
-    }
+    finish_methods(P, s_fin, s_sum, buf, t, true, 0u, trial_min, trial_max);
   }
   if (tid < 2u * kMethods) atomicAdd(&sums[tid], s_sum[tid]);
 }
@@ -761,9 +806,10 @@ __global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) v
 // wavefront sorts 2^LG nodes (BINS == 1: twice as many) at a time: 15 of the 21 stages (nodes of 8) then pair registers of one lane, at
 // 2 instead of 5 cycles an entry, and a row is mirrored by naming its registers backwards.  Needs as many nodes as
 // that, else lanes would idle.  LG == 0: any power of two up to 16; a bin lies in the 64 lanes, one node at a time.
-//   Measured (100 000 trials of 1 024 GPUs x 16, nodes of 8, five methods at once): 3.11 ms; one node at a time (LG == 0)
-// with thresholds compared 3.90; k_lbs_all<2>, whose draws were all searched, 5.31.  20 000 trials: snake alone 420 us
-// (k_lbs_local 637), nodes of 4: 688 (1168), 8 sequences a GPU: 351 (596), 64 GPUs: 158 (187).
+//   Measured (20 000 trials of 1 024 GPUs x 16, nodes of 8): snake alone 420 us (k_lbs_local 637), nodes of 4: 476 (1168 all five).  Bins that
+// are full go by k_lbs_nodes where there are many nodes; those with padding, datasets with flagged entries, other node sizes and few nodes
+// stay here.  Five methods, 24 414 trials of 128 nodes of 8: one node at a time 796 us, columns in registers 613 (792 before the two kinds of
+// draws shared the generator's outputs); 390 625 trials of 8 nodes: 1 302 and 1 965 (1 910).
 // A run of many short trials (one node a wavefront at most, and its strata fit in one bin) is better off with k_lbs_local, of
 // which eight workgroups are resident instead of six, once a workgroup runs this many of them; up to there its longer start
 // decides.  One node of 8, batch 8: 20 000 trials 110 us (k_lbs_local 207), 200 000 165 (243), 1 500 000 928 (826); four nodes of
@@ -852,7 +898,7 @@ __device__ __forceinline__ uint32_t column_sums(uint32_t (&x)[1 << LG], const ui
 }
 
 template <int LG, int BINS, bool WHOLE>
-__global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bins L, const uint32_t method,
+__global__ __launch_bounds__(kBlock, WHOLE && LG > 0 ? (LG == 3 ? 4 : 5) : 6) void k_lbs_bins(const Params P, const Bins L, const uint32_t method,
                                                          const uint32_t* __restrict__ cum, const uint32_t* __restrict__ guide,
                                                          uint32_t* trial_min, uint32_t* trial_max, unsigned long long* sums) {
   extern __shared__ uint32_t s_dyn[];  // histogram, guide tables; WHOLE: the trial's own histogram, one word per GPU
@@ -902,34 +948,37 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
     const uint32_t buf = round & 1u;
     const uint64_t k_trial = (P.first_trial + t) * (uint64_t)pool_all;
     if (WHOLE) {
-      uint32_t none_lo = 0xffffffffu, none_hi = 0u, glob_lo = 0xffffffffu, glob_hi = 0u;
-      whole_draws(P, s_dyn, s_whole, s_cnt, s_gpu, &s_base, s_scan, k_trial, none_lo, none_hi, glob_lo, glob_hi);
-      wave_min_max(none_lo, none_hi);
-      wave_min_max(glob_lo, glob_hi);
-      if (lane == 0) {
-        s_fin.lo[buf][LBS_NONE][wave] = none_lo, s_fin.hi[buf][LBS_NONE][wave] = none_hi;
-        s_fin.lo[buf][LBS_GLOBAL][wave] = glob_lo, s_fin.hi[buf][LBS_GLOBAL][wave] = glob_hi;
-      }
+      whole_clear(P, s_cnt, s_gpu, &s_base);
+      __syncthreads();
     }
-    // Running minima and maxima: LG > 0, of own, raster, snake in turn; LG == 0, one for all three, told apart by the lane.
-    // BINS == 1: 16-bit halves.
-    constexpr int M = LG > 0 ? 3 : 1;
+    // Running minima and maxima: LG > 0, of own, raster, snake and (WHOLE) what the GPUs draw from the whole dataset in turn;
+    // LG == 0, one for all, told apart by the lane.  BINS == 1: 16-bit halves.
+    constexpr int S = WHOLE ? 4 : 3, M = LG > 0 ? S : 1;
     uint32_t lo[M], hi[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) lo[m] = 0xffffffffu, hi[m] = 0u;
     for (uint32_t first = wave * kNodes; first < n_nodes; first += kWaves * kNodes) {
       const uint64_t z0 = state(P.seed, k_trial + (uint64_t)first * pool);
-      uint32_t v[R];
+      uint32_t v[R], whole[R];
       const auto draws = [&](auto fl) {
 #pragma unroll
         for (int c = 0; c < R; ++c) {
-          uint32_t d[2];
+          uint32_t d[2], w[2] = {};
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            d[h] = draw<kGuideBits, decltype(fl)::value>(
-                s_dyn, s_strata + goff[h], z0 + (uint64_t)c * next_column + step[h], base_len[h],
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t u = drawn(z0 + (uint64_t)c * next_column + step[h]);
+            d[h] = length_of<kGuideBits, decltype(fl)::value>(
+                s_dyn, s_strata + goff[h], u, base_len[h],
                 [&](uint32_t& before, uint32_t& size) { before = P.slot_lo[slot[h]], size = P.slot_size[slot[h]]; });
-          v[c] = d[0] | (d[1] << 16);
+            if (WHOLE) {
+              w[h] = length_of<kWholeGuideBits, decltype(fl)::value>(
+                  s_dyn, s_whole, u, 0u, [&](uint32_t& before, uint32_t& size) { before = 0u, size = P.total; });
+              // padding and nodes that are not there count for nothing
+              const uint32_t node = LG == 0 ? first + (BINS == 2 ? 0u : (uint32_t)h) : first + (BINS == 2 ? group : group * 2u + (uint32_t)h);
+              if (node < n_nodes && (real & (h == 0 ? 0xffffu : 0xffff0000u)) != 0u) atomicAdd(&s_cnt[w[h]], 1u);
+            }
+          }
+          v[c] = d[0] | (d[1] << 16), whole[c] = w[0] | (w[1] << 16);
         }
       };
       if (P.flagged != 0u) draws(std::true_type{});
@@ -939,7 +988,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
         // BINS == 1: a second node that is not there repeats the first; a whole group that is not there is left out below
         if (BINS == 1 && node + 1u >= n_nodes) {
 #pragma unroll
-          for (int c = 0; c < R; ++c) v[c] = (v[c] & 0xffffu) | (v[c] << 16);
+          for (int c = 0; c < R; ++c) v[c] = (v[c] & 0xffffu) | (v[c] << 16), whole[c] = (whole[c] & 0xffffu) | (whole[c] << 16);
         }
       }
       const bool there = LG == 0 || first + (BINS == 2 ? group : group * 2u) < n_nodes;
@@ -949,11 +998,15 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
       if (L.padded != 0u) {
         // 0xffff sorts behind every length, into the bin's last rows: again the padded ones
 #pragma unroll
-        for (int c = 0; c < R; ++c) own[c] &= real, v[c] |= ~real;
+        for (int c = 0; c < R; ++c) own[c] &= real, whole[c] &= real, v[c] |= ~real;
       }
-      uint32_t sum[3];
-      if constexpr (LG > 0) sum[0] = column_sums<LG>(own, bit);
-      else sum[0] = own[0];
+      uint32_t sum[4] = {};
+      if constexpr (LG > 0) {
+        sum[0] = column_sums<LG>(own, bit);
+        if (WHOLE) sum[3] = column_sums<LG>(whole, bit);
+      } else {
+        sum[0] = own[0], sum[3] = whole[0];
+      }
       sort_halves<LG>(v, bit);
       if (L.padded != 0u) {
 #pragma unroll
@@ -972,20 +1025,21 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
       }
       if (BINS == 2) {
 #pragma unroll
-        for (int m = 0; m < 3; ++m) sum[m] = (sum[m] & 0xffffu) + (sum[m] >> 16);
+        for (int m = 0; m < S; ++m) sum[m] = (sum[m] & 0xffffu) + (sum[m] >> 16);
       }
       if constexpr (LG > 0) {
         if (there) {
 #pragma unroll
-          for (int m = 0; m < 3; ++m) {
+          for (int m = 0; m < S; ++m) {
             lo[m] = BINS == 2 ? min(lo[m], sum[m]) : min_halves(lo[m], sum[m]);
             hi[m] = BINS == 2 ? max(hi[m], sum[m]) : max_halves(hi[m], sum[m]);
           }
         }
       } else {
-        // sums over the rows of 16 lanes: row 0 ends up with `own`, row 2 with `raster`, rows 1 and 3 with `snake`
+        // sums over the rows of 16 lanes: row 0 ends up with `own`, row 2 with `raster`, row 1 with `snake`, row 3 with it or
+        // (WHOLE) with the draws from the whole dataset
         const auto p = __builtin_amdgcn_permlane32_swap(sum[0], sum[1], false, false);
-        const auto q = __builtin_amdgcn_permlane32_swap(sum[2], sum[2], false, false);
+        const auto q = __builtin_amdgcn_permlane32_swap(sum[2], WHOLE ? sum[3] : sum[2], false, false);
         const auto r = __builtin_amdgcn_permlane16_swap(p[0] + p[1], q[0] + q[1], false, false);
         const uint32_t tokens = butterfly_sum(r[0] + r[1], gpn_bit, 4u);
         lo[0] = BINS == 2 ? min(lo[0], tokens) : min_halves(lo[0], tokens);
@@ -998,44 +1052,358 @@ __global__ __launch_bounds__(kBlock, 6) void k_lbs_bins(const Params P, const Bi
         lo[m] = lo[m] == 0xffffffffu ? lo[m] : min(lo[m] & 0xffffu, lo[m] >> 16);
         hi[m] = max(hi[m] & 0xffffu, hi[m] >> 16);
       }
-#pragma unroll
-      for (int lj = 0; lj < (LG > 0 ? 6 : 4); ++lj) lo[m] = min(lo[m], partner_of(lo[m], lj)), hi[m] = max(hi[m], partner_of(hi[m], lj));
-      if (LG > 0 ? lane == 0u : (lane & 15u) == 0u && lane < 48u) {
-        const uint32_t which = LG > 0 ? (uint32_t)m : lane == 0u ? 0u : lane == 16u ? 2u : 1u;
-        const uint32_t q = which == 0u ? LBS_STRATIFIED : which == 1u ? LBS_LOCAL_RASTER : LBS_LOCAL_SNAKE;
-        s_fin.lo[buf][q][wave] = lo[m], s_fin.hi[buf][q][wave] = hi[m];
+      if (LG > 0) {
+        file_min_max(s_fin, buf, m == 0 ? LBS_STRATIFIED : m == 1 ? LBS_LOCAL_RASTER : m == 2 ? LBS_LOCAL_SNAKE : LBS_NONE, lo[m], hi[m]);
+      } else {  // a row of lanes stands for the whole wavefront
+        row_min_max(lo[m], hi[m]);
+        const uint32_t which = lane >> 4, i = lane & 15u;
+        const uint32_t q = which == 0u ? LBS_STRATIFIED : which == 1u ? LBS_LOCAL_SNAKE : which == 2u ? LBS_LOCAL_RASTER : LBS_NONE;
+        if (i < 4u) s_fin.lo[buf][q][wave * 4u + i] = lo[m], s_fin.hi[buf][q][wave * 4u + i] = hi[m];
       }
     }
+    if (WHOLE) {
+      uint32_t glob_lo = 0xffffffffu, glob_hi = 0u;
+      __syncthreads();
+      whole_deal(P, s_cnt, s_gpu, &s_base, s_scan, glob_lo, glob_hi);
+      file_min_max(s_fin, buf, LBS_GLOBAL, glob_lo, glob_hi);
+    }
     __syncthreads();  // also: this trial's last reads of s_cnt and s_gpu lie before the next trial's clearing
-    if (tid < 2u * kMethods) {  // thread 2 q: method q's minimum; thread 2 q + 1: its maximum
-      const uint32_t m = tid >> 1;
-      if (WHOLE || m == method) {
-        const size_t at = WHOLE ? (size_t)m * P.n_trials + t : t;
-        uint32_t x;
-        if (tid & 1u) {
-          x = max(max(s_fin.hi[buf][m][0], s_fin.hi[buf][m][1]), max(s_fin.hi[buf][m][2], s_fin.hi[buf][m][3]));
-          if (trial_max) trial_max[at] = x;
-        } else {
-          x = min(min(s_fin.lo[buf][m][0], s_fin.lo[buf][m][1]), min(s_fin.lo[buf][m][2], s_fin.lo[buf][m][3]));
-          if (trial_min) trial_min[at] = x;
-        }
-        s_sum[tid] += x;
+    finish_methods(P, s_fin, s_sum, buf, t, WHOLE, method, trial_min, trial_max);
+  }
+  if (tid < 2u * kMethods && (WHOLE || (tid >> 1) == method)) atomicAdd(&sums[WHOLE ? tid : (tid & 1u)], s_sum[tid]);
+}
+
+// ---- node-local methods with the strata in full bins, most of the sort inside a lane --------------------
+// As k_lbs_bins, for nodes of 2^CB GPUs (CB 2 or 3) whose bins are full and datasets without flagged guide entries.  A
+// node (BINS == 2) or a pair of nodes (BINS == 1) lies in 64 / R lanes of R = 2^LG registers.  The more registers, the fewer
+// of the 21 stages cross lanes (R = 8: 6, 16: 3, 32: 1), and what happens inside a lane can use Batcher's odd-even merge
+// sort (63 comparisons for 16 values instead of the bitonic network's 80).
+//   Before the sort any entry of a bin may lie anywhere in it, so a lane draws all rows of a few columns, i.e. everything
+// that 2^(CB + LG - 6) GPUs draw: which stratum an entry is from is then the same in all lanes (scalar registers, not vector
+// ones), and what a GPU draws itself adds up within the lane.
+//   After the sort lanes with an odd number hold complements in falling order (sort_columns): entry (row, column) of such a lane
+// lies where the other lanes have the mirrored row and column, so that of two neighbours each keeps the first half of its
+// column sums and gets the other's second half, backwards, added to it.
+//   Bound: vector issue (0.87 of the time; a wavefront's 32 nodes cost 8 800 cycles, of which the generator takes 3 900, the look-ups
+// 2 100 and the sort 2 600).  100 000 trials of 1 024 GPUs x 16, nodes of 8, all five methods: 3 093 us before (every generator output made twice,
+// 8 registers), 2 240 with 8 registers, 2 006 with 16, 1 769 with 32; snake alone, 24 414 trials, 514 -> 341.  Which number of
+// registers, and where one node at a time is better, Cost says.
+template <int LG, int CB, int BINS>
+constexpr uint32_t kNodesAtOnce = (1u << LG) * (BINS == 2 ? 1u : 2u);  // nodes a wavefront takes at a time
+
+constexpr uint32_t kCountWords = 1028;  // a trial's histogram: lengths 0 .. LBS_MAX_LEN
+static_assert(kCountWords > LBS_MAX_LEN && kCountWords % 4 == 0);
+typedef const __attribute__((address_space(3))) uint32_t lds_word;
+struct NodesShared {
+  unsigned long long sum[2u * kMethods];
+  FinishAll fin;
+  uint32_t scan[2][kWaves];
+  uint32_t base, unused;
+};
+static_assert(sizeof(NodesShared) % 8 == 0);
+
+struct Rows {  // row r of bin h: base | stratum << 16 | slot << 24 (see Bins)
+  uint32_t row[2][16];
+  uint32_t odd[2];  // bit r: the slot of row r is odd
+};
+
+__device__ __forceinline__ void order_halves(uint32_t& a, uint32_t& b) {
+  const uint32_t x = min_halves(a, b), y = max_halves(a, b);
+  a = x, b = y;
+}
+
+// Sorts the halves of every group of 2^(6 - LG) lanes as sort_halves<LG> does, except that lanes with an odd number end up with
+// complements, their registers in reverse order.  In: values as they are, in any order.
+//   Runs that are merged next run in opposite directions, and as what a run's partner does in the merge after that is free, the
+// directions are taken such that the first stage of a merge finds every lane in the form that it needs.
+template <int LG>
+__device__ __forceinline__ void sort_columns(uint32_t (&v)[1 << LG], const uint32_t (&bit)[6]) {
+  constexpr int R = 1 << LG;
+  uint32_t falls[7];  // falls[lk]: lanes whose run of 2^lk entries is sorted in falling order
+  falls[6] = 0u;
+#pragma unroll
+  for (int lk = 5; lk >= LG; --lk) falls[lk] = falls[lk + 1] ^ bit[lk - LG];
+#pragma unroll
+  for (int c = 0; c < R; ++c) v[c] ^= falls[LG];
+  // odd-even merge sort of the registers: lanes that hold complements sort in falling order
+#pragma unroll
+  for (int p = 1; p < R; p <<= 1) {
+#pragma unroll
+    for (int k = p; k >= 1; k >>= 1) {
+#pragma unroll
+      for (int j = k % p; j + k < R; j += 2 * k) {
+#pragma unroll
+        for (int i = 0; i < k; ++i)
+          if (i + j + k < R && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order_halves(v[i + j], v[i + j + k]);
       }
     }
   }
-  if (tid < 2u * kMethods && (WHOLE || (tid >> 1) == method)) atomicAdd(&sums[WHOLE ? tid : (tid & 1u)], s_sum[tid]);
+#pragma unroll
+  for (int lk = LG + 1; lk <= 6; ++lk) {  // bitonic merges
+#pragma unroll
+    for (int lj = lk - 1; lj >= LG; --lj) {  // across lanes: see sort_halves
+#pragma unroll
+      for (int c = 0; c < R; ++c) v[c] = min_halves(v[c], ~partner_of(v[c], lj - LG));
+      // the form of the next stage; the last merge ends as it is
+      const uint32_t change = lj > LG ? bit[lj - LG] ^ bit[lj - 1 - LG] : lk < 6 ? bit[0] : 0u;
+      if (lj > LG || lk < 6) {
+#pragma unroll
+        for (int c = 0; c < R; ++c) v[c] ^= change;
+      }
+    }
+#pragma unroll
+    for (int lj = LG - 1; lj >= 0; --lj) {
+#pragma unroll
+      for (int c = 0; c < R; ++c)
+        if (!(c & (1 << lj))) order_halves(v[c], v[c | (1 << lj)]);
+    }
+  }
+}
+
+template <int LG, int CB, int BINS, bool WHOLE>
+__global__ __launch_bounds__(kBlock, LG == 5 ? 5 : 6) void k_lbs_nodes(
+    const Params P, const Rows L, const uint32_t method, const uint32_t* __restrict__ guide, uint32_t* trial_min, uint32_t* trial_max,
+    unsigned long long* sums) {
+  constexpr uint32_t R = 1u << LG, C = 1u << CB, LANES = 64u >> LG, ROWS = 64u >> CB;
+  constexpr uint32_t CPL = C / LANES;  // columns a lane draws
+  constexpr uint32_t RPL = R / C;      // rows a lane holds once sorted
+  static_assert(CPL >= 1 && RPL >= 1 && CPL * ROWS == R && RPL * LANES == ROWS && ROWS <= 16);
+  // (WHOLE) the whole dataset's guide table and the trial's own histogram; the strata's tables, NodesShared, a word per GPU.  The kernel
+  // has no static LDS, so that this is address 0 and a draw's upper bits are the address of its entry in the first table (an
+  // addition of the array's address, which the compiler does not fold away, is a fortieth of a draw).
+  extern __shared__ uint32_t s_dyn[];
+  constexpr uint32_t kCnt = kWholeGuideSize, kStrata = WHOLE ? kCnt + kCountWords : 0u;
+  uint32_t* s_strata = s_dyn + kStrata;
+  uint32_t* s_cnt = s_dyn + kCnt;
+  const uint32_t strata_words = P.guide_words - (WHOLE ? kWholeGuideSize : 0u);
+  NodesShared& sh = *reinterpret_cast<NodesShared*>(s_strata + strata_words);
+  uint32_t* s_gpu = s_strata + strata_words + sizeof(NodesShared) / sizeof(uint32_t);
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid < 2u * kMethods) sh.sum[tid] = 0ull;
+  if (WHOLE)
+    for (uint32_t i = tid; i < kWholeGuideSize; i += kBlock) s_dyn[i] = guide[i];
+  for (uint32_t i = tid; i < strata_words; i += kBlock) s_strata[i] = guide[kWholeGuideSize + i];
+  __syncthreads();
+
+  const uint32_t pool_all = P.n_gpus * P.local_batch;
+  const uint32_t n_nodes = P.n_gpus / C;
+  const uint32_t pool = C * P.local_batch;
+  const uint32_t group = lane / LANES, part = lane % LANES;
+  uint32_t bit[6];
+#pragma unroll
+  for (int q = 0; q < 6; ++q) bit[q] = 0u - ((lane >> q) & 1u);
+  uint32_t odd[RPL];  // halves of odd rows among those this lane holds once sorted
+#pragma unroll
+  for (uint32_t r = 0; r < RPL; ++r) {
+    const uint32_t row = part * RPL + ((part & 1u) ? RPL - 1u - r : r);
+    odd[r] = (((L.odd[0] >> row) & 1u) ? 0xffffu : 0u) | (((L.odd[BINS == 2 ? 1 : 0] >> row) & 1u) ? 0xffff0000u : 0u);
+  }
+  const uint32_t uncomplement = bit[0] & (1u - RPL);  // a sum of RPL complements is that many less one, complemented
+
+  uint32_t rows[BINS == 2 ? 2 : 1][ROWS];
+#pragma unroll
+  for (uint32_t h = 0; h < (BINS == 2 ? 2u : 1u); ++h)
+#pragma unroll
+    for (uint32_t r = 0; r < ROWS; ++r) rows[h][r] = L.row[h][r];
+
+  for (uint32_t t = blockIdx.x, round = 0; t < P.n_trials; t += gridDim.x, ++round) {
+    const uint32_t buf = round & 1u;
+    const uint64_t k_trial = (P.first_trial + t) * (uint64_t)pool_all;
+    if (WHOLE) {
+      whole_clear(P, s_cnt, s_gpu, &sh.base);
+      __syncthreads();
+    }
+    const uint64_t z_trial = state(P.seed, k_trial);
+    uint32_t lo[4], hi[4];  // none, own, raster, snake; BINS == 1: the last three are 16-bit halves
+#pragma unroll
+    for (int m = 0; m < 4; ++m) lo[m] = 0xffffffffu, hi[m] = 0u;
+    // `absent` (all ones where there is no node) leaves a minimum as it is, as zero leaves a maximum
+    const auto note = [&](int m, uint32_t x, uint32_t absent) { lo[m] = min(lo[m], x | absent), hi[m] = max(hi[m], x & ~absent); };
+    const auto note_halves = [&](int m, uint32_t x, uint32_t absent) {
+      if (BINS == 2) note(m, (x & 0xffffu) + (x >> 16), absent);
+      else lo[m] = min_halves(lo[m], x | absent), hi[m] = max_halves(hi[m], x & ~absent);
+    };
+    for (uint32_t first = wave * kNodesAtOnce<LG, CB, BINS>; first < n_nodes; first += kWaves * kNodesAtOnce<LG, CB, BINS>) {
+      // A group whose nodes are not there makes somebody else's draws (the same ones in several lanes would be counted one after
+      // the other), which count for nothing; the second of a pair that is not there repeats the first.
+      const bool there = first + (BINS == 2 ? group : group * 2u) < n_nodes;
+      const uint32_t absent = there ? 0u : 0xffffffffu;
+      uint64_t z[BINS == 2 ? 1 : 2];
+      uint32_t one[BINS == 2 ? 1 : 2];
+#pragma unroll
+      for (uint32_t h = 0; h < (BINS == 2 ? 1u : 2u); ++h) {
+        const uint32_t node = first + (BINS == 2 ? group : group * 2u + h);
+        one[h] = node < n_nodes ? 1u : 0u;
+        const uint32_t whose = BINS == 1 && h == 1 && there && node >= n_nodes ? node - 1u : node;
+        z[h] = z_trial + (uint64_t)(whose * pool + part * CPL * P.local_batch) * kGamma;
+      }
+      uint32_t v[R], own[CPL] = {}, none[BINS == 2 ? 1 : 2][CPL] = {};
+#pragma unroll
+      for (uint32_t r = 0; r < ROWS; ++r) {
+        uint32_t info[2], u[2][CPL], w[2][CPL], d[2][CPL];
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+          info[h] = rows[BINS == 2 ? h : 0][r];
+          asm volatile("" : "+s"(info[h]));  // what follows from it is recomputed here: kept from round to round, it would fill the scalar registers
+#pragma unroll
+          for (uint32_t c = 0; c < CPL; ++c) {
+            uint64_t ahead = (uint64_t)(c * P.local_batch + (info[h] >> 24)) * kGamma;
+            asm("" : "+s"(ahead));  // the product is the scalar unit's
+            u[h][c] = LG >= 4 ? drawn_dense(z[BINS == 2 ? 0 : h] + ahead) : drawn(z[BINS == 2 ? 0 : h] + ahead);
+          }
+        }
+        // every table lookup of the row is under way before the first one is needed
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+#pragma unroll
+          for (uint32_t c = 0; c < CPL; ++c) {
+            d[h][c] = s_strata[((info[h] >> 16) & 255u) * kGuideSize + (u[h][c] >> (32u - kGuideBits))];
+            if (WHOLE) w[h][c] = *reinterpret_cast<lds_word*>((u[h][c] >> (30u - kWholeGuideBits)) & ~3u);
+          }
+        }
+        const uint32_t base = (info[0] & 0xffffu) | info[1] << 16;
+#pragma unroll
+        for (uint32_t c = 0; c < CPL; ++c) {
+          const uint32_t low = (d[0][c] + u[0][c]) >> (32u - kGuideBits), high = (d[1][c] + u[1][c]) >> (16u - kGuideBits);
+          v[r * CPL + c] = ((high & 0xffff0000u) | low) + base;  // the upper 9 bits of either sum are its length
+          own[c] += v[r * CPL + c];
+          if (WHOLE) {
+#pragma unroll
+            for (uint32_t h = 0; h < 2; ++h) {
+              const uint32_t l4 = ((w[h][c] + u[h][c]) >> (30u - kWholeGuideBits)) & ~3u;  // four times the length
+              none[BINS == 2 ? 0 : h][c] += l4;
+              atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s_cnt) + l4), one[BINS == 2 ? 0 : h]);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (uint32_t c = 0; c < CPL; ++c) {
+        note_halves(1, own[c], absent);
+        if (WHOLE) {
+#pragma unroll
+          for (uint32_t h = 0; h < (BINS == 2 ? 1u : 2u); ++h) note(0, none[h][c] >> 2, absent);
+        }
+      }
+      sort_columns<LG>(v, bit);
+      uint32_t raster[C], snake[C / 2];
+#pragma unroll
+      for (uint32_t c = 0; c < C; ++c) {
+        raster[c] = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < RPL; ++r) raster[c] += v[r * C + c];
+        raster[c] = (raster[c] ^ bit[0]) + uncomplement;
+      }
+#pragma unroll
+      for (uint32_t c = 0; c < C / 2; ++c) {
+        snake[c] = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < RPL; ++r) snake[c] += (v[r * C + c] & ~odd[r]) | (v[r * C + C - 1u - c] & odd[r]);
+        snake[c] = (snake[c] ^ bit[0]) + uncomplement;
+      }
+#pragma unroll
+      for (uint32_t c = 0; c < C / 2; ++c) {  // the mirrored column of the snake has what is left of the two columns
+        const uint32_t mirrored = raster[c] + raster[C - 1u - c] - snake[c];
+        uint32_t x = raster[c] + from_partner<0>(raster[C - 1u - c]), y = snake[c] + from_partner<0>(mirrored);
+#pragma unroll
+        for (int b = 1; b < 6 - LG; ++b) x += partner_of(x, b), y += partner_of(y, b);
+        note_halves(2, x, absent), note_halves(3, y, absent);
+      }
+    }
+#pragma unroll
+    for (int m = WHOLE ? 0 : 1; m < 4; ++m) {
+      if (BINS == 1 && m > 0) {  // 0xffffffff: a wavefront that has seen no node
+        lo[m] = lo[m] == 0xffffffffu ? lo[m] : min(lo[m] & 0xffffu, lo[m] >> 16);
+        hi[m] = max(hi[m] & 0xffffu, hi[m] >> 16);
+      }
+      const uint32_t q = m == 0 ? LBS_NONE : m == 1 ? LBS_STRATIFIED : m == 2 ? LBS_LOCAL_RASTER : LBS_LOCAL_SNAKE;
+      file_min_max(sh.fin, buf, q, lo[m], hi[m]);
+    }
+    if (WHOLE) {
+      uint32_t glob_lo = 0xffffffffu, glob_hi = 0u;
+      __syncthreads();
+      whole_deal(P, s_cnt, s_gpu, &sh.base, sh.scan, glob_lo, glob_hi);
+      file_min_max(sh.fin, buf, LBS_GLOBAL, glob_lo, glob_hi);
+    }
+    __syncthreads();  // also: this trial's last reads of s_cnt and s_gpu lie before the next trial's clearing
+    finish_methods(P, sh.fin, sh.sum, buf, t, WHOLE, method, trial_min, trial_max);
+  }
+  if (tid < 2u * kMethods && (WHOLE || (tid >> 1) == method)) atomicAdd(&sums[WHOLE ? tid : (tid & 1u)], sh.sum[tid]);
+}
+
+// What a trial costs, in tenths of a nanosecond on the whole chip (256 compute units, measured at 1 to 256 nodes): a wavefront's rounds of
+// `at_once` nodes (BINS == 1: pairs) at `each`, a share of that for wavefronts that idle in the last turn, and the trial's own.  With the
+// draws from the whole dataset (all five methods) a trial has four more barriers, and idle wavefronts weigh more.
+struct Cost {
+  uint32_t n;  // nodes, or pairs of nodes
+  bool whole;
+  double rounds(uint32_t at_once, double each, double trial) const {
+    const uint32_t r = (n + at_once - 1u) / at_once;
+    return trial + each * (r + (kWaves - 1u - (r - 1u) % kWaves) / (whole ? 4.0 : 8.0));
+  }
+  // k_lbs_bins<0>: one at a time
+  double one() const { return whole ? 12.0 + 2.5 * n : 2.2 * n; }
+  // columns in registers, 2^lg of them: k_lbs_bins<2> and <3>
+  double columns(uint32_t lg) const {
+    return lg == 2 ? rounds(4, whole ? 8.2 : 7.2, whole ? 13.0 : 3.0) : rounds(8, whole ? 15.5 : 12.0, whole ? 20.0 : 6.0);
+  }
+  // k_lbs_nodes<lg>
+  double nodes(uint32_t lg) const {
+    const double each = lg == 3 ? (whole ? 13.0 : 10.8) : lg == 4 ? (whole ? 22.0 : 18.0) : (whole ? 41.0 : 33.0);
+    return rounds(1u << lg, each, whole ? 20.0 : 6.0);
+  }
+};
+inline Cost cost_of(const Bins& L, const Params& P, bool whole) {
+  const uint32_t n_nodes = P.n_gpus / P.gpus_per_node;
+  return Cost{L.count == 2 ? n_nodes : (n_nodes + 1u) / 2u, whole};
 }
 
 // k_lbs_bins for a run whose strata fit in L.count bins.  Columns in registers for nodes of 4 and 8: with two columns only 6 of the
 // 21 stages would stay within a lane (11 with four, 15 with eight), and sixteen are more columns than a group has lanes.
 template <bool WHOLE>
-auto pick_bins(const Bins& L, uint32_t gpus_per_node, uint32_t n_nodes) {
+auto pick_bins(const Bins& L, const Params& P, bool one_round) {
   const bool two = L.count == 2;
-  if (n_nodes >= gpus_per_node * (two ? 1u : 2u)) {
-    if (gpus_per_node == 4) return two ? k_lbs_bins<2, 2, WHOLE> : k_lbs_bins<2, 1, WHOLE>;
-    if (gpus_per_node == 8) return two ? k_lbs_bins<3, 2, WHOLE> : k_lbs_bins<3, 1, WHOLE>;
-  }
+  const Cost c = cost_of(L, P, WHOLE);
+  // one_round: a trial's time matters, not its cost, and several nodes at a time are through first
+  const auto columns = [&](uint32_t lg) { return one_round ? c.n >= P.gpus_per_node : c.columns(lg) < c.one(); };
+  if (P.gpus_per_node == 4 && columns(2)) return two ? k_lbs_bins<2, 2, WHOLE> : k_lbs_bins<2, 1, WHOLE>;
+  if (P.gpus_per_node == 8 && columns(3)) return two ? k_lbs_bins<3, 2, WHOLE> : k_lbs_bins<3, 1, WHOLE>;
   return two ? k_lbs_bins<0, 2, WHOLE> : k_lbs_bins<0, 1, WHOLE>;
+}
+
+// Dynamic LDS of k_lbs_nodes, in bytes.
+template <bool WHOLE>
+size_t nodes_lds(const Params& P) {
+  return sizeof(NodesShared) + sizeof(uint32_t) * ((size_t)P.guide_words + (WHOLE ? kCountWords + P.n_gpus : 0u));
+}
+
+// k_lbs_nodes for a run, or nullptr where it does not apply or k_lbs_bins is the better one; L: its rows.
+template <bool WHOLE>
+auto pick_nodes(const Bins& B, const Params& P, Rows* L) {
+  decltype(&k_lbs_nodes<4, 3, 2, WHOLE>) kernel = nullptr;
+  const uint32_t gpn = P.gpus_per_node;
+  if (B.count == 0 || B.padded != 0 || P.flagged != 0 || (gpn != 4 && gpn != 8)) return kernel;
+  const Cost c = cost_of(B, P, WHOLE);
+  const double nodes[] = {gpn == 8 ? c.nodes(3) : c.columns(2), c.nodes(4), c.nodes(5)};
+  const uint32_t lg = nodes[2] < std::min(nodes[0], nodes[1]) ? 5u : nodes[1] < nodes[0] ? 4u : gpn == 8 ? 3u : 0u;
+  if (lg == 0 || c.one() < nodes[lg - 3]) return kernel;
+  const uint32_t rows = 64u / gpn;
+  *L = Rows{};
+  for (uint32_t h = 0; h < B.count; ++h)
+    for (uint32_t r = 0; r < rows; ++r) {
+      const uint32_t j = B.slot[h][r];
+      L->row[h][r] = P.slot_base[j] | (P.slot_guide[j] / kGuideSize) << 16 | j << 24;
+      L->odd[h] |= (j & 1u) << r;
+    }
+  if (B.count == 2) {
+    if (gpn == 4) kernel = lg == 5 ? k_lbs_nodes<5, 2, 2, WHOLE> : k_lbs_nodes<4, 2, 2, WHOLE>;
+    else kernel = lg == 5 ? k_lbs_nodes<5, 3, 2, WHOLE> : lg == 4 ? k_lbs_nodes<4, 3, 2, WHOLE> : k_lbs_nodes<3, 3, 2, WHOLE>;
+  } else {
+    if (gpn == 4) kernel = lg == 5 ? k_lbs_nodes<5, 2, 1, WHOLE> : k_lbs_nodes<4, 2, 1, WHOLE>;
+    else kernel = lg == 5 ? k_lbs_nodes<5, 3, 1, WHOLE> : lg == 4 ? k_lbs_nodes<4, 3, 1, WHOLE> : k_lbs_nodes<3, 3, 1, WHOLE>;
+  }
+  return kernel;
 }
 
 __global__ __launch_bounds__(64) void k_lbs_clear_all(unsigned long long* sums) {
@@ -1050,7 +1418,7 @@ bool fill_guide(uint32_t* out, const std::vector<uint32_t>& cum, uint32_t before
   bool flagged = false;
   constexpr uint32_t kLow = 32u - BITS;
   uint32_t l = base + 1u;  // cells and their ends come in ascending order, and so do the lengths
-  const auto length_of = [&](uint32_t index) {  // smallest length with more than `index` entries up to it
+  const auto first_over = [&](uint32_t index) {  // smallest length with more than `index` entries up to it
     while (cum[l] <= index) ++l;
     return l;
   };
@@ -1060,14 +1428,14 @@ bool fill_guide(uint32_t* out, const std::vector<uint32_t>& cum, uint32_t before
       out[ub] = 0u;  // never drawn from
       continue;
     }
-    const uint32_t l_min = length_of(before + (uint32_t)((u_min * size) >> 32));
-    const uint32_t l_max = length_of(before + (uint32_t)((u_max * size) >> 32));
+    const uint32_t l_min = first_over(before + (uint32_t)((u_min * size) >> 32));
+    const uint32_t l_max = first_over(before + (uint32_t)((u_max * size) >> 32));
     if (l_max > l_min + 1u || l_max - base >= (1u << BITS) - 1u) {
-      out[ub] = kFlagged<BITS> | (l_min - 1u) | ((l_max - l_min) << 10);
+      out[ub] = (kFlagged<BITS> | (l_min - 1u) | ((l_max - l_min) << 10)) - (uint32_t)u_min;
       flagged = true;
       continue;
     }
-    out[ub] = (l_min - base) << kLow;
+    out[ub] = ((l_min - base) << kLow) - (uint32_t)u_min;
     if (l_max > l_min) {  // the first draw whose index reaches the entries of l_max
       const uint64_t from = (((uint64_t)(cum[l_min] - before) << 32) + size - 1u) / size;
       out[ub] += (uint32_t)((1ull << kLow) - (from - u_min));
@@ -1303,8 +1671,14 @@ static int simulate_one(const lbs_dataset* ds, const lbs_run* run, uint32_t meth
     const Bins L = local ? pack_bins(ds, run) : Bins{};
     const bool many_short = local && L.count == 1 && run->n_gpus / run->gpus_per_node <= kWaves &&
                             run->n_trials > (uint64_t)kBinsMostShortTrials * grid.x;
-    if (local && L.count != 0 && !many_short) {
-      hipLaunchKernelGGL(pick_bins<false>(L, run->gpus_per_node, run->n_gpus / run->gpus_per_node), grid, block, sizeof(uint32_t) * tables, s, P, L,
+    Rows rows;
+    // trials that are all resident at once take as long as one does, and k_lbs_bins, whose code is shorter, is through first: 500 trials of
+    // 33 nodes of 4, batch 16, 13.7 us against 14.5
+    const bool one_round = run->n_trials <= 6u * (uint64_t)ds->n_cus;
+    if (const auto nodes = local && !many_short && !one_round ? pick_nodes<false>(L, P, &rows) : nullptr) {
+      hipLaunchKernelGGL(nodes, grid, block, nodes_lds<false>(P), s, P, rows, method, ds->d_guide, trial_min, trial_max, ds_sums);
+    } else if (local && L.count != 0 && !many_short) {
+      hipLaunchKernelGGL(pick_bins<false>(L, P, one_round), grid, block, sizeof(uint32_t) * tables, s, P, L,
                          method, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);
     } else if (local) {
       const uint32_t gpn = run->gpus_per_node;
@@ -1375,8 +1749,11 @@ static int simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* tri
     const Bins L = pack_bins(ds, run);
     void (*kernel)(const Params, const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, unsigned long long*) =
         pool <= 64 ? k_lbs_all<1> : pool <= 128 ? k_lbs_all<2> : pool <= 256 ? k_lbs_all<4> : pool <= 512 ? k_lbs_all<8> : k_lbs_all<16>;
-    if (L.count != 0)
-      hipLaunchKernelGGL(pick_bins<true>(L, gpn, G / gpn), grid, block, lds, s, P, L, 0u, ds->d_cum,
+    Rows rows;
+    if (const auto nodes = pick_nodes<true>(L, P, &rows))
+      hipLaunchKernelGGL(nodes, grid, block, nodes_lds<true>(P), s, P, rows, 0u, ds->d_guide, trial_min, trial_max, ds_sums);
+    else if (L.count != 0)
+      hipLaunchKernelGGL(pick_bins<true>(L, P, run->n_trials <= 6u * (uint64_t)ds->n_cus), grid, block, lds, s, P, L, 0u, ds->d_cum,
                          ds->d_guide, trial_min, trial_max, ds_sums);
     else
       hipLaunchKernelGGL(kernel, grid, block, lds, s, P, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);

@@ -33,6 +33,23 @@ def test_quotas_that_fit_in_bins_and_quotas_that_do_not(gpn, batch, quota):
         check_all(CUM, ENDS, batch, gpn, gpn * n_nodes, quota, seed=17 * gpn + n_nodes, n=7, first=11)
 
 
+# Full bins of nodes of 4 and 8, where the number of nodes decides how many registers a node lies in (8, 16 or 32, or one column
+# a register): below, at and above the lines, numbers that leave wavefronts and groups of lanes without a node, and odd numbers where
+# two nodes share a register.  Slots whose rows change parity inside a bin ([5, 2, 3, 6]) and ones that do not.
+@pytest.mark.parametrize("gpn,batch,quota,nodes", [
+    (8, 16, [6, 3, 2, 5], (19, 22, 33, 50, 128, 131)), (8, 16, [5, 2, 3, 6], (32, 64, 97)),
+    (8, 8, [3, 2, 1, 2], (31, 45, 65, 130, 255)), (4, 16, [5, 2, 3, 6], (9, 61, 67, 129, 256)), (4, 32, [12, 6, 4, 10], (17, 33, 65, 130)),
+])
+def test_full_bins_by_number_of_nodes(gpn, batch, quota, nodes):
+    import torch
+    for n_nodes in nodes:
+        check_all(CUM, ENDS, batch, gpn, gpn * n_nodes, quota, seed=n_nodes, n=5, first=2)
+    # one method alone goes that way where there are more trials than are resident at once
+    n = 6 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+    for n_nodes, method in zip((nodes[0], nodes[1], nodes[-1]), LOCAL + LOCAL[:1]):
+        check(CUM, ENDS, method, batch, gpn, gpn * n_nodes, quota, seed=5 * n_nodes, n=n)
+
+
 @pytest.mark.parametrize("kind", ["gaps", "spike", "rare_tail", "wide_strata", "one_length"])
 def test_histograms_whose_cells_have_to_be_searched(kind):
     rng = np.random.default_rng(5)
