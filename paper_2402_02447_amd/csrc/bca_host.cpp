@@ -247,6 +247,14 @@ void build_work(bca_plan* p) {
   }
 }
 
+// Marks the Adam items that start with the launch (kEarlyPerCu), on a GPU of n_cus compute units.
+void mark_early(bca_plan* p, int n_cus) {
+  if (p->work.size() > kEarlyItems) return;
+  const size_t n = std::min<size_t>(p->work.size(), (size_t)std::max(n_cus, 1) * kEarlyPerCu);
+  for (size_t w = 0; w < n; ++w)
+    if (p->work[w] >> 30 == kItemAdam) p->work[w] |= kItemEarly;
+}
+
 // Items and work lists of LAMB in one pass (see k_lamb), for tables cut at kDefaultChunkApply.  `slots`: workgroups of
 // that kernel that are resident on the GPU at a time.
 //   An item is up to kLambItemChunks full chunks, or one short chunk.  Items are made in the order of the apply table (bucket
@@ -336,7 +344,7 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     }
     // a block of Adam items is whole groups; which ones, its first and last chunk say
     uint32_t end_chunk = 0;
-    for (; w < p->work.size() && p->work[w] >> 30 == kItemAdam; ++w) end_chunk = (p->work[w] & 0x3fffffffu) + 1u;
+    for (; w < p->work.size() && p->work[w] >> 30 == kItemAdam; ++w) end_chunk = (p->work[w] & kItemIndex) + 1u;
     while (g < p->groups.size() && A.bucket_off[p->groups[g].second] <= end_chunk) {
       for (; next < group_end[g]; ++next) p->lamb_clip_work.push_back((kItemAdam << 30) | place[next]);
       ++g;
@@ -673,7 +681,10 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
       p->lamb_items.clear(), p->lamb_clip_work.clear();
     }
   };
-  if (device < 0) lamb_items(kHostPlanCus, apply_to_lamb_map(p));
+  if (device < 0) {
+    mark_early(p, kHostPlanCus);
+    lamb_items(kHostPlanCus, apply_to_lamb_map(p));
+  }
   if (device >= 0) {
     int n_dev = 0;
     hipError_t e = hipGetDeviceCount(&n_dev);
@@ -690,6 +701,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
     const size_t nb = n_buckets;
     const size_t nl = std::max<size_t>(p->lamb_tab.chunks.size(), 1), nt = std::max<size_t>(n_tensors, 1);
     const std::vector<uint32_t> a2l = apply_to_lamb_map(p);
+    mark_early(p, prop.multiProcessorCount);
     lamb_items(prop.multiProcessorCount, a2l);
     // One block for LAMB in one pass, so that plans that never use it are set up about as fast as without (six allocations
     // and as many copies: 160 tensors of 64 K 620 us instead of 543).  Ready words and arrival counters lie on pages of their own:
@@ -902,7 +914,7 @@ int bca_plan_work_item(const bca_plan* p, uint32_t i, uint32_t* kind, uint32_t* 
   if (i >= p->work.size()) return fail(BCA_ERR_RANGE, "work item index out of range");
   const uint32_t item = p->work[i], k = item >> 30;
   if (kind) *kind = k;
-  if (first) *first = k == kItemAdam ? (item & 0x3fffffffu) : (item & 0x0fffffffu);
+  if (first) *first = k == kItemAdam ? (item & kItemIndex) : (item & 0x0fffffffu);
   if (count) *count = k == kItemNorm ? ((item >> 28) & 3u) + 1u : k == kItemAdam ? 1u : 0u;
   return BCA_OK;
 }

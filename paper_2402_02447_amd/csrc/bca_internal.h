@@ -140,9 +140,17 @@ enum : uint32_t {
 // Work items up to which the pipelined launch finishes itself instead of having k_finish behind it.  Measured, fused step, fp32
 // (k_finish / itself): 20 K elements 9.0 / 7.8 us, 1 M 13.3 / 12.8, 3 M 24.8 / 24.4, 8 M 51.1 / 50.9, 16 M 85.3 / 86.1.
 constexpr uint32_t kSelfFinishItems = 8192;
-// Work items of k_step: kind in bits 30..31; kItemAdam: apply-table chunk in bits 0..29; kItemNorm: first
+// Work items of k_step: kind in bits 30..31; kItemAdam: apply-table chunk in bits 0..28 and kItemEarly; kItemNorm: first
 // norm-table chunk in bits 0..27 and the number of consecutive chunks minus one in bits 28..29; kItemEmpty: bucket.
 constexpr uint32_t kItemNorm = 0u, kItemAdam = 1u, kItemEmpty = 2u;
+constexpr uint32_t kItemEarly = 1u << 29, kItemIndex = kItemEarly - 1u;
+// Adam items among the first kEarlyPerCu work items a compute unit (eight are resident at a time, and the squared-norm items at
+// the head of the list leave early) start before their bucket's coefficient exists: they load all they need first and wait then, while
+// the memory system has little else to do.  Fused step, us, with 0 / 4 / 8 / 10 / 12: 1 M elements 11.4 / 10.7 / 9.9 / 9.9 / 10.2, 3.4 M
+// 18.7 / 18.3 / 17.6 / 16.6 / 16.6, 11 M (bf16) 61.8 / 61.4 / 59.5 / 58.6 / 59.0, 20 M (bf16) 111.8 / 110.5 / 110.2 / 109.1 / 111.9.  In
+// plans of up to kEarlyItems work items, by a variant of its own: the code alone costs the large ones 1 % (BERT-Large
+// 1 567 -> 1 590 us), and 2 us is nothing to them.
+constexpr uint32_t kEarlyPerCu = 10, kEarlyItems = 32768;
 struct StepState {
   const Chunk* norm_tab;
   const Chunk* apply_tab;

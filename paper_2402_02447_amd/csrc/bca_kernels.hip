@@ -693,6 +693,26 @@ __device__ __forceinline__ void adam_chunk(const Entry& en, float coef, const Ad
   }
 }
 
+// One full chunk (four elements a thread) of the fused sweep whose coefficient is not known yet: everything is loaded first, then
+// wait() says whether there is a coefficient, and leaves it in *coef.  The arithmetic is adam_chunk's.
+template <int GDT, bool WB, typename W>
+__device__ __forceinline__ void adam_chunk_early(const Entry& en, const AdamK& k, const float* coef, W wait) {
+  typedef Grad<GDT> G;
+  const uint32_t tid = threadIdx.x;
+  f32x4* pv = reinterpret_cast<f32x4*>(en.p) + tid;
+  f32x4* mv = reinterpret_cast<f32x4*>(en.m) + tid;
+  f32x4* vv = reinterpret_cast<f32x4*>(en.v) + tid;
+  void* gv = reinterpret_cast<void*>(en.g);
+  f32x4 g = G::template load4<false>(gv, tid), p = ldv<true>(pv), m = ldv<true>(mv), v = ldv<true>(vv);
+  loads_issued();
+  if (!wait()) return;
+  const float c = *coef;
+  g = g * c;
+  adam4(g, p, m, v, k, chunk_wd(en, k));
+  stv<true>(pv, p), stv<true>(mv, m), stv<true>(vv, v);
+  if (WB && c != 1.f) G::template store4<false>(gv, tid, g);
+}
+
 template <int GDT, bool FUSED, bool WB, uint32_t U, bool GNT, bool STAGED>
 __global__ __launch_bounds__(kBlock) void k_adam(const Chunk* __restrict__ table, uint32_t c0, uint32_t n,
                                                   const float* __restrict__ coefs, const int32_t* skip_status,
@@ -1150,8 +1170,9 @@ __device__ __forceinline__ bool last_done(const StepState& st, uint32_t n_work, 
 // SELF: the launch needs no k_finish behind it.  Every workgroup is counted once its item is decided, and the one that
 // completes the count does what k_finish would.  Adam items are counted when their wait has ended, before they load
 // anything, so that the round trip is hidden behind the item itself.
-template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB, bool SELF = false>
-__global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,
+// EARLY: for lists with items that load before they wait (kItemEarly); eight workgroups a compute unit even so.
+template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB, bool SELF = false, bool EARLY = SELF>
+__global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,
                                                   const float* __restrict__ thresholds, float* __restrict__ norms,
                                                   float* __restrict__ coefs, const AdamK ka, int32_t* status) {
   __shared__ StepShared sh;
@@ -1187,16 +1208,24 @@ __global__ __launch_bounds__(kBlock) void k_step(StepState st, const uint32_t* _
   const uint32_t item = work[ticket];
   const uint32_t kind = item >> 30;
   if (kind == kItemAdam) {
-    const uint32_t idx = item & 0x3fffffffu;
+    const uint32_t idx = item & kItemIndex;
     const Entry en = read_entry(&st.apply_tab[idx]);
-    const bool ready = wait_for_bucket(st, en.bucket, epoch, idx, sh);
-    if constexpr (SELF) {
-      if (threadIdx.x == 0) {
-        if (!ready) wait_vmem();  // what the wait has filed has arrived
-        before = count_done(st);  // not looked at before the item is done
-      }
+    if constexpr (EARLY) {
+      const auto wait = [&] {
+        const bool ready = wait_for_bucket(st, en.bucket, epoch, idx, sh);
+        if constexpr (SELF) {
+          if (threadIdx.x == 0) {
+            if (!ready) wait_vmem();  // what the wait has filed has arrived
+            before = count_done(st);  // not looked at before the item is done
+          }
+        }
+        return ready;
+      };
+      if ((item & kItemEarly) != 0u && en.len == 4u * kBlock) adam_chunk_early<GDT, WB>(en, k, &sh.coef, wait);
+      else if (wait()) apply_item<GDT, WB, U, MODE>(st, en, idx, sh.coef, k, sh);
+    } else {
+      if (wait_for_bucket(st, en.bucket, epoch, idx, sh)) apply_item<GDT, WB, U, MODE>(st, en, idx, sh.coef, k, sh);
     }
-    if (ready) apply_item<GDT, WB, U, MODE>(st, en, idx, sh.coef, k, sh);
   } else {
     // squared-norm items carry their chunk count (1 .. 4) in bits 28..29
     norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
@@ -1796,7 +1825,8 @@ hipError_t launch_step(int gdt, const StepState& st, const uint32_t* work, uint3
                        float* norms, float* coefs, int32_t* status, bool write_back, const AdamK& k, uint32_t unroll,
                        bool tickets, bool lamb, hipEvent_t between, hipStream_t stream) {
   // Plans of few items finish themselves (kSelfFinishItems); with events to be recorded in between there are two launches.
-  const bool self = !lamb && !tickets && unroll == 1 && between == nullptr && n_work <= kSelfFinishItems;
+  const bool plain = !lamb && !tickets && unroll == 1;
+  const bool self = plain && between == nullptr && n_work <= kSelfFinishItems;
   if (n_work != 0) {
     if (self) {
       pick_gdt(gdt, [&](auto gd) {
@@ -1810,7 +1840,17 @@ hipError_t launch_step(int gdt, const StepState& st, const uint32_t* work, uint3
       });
       return hipGetLastError();
     }
-    if (lamb) {  // one variant per gradient type and write-back setting: items by workgroup index, no unrolling
+    if (plain && n_work <= kEarlyItems) {
+      pick_gdt(gdt, [&](auto gd) {
+        constexpr int GDT = decltype(gd)::value;
+        if (write_back)
+          hipLaunchKernelGGL((k_step<GDT, true, 1, false, false, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
+                             thresholds, norms, coefs, k, status);
+        else
+          hipLaunchKernelGGL((k_step<GDT, false, 1, false, false, false, true>), dim3(n_work), dim3(kBlock), 0, stream, st, work, n_work,
+                             thresholds, norms, coefs, k, status);
+      });
+    } else if (lamb) {  // one variant per gradient type and write-back setting: items by workgroup index, no unrolling
       pick_gdt(gdt, [&](auto gd) {
         constexpr int GDT = decltype(gd)::value;
         if (write_back)

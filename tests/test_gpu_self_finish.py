@@ -56,3 +56,35 @@ def test_status_bits_reach_the_caller_and_do_not_stay():
     plan.bucket_clip_adam(thr, HP, 3, 0, *out)
     assert int(out[2].item()) == B.BCA_STATUS_BAD_THRESHOLD
     plan.close()
+
+
+@pytest.mark.parametrize("dtype,gdt", [(torch.float16, B.BCA_GRAD_F16), (torch.bfloat16, B.BCA_GRAD_BF16), (torch.float32, B.BCA_GRAD_F32)])
+@pytest.mark.parametrize("sizes,cap", [([1023, 1024, 2049], 2000), ([300_001, 77], 65_536), ([30_000_000, 5], 1_048_576), ([33_000_000, 5], 1_048_576)])
+@pytest.mark.parametrize("flags", [0, B.BCA_WRITE_BACK_GRADS])
+def test_items_that_load_before_they_wait(dtype, gdt, sizes, cap, flags):
+    """Full and ragged chunks, arrays off the vectors' alignment, exempt tensors, and both sides of the number of work items
+    up to which such items exist."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    lay = W.layout_flat_split(sizes, cap)
+    thr = torch.full((lay.n_buckets,), 0.5, device="cuda")
+    runs = []
+    for tuning in ({}, {"tune_flags": B.BCA_TUNE_MULTI_LAUNCH}):
+        gen.manual_seed(7)
+        state = [[(torch.randn(n + 3, generator=gen, device="cuda") * s)[o:o + n] for n in sizes] for s, o in ((1e-2, 0), (0.02, 1), (3e-4, 2))]
+        state.append([(torch.rand(n + 3, generator=gen, device="cuda").add_(0.5) * 1e-6)[:n] for n in sizes])
+        state[0] = [torch.cat([x[:1], x]).to(dtype)[1:] for x in state[0]]
+        plan = B.Plan.from_layout(lay, gdt, **tuning)
+        plan.set_decay_mask([i % 2 for i in range(len(sizes))])
+        plan.bind(*state)
+        out = [torch.zeros(lay.n_buckets, device="cuda") for _ in range(2)] + [torch.full((1,), -1, dtype=torch.int32, device="cuda")]
+        if sizes[0] > 20_000_000:
+            assert (len(plan.work_items()) <= 32768) == (sizes[0] == 30_000_000)
+        for step in range(1, 4):
+            plan.bucket_clip_adam(thr, HP, step, flags, *out)
+        torch.cuda.synchronize()
+        assert int(out[2].item()) == 0
+        runs.append(([x.clone() for ts in state for x in ts] + out[:2], plan))
+    for a, b in zip(runs[0][0], runs[1][0]):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    for _, plan in runs:
+        plan.close()
