@@ -316,17 +316,30 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     if (p->lamb_items_of[t] > 1) shared_elems += p->tensor_numel[t], shared_items += p->lamb_items_of[t];
   const bool small = p->lamb_items.size() <= 2u * slots && shared_elems > all_elems / kLambIrregularShare &&
                      shared_elems < shared_items * kLambItemElemsMany;
-  // held items first, the others behind them: the order in which lamb_step works on them
+  // held tensors first, then what is swept again, then the held ends: the order in which lamb_step works on them
+  enum : int { kWhole, kSwept, kEnd };
+  p->lamb_clip_ends = true;
+  const auto part = [&](uint32_t i) {
+    const uint32_t t = p->lamb_items[i].tensor;
+    const uint64_t span = (uint64_t)last_item[t] - first_item[t] + 1u;
+    if (span <= most) return kWhole;
+    if (span < kLambEndsFrom * most || last_item[t] - i >= most) return kSwept;
+    if ((uint64_t)last_item[t] + slots / 4 < p->lamb_items.size()) p->lamb_clip_ends = false;
+    return kEnd;
+  };
+  for (uint32_t i = 0; i < p->lamb_items.size(); ++i) (void)part(i);
   std::vector<LambItem> sorted;
   std::vector<uint32_t> place(p->lamb_items.size());
-  for (const bool held : {true, false}) {
-    if (!held) p->lamb_first_large = (uint32_t)sorted.size();
+  for (const int now : {kWhole, kSwept, kEnd}) {
+    if (now == kSwept) p->lamb_first_large = (uint32_t)sorted.size();
+    if (now == kEnd) p->lamb_first_end = (uint32_t)sorted.size();
     for (uint32_t i = 0; i < p->lamb_items.size(); ++i) {
+      if (part(i) != now) continue;
       LambItem it = p->lamb_items[i];
-      if (((uint64_t)last_item[it.tensor] - first_item[it.tensor] + 1u <= most) != held) continue;
-      if (held) it.flags |= kLambHeld;
+      const bool ends_alone = now == kEnd && !p->lamb_clip_ends;
+      if (now != kSwept) it.flags |= ends_alone ? kLambHeldAlone : kLambHeld;
       // read again by the tail kernel: worth keeping cached unless it is more than a cache holds
-      else if (large_elems <= kLambGroupElems) it.flags |= kLambKeep;
+      if ((now == kSwept || ends_alone) && large_elems <= kLambGroupElems) it.flags |= kLambKeep;
       it.items = p->lamb_items_of[it.tensor], it.lo = p->tensor_off[it.tensor], it.hi = p->tensor_off[it.tensor + 1];
       place[i] = (uint32_t)sorted.size();
       sorted.push_back(it);
@@ -482,11 +495,12 @@ StepState step_state(const bca_plan* p) {
   return ss;
 }
 
-LambState lamb_state(const bca_plan* p, float* trust) {
+LambState lamb_state(const bca_plan* p, float* trust, bool clip) {
   LambState ls;
   ls.tab = p->lamb_tab.d_chunks, ls.items = p->d_lamb_items, ls.items_of = p->d_lamb_items_of;
   ls.arrived = p->d_lamb_arrived, ls.ready = p->d_lamb_ready, ls.sums = p->d_lamb_sums, ls.trust = trust, ls.late = p->d_lamb_late;
   ls.n_items = (uint32_t)p->lamb_items.size(), ls.first_large = p->lamb_first_large, ls.n_tensors = p->n_tensors;
+  ls.first_end = clip && !p->lamb_clip_ends ? ls.n_items : p->lamb_first_end;
   return ls;
 }
 
@@ -897,7 +911,7 @@ int bca_plan_lamb_item(const bca_plan* p, int clip, uint32_t i, uint32_t* kind, 
     if (first) *first = it.first;
     if (count) *count = it.count;
     if (tensor) *tensor = it.tensor;
-    if (held) *held = (it.flags & kLambHeld) ? 1u : 0u;
+    if (held) *held = (it.flags & (clip ? kLambHeld : kLambHeld | kLambHeldAlone)) ? 1u : 0u;
     return BCA_OK;
   }
   if (first) *first = item & 0x0fffffffu;
@@ -1232,7 +1246,7 @@ static int lamb_impl(bca_plan* p, const float* thresholds, const bca_adam* hp, u
   hipError_t e = hipSuccess;
   if (lamb_in_one_pass(p, thresholds != nullptr)) {
     const size_t n_work = thresholds ? p->lamb_clip_work.size() : p->lamb_items.size();
-    e = launch_lamb(p->grad_dtype, step_state(p), lamb_state(p, trust ? trust : p->d_trust),
+    e = launch_lamb(p->grad_dtype, step_state(p), lamb_state(p, trust ? trust : p->d_trust, thresholds != nullptr),
                     p->d_lamb_clip_work, (uint32_t)n_work, thresholds != nullptr, thresholds,
                     norms ? norms : p->d_norms, coefs ? coefs : p->d_coefs,
                     status, (flags & BCA_WRITE_BACK_GRADS) != 0, k, s);

@@ -182,6 +182,7 @@ static_assert(sizeof(LambItem) == 64, "item table entries are 4 x 16 bytes");
 constexpr uint32_t kLambRegular = 2u;  // full chunks only, and 16-byte vectors from the first element on
 constexpr uint32_t kLambHeld = 4u;     // p and u stay on the chip until the tensor's ratio is known
 constexpr uint32_t kLambKeep = 8u;     // moments are stored cacheable: the tail kernel reads them again
+constexpr uint32_t kLambHeldAlone = 16u;  // as kLambHeld, in lamb_step only
 // Workgroups of k_lamb that are resident at a time on a compute unit: what __launch_bounds__ asks for (128 VGPRs), and four
 // times the 33 KiB of LDS fit in 160 KiB.
 constexpr uint32_t kLambResidentPerCu = 4;
@@ -189,6 +190,14 @@ constexpr int kHostPlanCus = 256;  // compute units that a host-only plan (devic
 // A tensor is held if its items, with whatever lies between them in the work list, are at most this share of what is
 // resident on the whole GPU (3/4: a tensor's first workgroups hold their slots until its last one is through).
 constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
+// Of a tensor that is too large to be held, the end is (as many items as a held tensor may have) if it has at least kLambEndsFrom
+// times as many: the tail kernel then has so much less to read again.  lamb_step works on the ends last, when nobody else needs
+// their slots; bucket_clip_lamb, whose order is the buckets', holds them only if at most a quarter of the slots' items follow.
+// Without / with the ends, us, lamb_step and bucket_clip_lamb: BERT-Base (word embedding 1 908 items) 616 / 603 and 583 / 570 (fp16), BERT-Large 1 847 /
+// 1 833 and 1 743 / 1 732, thirty tensors of 1 M and one of 28 M 350 / 339 and 379 / 369; with ends of two thirds 608 and 576.  Embedding in the middle:
+// 614 / 604 and 569 / 572 (hence the second rule); tensors of 10 to 16 M 288 / 292 and 327 / 329 alone, 317 / 308 and 357 / 347 behind
+// the clip (hence the first one, which both calls share).
+constexpr uint32_t kLambEndsFrom = 2;
 // Plans go in one pass from this many elements on, and if at least half of them are in held tensors.  Below, the chain of
 // round trips to memory inside the launch costs more than it saves (two sweeps / one pass, lamb_step: 0.3 M elements
 // 12.3 / 18.5 us, 3.2 M 29.3 / 32.5, 7 M 50 / 45, 11 M 78 / 65; bucket_clip_lamb 3.2 M 42.4 / 45.6, 7 M 65 / 62);
@@ -242,7 +251,8 @@ struct LambState {
   double* sums;                     // two per chunk
   float* trust;                     // [n_tensors]
   uint32_t* late;                   // [n_items] held items whose wait expired
-  uint32_t n_items, first_large, n_tensors;  // items from first_large on are of tensors that are not held
+  // items [first_large, first_end) are swept again by the tail kernel; those from first_end on are held ends of the same tensors
+  uint32_t n_items, first_large, first_end, n_tensors;
 };
 
 // Kernel launchers (bca_kernels.hip).  All enqueue on `stream` and return the
@@ -340,7 +350,9 @@ struct bca_plan {
   std::vector<bca::LambItem> lamb_items;  // addresses not filled in
   std::vector<uint32_t> lamb_items_of, lamb_clip_work;
   std::vector<uint8_t> lamb_badly_cut;    // per tensor, see kLambItemElemsFew
-  uint32_t lamb_first_large = 0;  // items from here on are of tensors that are not held
+  uint32_t lamb_first_large = 0;  // items from here on are of tensors that are not held,
+  uint32_t lamb_first_end = 0;    // and from here on the ends of such tensors, which are,
+  bool lamb_clip_ends = false;    // in bucket_clip_lamb too
   bool lamb_one_pass = false, lamb_clip_one_pass = false;  // which calls go that way ...
   bool lamb_irregular = false;  // ... unless the bound tensors are not placed for it
   bool lamb_layout_one_pass = false, lamb_layout_clip_one_pass = false;  // which would in a plan without tuning

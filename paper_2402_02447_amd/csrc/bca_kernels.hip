@@ -1264,7 +1264,8 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
 // the gradients do not lie at the parameters' alignment, up to the grouping of the sums' fp32 terms).
 //
 // Tensors too large to be held (kLambHeldNum / kLambHeldDen; BERT's word embedding) are last in the list of lamb_step: their items store the
-// moments cacheable and the tail kernel carries out their second sweep, most recent item first.
+// moments cacheable and the tail kernel carries out their second sweep, most recent item first.  The end of such a tensor is held like a whole one
+// (kLambEndsFrom).
 //
 // Waiting.  Items wait for the rest of their own tensor, which the work list keeps together and which is resident at
 // once as a rule.  It need not be: another launch of this kind on the GPU may hold slots that it is waiting for, and
@@ -1365,6 +1366,7 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
   const uint32_t first = ip->first, count = ip->count, t = ip->tensor, flags = ip->flags;
   const uint32_t items = ip->items, lo = ip->lo, hi = ip->hi;
   const bool regular = HOLD && (flags & kLambRegular) != 0u;
+  const bool held = HOLD && (flags & (CLIP ? kLambHeld : kLambHeld | kLambHeldAlone)) != 0u;
   const float wd = (flags & kChunkNoDecay) ? 0.f : k.wd;
   f32x4 P[CH], U[CH - LD];
   if (regular) {
@@ -1372,7 +1374,7 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
     f32x4* pv = reinterpret_cast<f32x4*>(ip->p);
     f32x4* mv = reinterpret_cast<f32x4*>(ip->m);
     f32x4* vv = reinterpret_cast<f32x4*>(ip->v);
-    const bool keep = (flags & kLambKeep) != 0u, wb = WB && coef != 1.f;
+    const bool keep = (flags & kLambKeep) != 0u && !held, wb = WB && coef != 1.f;
     const auto sweep = [&](auto full) {
     constexpr bool FULL = decltype(full)::value;
 #pragma unroll
@@ -1451,7 +1453,7 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
   __syncthreads();
   const bool last = sh.last != 0u;
   if (last) tensor_ratio(ls, t, lo, hi, epoch, k.lr, sh);
-  if (!HOLD || !(flags & kLambHeld)) return;
+  if (!held) return;
   if (!last && tid == 0) {
     float scale = 0.f;
     sh.step.flag = wait_for_tensor(st, ls, t, epoch, self, &scale) ? 1u : 0u;
@@ -1542,7 +1544,7 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
     for (uint32_t j = from; j < end; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j]), sc, k);
   };
   const uint32_t back = w / kLambItemChunks, chunk = w % kLambItemChunks;
-  if (back < ls.n_items - ls.first_large) update(ls.n_items - 1u - back, chunk, chunk + 1u);
+  if (back < ls.first_end - ls.first_large) update(ls.first_end - 1u - back, chunk, chunk + 1u);
   if (w >= kLambTailWorkers) return;
   const uint32_t n_late = min(st.ctl[kCtlLate], ls.n_items), n_skipped = min(st.ctl[kCtlSkipped], st.skipped_cap);
   // Without late items a few workers do.  The others find zeros here whether they look before the reset below or after it;
@@ -1995,7 +1997,7 @@ hipError_t launch_lamb(int gdt, const StepState& st, const LambState& ls, const 
     e = hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_lamb_tail, dim3(std::max((ls.n_items - ls.first_large) * kLambItemChunks, kLambTailWorkers)), dim3(kBlock), 0, stream, st, ls, status, k);
+  hipLaunchKernelGGL(k_lamb_tail, dim3(std::max((ls.first_end - ls.first_large) * kLambItemChunks, kLambTailWorkers)), dim3(kBlock), 0, stream, st, ls, status, k);
   return hipGetLastError();
 }
 

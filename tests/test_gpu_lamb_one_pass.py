@@ -114,6 +114,29 @@ def test_tensors_too_large_to_be_held_beside_held_ones(clip, spin_limit):
 
 
 @pytest.mark.parametrize("clip", [False, True])
+@pytest.mark.parametrize("spin_limit", [0, 1])
+@pytest.mark.parametrize("where", [0, 4, 9])
+def test_held_ends_of_tensors_that_are_too_large(clip, spin_limit, where):
+    """First, in the middle and last in registration order (bucket_clip_lamb's buckets run the other way)."""
+    per = torch.cuda.get_device_properties(0).multi_processor_count * 3 * 12 * 1024          # elements that can be held
+    sizes = [4 << 20, 5000, 3 << 20, 1_000_001] + [4 << 20] * 5
+    sizes.insert(where, 2 * per + 5 * 12 * 1024 + 17)
+    lay = W.layout_flat_split(sizes, 6_553_600)
+    one = Run(lay, torch.float32, B.BCA_GRAD_F32, 9, spin_limit=spin_limit)
+    two = Run(lay, torch.float32, B.BCA_GRAD_F32, 9, **_two_sweeps(clip))
+    items = [i for i in one.plan.lamb_items(clip) if i[0] == 1]
+    assert two.plan.n_lamb_items(clip) == 0
+    assert len({h for _, _, _, t, h in items if t == where}) == (2 if where == 0 or not clip else 1)
+    for step in (3, 4):
+        one.go(clip, step)
+        two.go(clip, step)
+    torch.cuda.synchronize()
+    one.same(two)
+    one.plan.close()
+    two.plan.close()
+
+
+@pytest.mark.parametrize("clip", [False, True])
 def test_every_wait_expires_at_a_limit_of_one_poll(clip):
     sizes = [400_000, 5, 1_000_000, 20_000, 4_000_000, 1024]
     lay = W.layout_flat_split(sizes, 262_144)

@@ -442,6 +442,28 @@ def test_in_list_order_the_slots_of_the_gpu_are_enough_without_any_bound(clip):
     m.check(m.launch(list(range(len(m.items))), 100, 50, 50))
 
 
+@pytest.mark.parametrize("clip", [False, True])
+@pytest.mark.parametrize("front", [True, False])
+def test_the_held_end_of_a_tensor_that_is_too_large(clip, front):
+    """A tensor of more than twice what can be held, first (its buckets are the last) or last in registration order: its
+    last 768 items are held, by bucket_clip_lamb only where hardly anything follows them."""
+    big, rest = [19_200_000], [2_000_000] * 10 + [5, 70_000]
+    sizes = big + rest if front else rest + big
+    lay = W.layout_flat_split(sizes, 3 << 20)
+    plan, t = host_plan(lay), sizes.index(big[0])
+    m = LambModel(plan, lay.n_buckets, clip)
+    held = [h for k, _, _, u, h in m.items if k == A and u == t]
+    ends = 768 if front or not clip else 0
+    assert len(held) > 2 * 768 and sum(held) <= ends and sum(held) > ends - 2 and held == sorted(held)
+    assert all(h for k, _, _, u, h in m.items if k == A and u != t)
+    ident = list(range(len(m.items)))
+    for order in (ident, ident[::-1], [int(i) for i in np.random.default_rng(1).permutation(len(ident))]):
+        for slots, limits in ((100, (1, 1)), (1024, (30, 5)), (1024, (10_000, 10_000))):
+            r = m.launch(order, slots, *limits)
+            m.check(r)
+            assert order is not ident or limits[0] != 10_000 or r["status"] == 0
+
+
 def test_a_lost_item_is_reported_by_the_next_call_that_has_a_status_word():
     plan, lay = lamb_plan()
     m = LambModel(plan, lay.n_buckets, False)
