@@ -61,14 +61,6 @@ class AdamHyper:
     eps: float = 1e-6
     weight_decay: float = 0.01
 
-    def _c(self) -> _Adam:
-        return _Adam(self.lr, self.beta1, self.beta2, self.eps, self.weight_decay)
-
-
-def _hp(hp: Optional[AdamHyper]):
-    """byref of the C struct, or NULL (allowed once the plan takes hyper-parameters from device memory)."""
-    return C.byref(hp._c()) if hp is not None else None
-
 
 def pack_device_hyper(hp: Optional[AdamHyper], step: int) -> bytes:
     """The 48 bytes of a bca_adam_device: copy them into a device buffer and hand that to Plan.set_device_hyper."""
@@ -144,8 +136,25 @@ def load_library():
     L.bca_version.restype = i32
     for name in EXPORTS:
         getattr(L, name)          # raises AttributeError if a declared symbol is missing
+    _connect(L)
     _lib = L
     return L
+
+
+_calls = _table = None
+
+
+def _connect(L) -> None:
+    """The extension module that carries out the compute calls, given the addresses of this library's functions."""
+    global _calls, _table
+    try:
+        from . import _calls as module
+    except ImportError as e:
+        raise ImportError("the extension module _calls has not been built (python -c 'import __graft_entry__ as g; g.build()')") from e
+    _calls = module
+    _table = module.connect(*(C.cast(getattr(L, f), C.c_void_p).value for f in (
+        "bucket_clip_norms", "bucket_clip_apply", "bucket_clip", "bucket_clip_flat", "adam_step", "bucket_clip_adam", "lamb_step",
+        "bucket_clip_lamb")))
 
 
 def _check(rc: int) -> None:
@@ -183,8 +192,9 @@ def alg1_thresholds(c: float, n_buckets: int) -> np.ndarray:
 
 def bucket_clip_flat(g, n: int, grad_dtype: int, threshold, norm=None, coef=None, status=None, stream=None) -> None:
     """bucket_clip_flat: clip one contiguous bucket in place; no plan, no allocation (see bca.h)."""
-    _check(load_library().bucket_clip_flat(_ptr(g), int(n), grad_dtype, _ptr(threshold), _ptr(norm), _ptr(coef),
-                                           _ptr(status), _stream(stream)))
+    if _lib is None:
+        load_library()
+    _check(_calls.bucket_clip_flat(_table, g, int(n), grad_dtype, threshold, norm, coef, status, stream))
 
 
 class Plan:
@@ -341,30 +351,26 @@ class Plan:
         _check(self._L.bca_plan_wait_stats(self._h, out))
         return int(out[0]), int(out[1])
 
-    # -- compute (same names as the C ABI)
+    # -- compute (same names as the C ABI).  hp may be None once the plan takes hyper-parameters from device memory.
     def bucket_clip_norms(self, b0: int, b1: int, norms, stream=None) -> None:
-        _check(self._L.bucket_clip_norms(self._h, b0, b1, _ptr(norms), _stream(stream)))
+        _check(_calls.bucket_clip_norms(_table, self._h.value, b0, b1, norms, stream))
 
     def bucket_clip_apply(self, b0: int, b1: int, thresholds, norms, coefs=None, status=None, stream=None) -> None:
-        _check(self._L.bucket_clip_apply(self._h, b0, b1, _ptr(thresholds), _ptr(norms), _ptr(coefs), _ptr(status),
-                                         _stream(stream)))
+        _check(_calls.bucket_clip_apply(_table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
 
     def bucket_clip(self, b0: int, b1: int, thresholds, norms=None, coefs=None, status=None, stream=None) -> None:
-        _check(self._L.bucket_clip(self._h, b0, b1, _ptr(thresholds), _ptr(norms), _ptr(coefs), _ptr(status),
-                                   _stream(stream)))
+        _check(_calls.bucket_clip(_table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
 
     def adam_step(self, hp: Optional[AdamHyper], step: int, stream=None) -> None:
-        _check(self._L.adam_step(self._h, _hp(hp), step, _stream(stream)))
+        _check(_calls.adam_step(_table, self._h.value, hp, step, stream))
 
     def bucket_clip_adam(self, thresholds, hp: Optional[AdamHyper], step: int, flags: int = 0, norms=None, coefs=None,
                          status=None, stream=None) -> None:
-        _check(self._L.bucket_clip_adam(self._h, _ptr(thresholds), _hp(hp), step, flags, _ptr(norms), _ptr(coefs),
-                                        _ptr(status), _stream(stream)))
+        _check(_calls.bucket_clip_adam(_table, self._h.value, thresholds, hp, step, flags, norms, coefs, status, stream))
 
     def lamb_step(self, hp: Optional[AdamHyper], step: int, trust=None, stream=None) -> None:
-        _check(self._L.lamb_step(self._h, _hp(hp), step, _ptr(trust), _stream(stream)))
+        _check(_calls.lamb_step(_table, self._h.value, hp, step, trust, stream))
 
     def bucket_clip_lamb(self, thresholds, hp: Optional[AdamHyper], step: int, flags: int = 0, norms=None, coefs=None,
                          trust=None, status=None, stream=None) -> None:
-        _check(self._L.bucket_clip_lamb(self._h, _ptr(thresholds), _hp(hp), step, flags, _ptr(norms), _ptr(coefs),
-                                        _ptr(trust), _ptr(status), _stream(stream)))
+        _check(_calls.bucket_clip_lamb(_table, self._h.value, thresholds, hp, step, flags, norms, coefs, trust, status, stream))

@@ -1,0 +1,271 @@
+// The compute calls of libbca for Python, as a CPython extension module.  A call on a small plan takes the GPU about six
+// microseconds; taking its nine arguments apart in Python and converting them with ctypes took three on top of the launch, so that
+// such a program waited for its own marshalling.  Marshalling is all this does: arguments are what bca.h says, handed to
+// the functions whose addresses connect() was given, without the interpreter's lock, and the status is returned.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+#include <stdint.h>
+
+#include "bca.h"
+
+namespace {
+
+struct Functions {
+  decltype(&bucket_clip_norms) clip_norms;
+  decltype(&bucket_clip_apply) clip_apply;
+  decltype(&bucket_clip) clip;
+  decltype(&bucket_clip_flat) clip_flat;
+  decltype(&adam_step) adam;
+  decltype(&bucket_clip_adam) clip_adam;
+  decltype(&lamb_step) lamb;
+  decltype(&bucket_clip_lamb) clip_lamb;
+};
+
+PyObject *s_data_ptr, *s_cuda_stream, *s_hyper[5];
+
+// An object's address: None or 0 is NULL; an object with data_ptr() (a tensor) is what that returns; else a whole number.
+bool address(PyObject* x, void** out) {
+  *out = nullptr;
+  if (x == Py_None) return true;
+  PyObject* number = nullptr;
+  if (PyLong_CheckExact(x)) {
+    Py_INCREF(number = x);
+  } else {
+    PyObject* method = PyObject_GetAttr(x, s_data_ptr);
+    if (method) {
+      number = PyObject_CallNoArgs(method);
+      Py_DECREF(method);
+    } else if (PyErr_ExceptionMatches(PyExc_AttributeError)) {
+      PyErr_Clear();
+      number = PyNumber_Long(x);
+    }
+    if (!number) return false;
+  }
+  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(number);
+  Py_DECREF(number);
+  return !(*out == (void*)~(uintptr_t)0 && PyErr_Occurred());
+}
+
+// A stream: None, an object with cuda_stream (torch's), or a whole number.
+bool stream_of(PyObject* x, void** out) {
+  *out = nullptr;
+  if (x == Py_None) return true;
+  PyObject* number = PyObject_GetAttr(x, s_cuda_stream);
+  if (!number) {
+    if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+    PyErr_Clear();
+    Py_INCREF(number = x);
+  }
+  PyObject* whole = PyNumber_Long(number);
+  Py_DECREF(number);
+  if (!whole) return false;
+  *out = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(whole);
+  Py_DECREF(whole);
+  return !PyErr_Occurred();
+}
+
+// Hyper-parameters: None, or an object with the five fields.  *hp is left NULL for None.
+bool hyper(PyObject* x, bca_adam* room, const bca_adam** hp) {
+  *hp = nullptr;
+  if (x == Py_None) return true;
+  double v[5];
+  for (int i = 0; i < 5; ++i) {
+    PyObject* f = PyObject_GetAttr(x, s_hyper[i]);
+    if (!f) return false;
+    v[i] = PyFloat_AsDouble(f);
+    Py_DECREF(f);
+    if (v[i] == -1.0 && PyErr_Occurred()) return false;
+  }
+  room->lr = v[0], room->beta1 = v[1], room->beta2 = v[2], room->eps = v[3], room->weight_decay = v[4];
+  *hp = room;
+  return true;
+}
+
+// Whole numbers are taken modulo the parameter's width, as ctypes does.
+bool whole(PyObject* x, uint64_t* out) {
+  if (!PyLong_Check(x)) {
+    PyErr_Format(PyExc_TypeError, "an int is wanted, not %.100s", Py_TYPE(x)->tp_name);
+    return false;
+  }
+  *out = PyLong_AsUnsignedLongLongMask(x);
+  return !(*out == ~0ull && PyErr_Occurred());
+}
+
+// Arguments in turn: first the function table and, for plans, the handle.
+struct Args {
+  PyObject* const* a;
+  Py_ssize_t n, i = 0;
+  bool ok;
+  const Functions* f = nullptr;
+  Args(PyObject* const* args, Py_ssize_t given, Py_ssize_t want) : a(args), n(given), ok(given == want) {
+    if (!ok) {
+      PyErr_Format(PyExc_TypeError, "%zd arguments given, %zd wanted", given, want);
+      return;
+    }
+    f = static_cast<const Functions*>(PyCapsule_GetPointer(a[i++], "bca.functions"));
+    ok = f != nullptr;
+  }
+  void* ptr() {
+    void* p = nullptr;
+    if (ok) ok = address(a[i++], &p);
+    return p;
+  }
+  void* stream() {
+    void* p = nullptr;
+    if (ok) ok = stream_of(a[i++], &p);
+    return p;
+  }
+  uint64_t u64() {
+    uint64_t v = 0;
+    if (ok) ok = whole(a[i++], &v);
+    return v;
+  }
+  uint32_t u32() { return (uint32_t)u64(); }
+  const bca_adam* hp(bca_adam* room) {
+    const bca_adam* p = nullptr;
+    if (ok) ok = hyper(a[i++], room, &p);
+    return p;
+  }
+  bca_plan* plan() { return static_cast<bca_plan*>(ptr()); }
+  float* floats() { return static_cast<float*>(ptr()); }
+  int32_t* word() { return static_cast<int32_t*>(ptr()); }
+  // Carries the call out, unless an argument was wrong.
+  template <typename F>
+  PyObject* call(F go) {
+    if (!ok) return nullptr;
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = go();
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(rc);
+  }
+};
+
+PyObject* call_norms(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 6);
+  bca_plan* p = a.plan();
+  const uint32_t b0 = a.u32(), b1 = a.u32();
+  float* norms = a.floats();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip_norms(p, b0, b1, norms, s); });
+}
+
+PyObject* call_apply(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 9);
+  bca_plan* p = a.plan();
+  const uint32_t b0 = a.u32(), b1 = a.u32();
+  float *thr = a.floats(), *norms = a.floats(), *coefs = a.floats();
+  int32_t* status = a.word();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip_apply(p, b0, b1, thr, norms, coefs, status, s); });
+}
+
+PyObject* call_clip(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 9);
+  bca_plan* p = a.plan();
+  const uint32_t b0 = a.u32(), b1 = a.u32();
+  float *thr = a.floats(), *norms = a.floats(), *coefs = a.floats();
+  int32_t* status = a.word();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip(p, b0, b1, thr, norms, coefs, status, s); });
+}
+
+PyObject* call_flat(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 9);
+  void* g = a.ptr();
+  const uint64_t len = a.u64();
+  const int gdt = (int)a.u32();
+  float *thr = a.floats(), *norm = a.floats(), *coef = a.floats();
+  int32_t* status = a.word();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip_flat(g, len, gdt, thr, norm, coef, status, s); });
+}
+
+PyObject* call_adam(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 5);
+  bca_adam room;
+  bca_plan* p = a.plan();
+  const bca_adam* hp = a.hp(&room);
+  const uint64_t step = a.u64();
+  void* s = a.stream();
+  return a.call([&] { return a.f->adam(p, hp, step, s); });
+}
+
+PyObject* call_clip_adam(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 10);
+  bca_adam room;
+  bca_plan* p = a.plan();
+  float* thr = a.floats();
+  const bca_adam* hp = a.hp(&room);
+  const uint64_t step = a.u64();
+  const uint32_t flags = a.u32();
+  float *norms = a.floats(), *coefs = a.floats();
+  int32_t* status = a.word();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip_adam(p, thr, hp, step, flags, norms, coefs, status, s); });
+}
+
+PyObject* call_lamb(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 6);
+  bca_adam room;
+  bca_plan* p = a.plan();
+  const bca_adam* hp = a.hp(&room);
+  const uint64_t step = a.u64();
+  float* trust = a.floats();
+  void* s = a.stream();
+  return a.call([&] { return a.f->lamb(p, hp, step, trust, s); });
+}
+
+PyObject* call_clip_lamb(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  Args a(args, n, 11);
+  bca_adam room;
+  bca_plan* p = a.plan();
+  float* thr = a.floats();
+  const bca_adam* hp = a.hp(&room);
+  const uint64_t step = a.u64();
+  const uint32_t flags = a.u32();
+  float *norms = a.floats(), *coefs = a.floats(), *trust = a.floats();
+  int32_t* status = a.word();
+  void* s = a.stream();
+  return a.call([&] { return a.f->clip_lamb(p, thr, hp, step, flags, norms, coefs, trust, status, s); });
+}
+
+void release(PyObject* capsule) { PyMem_Free(PyCapsule_GetPointer(capsule, "bca.functions")); }
+
+// connect(addresses of the eight functions, in the order of Functions) -> the table that every call takes first
+PyObject* connect(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (n != 8) {
+    PyErr_SetString(PyExc_TypeError, "eight addresses are wanted");
+    return nullptr;
+  }
+  void* at[8];
+  for (int i = 0; i < 8; ++i)
+    if (!address(args[i], &at[i])) return nullptr;
+  Functions* f = static_cast<Functions*>(PyMem_Malloc(sizeof(Functions)));
+  if (!f) return PyErr_NoMemory();
+  f->clip_norms = (decltype(f->clip_norms))at[0], f->clip_apply = (decltype(f->clip_apply))at[1];
+  f->clip = (decltype(f->clip))at[2], f->clip_flat = (decltype(f->clip_flat))at[3];
+  f->adam = (decltype(f->adam))at[4], f->clip_adam = (decltype(f->clip_adam))at[5];
+  f->lamb = (decltype(f->lamb))at[6], f->clip_lamb = (decltype(f->clip_lamb))at[7];
+  PyObject* capsule = PyCapsule_New(f, "bca.functions", release);
+  if (!capsule) PyMem_Free(f);
+  return capsule;
+}
+
+#define METHOD(name, function) {name, (PyCFunction)(void (*)(void))function, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {METHOD("connect", connect), METHOD("bucket_clip_norms", call_norms), METHOD("bucket_clip_apply", call_apply),
+                         METHOD("bucket_clip", call_clip), METHOD("bucket_clip_flat", call_flat), METHOD("adam_step", call_adam),
+                         METHOD("bucket_clip_adam", call_clip_adam), METHOD("lamb_step", call_lamb),
+                         METHOD("bucket_clip_lamb", call_clip_lamb), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__calls(void) {
+  static const char* const fields[] = {"lr", "beta1", "beta2", "eps", "weight_decay"};
+  s_data_ptr = PyUnicode_InternFromString("data_ptr"), s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+  if (!s_data_ptr || !s_cuda_stream) return nullptr;
+  for (int i = 0; i < 5; ++i)
+    if (!(s_hyper[i] = PyUnicode_InternFromString(fields[i]))) return nullptr;
+  return PyModule_Create(&module);
+}

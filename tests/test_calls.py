@@ -1,0 +1,88 @@
+"""The extension module that Python makes its compute calls through: what it hands on, argument by argument, to functions that
+note what they are given (no GPU and no torch tensors needed)."""
+import ctypes as C
+import math
+
+import numpy as np
+import pytest
+
+from paper_2402_02447_amd import binding
+
+VP, U32, U64, I32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_int
+HP = C.POINTER(binding._Adam)
+SIGNATURES = [("bucket_clip_norms", (VP, U32, U32, VP, VP)), ("bucket_clip_apply", (VP, U32, U32, VP, VP, VP, VP, VP)),
+              ("bucket_clip", (VP, U32, U32, VP, VP, VP, VP, VP)), ("bucket_clip_flat", (VP, U64, I32, VP, VP, VP, VP, VP)),
+              ("adam_step", (VP, HP, U64, VP)), ("bucket_clip_adam", (VP, VP, HP, U64, U32, VP, VP, VP, VP)),
+              ("lamb_step", (VP, HP, U64, VP, VP)), ("bucket_clip_lamb", (VP, VP, HP, U64, U32, VP, VP, VP, VP, VP))]
+
+
+class Tensor:
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+class Stream:
+    cuda_stream = 0x7000_0000_1234
+
+
+@pytest.fixture(scope="module")
+def noted():
+    binding.load_library()
+    seen, keep, addresses = [], [], []
+    for name, types in SIGNATURES:
+        def note(*args, name=name):
+            seen.append((name, [[getattr(a.contents, f) for f, _ in binding._Adam._fields_] if isinstance(a, HP) and a else
+                                None if isinstance(a, HP) else a for a in args]))
+            return 7
+        keep.append(C.CFUNCTYPE(I32, *types)(note))
+        addresses.append(C.cast(keep[-1], VP).value)
+    table = binding._calls.connect(*addresses)
+    yield lambda name, *args: (getattr(binding._calls, name)(table, *args), seen.pop())
+    del keep
+
+
+@pytest.mark.parametrize("name,types", SIGNATURES)
+def test_every_argument_arrives_in_its_place(noted, name, types):
+    hp = binding.AdamHyper(1e-3, 0.9, 0.999, 1e-6, 0.01)
+    given, want = [], []
+    for i, t in enumerate(types):
+        if t is HP:
+            given.append(hp), want.append([1e-3, 0.9, 0.999, 1e-6, 0.01])
+        elif t is VP and i == len(types) - 1:
+            given.append(Stream()), want.append(Stream.cuda_stream)
+        elif t is VP:
+            at = 0x7F00_0000_0000 + 4096 * i
+            given.append((at, Tensor(at), np.int64(at))[i % 3]), want.append(at)
+        else:
+            at = (1 << 40) + i if t is U64 else 1 + i
+            given.append(at), want.append(at)
+    assert noted(name, *given) == (7, (name, want))
+    # nothing where something may be left out, and a stream given as a number
+    given = [None if t in (VP, HP) else 0 for t in types[:-1]] + [0x55]
+    want = [None if t in (VP, HP) else 0 for t in types[:-1]] + [0x55]
+    assert noted(name, *given) == (7, (name, want))
+
+
+def test_what_is_not_an_argument_is_refused(noted):
+    ok = (1, 2, binding.AdamHyper(), 3, 0, 4, 5, 6, None)
+    assert noted("bucket_clip_adam", *ok)[0] == 7
+    for i, bad, error in ((0, "x", ValueError), (1, object(), TypeError), (2, 5, AttributeError), (3, 1.5, TypeError), (3, "1", TypeError),
+                          (4, None, TypeError), (8, object(), TypeError)):
+        with pytest.raises(error):
+            noted("bucket_clip_adam", *ok[:i], bad, *ok[i + 1:])
+    with pytest.raises(TypeError):
+        noted("bucket_clip_adam", *ok[:-1])
+    with pytest.raises(TypeError):
+        noted("bucket_clip_adam", *ok, None)
+    with pytest.raises(TypeError):
+        noted("adam_step", 1, binding.AdamHyper(lr="fast"), 1, None)
+    with pytest.raises((TypeError, ValueError)):
+        binding._calls.adam_step(object(), 1, None, 1, None)
+
+
+def test_numbers_of_any_kind_in_the_hyper_parameters(noted):
+    _, (_, args) = noted("adam_step", 1, binding.AdamHyper(np.float32(0.5), 0, np.float64(0.25), float("inf"), -1.0), 2, None)
+    assert args[1] == [0.5, 0.0, 0.25, math.inf, -1.0]
