@@ -140,6 +140,7 @@ enum : uint32_t {
 // Work items up to which the pipelined launch finishes itself instead of having k_finish behind it.  Measured, fused step, fp32
 // (k_finish / itself): 20 K elements 9.0 / 7.8 us, 1 M 13.3 / 12.8, 3 M 24.8 / 24.4, 8 M 51.1 / 50.9, 16 M 85.3 / 86.1.
 constexpr uint32_t kSelfFinishItems = 8192;
+constexpr uint32_t kFewItems = 128;  // up to here its workgroups count themselves in a single word
 // Work items of k_step: kind in bits 30..31; kItemAdam: apply-table chunk in bits 0..28 and kItemEarly; kItemNorm: first
 // norm-table chunk in bits 0..27 and the number of consecutive chunks minus one in bits 28..29; kItemEmpty: bucket.
 constexpr uint32_t kItemNorm = 0u, kItemAdam = 1u, kItemEmpty = 2u;

@@ -1020,6 +1020,39 @@ __device__ __forceinline__ bool wait_for_bucket(const StepState& st, uint32_t b,
 // after its increment has returned.  A workgroup-scope release fence would not do: on
 // this target it does not wait for vector stores, so the arrival could be counted
 // while a partial is still on its way.
+// A thread's share of the sum of partials [lo, hi) of a bucket, in k_finalize's order: thread t adds partials lo + t, lo + t + 256, ...
+// one after the other.  The loads are issued eight at a time before the first addition (this workgroup is the one everybody else is
+// waiting for, and an agent-scope load that misses every cache takes a microsecond or two); a slot past the end adds +0.0, which
+// leaves a sum of squares as it is.
+__device__ __forceinline__ double agent_partials(const StepState& st, uint64_t lo, uint64_t hi) {
+  double s = 0.0;
+  for (uint64_t i = lo + threadIdx.x; i < hi; i += 8u * kBlock) {
+    double part[8];
+#pragma unroll
+    for (uint32_t q = 0; q < 8u; ++q) {
+      const uint64_t j = i + (uint64_t)q * kBlock;
+      part[q] = j < hi ? __hip_atomic_load(&st.partials[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8u; ++q) s += part[q];
+  }
+  return s;
+}
+
+// Norm and coefficient of bucket b from its sum of squares, and its ready word (thread 0).
+__device__ __forceinline__ void publish_bucket(const StepState& st, uint32_t b, double tot, float threshold, uint32_t epoch,
+                                               float* __restrict__ norms, float* __restrict__ coefs) {
+  const float norm = (float)sqrt(tot);
+  int32_t bst = 0;
+  const float coef = clip_coef(norm, threshold, bst);
+  norms[b] = norm;
+  coefs[b] = coef;
+  if (bst) ctl_or(&st.ctl[kCtlStatus], (uint32_t)bst);
+  // The coefficient travels inside the ready word, so a waiter needs nothing else that this item wrote.
+  const unsigned long long word = ((unsigned long long)epoch << 32) | (unsigned long long)__float_as_uint(coef);
+  __hip_atomic_store(&st.ready[b], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The tail of every squared-norm item.  `stored` chunks' partials of bucket b have just been written by this
 // workgroup (0: a bucket without elements, nothing to count): waits for them, counts the arrival, and if
 // this workgroup completes the bucket, finalizes it and publishes the ready word.
@@ -1041,37 +1074,11 @@ __device__ __forceinline__ void norm_arrive(const StepState& st, uint32_t b, uin
     __syncthreads();
     if (!sh.flag) return;
   }
-  // k_finalize's order: thread t adds partials lo + t, lo + t + 256, ... one after the other.  The loads are issued
-  // eight at a time before the first addition (this workgroup is the one everybody else is waiting for, and an
-  // agent-scope load that misses every cache takes a microsecond or two); a slot past the end adds +0.0, which
-  // leaves a sum of squares as it is.
   const uint64_t lo = (uint64_t)st.norm_bucket_off[b] * kWaves, hi = (uint64_t)st.norm_bucket_off[b + 1] * kWaves;
-  double s = 0.0;
-  for (uint64_t i = lo + tid; i < hi; i += 8u * kBlock) {
-    double part[8];
-#pragma unroll
-    for (uint32_t q = 0; q < 8u; ++q) {
-      const uint64_t j = i + (uint64_t)q * kBlock;
-      part[q] = j < hi ? __hip_atomic_load(&st.partials[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < 8u; ++q) s += part[q];
-  }
-  s = wave_sum(s);
+  const double s = wave_sum(agent_partials(st, lo, hi));
   if ((tid & 63u) == 0) sh.w[tid >> 6] = s;
   __syncthreads();
-  if (tid == 0) {
-    const double tot = ((sh.w[0] + sh.w[1]) + sh.w[2]) + sh.w[3];
-    const float norm = (float)sqrt(tot);
-    int32_t bst = 0;
-    const float coef = clip_coef(norm, thresholds[b], bst);
-    norms[b] = norm;
-    coefs[b] = coef;
-    if (bst) ctl_or(&st.ctl[kCtlStatus], (uint32_t)bst);
-    // The coefficient travels inside the ready word, so a waiter needs nothing else that this item wrote.
-    const unsigned long long word = ((unsigned long long)epoch << 32) | (unsigned long long)__float_as_uint(coef);
-    __hip_atomic_store(&st.ready[b], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (tid == 0) publish_bucket(st, b, ((sh.w[0] + sh.w[1]) + sh.w[2]) + sh.w[3], thresholds[b], epoch, norms, coefs);
 }
 
 __device__ __forceinline__ void store_partial(const StepState& st, uint32_t chunk, double ws) {
@@ -1099,6 +1106,45 @@ __device__ __forceinline__ void norm_item(const StepState& st, uint32_t kind, ui
     store_partial(st, c, sqnorm_chunk<GDT, false, 8, false>(en));
   }
   norm_arrive(st, b, count, epoch, thresholds, norms, coefs, sh);
+}
+
+// A squared-norm item where the launch is a chain of round trips to memory and little else (EARLY).  What finalizing the bucket takes is
+// fetched beside the gradients, and a bucket of one chunk needs no exchange with other workgroups.
+template <int GDT>
+__device__ __forceinline__ void norm_item_short(const StepState& st, uint32_t idx, uint32_t count, uint32_t epoch,
+                                                const float* __restrict__ thresholds, float* __restrict__ norms,
+                                                float* __restrict__ coefs, StepShared& sh) {
+  const uint32_t tid = threadIdx.x;
+  Entry en = read_entry(&st.norm_tab[idx]);
+  const uint32_t b = en.bucket;
+  const uint32_t lo = st.norm_bucket_off[b], total = st.norm_bucket_off[b + 1] - lo;
+  const float threshold = thresholds[b];
+  if (total == 1u) {
+    const double ws = sqnorm_chunk<GDT, false, 8, false>(en);
+    if ((tid & 63u) == 0) sh.w[tid >> 6] = ws;
+    __syncthreads();
+    // as four partials in the first four lanes of a wavefront are added up
+    if (tid == 0) publish_bucket(st, b, (sh.w[0] + sh.w[2]) + (sh.w[1] + sh.w[3]), threshold, epoch, norms, coefs);
+    return;
+  }
+  for (uint32_t c = idx;;) {
+    store_partial(st, c, sqnorm_chunk<GDT, false, 8, false>(en));
+    if (++c == idx + count) break;
+    en = read_entry(&st.norm_tab[c]);
+  }
+  wait_vmem();  // and so on as in norm_arrive
+  __syncthreads();
+  if (tid == 0) {
+    const bool last = atomicAdd(&st.arrived[b], count) + count == total;
+    if (last) ctl_store(&st.arrived[b], 0u);
+    sh.flag = last ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!sh.flag) return;
+  const double s = wave_sum(agent_partials(st, (uint64_t)lo * kWaves, (uint64_t)(lo + total) * kWaves));
+  if ((tid & 63u) == 0) sh.w[tid >> 6] = s;
+  __syncthreads();
+  if (tid == 0) publish_bucket(st, b, ((sh.w[0] + sh.w[1]) + sh.w[2]) + sh.w[3], threshold, epoch, norms, coefs);
 }
 
 // What the items that wait for a coefficient do with it.
@@ -1139,8 +1185,7 @@ __device__ __forceinline__ uint32_t finish_items(const StepState& st, uint32_t e
 }
 
 // Hands the status bits collected during the call to the caller and resets the per-call state, epoch included (thread 0).
-__device__ __forceinline__ void finish_state(const StepState& st, uint32_t epoch, uint32_t bits, int32_t* status) {
-  const uint32_t collected = ctl_load(&st.ctl[kCtlStatus]) | bits;
+__device__ __forceinline__ void finish_state(const StepState& st, uint32_t epoch, uint32_t collected, int32_t* status) {
   if (status != nullptr) *status = (int32_t)collected;
   // without a status word a lost item is reported by the plan's next pipelined call that has one
   ctl_store(&st.ctl[kCtlStatus], status != nullptr ? 0u : collected & (uint32_t)BCA_STATUS_INCOMPLETE);
@@ -1152,12 +1197,18 @@ __device__ __forceinline__ void finish_state(const StepState& st, uint32_t epoch
 
 // SELF: a workgroup whose item is decided (its squared norms are published, or its wait has ended, one way or the other, with
 // everything it has filed in place) counts itself in one of kDoneSlots words, so that no word sees more than a share of
-// the increments (about 8 ns each, one after the other); those that complete a word count it in one more.  Thread 0 only.
-__device__ __forceinline__ uint32_t count_done(const StepState& st) {
-  return atomicAdd(&st.ctl[kCtlDone + 32u * (blockIdx.x % kDoneSlots)], 1u);
+// the increments (about 8 ns each, one after the other); those that complete a word count it in one more.  Launches of at most
+// kFewItems count there at once, which is a round trip less at their end.  Thread 0 only.
+__device__ __forceinline__ uint32_t count_done(const StepState& st, uint32_t n_work) {
+  return atomicAdd(&st.ctl[kCtlDone + 32u * (n_work <= kFewItems ? (uint32_t)kDoneSlots : blockIdx.x % kDoneSlots)], 1u);
 }
 // Whether the workgroup that `count_done` gave `before` is the last of the launch.
 __device__ __forceinline__ bool last_done(const StepState& st, uint32_t n_work, uint32_t before) {
+  if (n_work <= kFewItems) {
+    if (before + 1u != n_work) return false;
+    ctl_store(&st.ctl[kCtlDone + 32u * kDoneSlots], 0u);
+    return true;
+  }
   const uint32_t slot = blockIdx.x % kDoneSlots;
   if (before + 1u != n_work / kDoneSlots + (slot < n_work % kDoneSlots ? 1u : 0u)) return false;
   ctl_store(&st.ctl[kCtlDone + 32u * slot], 0u);  // left at zero for the next call
@@ -1216,7 +1267,7 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
         if constexpr (SELF) {
           if (threadIdx.x == 0) {
             if (!ready) wait_vmem();  // what the wait has filed has arrived
-            before = count_done(st);  // not looked at before the item is done
+            before = count_done(st, n_work);  // not looked at before the item is done
           }
         }
         return ready;
@@ -1228,11 +1279,14 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
     }
   } else {
     // squared-norm items carry their chunk count (1 .. 4) in bits 28..29
-    norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
+    if (EARLY && kind == kItemNorm)
+      norm_item_short<GDT>(st, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
+    else
+      norm_item<GDT>(st, kind, item & 0x0fffffffu, ((item >> 28) & 3u) + 1u, epoch, thresholds, norms, coefs, sh);
     if constexpr (SELF) {
       if (threadIdx.x == 0) {
         wait_vmem();  // status bits and ready word have arrived
-        before = count_done(st);
+        before = count_done(st, n_work);
       }
     }
   }
@@ -1240,8 +1294,13 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
     if (threadIdx.x == 0) sh.item = last_done(st, n_work, before) ? 1u : 0u;
     __syncthreads();
     if (sh.item == 0u) return;
-    const uint32_t bits = finish_items<GDT, WB, U, MODE>(st, epoch, ka, sh);
-    if (threadIdx.x == 0) finish_state(st, epoch, bits, status);
+    const uint32_t skipped = ctl_load(&st.ctl[kCtlSkipped]);
+    uint32_t collected = ctl_load(&st.ctl[kCtlStatus]);
+    if (skipped != 0u) {
+      const uint32_t bits = finish_items<GDT, WB, U, MODE>(st, epoch, ka, sh);
+      collected = ctl_load(&st.ctl[kCtlStatus]) | bits;
+    }
+    if (threadIdx.x == 0) finish_state(st, epoch, collected, status);
   }
 }
 
@@ -1660,7 +1719,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(StepState st, int32_t* status
   __shared__ StepShared sh;
   const uint32_t epoch = ctl_load(&st.ctl[kCtlEpoch]);
   const uint32_t bits = finish_items<GDT, WB, U, MODE>(st, epoch, ka, sh);
-  if (threadIdx.x == 0) finish_state(st, epoch, bits, status);
+  if (threadIdx.x == 0) finish_state(st, epoch, ctl_load(&st.ctl[kCtlStatus]) | bits, status);
 }
 
 // ---- clipping one contiguous bucket without a plan and without allocating ---------------

@@ -88,3 +88,28 @@ def test_items_that_load_before_they_wait(dtype, gdt, sizes, cap, flags):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     for _, plan in runs:
         plan.close()
+
+
+@pytest.mark.parametrize("sizes,cap,items", [([120 * 1024], 1 << 30, 128), ([121 * 1024], 1 << 30, 129), ([16_384, 1], 16_384, None), ([16_385], 1 << 30, None),
+                                             ([16_383, 0, 5], 16_383, None), ([40_000, 16_384, 3], 16_384, None), ([1, 1, 1], 1, 6)])
+@pytest.mark.parametrize("spin_limit", [0, 1])
+def test_buckets_of_one_chunk_and_launches_of_few_items(sizes, cap, items, spin_limit):
+    """Buckets of one squared-norm chunk (16 384 elements), one more, one less; launches on both sides of 128 work items."""
+    plan, state, out, thr = _plan(sizes, cap, 3, spin_limit=spin_limit)
+    ref, rstate, rout, _ = _plan(sizes, cap, 3, tune_flags=B.BCA_TUNE_MULTI_LAUNCH)
+    assert items is None or len(plan.work_items()) == items
+    for step in range(1, 6):
+        plan.bucket_clip_adam(thr, HP, step, 0, *out)
+        ref.bucket_clip_adam(thr, HP, step, 0, *rout)
+        if step == 3:      # the next calls: a threshold that is none, a gradient that is infinite
+            thr[-1] = 0.0
+            for s in (state, rstate):
+                s[0][0][0] = float("inf")
+        torch.cuda.synchronize()
+        for a, b in zip([x for ts in state for x in ts] + out[:2], [x for ts in rstate for x in ts] + rout[:2]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+        want = int(rout[2].item())
+        assert want == (0 if step <= 3 else B.BCA_STATUS_NONFINITE | B.BCA_STATUS_BAD_THRESHOLD)
+        assert int(out[2].item()) in ((want,) if spin_limit == 0 else (want, want | B.BCA_STATUS_TIMEOUT))
+    plan.close()
+    ref.close()
