@@ -579,14 +579,18 @@ __device__ __forceinline__ AdamK resolve(const AdamK& a) {
   return a;
 }
 
-// Hyper-parameters in device memory -> the sweeps' constants, as the host derives them from a bca_adam.
+// Hyper-parameters in device memory -> the sweeps' constants, as the host derives them from a bca_adam.  The call's other launches
+// wait for this one, whose time is that of a power in fp64: lane 0 takes beta1's while lane 1 takes beta2's.
 __global__ __launch_bounds__(64) void k_hyper(const bca_adam_device* __restrict__ dev, AdamK* __restrict__ out) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x > 1) return;
   const double t = (double)dev->step;
+  const float rbc = (float)(1.0 / (1.0 - pow(threadIdx.x == 0 ? dev->beta1 : dev->beta2, t)));
+  const float rbc2 = __shfl(rbc, 1, 64);
+  if (threadIdx.x != 0) return;
   AdamK k;
   k.b1 = (float)dev->beta1, k.omb1 = (float)(1.0 - dev->beta1);
   k.b2 = (float)dev->beta2, k.omb2 = (float)(1.0 - dev->beta2);
-  k.rbc1 = (float)(1.0 / (1.0 - pow(dev->beta1, t))), k.rbc2 = (float)(1.0 / (1.0 - pow(dev->beta2, t)));
+  k.rbc1 = rbc, k.rbc2 = rbc2;
   k.eps = (float)dev->eps;
   k.neg_lr = (float)(-dev->lr);
   k.wd = (float)dev->weight_decay;
