@@ -113,3 +113,38 @@ def test_buckets_of_one_chunk_and_launches_of_few_items(sizes, cap, items, spin_
         assert int(out[2].item()) in ((want,) if spin_limit == 0 else (want, want | B.BCA_STATUS_TIMEOUT))
     plan.close()
     ref.close()
+
+
+@pytest.mark.parametrize("sizes,cap", [([1000, 17_000], 8192), ([120 * 1024], 1 << 30), ([118 * 1024 + 5], 1 << 30), ([300_001, 77], 65_536),
+                                       ([8_500_000, 3], 1_048_576), ([33_000_000], 1_048_576)])
+@pytest.mark.parametrize("flags", [0, B.BCA_WRITE_BACK_GRADS])
+@pytest.mark.parametrize("spin_limit", [0, 1])
+def test_hyper_parameters_in_device_memory_with_items_that_load_early(sizes, cap, flags, spin_limit):
+    """Hyper-parameters in device memory, changed between replays of a captured step, against separate launches with k_hyper in front."""
+    plan, state, out, thr = _plan(sizes, cap, 4, spin_limit=spin_limit)
+    ref, rstate, rout, _ = _plan(sizes, cap, 4, tune_flags=B.BCA_TUNE_MULTI_LAUNCH)
+    dev = torch.frombuffer(bytearray(B.pack_device_hyper(HP, 1)), dtype=torch.int64).cuda()
+    for p in (plan, ref):
+        p.set_device_hyper(dev)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.bucket_clip_adam(thr, None, 0, flags, *out, stream=torch.cuda.current_stream())
+    for step in range(1, 7):
+        hp = B.AdamHyper(1e-3 / step, 0.9 - 0.1 * (step % 2), 0.999, 1e-6, 0.01 * step)
+        dev.copy_(torch.frombuffer(bytearray(B.pack_device_hyper(hp, 3 * step)), dtype=torch.int64))
+        if step % 3:
+            graph.replay()
+        else:
+            plan.bucket_clip_adam(thr, None, 0, flags, *out)
+        ref.bucket_clip_adam(thr, None, 0, flags, *rout)
+        torch.cuda.synchronize()
+        for a, b in zip([x for ts in state for x in ts] + out[:2], [x for ts in rstate for x in ts] + rout[:2]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), step
+        assert int(out[2].item()) in ((0,) if spin_limit == 0 else (0, B.BCA_STATUS_TIMEOUT))
+    plan.adam_step(None, 0)                       # and a call that has the constants derived in front of it
+    ref.adam_step(None, 0)
+    torch.cuda.synchronize()
+    for a, b in zip([x for ts in state for x in ts], [x for ts in rstate for x in ts]):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    plan.close()
+    ref.close()
