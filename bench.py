@@ -200,7 +200,7 @@ def other_ops(a, w, plan, g, p, m, v, dev):
 
 def issue_rate_bench(a, dev):
     """Vector issue rates of the instruction kinds the load-balancing simulation is made of (lbs_issue_rate_probe):
-    the evidence for the "alu" peak that k_lbs_bins is priced on.  One JSON line."""
+    the evidence for the "alu" peak that k_lbs_nodes is priced on.  One JSON line."""
     import torch
 
     from paper_2402_02447_amd import lbs
@@ -279,15 +279,15 @@ def lbs_bench(a, dev):
         dt = time.perf_counter() - t1
         cpu = {"value": round(5 * n_cpu * G * b / dt / 1e6, 2), "unit": "M draws/s", "cores": 1, "kind": "oracle",
                "sample": f"{n_cpu} trials of each of the five methods, same setting, single thread"}
-    # The step is one kernel, k_lbs_bins.  Vector instructions it executes, from a rocprofv3 --pmc SQ_INSTS_VALU run of
-    # this command (profiles/lbs_table5_setting_kernel_stats.txt): 2.072e9 wavefront instructions per 100 000 trials at
-    # 1 024 GPUs, i.e. 2 x 1.638e9 draws made (one set from the whole dataset, one stratified) = 40.5 lane-operation
+    # The step is one kernel, k_lbs_nodes.  Vector instructions it executes, from a rocprofv3 --pmc SQ_INSTS_VALU run of
+    # this workload (profiles/lbs_table5_setting_kernel_stats.txt): 1.202e9 wavefront instructions per 100 000 trials at
+    # 1 024 GPUs, i.e. 1.638e9 draws made (one generator output serves all five methods) = 47.0 lane-operation
     # slots per draw made (64 lanes per instruction).  Peak: a SIMD issues a 64-lane move, add or xor in 2 cycles and
     # a multiply, minimum or median in 4 (measured); the bound taken is every instruction at the faster rate,
     # 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78.6 T lane-operations/s, which is also the rate behind the chip's
     # 157.3 TFLOP/s of fp32 vector FMAs.
-    ops_per_draw_made = 40.5
-    draws_made = 2 * n * G * b
+    ops_per_draw_made = 47.0
+    draws_made = n * G * b
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record(stream)
     for _ in range(a.steps):
@@ -305,8 +305,8 @@ def lbs_bench(a, dev):
         "data": "synthetic",
         "config": {"workload": f"Table 5 setting: {G} simulated GPUs, local batch {b}, nodes of {P}, {n} trials per method, "
                                f"piecewise-uniform length histogram with the printed stratum shares, quota {quota}"},
-        "roofline": {"bound": "alu", "kernel": "k_lbs_bins (both sets of draws, counting sort over all GPUs, bitonic sort of each "
-                                               "node's pool in registers, the five methods' deals)",
+        "roofline": {"bound": "alu", "kernel": "k_lbs_nodes (draws, counting sort over all GPUs, sort of each node's strata in "
+                                               "registers, the five methods' deals)",
                      "achieved": round(achieved, 2), "peak": round(peak, 1), "unit": "T lane-ops/s",
                      "frac": round(achieved / peak, 3), "traffic": None, "ops_per_draw_made": ops_per_draw_made,
                      "draws_made_per_step": draws_made, "ms_per_launch": round(t_all * 1e3, 3)},
