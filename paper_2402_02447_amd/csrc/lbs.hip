@@ -1342,8 +1342,8 @@ struct Cost {
     const uint32_t r = (n + at_once - 1u) / at_once;
     return trial + each * (r + (kWaves - 1u - (r - 1u) % kWaves) / (whole ? 4.0 : 8.0));
   }
-  // k_lbs_bins<0>: one at a time
-  double one() const { return whole ? 12.0 + 2.5 * n : 2.2 * n; }
+  // k_lbs_bins<0>: one at a time (one method alone 2.2; where that is no more than a tenth better, runs of few trials are through first with several)
+  double one() const { return whole ? 12.0 + 2.5 * n : 2.4 * n; }
   // columns in registers, 2^lg of them: k_lbs_bins<2> and <3>
   double columns(uint32_t lg) const {
     return lg == 2 ? rounds(4, whole ? 8.2 : 7.2, whole ? 13.0 : 3.0) : rounds(8, whole ? 15.5 : 12.0, whole ? 20.0 : 6.0);
