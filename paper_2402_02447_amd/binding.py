@@ -1,9 +1,11 @@
-"""ctypes binding of libbca.so: same names as the C ABI, argument marshalling only.
+"""Python binding of libbca.so: same names as the C ABI, argument marshalling only.  The compute calls go through the
+extension module _calls, everything else through ctypes.
 
 Device buffers are passed as anything with a ``data_ptr()`` method (torch
 tensors) or as plain integers; streams as a ``torch.cuda.Stream``, an integer
 handle, or None for the default stream.  There is no CPU fallback: if the
-shared library is missing or fails to load, importing a symbol raises.
+shared library is missing or fails to load, importing a symbol raises; if the
+extension module is missing, the first compute call does.
 """
 from __future__ import annotations
 
@@ -141,6 +143,16 @@ def load_library():
     return L
 
 
+class _NotBuilt:
+    """Stands in for the extension module where there is none: only the compute calls need it, and they say so."""
+
+    def __init__(self, why: ImportError):
+        self.why = why
+
+    def __getattr__(self, name):
+        raise ImportError("the extension module _calls has not been built (python -c 'import __graft_entry__ as g; g.build()')") from self.why
+
+
 _calls = _table = None
 
 
@@ -150,7 +162,8 @@ def _connect(L) -> None:
     try:
         from . import _calls as module
     except ImportError as e:
-        raise ImportError("the extension module _calls has not been built (python -c 'import __graft_entry__ as g; g.build()')") from e
+        _calls = _NotBuilt(e)
+        return
     _calls = module
     _table = module.connect(*(C.cast(getattr(L, f), C.c_void_p).value for f in (
         "bucket_clip_norms", "bucket_clip_apply", "bucket_clip", "bucket_clip_flat", "adam_step", "bucket_clip_adam", "lamb_step",

@@ -27,6 +27,8 @@ def build(verbose: bool = False, extra: list | None = None, out: str = LIB) -> s
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
+    if out == LIB:  # the package as it is imported: both parts
+        build_calls()
     return out
 
 
@@ -39,4 +41,3 @@ def build_calls(out: str = CALLS) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True))
-    print(build_calls())

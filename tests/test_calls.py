@@ -2,6 +2,9 @@
 note what they are given (no GPU and no torch tensors needed)."""
 import ctypes as C
 import math
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -86,3 +89,40 @@ def test_what_is_not_an_argument_is_refused(noted):
 def test_numbers_of_any_kind_in_the_hyper_parameters(noted):
     _, (_, args) = noted("adam_step", 1, binding.AdamHyper(np.float32(0.5), 0, np.float64(0.25), float("inf"), -1.0), 2, None)
     assert args[1] == [0.5, 0.0, 0.25, math.inf, -1.0]
+
+
+def test_only_the_compute_calls_need_the_extension_module():
+    """Without it (another interpreter, a library named by BCA_LIB) plans, thresholds and the simulation's host side work, and a compute call
+    says what is missing."""
+    script = """
+import sys
+sys.modules["torch"] = sys.modules["paper_2402_02447_amd._calls"] = None
+import paper_2402_02447_amd as B, workloads as W
+from paper_2402_02447_amd import lbs
+assert len(B.alg1_thresholds(1.0, 4)) == 4
+lbs.Dataset(W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END, device=-1).close()
+with B.Plan.from_layout(W.layout_flat_split([5000], 4096), B.BCA_GRAD_F32, device=-1) as plan:
+    assert plan.n_buckets == 2 and plan.work_items()
+    for call in (lambda: plan.adam_step(B.AdamHyper(), 1), lambda: plan.bucket_clip(0, 1, 64), lambda: B.bucket_clip_flat(64, 1, 0, 64)):
+        try:
+            call()
+        except ImportError as e:
+            assert "_calls" in str(e)
+        else:
+            raise AssertionError("went through")
+print("as it should")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", script], cwd=root, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "as it should" in r.stdout, r.stderr[-2000:]
+
+
+def test_building_the_package_builds_both_parts(monkeypatch):
+    from paper_2402_02447_amd import build
+    made = []
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: made.append(cmd[cmd.index("-o") + 1]))
+    build.build()
+    assert set(made) == {build.LIB, build.CALLS}
+    made.clear()
+    build.build(out="/tmp/variant.so")      # a variant of the library alone
+    assert made == ["/tmp/variant.so"]
