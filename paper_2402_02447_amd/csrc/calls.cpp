@@ -21,9 +21,12 @@ struct Functions {
   decltype(&bucket_clip_lamb) clip_lamb;
 };
 
-PyObject *s_data_ptr, *s_cuda_stream, *s_hyper[5];
+PyObject *s_data_ptr, *s_cuda_stream, *s_value, *s_as_parameter, *s_hyper[5];
+// ctypes' integer types, whose instances are taken as whole numbers of that width, and what is raised for what is none: ctypes'
+// ArgumentError and a TypeError in one
+PyObject *t_u32, *t_u64, *t_int, *e_argument;
 
-// An object's address: None or 0 is NULL; an object with data_ptr() (a tensor) is what that returns; else a whole number.
+// An object's address: None or 0 is NULL; an object with data_ptr() (a tensor) is what that returns; else int() of the object.
 bool address(PyObject* x, void** out) {
   *out = nullptr;
   if (x == Py_None) return true;
@@ -33,8 +36,11 @@ bool address(PyObject* x, void** out) {
   } else {
     PyObject* method = PyObject_GetAttr(x, s_data_ptr);
     if (method) {
-      number = PyObject_CallNoArgs(method);
+      PyObject* at = PyObject_CallNoArgs(method);
       Py_DECREF(method);
+      if (!at) return false;
+      number = PyNumber_Long(at);
+      Py_DECREF(at);
     } else if (PyErr_ExceptionMatches(PyExc_AttributeError)) {
       PyErr_Clear();
       number = PyNumber_Long(x);
@@ -81,14 +87,31 @@ bool hyper(PyObject* x, bca_adam* room, const bca_adam** hp) {
   return true;
 }
 
-// Whole numbers are taken modulo the parameter's width, as ctypes does.
-bool whole(PyObject* x, uint64_t* out) {
-  if (!PyLong_Check(x)) {
-    PyErr_Format(PyExc_TypeError, "an int is wanted, not %.100s", Py_TYPE(x)->tp_name);
+// A whole number for C argument number `place`, modulo the parameter's width, from what ctypes takes for a parameter of `type`: an int or
+// another object with __index__ (numpy's integers, tensors of one integer), an instance of the type, or an object whose
+// _as_parameter_ is one of these.
+bool whole(PyObject* x, PyObject* type, Py_ssize_t place, uint64_t* out) {
+  if (PyIndex_Check(x)) {
+    *out = PyLong_AsUnsignedLongLongMask(x);
+    if (*out != ~0ull || !PyErr_Occurred()) return true;
+    PyErr_Clear();  // __index__ refuses, as for a tensor of several elements
+  }
+  const int instance = PyObject_IsInstance(x, type);
+  if (instance < 0) return false;
+  PyObject* inner = PyObject_GetAttr(x, instance ? s_value : s_as_parameter);
+  if (!inner) {
+    if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+    PyErr_Clear();
+    PyErr_Format(e_argument, "argument %zd: an int is wanted, not %.100s", place, Py_TYPE(x)->tp_name);
     return false;
   }
-  *out = PyLong_AsUnsignedLongLongMask(x);
-  return !(*out == ~0ull && PyErr_Occurred());
+  bool ok = Py_EnterRecursiveCall("while processing _as_parameter_") == 0;
+  if (ok) {
+    ok = whole(inner, type, place, out);
+    Py_LeaveRecursiveCall();
+  }
+  Py_DECREF(inner);
+  return ok;
 }
 
 // Arguments in turn: first the function table and, for plans, the handle.
@@ -115,12 +138,14 @@ struct Args {
     if (ok) ok = stream_of(a[i++], &p);
     return p;
   }
-  uint64_t u64() {
+  uint64_t number(PyObject* type) {
     uint64_t v = 0;
-    if (ok) ok = whole(a[i++], &v);
+    if (ok) ok = whole(a[i], type, i, &v), ++i;
     return v;
   }
-  uint32_t u32() { return (uint32_t)u64(); }
+  uint64_t u64() { return number(t_u64); }
+  uint32_t u32() { return (uint32_t)number(t_u32); }
+  int whole_int() { return (int)(uint32_t)number(t_int); }
   const bca_adam* hp(bca_adam* room) {
     const bca_adam* p = nullptr;
     if (ok) ok = hyper(a[i++], room, &p);
@@ -174,7 +199,7 @@ PyObject* call_flat(PyObject*, PyObject* const* args, Py_ssize_t n) {
   Args a(args, n, 9);
   void* g = a.ptr();
   const uint64_t len = a.u64();
-  const int gdt = (int)a.u32();
+  const int gdt = a.whole_int();
   float *thr = a.floats(), *norm = a.floats(), *coef = a.floats();
   int32_t* status = a.word();
   void* s = a.stream();
@@ -264,8 +289,20 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 PyMODINIT_FUNC PyInit__calls(void) {
   static const char* const fields[] = {"lr", "beta1", "beta2", "eps", "weight_decay"};
   s_data_ptr = PyUnicode_InternFromString("data_ptr"), s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-  if (!s_data_ptr || !s_cuda_stream) return nullptr;
+  s_value = PyUnicode_InternFromString("value"), s_as_parameter = PyUnicode_InternFromString("_as_parameter_");
+  if (!s_data_ptr || !s_cuda_stream || !s_value || !s_as_parameter) return nullptr;
   for (int i = 0; i < 5; ++i)
     if (!(s_hyper[i] = PyUnicode_InternFromString(fields[i]))) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* ctypes = PyImport_ImportModule("ctypes");
+  if (!ctypes) return nullptr;
+  t_u32 = PyObject_GetAttrString(ctypes, "c_uint32"), t_u64 = PyObject_GetAttrString(ctypes, "c_uint64");
+  t_int = PyObject_GetAttrString(ctypes, "c_int");
+  PyObject* error = PyObject_GetAttrString(ctypes, "ArgumentError");
+  Py_DECREF(ctypes);
+  PyObject* bases = t_u32 && t_u64 && t_int && error ? PyTuple_Pack(2, error, PyExc_TypeError) : nullptr;
+  Py_XDECREF(error);
+  if (!bases) return nullptr;
+  e_argument = PyErr_NewException("paper_2402_02447_amd._calls.ArgumentError", bases, nullptr);
+  Py_DECREF(bases);
+  return e_argument ? PyModule_Create(&module) : nullptr;
 }

@@ -126,3 +126,58 @@ def test_building_the_package_builds_both_parts(monkeypatch):
     made.clear()
     build.build(out="/tmp/variant.so")      # a variant of the library alone
     assert made == ["/tmp/variant.so"]
+
+
+class Parameter:
+    def __init__(self, x):
+        self._as_parameter_ = x
+
+
+class Index:
+    def __index__(self):
+        return 12
+
+
+NUMBERS = [True, 3, -1, 1 << 70, -(1 << 70), 1.5, "1", b"1", None, np.int64(4), np.uint32(4), C.c_uint32(5), C.c_uint64(6), C.c_int(-7), C.c_long(8), C.c_int64(8),
+           C.c_uint16(9), C.c_bool(True), C.c_float(1.0), Parameter(10), Parameter(Parameter(11)), Parameter("x"), Parameter(C.c_uint32(12)),
+           Index(), object(), (1,)]
+ADDRESSES = [None, True, 0, 5, -1, 1 << 70, -(1 << 70), 2.5, "7", b"8", "x", float("inf"), np.int64(9), np.float32(3), C.c_void_p(3), C.c_uint32(4), Parameter(10), Index(),
+             object(), Tensor(0), Tensor(64), Tensor(np.int64(64)), Tensor(64.0), Tensor("64"), Tensor(None)]
+
+
+def outcome(call):
+    try:
+        return call()
+    except Exception as e:
+        return type(e)
+
+
+def test_arguments_are_taken_and_refused_as_by_ctypes(noted):
+    """What arrives for, and which exception comes of, arguments of every kind, against the same call made through ctypes."""
+    binding.load_library()
+
+    def note(types):
+        seen = []
+        f = C.CFUNCTYPE(I32, *types)(lambda *a: seen.append(list(a)) or 7)
+        return f, seen
+    for name, types in SIGNATURES:
+        plain = [None if t in (VP, HP) else 1 for t in types]
+        for i, t in enumerate(types):
+            if t is HP:
+                continue
+            stream = t is VP and i == len(types) - 1
+            f, seen = note([VP if u is HP else u for u in types])
+
+            def through_ctypes(x):
+                if t is VP:
+                    x = (binding._stream if stream else binding._ptr)(x)
+                assert f(*plain[:i], x, *plain[i + 1:]) == 7
+                return seen.pop()
+
+            for x in ADDRESSES if t is VP else NUMBERS:
+                want = outcome(lambda: through_ctypes(x))
+                got = outcome(lambda: noted(name, *plain[:i], x, *plain[i + 1:])[1][1])
+                if isinstance(want, type):
+                    assert isinstance(got, type) and issubclass(got, want), (name, i, x, want, got)
+                else:
+                    assert got == want, (name, i, x, want, got)
