@@ -22,9 +22,9 @@ struct Functions {
 };
 
 PyObject *s_data_ptr, *s_cuda_stream, *s_value, *s_as_parameter, *s_hyper[5];
-// ctypes' integer types, whose instances are taken as whole numbers of that width, and what is raised for what is none: ctypes'
+// ctypes' types, whose instances are taken as numbers, and what is raised for what is none: ctypes'
 // ArgumentError and a TypeError in one
-PyObject *t_u32, *t_u64, *t_int, *e_argument;
+PyObject *t_u32, *t_u64, *t_int, *t_double, *e_argument;
 
 // An object's address: None or 0 is NULL; an object with data_ptr() (a tensor) is what that returns; else int() of the object.
 bool address(PyObject* x, void** out) {
@@ -70,7 +70,7 @@ bool stream_of(PyObject* x, void** out) {
   return !PyErr_Occurred();
 }
 
-// Hyper-parameters: None, or an object with the five fields.  *hp is left NULL for None.
+// Hyper-parameters: None, or an object with the five fields, each a number or a ctypes.c_double.  *hp is left NULL for None.
 bool hyper(PyObject* x, bca_adam* room, const bca_adam** hp) {
   *hp = nullptr;
   if (x == Py_None) return true;
@@ -78,6 +78,11 @@ bool hyper(PyObject* x, bca_adam* room, const bca_adam** hp) {
   for (int i = 0; i < 5; ++i) {
     PyObject* f = PyObject_GetAttr(x, s_hyper[i]);
     if (!f) return false;
+    if (PyObject_TypeCheck(f, reinterpret_cast<PyTypeObject*>(t_double))) {
+      PyObject* inner = PyObject_GetAttr(f, s_value);
+      Py_DECREF(f);
+      if (!(f = inner)) return false;
+    }
     v[i] = PyFloat_AsDouble(f);
     Py_DECREF(f);
     if (v[i] == -1.0 && PyErr_Occurred()) return false;
@@ -296,10 +301,10 @@ PyMODINIT_FUNC PyInit__calls(void) {
   PyObject* ctypes = PyImport_ImportModule("ctypes");
   if (!ctypes) return nullptr;
   t_u32 = PyObject_GetAttrString(ctypes, "c_uint32"), t_u64 = PyObject_GetAttrString(ctypes, "c_uint64");
-  t_int = PyObject_GetAttrString(ctypes, "c_int");
+  t_int = PyObject_GetAttrString(ctypes, "c_int"), t_double = PyObject_GetAttrString(ctypes, "c_double");
   PyObject* error = PyObject_GetAttrString(ctypes, "ArgumentError");
   Py_DECREF(ctypes);
-  PyObject* bases = t_u32 && t_u64 && t_int && error ? PyTuple_Pack(2, error, PyExc_TypeError) : nullptr;
+  PyObject* bases = t_u32 && t_u64 && t_int && t_double && error ? PyTuple_Pack(2, error, PyExc_TypeError) : nullptr;
   Py_XDECREF(error);
   if (!bases) return nullptr;
   e_argument = PyErr_NewException("paper_2402_02447_amd._calls.ArgumentError", bases, nullptr);

@@ -181,3 +181,22 @@ def test_arguments_are_taken_and_refused_as_by_ctypes(noted):
                     assert isinstance(got, type) and issubclass(got, want), (name, i, x, want, got)
                 else:
                     assert got == want, (name, i, x, want, got)
+
+
+class Float:
+    def __float__(self):
+        return 0.125
+
+
+HYPER = [0.5, 1, True, -1.0, float("nan"), 1 << 70, 1 << 2000, np.float32(0.25), np.float64(0.25), np.int64(3), np.array(0.5), np.array([0.5, 1.0]), C.c_double(0.75), C.c_float(0.75),
+         Float(), Index(), Parameter(0.5), "0.5", None, object()]
+
+
+def test_hyper_parameters_are_taken_and_refused_as_by_ctypes(noted):
+    for i, (field, _) in enumerate(binding._Adam._fields_):
+        for x in HYPER:
+            values = [0.5] * 5
+            values[i] = x
+            want = outcome(lambda: repr([getattr(binding._Adam(*values), f) for f, _ in binding._Adam._fields_]))
+            got = outcome(lambda: repr(noted("adam_step", 1, binding.AdamHyper(*values), 1, None)[1][1][1]))
+            assert got == want, (field, x, want, got)
