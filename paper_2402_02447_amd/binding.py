@@ -153,19 +153,20 @@ class _NotBuilt:
         raise ImportError("the extension module _calls has not been built (python -c 'import __graft_entry__ as g; g.build()')") from self.why
 
 
-_calls = _table = None
+_calls = None
 
 
 def _connect(L) -> None:
-    """The extension module that carries out the compute calls, given the addresses of this library's functions."""
-    global _calls, _table
+    """The extension module that carries out the compute calls, and this library's function table for it (L.calls_table)."""
+    global _calls
+    L.calls_table = None
     try:
         from . import _calls as module
     except ImportError as e:
         _calls = _NotBuilt(e)
         return
     _calls = module
-    _table = module.connect(*(C.cast(getattr(L, f), C.c_void_p).value for f in (
+    L.calls_table = module.connect(*(C.cast(getattr(L, f), C.c_void_p).value for f in (
         "bucket_clip_norms", "bucket_clip_apply", "bucket_clip", "bucket_clip_flat", "adam_step", "bucket_clip_adam", "lamb_step",
         "bucket_clip_lamb")))
 
@@ -205,9 +206,8 @@ def alg1_thresholds(c: float, n_buckets: int) -> np.ndarray:
 
 def bucket_clip_flat(g, n: int, grad_dtype: int, threshold, norm=None, coef=None, status=None, stream=None) -> None:
     """bucket_clip_flat: clip one contiguous bucket in place; no plan, no allocation (see bca.h)."""
-    if _lib is None:
-        load_library()
-    _check(_calls.bucket_clip_flat(_table, g, int(n), grad_dtype, threshold, norm, coef, status, stream))
+    L = _lib or load_library()
+    _check(_calls.bucket_clip_flat(L.calls_table, g, int(n), grad_dtype, threshold, norm, coef, status, stream))
 
 
 class Plan:
@@ -219,7 +219,7 @@ class Plan:
                  unroll_apply: int = 0, tune_flags: int = 0, group_bytes: int = 0, adam_lds_reserve: int = 0,
                  spin_limit: int = 0, norm_item_chunks: int = 0, norm_lead: int = 0, lamb_group_elems: int = 0):
         L = load_library()
-        self._L = L
+        self._L, self._table = L, L.calls_table
         self._h = C.c_void_p()
         numel = np.ascontiguousarray(tensor_numel, dtype=np.uint64)
         off = np.ascontiguousarray(bucket_seg_off, dtype=np.uint64)
@@ -366,24 +366,24 @@ class Plan:
 
     # -- compute (same names as the C ABI).  hp may be None once the plan takes hyper-parameters from device memory.
     def bucket_clip_norms(self, b0: int, b1: int, norms, stream=None) -> None:
-        _check(_calls.bucket_clip_norms(_table, self._h.value, b0, b1, norms, stream))
+        _check(_calls.bucket_clip_norms(self._table, self._h.value, b0, b1, norms, stream))
 
     def bucket_clip_apply(self, b0: int, b1: int, thresholds, norms, coefs=None, status=None, stream=None) -> None:
-        _check(_calls.bucket_clip_apply(_table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
+        _check(_calls.bucket_clip_apply(self._table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
 
     def bucket_clip(self, b0: int, b1: int, thresholds, norms=None, coefs=None, status=None, stream=None) -> None:
-        _check(_calls.bucket_clip(_table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
+        _check(_calls.bucket_clip(self._table, self._h.value, b0, b1, thresholds, norms, coefs, status, stream))
 
     def adam_step(self, hp: Optional[AdamHyper], step: int, stream=None) -> None:
-        _check(_calls.adam_step(_table, self._h.value, hp, step, stream))
+        _check(_calls.adam_step(self._table, self._h.value, hp, step, stream))
 
     def bucket_clip_adam(self, thresholds, hp: Optional[AdamHyper], step: int, flags: int = 0, norms=None, coefs=None,
                          status=None, stream=None) -> None:
-        _check(_calls.bucket_clip_adam(_table, self._h.value, thresholds, hp, step, flags, norms, coefs, status, stream))
+        _check(_calls.bucket_clip_adam(self._table, self._h.value, thresholds, hp, step, flags, norms, coefs, status, stream))
 
     def lamb_step(self, hp: Optional[AdamHyper], step: int, trust=None, stream=None) -> None:
-        _check(_calls.lamb_step(_table, self._h.value, hp, step, trust, stream))
+        _check(_calls.lamb_step(self._table, self._h.value, hp, step, trust, stream))
 
     def bucket_clip_lamb(self, thresholds, hp: Optional[AdamHyper], step: int, flags: int = 0, norms=None, coefs=None,
                          trust=None, status=None, stream=None) -> None:
-        _check(_calls.bucket_clip_lamb(_table, self._h.value, thresholds, hp, step, flags, norms, coefs, trust, status, stream))
+        _check(_calls.bucket_clip_lamb(self._table, self._h.value, thresholds, hp, step, flags, norms, coefs, trust, status, stream))

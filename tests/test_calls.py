@@ -3,6 +3,7 @@ note what they are given (no GPU and no torch tensors needed)."""
 import ctypes as C
 import math
 import os
+import shutil
 import subprocess
 import sys
 
@@ -200,3 +201,21 @@ def test_hyper_parameters_are_taken_and_refused_as_by_ctypes(noted):
             want = outcome(lambda: repr([getattr(binding._Adam(*values), f) for f, _ in binding._Adam._fields_]))
             got = outcome(lambda: repr(noted("adam_step", 1, binding.AdamHyper(*values), 1, None)[1][1][1]))
             assert got == want, (field, x, want, got)
+
+
+def test_a_plan_calls_the_library_that_made_it(monkeypatch, tmp_path):
+    """Also once another library has been loaded: each of the two keeps its own last error."""
+    first = binding.load_library()
+    layout = dict(tensor_numel=[5000], bucket_seg_off=[0, 1], seg_tensor=[0], seg_begin=[0], seg_len=[5000])
+    with binding.Plan(**layout, device=-1) as plan:
+        monkeypatch.setattr(binding, "_lib", None)
+        monkeypatch.setenv("BCA_LIB", str(shutil.copy(binding.library_path(), tmp_path / "other.so")))
+        second = binding.load_library()
+        assert second is not first
+        assert first.bca_plan_set_decay_mask(None, None) != 0       # its last error is this one now
+        assert second.bca_last_error() == b""
+        before = first.bca_last_error()
+        for call in (lambda: plan.adam_step(binding.AdamHyper(), 1), lambda: plan.bucket_clip(0, 1, 64, 64, 64, 64)):
+            with pytest.raises(binding.BcaError):
+                call()
+            assert first.bca_last_error() != before and second.bca_last_error() == b""
