@@ -61,6 +61,7 @@ struct lbs_dataset {
   uint32_t* d_cum = nullptr;
   uint32_t n_cus = 1;           // compute units of the device
   bool flagged = false;         // some guide entry has to be searched
+  bool whole_first = false;     // k_lbs_nodes with the whole dataset's table has no LDS in front of that table
   uint32_t* d_guide = nullptr;  // the whole dataset's table (kWholeGuideSize entries), then one of kGuideSize per stratum
 };
 
@@ -1178,7 +1179,8 @@ __global__ __launch_bounds__(kBlock, LG == 5 ? 5 : 6) void k_lbs_nodes(
   static_assert(CPL >= 1 && RPL >= 1 && CPL * ROWS == R && RPL * LANES == ROWS && ROWS <= 16);
   // (WHOLE) the whole dataset's guide table and the trial's own histogram; the strata's tables, NodesShared, a word per GPU.  The kernel
   // has no static LDS, so that this is address 0 and a draw's upper bits are the address of its entry in the first table (an
-  // addition of the array's address, which the compiler does not fold away, is a fortieth of a draw).
+  // addition of the array's address, which the compiler does not fold away, is a fortieth of a draw).  whole_tables_first() looks
+  // whether that is so; where it is not, the kernel is not launched.
   extern __shared__ uint32_t s_dyn[];
   constexpr uint32_t kCnt = kWholeGuideSize, kStrata = WHOLE ? kCnt + kCountWords : 0u;
   uint32_t* s_strata = s_dyn + kStrata;
@@ -1414,6 +1416,19 @@ auto pick_nodes(const Bins& B, const Params& P, Rows* L) {
   return kernel;
 }
 
+// Whether no LDS lies in front of the dynamic one in any k_lbs_nodes that takes the whole dataset's table for address 0.
+hipError_t whole_tables_first(bool* first) {
+  *first = true;
+  for (const auto kernel : {k_lbs_nodes<4, 2, 1, true>, k_lbs_nodes<4, 2, 2, true>, k_lbs_nodes<5, 2, 1, true>, k_lbs_nodes<5, 2, 2, true>,
+                            k_lbs_nodes<3, 3, 1, true>, k_lbs_nodes<3, 3, 2, true>, k_lbs_nodes<4, 3, 1, true>, k_lbs_nodes<4, 3, 2, true>,
+                            k_lbs_nodes<5, 3, 1, true>, k_lbs_nodes<5, 3, 2, true>}) {
+    hipFuncAttributes a;
+    if (const hipError_t e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(kernel))) return e;
+    if (a.sharedSizeBytes != 0) *first = false;
+  }
+  return hipSuccess;
+}
+
 __global__ __launch_bounds__(64) void k_lbs_clear_all(unsigned long long* sums) {
   if (threadIdx.x < 2u * kMethods) sums[threadIdx.x] = 0ull;
 }
@@ -1547,6 +1562,7 @@ static int dataset_create(lbs_dataset** out, int device, uint32_t max_len, const
     int n_cus = 0;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e == hipSuccess) ds->n_cus = (uint32_t)std::max(n_cus, 1);
+    if (e == hipSuccess) e = whole_tables_first(&ds->whole_first);
     if (e == hipSuccess) e = hipMalloc((void**)&ds->d_cum, (max_len + 1) * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemcpy(ds->d_cum, cum, (max_len + 1) * sizeof(uint32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&ds->d_guide, guide.size() * sizeof(uint32_t));
@@ -1758,7 +1774,7 @@ static int simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* tri
     void (*kernel)(const Params, const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, unsigned long long*) =
         pool <= 64 ? k_lbs_all<1> : pool <= 128 ? k_lbs_all<2> : pool <= 256 ? k_lbs_all<4> : pool <= 512 ? k_lbs_all<8> : k_lbs_all<16>;
     Rows rows;
-    if (const auto nodes = pick_nodes<true>(L, P, &rows))
+    if (const auto nodes = ds->whole_first ? pick_nodes<true>(L, P, &rows) : nullptr)
       hipLaunchKernelGGL(nodes, grid, block, nodes_lds<true>(P), s, P, rows, 0u, ds->d_guide, trial_min, trial_max, ds_sums);
     else if (L.count != 0)
       hipLaunchKernelGGL(pick_bins<true>(L, P, run->n_trials <= 6u * (uint64_t)ds->n_cus), grid, block, lds, s, P, L, 0u, ds->d_cum,

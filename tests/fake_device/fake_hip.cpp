@@ -26,6 +26,7 @@ std::vector<Launch>& launches() {
 bool g_fail = false;
 unsigned long long g_mallocs = 0, g_frees = 0;
 int g_cus = 256;
+size_t g_static_lds = 0;
 struct Config {
   dim3 grid, block;
   size_t lds;
@@ -51,6 +52,7 @@ void fake_fail_host_allocations(int on) { g_fail = on != 0; }
 unsigned long long fake_device_allocations() { return g_mallocs; }
 unsigned long long fake_device_frees() { return g_frees; }
 void fake_set_cus(int n) { g_cus = n; }
+void fake_set_static_lds(unsigned n) { g_static_lds = n; }  // what every kernel is said to have
 unsigned fake_num_launches() { return (unsigned)launches().size(); }
 const char* fake_launch_name(unsigned i) { return names()[launches()[i].kernel].c_str(); }
 unsigned fake_launch_grid(unsigned i) { return launches()[i].grid; }
@@ -119,6 +121,11 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t* prop, int) {
 }
 hipError_t hipDeviceGetAttribute(int* x, hipDeviceAttribute_t, int) {
   *x = g_cus;
+  return hipSuccess;
+}
+hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) {
+  memset(a, 0, sizeof *a);
+  a->sharedSizeBytes = g_static_lds;
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }

@@ -123,3 +123,19 @@ def allocations(n, **tuning):
 assert (a, b, c) == (False, True, False)
 assert large == small + 1 == multi + 1, (small, large, multi)
 """)
+
+
+def test_the_form_whose_table_lies_at_address_zero_is_taken_only_where_it_does(device):
+    """All five methods, nodes of 8 in full bins: k_lbs_nodes addresses its first table as if nothing lay in front of it, so a kernel with LDS
+    of its own is not launched; one method alone has no such table."""
+    fake_device.run(device, """
+cum, ends, quota = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END, [6, 3, 2, 5]
+for own, want in ((0, "k_lbs_nodes"), (16, "k_lbs_bins"), (0, "k_lbs_nodes")):
+    fake.fake_set_static_lds(own)
+    with lbs.Dataset(cum, ends, device=0) as ds:
+        kernels()
+        ds.lbs_simulate_all(16, 8, 1024, quota, 1, 5000, 4096)
+        assert [k for k, _ in kernels()] == ["k_lbs_clear_all", want], own
+        ds.lbs_simulate(lbs.LBS_LOCAL_SNAKE, 16, 8, 1024, quota, 1, 5000, 4096)
+        assert [k for k, _ in kernels()] == ["k_lbs_clear", "k_lbs_nodes"], own
+""")
