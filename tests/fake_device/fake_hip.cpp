@@ -5,6 +5,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <new>
 #include <string>
@@ -56,6 +57,8 @@ void fake_set_static_lds(unsigned n) { g_static_lds = n; }  // what every kernel
 unsigned fake_num_launches() { return (unsigned)launches().size(); }
 const char* fake_launch_name(unsigned i) { return names()[launches()[i].kernel].c_str(); }
 unsigned fake_launch_grid(unsigned i) { return launches()[i].grid; }
+unsigned fake_num_kernels() { return (unsigned)names().size(); }
+const char* fake_kernel_name(unsigned i) { return std::next(names().begin(), i)->second.c_str(); }  // every kernel the library has
 void fake_forget_launches() { launches().clear(); }
 
 // ---- the runtime

@@ -1,6 +1,7 @@
 """Host code of the compute calls, on a device that only notes what is launched on it (tests/fake_device)."""
 import numpy as np
 import pytest
+import torch
 
 import fake_device
 import paper_2402_02447_amd as B
@@ -139,3 +140,34 @@ for own, want in ((0, "k_lbs_nodes"), (16, "k_lbs_bins"), (0, "k_lbs_nodes")):
         ds.lbs_simulate(lbs.LBS_LOCAL_SNAKE, 16, 8, 1024, quota, 1, 5000, 4096)
         assert [k for k, _ in kernels()] == ["k_lbs_clear", "k_lbs_nodes"], own
 """)
+
+
+def test_the_gpu_tests_run_every_form_of_nodes_and_bins(device, monkeypatch):
+    """What the GPU tests of the simulation ask for, noted instead of carried out and put to the host code: each k_lbs_nodes and k_lbs_bins
+    that the library holds has to be among the kernels that it picks."""
+    import test_gpu_lbs_bins as T
+    calls = []
+    monkeypatch.setattr(T, "check", lambda cum, ends, method, batch, gpn, gpus, quota, seed, n, first=0: calls.append((method, batch, gpn, gpus, quota, n)))
+    monkeypatch.setattr(T, "check_all", lambda cum, ends, batch, gpn, gpus, quota, seed, n, first=0: calls.append((None, batch, gpn, gpus, quota, n)))
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda device: type("Properties", (), {"multi_processor_count": 256}))
+    for test in (T.test_quotas_that_fit_in_bins_and_quotas_that_do_not, T.test_full_bins_by_number_of_nodes, T.test_forms_of_full_bins):
+        names, values = test.pytestmark[0].args
+        for row in values:
+            test(**dict(zip(names.split(","), row)))
+    out = fake_device.run(device, f"""
+cum, ends, picked = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END, set()
+with lbs.Dataset(cum, ends, device=0) as ds:
+    for method, batch, gpn, gpus, quota, n in {calls!r}:
+        kernels()
+        if method is None:
+            ds.lbs_simulate_all(batch, gpn, gpus, quota, 1, n, 4096)
+        else:
+            ds.lbs_simulate(method, batch, gpn, gpus, quota, 1, n, 4096)
+        picked |= set(fake.fake_launch_name(i) for i in range(fake.fake_num_launches()))
+held = set(fake.fake_kernel_name(i) for i in range(fake.fake_num_kernels()))
+for kind, n in ((b"k_lbs_nodes", 20), (b"k_lbs_bins", 12)):
+    forms = set(k for k in held if kind in k)
+    assert len(forms) == n, (kind, len(forms))
+    print(sorted(forms - picked))
+""")
+    assert out.split() == ["[]", "[]"], out

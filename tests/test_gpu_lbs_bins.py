@@ -50,6 +50,22 @@ def test_full_bins_by_number_of_nodes(gpn, batch, quota, nodes):
         check(CUM, ENDS, method, batch, gpn, gpn * n_nodes, quota, seed=5 * n_nodes, n=n)
 
 
+# Each number of registers a node of full bins can lie in, by all five methods at once and by one alone (test_fake_device.py looks that no form
+# is left out): numbers of nodes that leave part of the last wavefront, or the second node of a pair, without one.
+@pytest.mark.parametrize("gpn,batch,quota,nodes_all,nodes_alone", [
+    (8, 16, [6, 3, 2, 5], 31, 23), (8, 16, [6, 3, 2, 5], 47, 47), (8, 16, [6, 3, 2, 5], 95, 95),            # two bins: 8, 16, 32 registers
+    (8, 8, [3, 2, 1, 2], 63, 47), (8, 8, [3, 2, 1, 2], 127, 127), (8, 8, [3, 2, 1, 2], 191, 191),            # one bin
+    (4, 32, [12, 6, 4, 10], 79, 79), (4, 32, [12, 6, 4, 10], 95, 95), (4, 32, [12, 6, 4, 10], 128, 128),     # two bins: 16, 32
+    (4, 16, [5, 2, 3, 6], 127, 127), (4, 16, [5, 2, 3, 6], 191, 191),                                         # one bin
+])
+def test_forms_of_full_bins(gpn, batch, quota, nodes_all, nodes_alone):
+    import torch
+    n = 6 * torch.cuda.get_device_properties(0).multi_processor_count + 1
+    check_all(CUM, ENDS, batch, gpn, gpn * nodes_all, quota, seed=nodes_all, n=n, first=5)
+    for method in LOCAL:
+        check(CUM, ENDS, method, batch, gpn, gpn * nodes_alone, quota, seed=7 * nodes_alone, n=n, first=1 << 40)
+
+
 @pytest.mark.parametrize("kind", ["gaps", "spike", "rare_tail", "wide_strata", "one_length"])
 def test_histograms_whose_cells_have_to_be_searched(kind):
     rng = np.random.default_rng(5)
