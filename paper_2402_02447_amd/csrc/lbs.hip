@@ -1342,43 +1342,66 @@ __global__ __launch_bounds__(kBlock, LG == 5 ? 5 : 6) void k_lbs_nodes(
   if (tid < 2u * kMethods && (WHOLE || (tid >> 1) == method)) atomicAdd(&sums[WHOLE ? tid : (tid & 1u)], sh.sum[tid]);
 }
 
-// What a trial costs, in tenths of a nanosecond on the whole chip (256 compute units, measured at 1 to 256 nodes): a wavefront's rounds of
-// `at_once` nodes (BINS == 1: pairs) at `each`, a share of that for wavefronts that idle in the last turn, and the trial's own.  With the
-// draws from the whole dataset (all five methods) a trial has four more barriers, and idle wavefronts weigh more.
+// Which form a run of node-local methods takes: k_lbs_bins with one node at a time (the only one for nodes of 1, 2 and 16), with the columns in
+// registers (nodes of 4 and 8: with two columns only 6 of the 21 stages would stay within a lane, 11 with four and 15 with eight, and
+// sixteen are more columns than a group has lanes), or k_lbs_nodes with 8, 16 or 32 registers.
+enum Form : uint32_t { kOneNode, kColumns, kNodes8, kNodes16, kNodes32, kForms };
+
+// What it takes, in microseconds beyond what every launch does: workgroups start one every `launch` nanoseconds or, where that is more, one when the
+// chip has got through a workgroup's trials; a wavefront's rounds in one trial, for the last workgroup; and, where the workgroups are more than
+// fit on the chip at a time, what the last turn leaves idle.  A trial is a wavefront's rounds of `at_once` nodes (BINS == 1: pairs) at `each` (ns,
+// whole chip), and a share of that for wavefronts without one in the last round, which weigh more where it is the only one.
+//   Fitted to 4 180 runs, five methods at once and one alone, in every form: nodes of 4 and 8 in one and in two full bins, 2 to 256 nodes, 200
+// to 100 000 trials.  The form taken is 0.3 and 0.4 % slower than the fastest of them on average (one method, all five).  Why the number of trials counts: 30
+// nodes of 4, batch 16, snake alone, us, columns / 16 registers: 1 700 trials 28.1 / 33.4 (eight workgroups a compute unit against six), 30 000
+// 115.5 / 140.3, where so few nodes leave three wavefronts idle; 64 such nodes: 16 000 trials 111.2 / 124.8, 100 000 613 / 511.
 struct Cost {
   uint32_t n;  // nodes, or pairs of nodes
+  uint32_t gpn;
+  bool two;    // bins
+  uint32_t grid, n_cus;
+  double trials;  // per workgroup
   bool whole;
-  double rounds(uint32_t at_once, double each, double trial) const {
-    const uint32_t r = (n + at_once - 1u) / at_once;
-    return trial + each * (r + (kWaves - 1u - (r - 1u) % kWaves) / (whole ? 4.0 : 8.0));
-  }
-  // k_lbs_bins<0>: one at a time (one method alone 2.2; where that is no more than a tenth better, runs of few trials are through first with several)
-  double one() const { return whole ? 12.0 + 2.5 * n : 2.4 * n; }
-  // columns in registers, 2^lg of them: k_lbs_bins<2> and <3>
-  double columns(uint32_t lg) const {
-    return lg == 2 ? rounds(4, whole ? 8.2 : 7.2, whole ? 13.0 : 3.0) : rounds(8, whole ? 15.5 : 12.0, whole ? 20.0 : 6.0);
-  }
-  // k_lbs_nodes<lg>
-  double nodes(uint32_t lg) const {
-    const double each = lg == 3 ? (whole ? 13.0 : 10.8) : lg == 4 ? (whole ? 22.0 : 18.0) : (whole ? 41.0 : 33.0);
-    return rounds(1u << lg, each, whole ? 20.0 : 6.0);
+  double us(Form form) const {
+    struct Entry {
+      uint32_t at_once, resident;  // workgroups a compute unit
+      double turn, trial, each;
+    };
+    static constexpr Entry one[] = {{1, 8, 0.58, 0.35, 0.2}, {8, 7, 1.7, 0.5, 1.3}, {8, 7, 1.3, 0.38, 1.11}, {16, 7, 2.0, 0.43, 1.77}, {32, 5, 3.2, 0.32, 3.31}};
+    static constexpr Entry all[] = {{1, 6, 0.69, 1.2, 0.21}, {8, 4, 3.0, 1.2, 1.4}, {8, 6, 1.4, 1.8, 1.02}, {16, 6, 2.55, 1.55, 1.86}, {32, 5, 5.3, 2.37, 3.31}};
+    Entry e = (whole ? all : one)[form];
+    if (gpn == 4u) {
+      if (form == kColumns) e = whole ? Entry{4, two ? 5u : 6u, 1.16, 1.02, 0.73} : Entry{4, 8, 0.75, 0.18, 0.74};
+      if (form == kNodes16) e.resident = 6;
+      if (form == kNodes32 && !whole && !two) e.resident = 6;
+    }
+    const uint32_t rounds = (n + e.at_once - 1u) / e.at_once, turns = (rounds + kWaves - 1u) / kWaves, idle = turns * kWaves - rounds;
+    const double trial = e.trial + e.each * (rounds + idle * (turns == 1u ? (whole ? 0.25 : 0.29) : (whole ? 0.21 : 0.05)));
+    const uint32_t slots = e.resident * n_cus, last = grid > slots ? grid % slots : 0u;
+    return e.turn * turns + 1e-3 * grid * std::max(whole ? 13.0 : 13.6, trial * trials) + (last != 0u ? (whole ? 2.15 : 1.2) * (slots - last) / slots : 0.0);
   }
 };
-inline Cost cost_of(const Bins& L, const Params& P, bool whole) {
-  const uint32_t n_nodes = P.n_gpus / P.gpus_per_node;
-  return Cost{L.count == 2 ? n_nodes : (n_nodes + 1u) / 2u, whole};
+Form pick_form(const Bins& B, const Params& P, uint32_t grid, uint32_t n_cus, bool whole, bool nodes) {
+  const uint32_t gpn = P.gpus_per_node, n_nodes = P.n_gpus / gpn;
+  if (gpn != 4u && gpn != 8u) return kOneNode;
+  nodes = nodes && B.padded == 0 && P.flagged == 0;
+  const Cost c{B.count == 2 ? n_nodes : (n_nodes + 1u) / 2u, gpn, B.count == 2, grid, n_cus, (double)P.n_trials / grid, whole};
+  Form best = kOneNode;
+  double least = c.us(kOneNode);
+  for (uint32_t f = kColumns; f < (nodes ? kForms : kNodes8); ++f) {
+    if (f == kNodes8 && gpn == 4u) continue;  // that is the columns
+    const double t = c.us((Form)f);
+    if (t < least) least = t, best = (Form)f;
+  }
+  return best;
 }
 
-// k_lbs_bins for a run whose strata fit in L.count bins.  Columns in registers for nodes of 4 and 8: with two columns only 6 of the
-// 21 stages would stay within a lane (11 with four, 15 with eight), and sixteen are more columns than a group has lanes.
+// k_lbs_bins for a run whose strata fit in L.count bins.
 template <bool WHOLE>
-auto pick_bins(const Bins& L, const Params& P, bool one_round) {
+auto bins_kernel(const Bins& L, const Params& P, Form form) {
   const bool two = L.count == 2;
-  const Cost c = cost_of(L, P, WHOLE);
-  // one_round: a trial's time matters, not its cost, and several nodes at a time are through first
-  const auto columns = [&](uint32_t lg) { return one_round ? c.n >= P.gpus_per_node : c.columns(lg) < c.one(); };
-  if (P.gpus_per_node == 4 && columns(2)) return two ? k_lbs_bins<2, 2, WHOLE> : k_lbs_bins<2, 1, WHOLE>;
-  if (P.gpus_per_node == 8 && columns(3)) return two ? k_lbs_bins<3, 2, WHOLE> : k_lbs_bins<3, 1, WHOLE>;
+  if (form == kColumns && P.gpus_per_node == 4) return two ? k_lbs_bins<2, 2, WHOLE> : k_lbs_bins<2, 1, WHOLE>;
+  if (form == kColumns) return two ? k_lbs_bins<3, 2, WHOLE> : k_lbs_bins<3, 1, WHOLE>;
   return two ? k_lbs_bins<0, 2, WHOLE> : k_lbs_bins<0, 1, WHOLE>;
 }
 
@@ -1388,17 +1411,10 @@ size_t nodes_lds(const Params& P) {
   return sizeof(NodesShared) + sizeof(uint32_t) * ((size_t)P.guide_words + (WHOLE ? kCountWords + P.n_gpus : 0u));
 }
 
-// k_lbs_nodes for a run, or nullptr where it does not apply or k_lbs_bins is the better one; L: its rows.
+// k_lbs_nodes for a run that takes one of its forms; L: its rows.
 template <bool WHOLE>
-auto pick_nodes(const Bins& B, const Params& P, Rows* L) {
-  decltype(&k_lbs_nodes<4, 3, 2, WHOLE>) kernel = nullptr;
-  const uint32_t gpn = P.gpus_per_node;
-  if (B.count == 0 || B.padded != 0 || P.flagged != 0 || (gpn != 4 && gpn != 8)) return kernel;
-  const Cost c = cost_of(B, P, WHOLE);
-  const double nodes[] = {gpn == 8 ? c.nodes(3) : c.columns(2), c.nodes(4), c.nodes(5)};
-  const uint32_t lg = nodes[2] < std::min(nodes[0], nodes[1]) ? 5u : nodes[1] < nodes[0] ? 4u : gpn == 8 ? 3u : 0u;
-  if (lg == 0 || c.one() < nodes[lg - 3]) return kernel;
-  const uint32_t rows = 64u / gpn;
+auto nodes_kernel(const Bins& B, const Params& P, Form form, Rows* L) {
+  const uint32_t gpn = P.gpus_per_node, rows = 64u / gpn;
   *L = Rows{};
   for (uint32_t h = 0; h < B.count; ++h)
     for (uint32_t r = 0; r < rows; ++r) {
@@ -1407,13 +1423,11 @@ auto pick_nodes(const Bins& B, const Params& P, Rows* L) {
       L->odd[h] |= (j & 1u) << r;
     }
   if (B.count == 2) {
-    if (gpn == 4) kernel = lg == 5 ? k_lbs_nodes<5, 2, 2, WHOLE> : k_lbs_nodes<4, 2, 2, WHOLE>;
-    else kernel = lg == 5 ? k_lbs_nodes<5, 3, 2, WHOLE> : lg == 4 ? k_lbs_nodes<4, 3, 2, WHOLE> : k_lbs_nodes<3, 3, 2, WHOLE>;
-  } else {
-    if (gpn == 4) kernel = lg == 5 ? k_lbs_nodes<5, 2, 1, WHOLE> : k_lbs_nodes<4, 2, 1, WHOLE>;
-    else kernel = lg == 5 ? k_lbs_nodes<5, 3, 1, WHOLE> : lg == 4 ? k_lbs_nodes<4, 3, 1, WHOLE> : k_lbs_nodes<3, 3, 1, WHOLE>;
+    if (gpn == 4) return form == kNodes32 ? k_lbs_nodes<5, 2, 2, WHOLE> : k_lbs_nodes<4, 2, 2, WHOLE>;
+    return form == kNodes32 ? k_lbs_nodes<5, 3, 2, WHOLE> : form == kNodes16 ? k_lbs_nodes<4, 3, 2, WHOLE> : k_lbs_nodes<3, 3, 2, WHOLE>;
   }
-  return kernel;
+  if (gpn == 4) return form == kNodes32 ? k_lbs_nodes<5, 2, 1, WHOLE> : k_lbs_nodes<4, 2, 1, WHOLE>;
+  return form == kNodes32 ? k_lbs_nodes<5, 3, 1, WHOLE> : form == kNodes16 ? k_lbs_nodes<4, 3, 1, WHOLE> : k_lbs_nodes<3, 3, 1, WHOLE>;
 }
 
 // Whether no LDS lies in front of the dynamic one in any k_lbs_nodes that takes the whole dataset's table for address 0.
@@ -1696,14 +1710,13 @@ static int simulate_one(const lbs_dataset* ds, const lbs_run* run, uint32_t meth
     const bool many_short = local && L.count == 1 && run->n_gpus / run->gpus_per_node <= kWaves &&
                             run->n_trials > (uint64_t)kBinsMostShortTrials * grid.x;
     Rows rows;
-    // trials that are all resident at once take as long as one does, and k_lbs_bins, whose code is shorter, is through first: 500 trials of
-    // 33 nodes of 4, batch 16, 13.7 us against 14.5
-    const bool one_round = run->n_trials <= 6u * (uint64_t)ds->n_cus;
-    if (const auto nodes = local && !many_short && !one_round ? pick_nodes<false>(L, P, &rows) : nullptr) {
-      hipLaunchKernelGGL(nodes, grid, block, nodes_lds<false>(P), s, P, rows, method, ds->d_guide, trial_min, trial_max, ds_sums);
+    const Form form = local && L.count != 0 && !many_short ? pick_form(L, P, grid.x, ds->n_cus, false, true) : kOneNode;
+    if (form >= kNodes8) {
+      hipLaunchKernelGGL(nodes_kernel<false>(L, P, form, &rows), grid, block, nodes_lds<false>(P), s, P, rows, method, ds->d_guide, trial_min,
+                         trial_max, ds_sums);
     } else if (local && L.count != 0 && !many_short) {
-      hipLaunchKernelGGL(pick_bins<false>(L, P, one_round), grid, block, sizeof(uint32_t) * tables, s, P, L,
-                         method, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);
+      hipLaunchKernelGGL(bins_kernel<false>(L, P, form), grid, block, sizeof(uint32_t) * tables, s, P, L, method, ds->d_cum, ds->d_guide, trial_min,
+                         trial_max, ds_sums);
     } else if (local) {
       const uint32_t gpn = run->gpus_per_node;
       const bool in_lanes = gpn <= 32 && (gpn & (gpn - 1u)) == 0;
@@ -1774,11 +1787,12 @@ static int simulate_all(const lbs_dataset* ds, const lbs_run* run, uint32_t* tri
     void (*kernel)(const Params, const uint32_t*, const uint32_t*, uint32_t*, uint32_t*, unsigned long long*) =
         pool <= 64 ? k_lbs_all<1> : pool <= 128 ? k_lbs_all<2> : pool <= 256 ? k_lbs_all<4> : pool <= 512 ? k_lbs_all<8> : k_lbs_all<16>;
     Rows rows;
-    if (const auto nodes = ds->whole_first ? pick_nodes<true>(L, P, &rows) : nullptr)
-      hipLaunchKernelGGL(nodes, grid, block, nodes_lds<true>(P), s, P, rows, 0u, ds->d_guide, trial_min, trial_max, ds_sums);
+    const Form form = L.count != 0 ? pick_form(L, P, grid.x, ds->n_cus, true, ds->whole_first) : kOneNode;
+    if (form >= kNodes8)
+      hipLaunchKernelGGL(nodes_kernel<true>(L, P, form, &rows), grid, block, nodes_lds<true>(P), s, P, rows, 0u, ds->d_guide, trial_min, trial_max,
+                         ds_sums);
     else if (L.count != 0)
-      hipLaunchKernelGGL(pick_bins<true>(L, P, run->n_trials <= 6u * (uint64_t)ds->n_cus), grid, block, lds, s, P, L, 0u, ds->d_cum,
-                         ds->d_guide, trial_min, trial_max, ds_sums);
+      hipLaunchKernelGGL(bins_kernel<true>(L, P, form), grid, block, lds, s, P, L, 0u, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);
     else
       hipLaunchKernelGGL(kernel, grid, block, lds, s, P, ds->d_cum, ds->d_guide, trial_min, trial_max, ds_sums);
     e = hipGetLastError();

@@ -147,17 +147,20 @@ def test_the_gpu_tests_run_every_form_of_nodes_and_bins(device, monkeypatch):
     that the library holds has to be among the kernels that it picks."""
     import test_gpu_lbs_bins as T
     calls = []
-    monkeypatch.setattr(T, "check", lambda cum, ends, method, batch, gpn, gpus, quota, seed, n, first=0: calls.append((method, batch, gpn, gpus, quota, n)))
-    monkeypatch.setattr(T, "check_all", lambda cum, ends, batch, gpn, gpus, quota, seed, n, first=0: calls.append((None, batch, gpn, gpus, quota, n)))
+
+    def note(method):
+        return lambda cum, ends, *rest, n, seed, first=0: calls.append((cum is T.SPIKE, *((None,) if method else ()), *rest, n))
+    monkeypatch.setattr(T, "check", note(False))
+    monkeypatch.setattr(T, "check_all", note(True))
     monkeypatch.setattr(torch.cuda, "get_device_properties", lambda device: type("Properties", (), {"multi_processor_count": 256}))
     for test in (T.test_quotas_that_fit_in_bins_and_quotas_that_do_not, T.test_full_bins_by_number_of_nodes, T.test_forms_of_full_bins):
         names, values = test.pytestmark[0].args
         for row in values:
             test(**dict(zip(names.split(","), row)))
     out = fake_device.run(device, f"""
-cum, ends, picked = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END, set()
-with lbs.Dataset(cum, ends, device=0) as ds:
-    for method, batch, gpn, gpus, quota, n in {calls!r}:
+plain, spike, picked = W.length_histogram_piecewise_uniform(), np.array({T.SPIKE.tolist()}, np.uint32), set()
+for searched, method, batch, gpn, gpus, quota, n in {calls!r}:
+    with lbs.Dataset(spike if searched else plain, W.LENGTH_STRATUM_END, device=0) as ds:
         kernels()
         if method is None:
             ds.lbs_simulate_all(batch, gpn, gpus, quota, 1, n, 4096)
@@ -171,3 +174,34 @@ for kind, n in ((b"k_lbs_nodes", 20), (b"k_lbs_bins", 12)):
     print(sorted(forms - picked))
 """)
     assert out.split() == ["[]", "[]"], out
+
+
+def test_the_form_of_a_run_is_not_one_that_was_measured_slower(device):
+    """Nodes of 4 and 8 in full bins on 256 compute units: sizes at which the forms differ by a tenth and more (us beside them)."""
+    out = fake_device.run(device, """
+cum, ends = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END
+quota = {(8, 16): [6, 3, 2, 5], (8, 8): [3, 2, 1, 2], (4, 16): [5, 2, 3, 6], (4, 32): [12, 6, 4, 10]}
+with lbs.Dataset(cum, ends, device=0) as ds:
+    for gpn, batch, nodes, n, alone, good in [
+            (4, 16, 30, 30000, True, ["bins 2"]),                   # 116; one node at a time 136, 16 registers 140
+            (4, 16, 30, 1700, True, ["bins 0", "bins 2"]),          # 30, 28; 33
+            (4, 16, 64, 1700, True, ["bins 2"]),                    # 29; 33, 34
+            (4, 16, 64, 16000, True, ["bins 2"]),                   # 111; 128, 125
+            (4, 16, 64, 100000, True, ["nodes 4"]),                 # 511; 713, columns 613
+            (8, 16, 30, 16000, True, ["bins 3", "nodes 3"]),        # 115, 113; 123, 16 registers 128
+            (8, 8, 60, 16000, True, ["bins 3", "nodes 3"]),
+            (8, 16, 128, 1000, True, ["nodes 4", "nodes 5"]),       # 26, 23; columns 31
+            (8, 16, 20, 1100, False, ["bins 0", "nodes 3"]),        # 25; columns 30
+            (8, 8, 30, 1200, False, ["bins 0", "nodes 3"]),
+            (4, 32, 18, 1300, False, ["bins 0", "nodes 4"]),        # 28, 28; columns 34
+            (8, 16, 128, 100000, False, ["nodes 5"])]:              # 1770; 16 registers 2006
+        kernels()
+        if alone:
+            ds.lbs_simulate(lbs.LBS_LOCAL_SNAKE, batch, gpn, gpn * nodes, quota[gpn, batch], 1, n, 4096)
+        else:
+            ds.lbs_simulate_all(batch, gpn, gpn * nodes, quota[gpn, batch], 1, n, 4096)
+        kind, lg = re.search(r"k_lbs_(bins|nodes)ILi(\\d)", fake.fake_launch_name(1).decode()).groups()
+        if f"{kind} {lg}" not in good:
+            print(gpn, batch, nodes, n, alone, kind, lg)
+""")
+    assert out == "", out

@@ -17,6 +17,9 @@ def _cum(hist):
     return np.concatenate([[0], np.cumsum(hist)]).astype(np.uint32)
 
 
+SPIKE = _cum(np.where(np.arange(512) == 99, 4_000_000, 1))     # one length holds nearly everything
+
+
 # (gpus per node, local batch, quota): what of 64 / gpus_per_node rows the strata fill
 @pytest.mark.parametrize("gpn,batch,quota", [
     (8, 16, [6, 3, 2, 5]), (4, 32, [12, 6, 4, 10]), (2, 44, [20, 12, 12, 0]),       # two bins, full
@@ -33,8 +36,7 @@ def test_quotas_that_fit_in_bins_and_quotas_that_do_not(gpn, batch, quota):
         check_all(CUM, ENDS, batch, gpn, gpn * n_nodes, quota, seed=17 * gpn + n_nodes, n=7, first=11)
 
 
-# Full bins of nodes of 4 and 8, where the number of nodes decides how many registers a node lies in (8, 16 or 32, or one column
-# a register): below, at and above the lines, numbers that leave wavefronts and groups of lanes without a node, and odd numbers where
+# Full bins of nodes of 4 and 8: numbers of nodes that leave wavefronts and groups of lanes without a node, and odd numbers where
 # two nodes share a register.  Slots whose rows change parity inside a bin ([5, 2, 3, 6]) and ones that do not.
 @pytest.mark.parametrize("gpn,batch,quota,nodes", [
     (8, 16, [6, 3, 2, 5], (19, 22, 33, 50, 128, 131)), (8, 16, [5, 2, 3, 6], (32, 64, 97)),
@@ -44,26 +46,26 @@ def test_full_bins_by_number_of_nodes(gpn, batch, quota, nodes):
     import torch
     for n_nodes in nodes:
         check_all(CUM, ENDS, batch, gpn, gpn * n_nodes, quota, seed=n_nodes, n=5, first=2)
-    # one method alone goes that way where there are more trials than are resident at once
+    # one method alone: more trials than are resident at once
     n = 6 * torch.cuda.get_device_properties(0).multi_processor_count + 1
     for n_nodes, method in zip((nodes[0], nodes[1], nodes[-1]), LOCAL + LOCAL[:1]):
         check(CUM, ENDS, method, batch, gpn, gpn * n_nodes, quota, seed=5 * n_nodes, n=n)
 
 
-# Each number of registers a node of full bins can lie in, by all five methods at once and by one alone (test_fake_device.py looks that no form
-# is left out): numbers of nodes that leave part of the last wavefront, or the second node of a pair, without one.
-@pytest.mark.parametrize("gpn,batch,quota,nodes_all,nodes_alone", [
-    (8, 16, [6, 3, 2, 5], 31, 23), (8, 16, [6, 3, 2, 5], 47, 47), (8, 16, [6, 3, 2, 5], 95, 95),            # two bins: 8, 16, 32 registers
-    (8, 8, [3, 2, 1, 2], 63, 47), (8, 8, [3, 2, 1, 2], 127, 127), (8, 8, [3, 2, 1, 2], 191, 191),            # one bin
-    (4, 32, [12, 6, 4, 10], 79, 79), (4, 32, [12, 6, 4, 10], 95, 95), (4, 32, [12, 6, 4, 10], 128, 128),     # two bins: 16, 32
-    (4, 16, [5, 2, 3, 6], 127, 127), (4, 16, [5, 2, 3, 6], 191, 191),                                         # one bin
+# Each number of registers a node of full bins can lie in, by all five methods at once and by one alone, and the columns in registers where cells
+# have to be searched.  Which form a size takes is a fitted cost: test_fake_device.py looks that these tests leave none out.
+@pytest.mark.parametrize("gpn,batch,quota,n_nodes,n,searched", [
+    (8, 16, [6, 3, 2, 5], 23, 7, False), (8, 16, [6, 3, 2, 5], 47, 7, False), (8, 16, [6, 3, 2, 5], 113, 301, False),   # two bins: 8, 16, 32 registers
+    (8, 8, [3, 2, 1, 2], 39, 7, False), (8, 8, [3, 2, 1, 2], 79, 7, False), (8, 8, [3, 2, 1, 2], 255, 301, False),      # one bin
+    (4, 32, [12, 6, 4, 10], 51, 7, False), (4, 32, [12, 6, 4, 10], 113, 301, False),                                    # two bins: 16, 32
+    (4, 16, [5, 2, 3, 6], 99, 7, False), (4, 16, [5, 2, 3, 6], 255, 301, False),                                        # one bin
+    (8, 16, [6, 3, 2, 5], 19, 7, True), (8, 4, [1, 1, 1, 1], 35, 7, True),
 ])
-def test_forms_of_full_bins(gpn, batch, quota, nodes_all, nodes_alone):
-    import torch
-    n = 6 * torch.cuda.get_device_properties(0).multi_processor_count + 1
-    check_all(CUM, ENDS, batch, gpn, gpn * nodes_all, quota, seed=nodes_all, n=n, first=5)
+def test_forms_of_full_bins(gpn, batch, quota, n_nodes, n, searched):
+    cum = SPIKE if searched else CUM
+    check_all(cum, ENDS, batch, gpn, gpn * n_nodes, quota, seed=n_nodes, n=n, first=5)
     for method in LOCAL:
-        check(CUM, ENDS, method, batch, gpn, gpn * nodes_alone, quota, seed=7 * nodes_alone, n=n, first=1 << 40)
+        check(cum, ENDS, method, batch, gpn, gpn * n_nodes, quota, seed=7 * n_nodes, n=n, first=1 << 40)
 
 
 @pytest.mark.parametrize("kind", ["gaps", "spike", "rare_tail", "wide_strata", "one_length"])
