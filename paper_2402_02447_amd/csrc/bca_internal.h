@@ -140,7 +140,10 @@ enum : uint32_t {
 // Work items up to which the pipelined launch finishes itself instead of having k_finish behind it.  Measured, fused step, fp32
 // (k_finish / itself): 20 K elements 9.0 / 7.8 us, 1 M 13.3 / 12.8, 3 M 24.8 / 24.4, 8 M 51.1 / 50.9, 16 M 85.3 / 86.1.
 constexpr uint32_t kSelfFinishItems = 8192;
-constexpr uint32_t kFewItems = 128;  // up to here its workgroups count themselves in a single word
+// Up to here its workgroups count themselves in a single word, which saves a round trip as long as the increments, one after the other, take
+// no longer.  One word / kDoneSlots of them and one more, us a step (fp32): 53 items 7.4 / 7.8, 104 7.8 / 8.1, 146 8.5 / 8.0, 208 9.2 / 8.2, 314
+// 10.4 / 8.5, 1 040 19.3 / 10.1.
+constexpr uint32_t kFewItems = 128;
 // Work items of k_step: kind in bits 30..31; kItemAdam: apply-table chunk in bits 0..28 and kItemEarly; kItemNorm: first
 // norm-table chunk in bits 0..27 and the number of consecutive chunks minus one in bits 28..29; kItemEmpty: bucket.
 constexpr uint32_t kItemNorm = 0u, kItemAdam = 1u, kItemEmpty = 2u;
@@ -194,9 +197,10 @@ constexpr uint32_t kLambHeldNum = 3, kLambHeldDen = 4;
 // Of a tensor that is too large to be held, the end is (as many items as a held tensor may have) if it has at least kLambEndsFrom
 // times as many: the tail kernel then has so much less to read again.  lamb_step works on the ends last, when nobody else needs
 // their slots; bucket_clip_lamb, whose order is the buckets', holds them only if at most a quarter of the slots' items follow.
-// Without / with the ends, us, lamb_step and bucket_clip_lamb: BERT-Base (word embedding 1 908 items) 616 / 603 and 583 / 570 (fp16), BERT-Large 1 847 /
-// 1 833 and 1 743 / 1 732, thirty tensors of 1 M and one of 28 M 350 / 339 and 379 / 369; with ends of two thirds 608 and 576.  Embedding in the middle:
-// 614 / 604 and 569 / 572 (hence the second rule); tensors of 10 to 16 M 288 / 292 and 327 / 329 alone, 317 / 308 and 357 / 347 behind
+// Without / with the ends, us, lamb_step and bucket_clip_lamb, in turn and in both orders: BERT-Base (word embedding 1 908 items, fp16) 574 / 566 and
+// 578 / 570, BERT-Large (fp32) 1 844 / 1 833 and 1 960 / 1 950, thirty tensors of 1 M and one of 28 M, the large one first, 347 / 342 and 377 / 368,
+// last 348 / 343 and (not held) 386 / 387; ends of two thirds gain less (8 and 7 us where these gained 13).  Embedding in the middle and held by both
+// calls: 614 / 604 and 569 / 572 (hence the second rule); tensors of 10 to 16 M 288 / 292 and 327 / 329 alone, 317 / 308 and 357 / 347 behind
 // the clip (hence the first one, which both calls share).
 constexpr uint32_t kLambEndsFrom = 2;
 // Plans go in one pass from this many elements on, and if at least half of them are in held tensors.  Below, the chain of

@@ -1006,24 +1006,6 @@ __device__ __forceinline__ bool wait_for_bucket(const StepState& st, uint32_t b,
   return sh.flag != 0u;
 }
 
-// A squared-norm item (kind kItemNorm, idx = chunk of the norm table) or the
-// stand-in for a bucket without elements (kItemEmpty, idx = bucket).  The last
-// workgroup of a bucket to get here adds the bucket's partials in the fixed
-// order of k_finalize, writes norm and coefficient and publishes the ready word.
-//
-// Why the last arriver sees every partial.  A partial is written by an agent-scope
-// atomic store, which on this target is a write-through store that is acknowledged
-// once it has reached the level at which the whole device is coherent; the storing
-// wavefront then waits for that acknowledgement (vmcnt(0)) *before* the workgroup
-// barrier, so when thread 0 counts the workgroup's arrival (after the barrier) all
-// four partials of the chunk are visible to any agent-scope load.  Read-modify-write
-// operations on arrived[b] are totally ordered; the workgroup whose increment makes the
-// count complete therefore runs after every other arrival, hence after every partial
-// of the bucket became visible, and its own loads of the partials (agent scope: they
-// do not hit lines a per-XCD L2 may still hold from an earlier call) are issued only
-// after its increment has returned.  A workgroup-scope release fence would not do: on
-// this target it does not wait for vector stores, so the arrival could be counted
-// while a partial is still on its way.
 // A thread's share of the sum of partials [lo, hi) of a bucket, in k_finalize's order: thread t adds partials lo + t, lo + t + 256, ...
 // one after the other.  The loads are issued eight at a time before the first addition (this workgroup is the one everybody else is
 // waiting for, and an agent-scope load that misses every cache takes a microsecond or two); a slot past the end adds +0.0, which
@@ -1057,7 +1039,24 @@ __device__ __forceinline__ void publish_bucket(const StepState& st, uint32_t b, 
   __hip_atomic_store(&st.ready[b], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The tail of every squared-norm item.  `stored` chunks' partials of bucket b have just been written by this
+// The tail of every squared-norm item (kItemNorm, or kItemEmpty, the stand-in for a bucket without elements).  The last workgroup of a
+// bucket to get here adds the bucket's partials in the fixed order of k_finalize, writes norm and coefficient and publishes the ready word.
+//
+// Why the last arriver sees every partial.  A partial is written by an agent-scope
+// atomic store, which on this target is a write-through store that is acknowledged
+// once it has reached the level at which the whole device is coherent; the storing
+// wavefront then waits for that acknowledgement (vmcnt(0)) *before* the workgroup
+// barrier, so when thread 0 counts the workgroup's arrival (after the barrier) all
+// four partials of the chunk are visible to any agent-scope load.  Read-modify-write
+// operations on arrived[b] are totally ordered; the workgroup whose increment makes the
+// count complete therefore runs after every other arrival, hence after every partial
+// of the bucket became visible, and its own loads of the partials (agent scope: they
+// do not hit lines a per-XCD L2 may still hold from an earlier call) are issued only
+// after its increment has returned.  A workgroup-scope release fence would not do: on
+// this target it does not wait for vector stores, so the arrival could be counted
+// while a partial is still on its way.
+//
+// `stored` chunks' partials of bucket b have just been written by this
 // workgroup (0: a bucket without elements, nothing to count): waits for them, counts the arrival, and if
 // this workgroup completes the bucket, finalizes it and publishes the ready word.
 __device__ __forceinline__ void norm_arrive(const StepState& st, uint32_t b, uint32_t stored, uint32_t epoch,
@@ -1113,7 +1112,8 @@ __device__ __forceinline__ void norm_item(const StepState& st, uint32_t kind, ui
 }
 
 // A squared-norm item where the launch is a chain of round trips to memory and little else (EARLY).  What finalizing the bucket takes is
-// fetched beside the gradients, and a bucket of one chunk needs no exchange with other workgroups.
+// fetched beside the gradients, and a bucket of one chunk needs no exchange with other workgroups.  Others exchange their partials as in
+// norm_arrive, for whose reasons the stores, the wait, the barrier and the count come in this order.
 template <int GDT>
 __device__ __forceinline__ void norm_item_short(const StepState& st, uint32_t idx, uint32_t count, uint32_t epoch,
                                                 const float* __restrict__ thresholds, float* __restrict__ norms,
@@ -1136,8 +1136,8 @@ __device__ __forceinline__ void norm_item_short(const StepState& st, uint32_t id
     if (++c == idx + count) break;
     en = read_entry(&st.norm_tab[c]);
   }
-  wait_vmem();  // and so on as in norm_arrive
-  __syncthreads();
+  wait_vmem();      // the partials have been acknowledged ...
+  __syncthreads();  // ... for every wavefront of the workgroup: only now is the arrival counted
   if (tid == 0) {
     const bool last = atomicAdd(&st.arrived[b], count) + count == total;
     if (last) ctl_store(&st.arrived[b], 0u);
@@ -1223,8 +1223,9 @@ __device__ __forceinline__ bool last_done(const StepState& st, uint32_t n_work, 
 }
 
 // SELF: the launch needs no k_finish behind it.  Every workgroup is counted once its item is decided, and the one that
-// completes the count does what k_finish would.  Adam items are counted when their wait has ended, before they load
-// anything, so that the round trip is hidden behind the item itself.
+// completes the count does what k_finish would.  Adam items are counted when their wait has ended and before they store
+// anything, so that the round trip is hidden behind the item itself.  That is early enough: the workgroup that completes the count
+// touches nothing but the items that were filed, whose owners return without a store, and the call's state.
 // EARLY: for lists with items that load before they wait (kItemEarly); eight workgroups a compute unit even so.
 template <int GDT, bool WB, uint32_t U, bool TICKETS, bool LAMB, bool SELF = false, bool EARLY = SELF>
 __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, const uint32_t* __restrict__ work, uint32_t n_work,

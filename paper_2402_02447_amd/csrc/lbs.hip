@@ -1103,6 +1103,8 @@ __global__ __launch_bounds__(kBlock, WHOLE && LG > 0 ? (LG == 3 ? 4 : 5) : 6) vo
 // 2 100 and the sort 2 600).  100 000 trials of 1 024 GPUs x 16, nodes of 8, all five methods: 3 093 us before (every generator output made twice,
 // 8 registers), 2 240 with 8 registers, 2 006 with 16, 1 769 with 32; snake alone, 24 414 trials, 514 -> 341.  Which number of
 // registers, and where one node at a time is better, Cost says.
+//   The registers that so many workgroups a compute unit leave (96 and 80) are a few too few for some: <5, 3, 2, true>, whose time is above, spills
+// four a lane, <5, 3, 1, true> ten, <5, 3, 1, false> three, <5, 2, 2, true> and <4, 3, 1, true> two, the others none.
 template <int LG, int CB, int BINS>
 constexpr uint32_t kNodesAtOnce = (1u << LG) * (BINS == 2 ? 1u : 2u);  // nodes a wavefront takes at a time
 
