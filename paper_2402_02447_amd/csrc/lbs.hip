@@ -816,6 +816,8 @@ __global__ __launch_bounds__(kBlock, E <= 1 ? 6 : E == 2 ? 5 : E == 4 ? 4 : E ==
 // wavefront sorts 2^LG nodes (BINS == 1: twice as many) at a time: 15 of the 21 stages (nodes of 8) then pair registers of one lane, at
 // 2 instead of 5 cycles an entry, and a row is mirrored by naming its registers backwards.  Needs as many nodes as
 // that, else lanes would idle.  LG == 0: any power of two up to 16; a bin lies in the 64 lanes, one node at a time.
+//   Workgroups a compute unit: six, but for all five methods with eight columns a lane five (99 registers at four of them; 12 000 trials of 64 nodes of 8,
+// cells to be searched: at four 383 us, five 347, six 341; 30 nodes in one bin 191, 172, 175).
 //   Measured (20 000 trials of 1 024 GPUs x 16, nodes of 8): snake alone 420 us (k_lbs_local 637), nodes of 4: 476 (1168 all five).  Bins that
 // are full go by k_lbs_nodes where there are many nodes; those with padding, datasets with flagged entries, other node sizes and few nodes
 // stay here.  Five methods, 24 414 trials of 128 nodes of 8: one node at a time 796 us, columns in registers 613 (792 before the two kinds of
@@ -908,7 +910,7 @@ __device__ __forceinline__ uint32_t column_sums(uint32_t (&x)[1 << LG], const ui
 }
 
 template <int LG, int BINS, bool WHOLE>
-__global__ __launch_bounds__(kBlock, WHOLE && LG > 0 ? (LG == 3 ? 4 : 5) : 6) void k_lbs_bins(const Params P, const Bins L, const uint32_t method,
+__global__ __launch_bounds__(kBlock, WHOLE && LG == 3 ? 5 : 6) void k_lbs_bins(const Params P, const Bins L, const uint32_t method,
                                                          const uint32_t* __restrict__ cum, const uint32_t* __restrict__ guide,
                                                          uint32_t* trial_min, uint32_t* trial_max, unsigned long long* sums) {
   extern __shared__ uint32_t s_dyn[];  // histogram, guide tables; WHOLE: the trial's own histogram, one word per GPU
@@ -1360,7 +1362,7 @@ enum Form : uint32_t { kOneNode, kColumns, kNodes8, kNodes16, kNodes32, kForms }
 // fit on the chip at a time, what the last turn leaves idle.  A trial is a wavefront's rounds of `at_once` nodes (BINS == 1: pairs) at `each` (ns,
 // whole chip), and a share of that for wavefronts without one in the last round, which weigh more where it is the only one.
 //   Fitted to 4 180 runs, five methods at once and one alone, in every form: nodes of 4 and 8 in one and in two full bins, 2 to 256 nodes, 200
-// to 100 000 trials.  The form taken is 0.3 and 0.4 % slower than the fastest of them on average (one method, all five).  Why the number of trials counts: 30
+// to 100 000 trials (bins with padding and cells that have to be searched, nodes of 8 and five methods at once: 540 more).  The form taken is 0.3 and 0.4 % slower than the fastest of them on average (one method, all five).  Why the number of trials counts: 30
 // nodes of 4, batch 16, snake alone, us, columns / 16 registers: 1 700 trials 28.1 / 33.4 (eight workgroups a compute unit against six), 30 000
 // 115.5 / 140.3, where so few nodes leave three wavefronts idle; 64 such nodes: 16 000 trials 111.2 / 124.8, 100 000 613 / 511.
 struct Cost {
@@ -1369,19 +1371,21 @@ struct Cost {
   bool two;    // bins
   uint32_t grid, n_cus;
   double trials;  // per workgroup
-  bool whole;
+  bool whole, searched;
   double us(Form form) const {
     struct Entry {
       uint32_t at_once, resident;  // workgroups a compute unit
       double turn, trial, each;
     };
     static constexpr Entry one[] = {{1, 8, 0.58, 0.35, 0.2}, {8, 7, 1.7, 0.5, 1.3}, {8, 7, 1.3, 0.38, 1.11}, {16, 7, 2.0, 0.43, 1.77}, {32, 5, 3.2, 0.32, 3.31}};
-    static constexpr Entry all[] = {{1, 6, 0.69, 1.2, 0.21}, {8, 4, 3.0, 1.2, 1.4}, {8, 6, 1.4, 1.8, 1.02}, {16, 6, 2.55, 1.55, 1.86}, {32, 5, 5.3, 2.37, 3.31}};
+    static constexpr Entry all[] = {{1, 6, 0.69, 1.2, 0.21}, {8, 5, 3.7, 1.56, 1.18}, {8, 6, 1.4, 1.8, 1.02}, {16, 6, 2.55, 1.55, 1.86}, {32, 5, 5.3, 2.37, 3.31}};
     Entry e = (whole ? all : one)[form];
     if (gpn == 4u) {
-      if (form == kColumns) e = whole ? Entry{4, two ? 5u : 6u, 1.16, 1.02, 0.73} : Entry{4, 8, 0.75, 0.18, 0.74};
+      if (form == kColumns) e = whole ? Entry{4, 6, 1.16, 1.02, 0.73} : Entry{4, 8, 0.75, 0.18, 0.74};
       if (form == kNodes16) e.resident = 6;
       if (form == kNodes32 && !whole && !two) e.resident = 6;
+    } else if (whole && searched) {  // cells that have to be searched
+      e = form == kOneNode ? Entry{1, 6, 0.89, 0.96, 0.32} : Entry{8, 5, 5.0, 1.6, 2.3};
     }
     const uint32_t rounds = (n + e.at_once - 1u) / e.at_once, turns = (rounds + kWaves - 1u) / kWaves, idle = turns * kWaves - rounds;
     const double trial = e.trial + e.each * (rounds + idle * (turns == 1u ? (whole ? 0.25 : 0.29) : (whole ? 0.21 : 0.05)));
@@ -1393,7 +1397,7 @@ Form pick_form(const Bins& B, const Params& P, uint32_t grid, uint32_t n_cus, bo
   const uint32_t gpn = P.gpus_per_node, n_nodes = P.n_gpus / gpn;
   if (gpn != 4u && gpn != 8u) return kOneNode;
   nodes = nodes && B.padded == 0 && P.flagged == 0;
-  const Cost c{B.count == 2 ? n_nodes : (n_nodes + 1u) / 2u, gpn, B.count == 2, grid, n_cus, (double)P.n_trials / grid, whole};
+  const Cost c{B.count == 2 ? n_nodes : (n_nodes + 1u) / 2u, gpn, B.count == 2, grid, n_cus, (double)P.n_trials / grid, whole, P.flagged != 0};
   Form best = kOneNode;
   double least = c.us(kOneNode);
   for (uint32_t f = kColumns; f < (nodes ? kForms : kNodes8); ++f) {

@@ -177,24 +177,28 @@ for kind, n in ((b"k_lbs_nodes", 20), (b"k_lbs_bins", 12)):
 
 
 def test_the_form_of_a_run_is_not_one_that_was_measured_slower(device):
-    """Nodes of 4 and 8 in full bins on 256 compute units: sizes at which the forms differ by a tenth and more (us beside them)."""
+    """Nodes of 4 and 8 on 256 compute units, full bins and a histogram whose cells have to be searched: sizes at which the forms differ, most by a
+    tenth and more (us beside them)."""
     out = fake_device.run(device, """
-cum, ends = W.length_histogram_piecewise_uniform(), W.LENGTH_STRATUM_END
-quota = {(8, 16): [6, 3, 2, 5], (8, 8): [3, 2, 1, 2], (4, 16): [5, 2, 3, 6], (4, 32): [12, 6, 4, 10]}
-with lbs.Dataset(cum, ends, device=0) as ds:
-    for gpn, batch, nodes, n, alone, good in [
-            (4, 16, 30, 30000, True, ["bins 2"]),                   # 116; one node at a time 136, 16 registers 140
-            (4, 16, 30, 1700, True, ["bins 0", "bins 2"]),          # 30, 28; 33
-            (4, 16, 64, 1700, True, ["bins 2"]),                    # 29; 33, 34
-            (4, 16, 64, 16000, True, ["bins 2"]),                   # 111; 128, 125
-            (4, 16, 64, 100000, True, ["nodes 4"]),                 # 511; 713, columns 613
-            (8, 16, 30, 16000, True, ["bins 3", "nodes 3"]),        # 115, 113; 123, 16 registers 128
-            (8, 8, 60, 16000, True, ["bins 3", "nodes 3"]),
-            (8, 16, 128, 1000, True, ["nodes 4", "nodes 5"]),       # 26, 23; columns 31
-            (8, 16, 20, 1100, False, ["bins 0", "nodes 3"]),        # 25; columns 30
-            (8, 8, 30, 1200, False, ["bins 0", "nodes 3"]),
-            (4, 32, 18, 1300, False, ["bins 0", "nodes 4"]),        # 28, 28; columns 34
-            (8, 16, 128, 100000, False, ["nodes 5"])]:              # 1770; 16 registers 2006
+ends, quota = W.LENGTH_STRATUM_END, {(8, 16): [6, 3, 2, 5], (8, 8): [3, 2, 1, 2], (4, 16): [5, 2, 3, 6], (4, 32): [12, 6, 4, 10]}
+plain, searched = W.length_histogram_piecewise_uniform(), np.concatenate([[0], np.cumsum((1e6 / (1 + np.arange(512.)) ** 2 + 1).astype(np.int64))])
+for cum, cases in ((searched, [
+        (8, 8, 30, 12000, False, ["bins 0"]),                   # 154; columns 172
+        (8, 16, 16, 12000, False, ["bins 0"]),                  # 156; columns 173
+        (8, 16, 64, 12000, False, ["bins 3"])]), (plain, [      # 347; 354
+        (4, 16, 30, 30000, True, ["bins 2"]),                   # 116; one node at a time 136, 16 registers 140
+        (4, 16, 30, 1700, True, ["bins 0", "bins 2"]),          # 30, 28; 33
+        (4, 16, 64, 1700, True, ["bins 2"]),                    # 29; 33, 34
+        (4, 16, 64, 16000, True, ["bins 2"]),                   # 111; 128, 125
+        (4, 16, 64, 100000, True, ["nodes 4"]),                 # 511; 713, columns 613
+        (8, 16, 30, 16000, True, ["bins 3", "nodes 3"]),        # 115, 113; 123, 16 registers 128
+        (8, 8, 60, 16000, True, ["bins 3", "nodes 3"]),
+        (8, 16, 128, 1000, True, ["nodes 4", "nodes 5"]),       # 26, 23; columns 31
+        (8, 16, 20, 1100, False, ["bins 0", "nodes 3"]),        # 25; columns 30
+        (8, 8, 30, 1200, False, ["bins 0", "nodes 3"]),
+        (8, 16, 128, 100000, False, ["nodes 5"])])):             # 1770; 16 registers 2006
+    with lbs.Dataset(cum, ends, device=0) as ds:
+      for gpn, batch, nodes, n, alone, good in cases:
         kernels()
         if alone:
             ds.lbs_simulate(lbs.LBS_LOCAL_SNAKE, batch, gpn, gpn * nodes, quota[gpn, batch], 1, n, 4096)

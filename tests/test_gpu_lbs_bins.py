@@ -59,7 +59,7 @@ def test_full_bins_by_number_of_nodes(gpn, batch, quota, nodes):
     (8, 8, [3, 2, 1, 2], 39, 7, False), (8, 8, [3, 2, 1, 2], 79, 7, False), (8, 8, [3, 2, 1, 2], 255, 301, False),      # one bin
     (4, 32, [12, 6, 4, 10], 51, 7, False), (4, 32, [12, 6, 4, 10], 113, 301, False),                                    # two bins: 16, 32
     (4, 16, [5, 2, 3, 6], 99, 7, False), (4, 16, [5, 2, 3, 6], 255, 301, False),                                        # one bin
-    (8, 16, [6, 3, 2, 5], 19, 7, True), (8, 4, [1, 1, 1, 1], 35, 7, True),
+    (8, 16, [6, 3, 2, 5], 27, 7, True), (8, 4, [1, 1, 1, 1], 51, 7, True),
 ])
 def test_forms_of_full_bins(gpn, batch, quota, n_nodes, n, searched):
     cum = SPIKE if searched else CUM
