@@ -652,11 +652,15 @@ __device__ __forceinline__ void whole_deal(const Params& P, const uint32_t* s_cn
   }
 }
 
-// Minima and maxima of a trial, one for every row of 16 lanes, double-buffered by the parity of the workgroup's trial count.
-constexpr uint32_t kRows = 4u * kWaves;
+// Minima and maxima of a trial, one for every 32 lanes.  BUFFERS == 2: in turn by the parity of the workgroup's trial count; trials of all five methods
+// have a barrier between one's reading and the next one's filing, and need one.  Kept small: with 8 000 simulated GPUs 960 bytes more made three
+// workgroups a compute unit two (12 000 trials of 250 nodes of 32, batch 4: 1 891 -> 2 326 us).
+constexpr uint32_t kRows = 2u * kWaves;
+template <uint32_t BUFFERS>
 struct FinishAll {
-  uint32_t lo[2][kMethods][kRows], hi[2][kMethods][kRows];
+  uint32_t lo[BUFFERS][kMethods][kRows], hi[BUFFERS][kMethods][kRows];
 };
+static_assert(sizeof(FinishAll<1>) <= 320);
 
 // Minimum and maximum over each row of 16 lanes, in all of its lanes.
 __device__ __forceinline__ void row_min_max(uint32_t& lo, uint32_t& hi) {
@@ -669,16 +673,20 @@ __device__ __forceinline__ void row_min_max(uint32_t& lo, uint32_t& hi) {
 }
 
 // Files the minimum and maximum that the wavefront's lanes have seen of method q.
-__device__ __forceinline__ void file_min_max(FinishAll& fin, uint32_t buf, uint32_t q, uint32_t lo, uint32_t hi) {
+template <uint32_t BUFFERS>
+__device__ __forceinline__ void file_min_max(FinishAll<BUFFERS>& fin, uint32_t buf, uint32_t q, uint32_t lo, uint32_t hi) {
   row_min_max(lo, hi);
+  // rows 0 and 2 to rows 1 and 3
+  lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, 0x142, 0xa, 0xf, false));
+  hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, 0x142, 0xa, 0xf, false));
   const uint32_t tid = threadIdx.x;
-  if ((tid & 15u) == 0) fin.lo[buf][q][tid >> 4] = lo, fin.hi[buf][q][tid >> 4] = hi;
+  if ((tid & 31u) == 16u) fin.lo[buf][q][tid >> 5] = lo, fin.hi[buf][q][tid >> 5] = hi;
 }
 
 // A trial's results from what has been filed in the first ROWS places: thread 2 q stores method q's minimum, thread 2 q + 1 its
 // maximum, and adds it to the workgroup's sums.  all: the five methods, else `method` alone.
-template <uint32_t ROWS = kRows>
-__device__ __forceinline__ void finish_methods(const Params& P, const FinishAll& fin, unsigned long long* s_sum, uint32_t buf, uint32_t t,
+template <uint32_t ROWS = kRows, uint32_t BUFFERS>
+__device__ __forceinline__ void finish_methods(const Params& P, const FinishAll<BUFFERS>& fin, unsigned long long* s_sum, uint32_t buf, uint32_t t,
                                                bool all, uint32_t method, uint32_t* trial_min, uint32_t* trial_max) {
   const uint32_t tid = threadIdx.x, m = tid >> 1;
   if (tid >= 2u * kMethods || (!all && m != method)) return;
@@ -702,13 +710,13 @@ __device__ __forceinline__ void finish_methods(const Params& P, const FinishAll&
 // k_lbs_local<E, true>; a GPU's own draws are local_batch consecutive entries, added up by a butterfly over the low lane
 // bits.  Needs gpus_per_node and local_batch to be powers of two (<= 32 and <= 64).
 template <int E>
-__global__ __launch_bounds__(kBlock, E <= 1 ? 6 : E == 2 ? 5 : E == 4 ? 4 : E == 8 ? 3 : 2) void k_lbs_all(const Params P, const uint32_t* __restrict__ cum,
+__global__ __launch_bounds__(kBlock, E <= 2 ? 6 : E == 4 ? 4 : E == 8 ? 3 : 2) void k_lbs_all(const Params P, const uint32_t* __restrict__ cum,
                                                      const uint32_t* __restrict__ guide, uint32_t* trial_min,
                                                      uint32_t* trial_max, unsigned long long* sums) {
   extern __shared__ uint32_t s_dyn[];  // histogram, all guide tables, the trial's own histogram, one word per GPU
   __shared__ uint32_t s_scan[2][kWaves];
   __shared__ uint32_t s_base;
-  __shared__ FinishAll s_fin;
+  __shared__ FinishAll<1> s_fin;
   __shared__ unsigned long long s_sum[2u * kMethods];  // the workgroup's share of the sums: thread i keeps sum i
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
   if (tid < 2u * kMethods) s_sum[tid] = 0ull;
@@ -737,8 +745,7 @@ __global__ __launch_bounds__(kBlock, E <= 1 ? 6 : E == 2 ? 5 : E == 4 ? 4 : E ==
   const uint32_t gpn_bit = (uint32_t)__ffs((int)P.gpus_per_node) - 1u, batch_bit = (uint32_t)__ffs((int)P.local_batch) - 1u;
   const bool halves = P.local_batch * P.max_len < 65536u;
 
-  for (uint32_t t = blockIdx.x, round = 0; t < P.n_trials; t += gridDim.x, ++round) {
-    const uint32_t buf = round & 1u;
+  for (uint32_t t = blockIdx.x; t < P.n_trials; t += gridDim.x) {
     uint32_t lo[kMethods], hi[kMethods];
 #pragma unroll
     for (uint32_t q = 0; q < kMethods; ++q) lo[q] = 0xffffffffu, hi[q] = 0u;
@@ -794,9 +801,9 @@ __global__ __launch_bounds__(kBlock, E <= 1 ? 6 : E == 2 ? 5 : E == 4 ? 4 : E ==
     whole_deal(P, s_cnt, s_gpu, &s_base, s_scan, lo[LBS_GLOBAL], hi[LBS_GLOBAL]);
     // ---- the trial's five results
 #pragma unroll
-    for (uint32_t q = 0; q < kMethods; ++q) file_min_max(s_fin, buf, q, lo[q], hi[q]);
+    for (uint32_t q = 0; q < kMethods; ++q) file_min_max(s_fin, 0u, q, lo[q], hi[q]);
     __syncthreads();  // also: this trial's last reads of s_cnt and s_gpu lie before the next trial's clearing
-    finish_methods(P, s_fin, s_sum, buf, t, true, 0u, trial_min, trial_max);
+    finish_methods(P, s_fin, s_sum, 0u, t, true, 0u, trial_min, trial_max);
   }
   if (tid < 2u * kMethods) atomicAdd(&sums[tid], s_sum[tid]);
 }
@@ -916,7 +923,7 @@ __global__ __launch_bounds__(kBlock, WHOLE && LG == 3 ? 5 : 6) void k_lbs_bins(c
   extern __shared__ uint32_t s_dyn[];  // histogram, guide tables; WHOLE: the trial's own histogram, one word per GPU
   __shared__ uint32_t s_scan[2][kWaves];
   __shared__ uint32_t s_base;
-  __shared__ FinishAll s_fin;
+  __shared__ FinishAll<WHOLE ? 1 : 2> s_fin;
   __shared__ unsigned long long s_sum[2u * kMethods];
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -957,7 +964,7 @@ __global__ __launch_bounds__(kBlock, WHOLE && LG == 3 ? 5 : 6) void k_lbs_bins(c
   const uint64_t next_column = (uint64_t)P.local_batch * kGamma;
 
   for (uint32_t t = blockIdx.x, round = 0; t < P.n_trials; t += gridDim.x, ++round) {
-    const uint32_t buf = round & 1u;
+    const uint32_t buf = WHOLE ? 0u : round & 1u;
     const uint64_t k_trial = (P.first_trial + t) * (uint64_t)pool_all;
     if (WHOLE) {
       whole_clear(P, s_cnt, s_gpu, &s_base);
@@ -1072,8 +1079,8 @@ __global__ __launch_bounds__(kBlock, WHOLE && LG == 3 ? 5 : 6) void k_lbs_bins(c
         const uint32_t q = which == 0u ? LBS_STRATIFIED : which == 1u ? LBS_LOCAL_SNAKE : which == 2u ? LBS_LOCAL_RASTER : LBS_NONE;
         // One method alone: one place a wavefront, as a trial of a node or two is hardly longer than its end (one node of 8, batch 16, 400 000
         // trials: 276 us, with four places a wavefront 293).
-        if (WHOLE ? i < 4u : i == 0u && which < 3u) {
-          const uint32_t at = WHOLE ? wave * 4u + i : wave;
+        if (WHOLE ? i < 2u : i == 0u && which < 3u) {
+          const uint32_t at = WHOLE ? wave * 2u + i : wave;
           s_fin.lo[buf][q][at] = lo[m], s_fin.hi[buf][q][at] = hi[m];
         }
       }
@@ -1113,13 +1120,14 @@ constexpr uint32_t kNodesAtOnce = (1u << LG) * (BINS == 2 ? 1u : 2u);  // nodes 
 constexpr uint32_t kCountWords = 1028;  // a trial's histogram: lengths 0 .. LBS_MAX_LEN
 static_assert(kCountWords > LBS_MAX_LEN && kCountWords % 4 == 0);
 typedef const __attribute__((address_space(3))) uint32_t lds_word;
+template <bool WHOLE>
 struct NodesShared {
   unsigned long long sum[2u * kMethods];
-  FinishAll fin;
+  FinishAll<WHOLE ? 1 : 2> fin;
   uint32_t scan[2][kWaves];
   uint32_t base, unused;
 };
-static_assert(sizeof(NodesShared) % 8 == 0);
+static_assert(sizeof(NodesShared<false>) % 8 == 0 && sizeof(NodesShared<true>) % 8 == 0);
 
 struct Rows {  // row r of bin h: base | stratum << 16 | slot << 24 (see Bins)
   uint32_t row[2][16];
@@ -1196,8 +1204,8 @@ __global__ __launch_bounds__(kBlock, LG == 5 ? 5 : 6) void k_lbs_nodes(
   uint32_t* s_strata = s_dyn + kStrata;
   uint32_t* s_cnt = s_dyn + kCnt;
   const uint32_t strata_words = P.guide_words - (WHOLE ? kWholeGuideSize : 0u);
-  NodesShared& sh = *reinterpret_cast<NodesShared*>(s_strata + strata_words);
-  uint32_t* s_gpu = s_strata + strata_words + sizeof(NodesShared) / sizeof(uint32_t);
+  NodesShared<WHOLE>& sh = *reinterpret_cast<NodesShared<WHOLE>*>(s_strata + strata_words);
+  uint32_t* s_gpu = s_strata + strata_words + sizeof(NodesShared<WHOLE>) / sizeof(uint32_t);
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid < 2u * kMethods) sh.sum[tid] = 0ull;
@@ -1228,7 +1236,7 @@ __global__ __launch_bounds__(kBlock, LG == 5 ? 5 : 6) void k_lbs_nodes(
     for (uint32_t r = 0; r < ROWS; ++r) rows[h][r] = L.row[h][r];
 
   for (uint32_t t = blockIdx.x, round = 0; t < P.n_trials; t += gridDim.x, ++round) {
-    const uint32_t buf = round & 1u;
+    const uint32_t buf = WHOLE ? 0u : round & 1u;
     const uint64_t k_trial = (P.first_trial + t) * (uint64_t)pool_all;
     if (WHOLE) {
       whole_clear(P, s_cnt, s_gpu, &sh.base);
@@ -1420,7 +1428,7 @@ auto bins_kernel(const Bins& L, const Params& P, Form form) {
 // Dynamic LDS of k_lbs_nodes, in bytes.
 template <bool WHOLE>
 size_t nodes_lds(const Params& P) {
-  return sizeof(NodesShared) + sizeof(uint32_t) * ((size_t)P.guide_words + (WHOLE ? kCountWords + P.n_gpus : 0u));
+  return sizeof(NodesShared<WHOLE>) + sizeof(uint32_t) * ((size_t)P.guide_words + (WHOLE ? kCountWords + P.n_gpus : 0u));
 }
 
 // k_lbs_nodes for a run that takes one of its forms; L: its rows.
