@@ -1370,8 +1370,9 @@ enum Form : uint32_t { kOneNode, kColumns, kNodes8, kNodes16, kNodes32, kForms }
 // fit on the chip at a time, what the last turn leaves idle.  A trial is a wavefront's rounds of `at_once` nodes (BINS == 1: pairs) at `each` (ns,
 // whole chip), and a share of that for wavefronts without one in the last round, which weigh more where it is the only one.
 //   Fitted to 4 180 runs, five methods at once and one alone, in every form: nodes of 4 and 8 in one and in two full bins, 2 to 256 nodes, 200
-// to 100 000 trials (bins with padding and cells that have to be searched, nodes of 8 and five methods at once: 540 more).  The form taken is 0.3 and 0.4 % slower than the fastest of them on average (one method, all five).  Why the number of trials counts: 30
-// nodes of 4, batch 16, snake alone, us, columns / 16 registers: 1 700 trials 28.1 / 33.4 (eight workgroups a compute unit against six), 30 000
+// to 100 000 trials (bins with padding and cells that have to be searched, nodes of 8 and five methods at once: 540 more).  The form
+// taken is 0.3 and 0.4 % slower than the fastest of them on average (one method, all five).  Why the number of trials counts: 30 nodes of 4,
+// batch 16, snake alone, us, columns / 16 registers: 1 700 trials 28.1 / 33.4 (eight workgroups a compute unit against six), 30 000
 // 115.5 / 140.3, where so few nodes leave three wavefronts idle; 64 such nodes: 16 000 trials 111.2 / 124.8, 100 000 613 / 511.
 struct Cost {
   uint32_t n;  // nodes, or pairs of nodes
