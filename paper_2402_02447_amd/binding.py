@@ -206,7 +206,7 @@ def alg1_thresholds(c: float, n_buckets: int) -> np.ndarray:
 
 def bucket_clip_flat(g, n: int, grad_dtype: int, threshold, norm=None, coef=None, status=None, stream=None) -> None:
     """bucket_clip_flat: clip one contiguous bucket in place; no plan, no allocation (see bca.h)."""
-    L = _lib or load_library()
+    L = _lib if _lib is not None else load_library()
     _check(_calls.bucket_clip_flat(L.calls_table, g, int(n), grad_dtype, threshold, norm, coef, status, stream))
 
 
