@@ -329,10 +329,38 @@ __device__ __forceinline__ uint32_t vector_head(uint32_t len, uint64_t p, uint64
 
 // ---- wavefront reduction (fixed order) ----------------------------------------
 
+// Sums by butterfly, distances 32, 16, 8, 4, 2, 1.  Lanes meet by permlane swaps (32, 16) and by DPP rotations inside rows of 16:
+// with the value 8 lanes on already added, rotating by 4 brings the one 4 lanes across, and so on down.  Every one of these launches
+// ends in a chain of such sums, and a move is a vector instruction where a shuffle is a trip through LDS: three buckets of 17 K
+// elements 6.01 -> 5.88 us a fused step, LAMB on 335 M elements (two sums a chunk) 1 862 -> 1 850.
+__device__ __forceinline__ double join(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); }
+// Rows 2, 3 of a and rows 0, 1 of b change places, then the two are added: lanes 0 .. 31 hold the sums of a's lanes 32 apart, lanes
+// 32 .. 63 those of b's.  add16: the same with the odd rows of a, the even rows of b and lanes 16 apart.
+__device__ __forceinline__ double add32(double a, double b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return join(lo[0], hi[0]) + join(lo[1], hi[1]);
+}
+__device__ __forceinline__ double add16(double a, double b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return join(lo[0], hi[0]) + join(lo[1], hi[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double add_rotated(double a) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, CTRL, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, false);
+  return a + join(lo, hi);
+}
+__device__ __forceinline__ double row_sum(double x) {
+  return add_rotated<0x121>(add_rotated<0x122>(add_rotated<0x124>(add_rotated<0x128>(x))));  // row_ror by 8, 4, 2, 1
+}
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+  x = add32(x, x);
+  return row_sum(add16(x, x));
 }
 
 // ---- squared-norm partials ------------------------------------------------------
