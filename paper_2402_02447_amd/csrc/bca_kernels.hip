@@ -1349,8 +1349,7 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
 // workgroups wait until its last one is through, so the slots of half a tensor idle on average: larger items
 // beat smaller ones although those stream better (335 M elements in tensors of 4 M: 8 chunks an item 1.83 ms, 12 with
 // part of u in LDS 1.67; in tensors of 1 M: 1.58 and 1.64; two sweeps in runs 2.05).
-//   BERT-Large, fp32: lamb_step 2085 -> 1875 us (two sweeps in runs before); with bf16 gradients 2017 -> 1743,
-// bucket_clip_lamb 2088 -> 1752; BERT-Base, fp16, behind clipping 695 -> 588.
+//   BERT-Large, fp32: lamb_step 2085 us in two sweeps in runs, 1748 like this; BERT-Base, fp16, behind clipping 695 and 534.
 //
 // Sums are taken chunk by chunk and added in k_lamb_trust's order: results are those of the two sweeps bit for bit (where
 // the gradients do not lie at the parameters' alignment, up to the grouping of the sums' fp32 terms).
@@ -1467,8 +1466,11 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
     f32x4* mv = reinterpret_cast<f32x4*>(ip->m);
     f32x4* vv = reinterpret_cast<f32x4*>(ip->v);
     const bool keep = (flags & kLambKeep) != 0u && !held, wb = WB && coef != 1.f;
-    const auto sweep = [&](auto full) {
-    constexpr bool FULL = decltype(full)::value;
+    // Whether the moments stay cached is decided out here, a sweep for each: with the two kinds of store in the arms of one branch the compiler
+    // makes one store of them, without the streaming hint (BERT-Large lamb_step 1 848 us like that, 1 748 so; BERT-Base fp16 behind
+    // the clip 568 and 534).
+    const auto sweep = [&](auto full, auto kept) {
+    constexpr bool FULL = decltype(full)::value, KEEP = decltype(kept)::value;
 #pragma unroll
     for (uint32_t j = 0; j < CH; ++j)  // p stays in registers anyway: all of it is fetched at once
       if (FULL || j < count) P[j] = ldv<true>(pv + j * kBlock + tid);
@@ -1500,11 +1502,7 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
               pp = __fmaf_rn(P[j + q][i], P[j + q][i], pp), uu = __fmaf_rn(d, d, uu);
               m[q][i] = mi, v[q][i] = vi, u[i] = d;
             }
-            if (keep) {
-              stv<false>(mv + (j + q) * kBlock + tid, m[q]), stv<false>(vv + (j + q) * kBlock + tid, v[q]);
-            } else {
-              stv<true>(mv + (j + q) * kBlock + tid, m[q]), stv<true>(vv + (j + q) * kBlock + tid, v[q]);
-            }
+            stv<!KEEP>(mv + (j + q) * kBlock + tid, m[q]), stv<!KEEP>(vv + (j + q) * kBlock + tid, v[q]);
             if (wb)
               G::template store4<GNT>(reinterpret_cast<void*>(ga + (uint64_t)(j + q) * 1024u * sizeof(typename G::elem)), tid, g[q]);
             if (j + q < LD) sh.u[j + q < LD ? j + q : 0][tid] = u;
@@ -1517,8 +1515,9 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
       }
     }
     };
-    if (count == CH) sweep(std::true_type{});
-    else sweep(std::false_type{});
+    if (keep) sweep(std::false_type{}, std::true_type{});
+    else if (count == CH) sweep(std::true_type{}, std::false_type{});
+    else sweep(std::false_type{}, std::false_type{});
     __syncthreads();
     if (tid < 2u * count) {  // the four wavefronts' sums in index order; all in wavefront 0
       const uint32_t j = tid >> 1;
