@@ -216,7 +216,8 @@ int bca_plan_work_item(const bca_plan* plan, uint32_t i, uint32_t* kind, uint32_
  * bucket_clip_lamb (clip = 1).  bca_plan_num_lamb_items is 0 where that call goes in two sweeps, which also depends on
  * where the bound tensors lie.  Item i is kind 0 or 2 as above, or kind 1 = LAMB on `count` consecutive chunks of
  * BCA_TABLE_LAMB from `first` on, all of `tensor`; *held: 1 if they wait on the chip for that tensor's ratio, 0 if the
- * tensor is swept twice.  Any out pointer may be NULL.  BCA_ERR_RANGE for i out of range. */
+ * tensor is swept twice.  Eight items of twelve chunks side by side in one tensor and bucket are carried out
+ * together: each workgroup takes every eighth of their 96 chunks.  Any out pointer may be NULL.  BCA_ERR_RANGE for i out of range. */
 uint32_t bca_plan_num_lamb_items(const bca_plan* plan, int clip);
 int bca_plan_lamb_item(const bca_plan* plan, int clip, uint32_t i, uint32_t* kind, uint32_t* first, uint32_t* count,
                        uint32_t* tensor, uint32_t* held);

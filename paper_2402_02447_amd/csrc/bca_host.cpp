@@ -257,7 +257,8 @@ void mark_early(bca_plan* p, int n_cus) {
 
 // Items and work lists of LAMB in one pass (see k_lamb), for tables cut at kDefaultChunkApply.  `slots`: workgroups of
 // that kernel that are resident on the GPU at a time.
-//   An item is up to kLambItemChunks full chunks, or one short chunk.  Items are made in the order of the apply table (bucket
+//   An item is up to kLambItemChunks full chunks, or one short chunk; where a run is long enough its chunks are dealt to kLambStride items
+// at a time (kLambSpread).  Items are made in the order of the apply table (bucket
 // by bucket, as the segments lie), which is also the order in which they are worked on, so that a tensor's items
 // follow one another.
 void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& apply_to_lamb) {
@@ -275,19 +276,23 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     for (uint32_t c = A.bucket_off[g.first]; c < A.bucket_off[g.second];) {
       const ChunkInfo& head = A.chunks[c];
       uint32_t n = 1;
-      while (head.len == kDefaultChunkApply && n < kLambItemChunks && c + n < A.bucket_off[g.second]) {
+      while (head.len == kDefaultChunkApply && n < kLambStride * kLambItemChunks && c + n < A.bucket_off[g.second]) {
         const ChunkInfo& x = A.chunks[c + n];
         if (x.tensor != head.tensor || x.bucket != head.bucket || x.len != kDefaultChunkApply ||
             x.begin != head.begin + (uint64_t)n * kDefaultChunkApply)
           break;
         ++n;
       }
-      LambItem it = {};
-      it.first = apply_to_lamb[c], it.count = n, it.tensor = head.tensor, it.bucket = head.bucket;
-      const uint32_t index = (uint32_t)p->lamb_items.size();
-      if (p->lamb_items_of[it.tensor]++ == 0) first_item[it.tensor] = index;
-      last_item[it.tensor] = index;
-      p->lamb_items.push_back(it);
+      const bool spread = n == kLambStride * kLambItemChunks;
+      for (uint32_t done = 0, k = 0; done < n; done += kLambItemChunks, ++k) {
+        LambItem it = {};
+        it.first = apply_to_lamb[c] + (spread ? k : done), it.count = std::min(n - done, kLambItemChunks);
+        it.tensor = head.tensor, it.bucket = head.bucket, it.flags = spread ? kLambSpread | (k << kLambPlaceShift) : 0u;
+        const uint32_t index = (uint32_t)p->lamb_items.size();
+        if (p->lamb_items_of[it.tensor]++ == 0) first_item[it.tensor] = index;
+        last_item[it.tensor] = index;
+        p->lamb_items.push_back(it);
+      }
       c += n;
     }
     group_end.push_back((uint32_t)p->lamb_items.size());
@@ -908,7 +913,8 @@ int bca_plan_lamb_item(const bca_plan* p, int clip, uint32_t i, uint32_t* kind, 
   if (kind) *kind = k;
   if (k == kItemAdam) {
     const LambItem& it = p->lamb_items[item & 0x3fffffffu];
-    if (first) *first = it.first;
+    // of items that share a run, each is listed with as many consecutive chunks as it has
+    if (first) *first = it.first + (it.flags >> kLambPlaceShift) * (kLambItemChunks - 1u);
     if (count) *count = it.count;
     if (tensor) *tensor = it.tensor;
     if (held) *held = (it.flags & (clip ? kLambHeld : kLambHeld | kLambHeldAlone)) ? 1u : 0u;

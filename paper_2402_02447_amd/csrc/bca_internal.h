@@ -187,6 +187,12 @@ constexpr uint32_t kLambRegular = 2u;  // full chunks only, and 16-byte vectors 
 constexpr uint32_t kLambHeld = 4u;     // p and u stay on the chip until the tensor's ratio is known
 constexpr uint32_t kLambKeep = 8u;     // moments are stored cacheable: the tail kernel reads them again
 constexpr uint32_t kLambHeldAlone = 16u;  // as kLambHeld, in lamb_step only
+// kLambSpread: the item's chunks are not consecutive ones but kLambStride apart, so that what it has in flight lies 32 KiB apart.  Items of
+// consecutive chunks read 4 to 16 KiB in a piece, from as many places as there are workgroups, and the memory system is slow at that.  Probe
+// of the held sweep (334 M elements, 4 reads and 3 writes, twelve chunks an item, four fetched at a time), ms by stride: 1 1.73, 2 1.67, 4 1.61,
+// 6 1.69, 8 1.55, 12 1.70, 16 1.58, 24 1.64, 32 1.69, 40 1.75, 64 1.71, 1024 2.0.  In runs of kLambStride * kLambItemChunks full
+// chunks; what is left of a tensor or bucket goes in items of consecutive chunks.
+constexpr uint32_t kLambSpread = 32u, kLambStride = 8, kLambPlaceShift = 8;  // from that bit on: which of its run's items it is
 // Workgroups of k_lamb that are resident at a time on a compute unit: what __launch_bounds__ asks for (128 VGPRs), and four
 // times the 33 KiB of LDS fit in 160 KiB.
 constexpr uint32_t kLambResidentPerCu = 4;

@@ -1349,7 +1349,10 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
 // workgroups wait until its last one is through, so the slots of half a tensor idle on average: larger items
 // beat smaller ones although those stream better (335 M elements in tensors of 4 M: 8 chunks an item 1.83 ms, 12 with
 // part of u in LDS 1.67; in tensors of 1 M: 1.58 and 1.64; two sweeps in runs 2.05).
-//   BERT-Large, fp32: lamb_step 2085 us in two sweeps in runs, 1748 like this; BERT-Base, fp16, behind clipping 695 and 534.
+// An item's chunks lie kLambStride apart where the tensor is long enough, and four of them are fetched at a time: BERT-Large lamb_step
+// 1 748 us with items of consecutive chunks, two at a time; consecutive, four at a time 1 731; kLambStride apart, two 1 685, four 1 675;
+// BERT-Base, fp16, behind clipping 534, 533, 524 and 520.
+//   BERT-Large, fp32: lamb_step 2085 us in two sweeps in runs, 1675 like this; BERT-Base, fp16, behind clipping 695 and 520.
 //
 // Sums are taken chunk by chunk and added in k_lamb_trust's order: results are those of the two sweeps bit for bit (where
 // the gradients do not lie at the parameters' alignment, up to the grouping of the sums' fp32 terms).
@@ -1446,16 +1449,19 @@ __device__ __forceinline__ bool wait_for_tensor(const StepState& st, const LambS
   return false;
 }
 
+// Chunks of the tensor-major table from one chunk of an item to the next.
+__device__ __forceinline__ uint32_t lamb_stride(uint32_t flags) { return (flags & kLambSpread) ? kLambStride : 1u; }
+
 // One item: moments, sums, arrival, ratio; HOLD: then the wait and the update of a held item.
 template <int GDT, bool CLIP, bool WB, bool HOLD>
 __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& ls, const LambItem* __restrict__ ip, uint32_t self,
                                           float coef, const AdamK& k, uint32_t epoch, LambShared& sh) {
   typedef Grad<GDT> G;
-  constexpr uint32_t CH = kLambItemChunks, LD = 2 * CH / 3, B = 2;  // chunks; those whose u is in LDS; chunks loaded at a time
+  constexpr uint32_t CH = kLambItemChunks, LD = 2 * CH / 3, B = WB ? 2 : 4;  // chunks; those whose u is in LDS; chunks loaded at a time (with write-back, four spill)
   constexpr bool GNT = !CLIP;  // behind clipping the gradients are in cache
   const uint32_t tid = threadIdx.x;
   const uint32_t first = ip->first, count = ip->count, t = ip->tensor, flags = ip->flags;
-  const uint32_t items = ip->items, lo = ip->lo, hi = ip->hi;
+  const uint32_t items = ip->items, lo = ip->lo, hi = ip->hi, S = lamb_stride(flags);
   const bool regular = HOLD && (flags & kLambRegular) != 0u;
   const bool held = HOLD && (flags & (CLIP ? kLambHeld : kLambHeld | kLambHeldAlone)) != 0u;
   const float wd = (flags & kChunkNoDecay) ? 0.f : k.wd;
@@ -1473,18 +1479,19 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
     constexpr bool FULL = decltype(full)::value, KEEP = decltype(kept)::value;
 #pragma unroll
     for (uint32_t j = 0; j < CH; ++j)  // p stays in registers anyway: all of it is fetched at once
-      if (FULL || j < count) P[j] = ldv<true>(pv + j * kBlock + tid);
+      if (FULL || j < count) P[j] = ldv<true>(pv + j * S * kBlock + tid);
     loads_issued();
 #pragma unroll
     for (uint32_t j = 0; j < CH; j += B) {
       if (FULL || j < count) {
         f32x4 g[B], m[B], v[B];
+        float pp[B] = {}, uu[B] = {};
 #pragma unroll
         for (uint32_t q = 0; q < B; ++q) {
           if (FULL || j + q < count) {
-            g[q] = G::template load4<GNT>(reinterpret_cast<const void*>(ga + (uint64_t)(j + q) * 1024u * sizeof(typename G::elem)), tid);
-            m[q] = ldv<true>(mv + (j + q) * kBlock + tid);
-            v[q] = ldv<true>(vv + (j + q) * kBlock + tid);
+            g[q] = G::template load4<GNT>(reinterpret_cast<const void*>(ga + (uint64_t)((j + q) * S) * 1024u * sizeof(typename G::elem)), tid);
+            m[q] = ldv<true>(mv + (j + q) * S * kBlock + tid);
+            v[q] = ldv<true>(vv + (j + q) * S * kBlock + tid);
           }
         }
         loads_issued();
@@ -1492,24 +1499,27 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
         for (uint32_t q = 0; q < B; ++q) {
           if (FULL || j + q < count) {
             if constexpr (CLIP) g[q] = g[q] * coef;
-            float pp = 0.f, uu = 0.f;
             f32x4 u;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               float mi = m[q][i], vi = v[q][i];
               adam_moments(g[q][i], mi, vi, k);
               const float d = adam_direction(P[j + q][i], mi, vi, k, wd);
-              pp = __fmaf_rn(P[j + q][i], P[j + q][i], pp), uu = __fmaf_rn(d, d, uu);
+              pp[q] = __fmaf_rn(P[j + q][i], P[j + q][i], pp[q]), uu[q] = __fmaf_rn(d, d, uu[q]);
               m[q][i] = mi, v[q][i] = vi, u[i] = d;
             }
-            stv<!KEEP>(mv + (j + q) * kBlock + tid, m[q]), stv<!KEEP>(vv + (j + q) * kBlock + tid, v[q]);
+            stv<!KEEP>(mv + (j + q) * S * kBlock + tid, m[q]), stv<!KEEP>(vv + (j + q) * S * kBlock + tid, v[q]);
             if (wb)
-              G::template store4<GNT>(reinterpret_cast<void*>(ga + (uint64_t)(j + q) * 1024u * sizeof(typename G::elem)), tid, g[q]);
+              G::template store4<GNT>(reinterpret_cast<void*>(ga + (uint64_t)((j + q) * S) * 1024u * sizeof(typename G::elem)), tid, g[q]);
             if (j + q < LD) sh.u[j + q < LD ? j + q : 0][tid] = u;
             else U[j + q < LD ? 0 : j + q - LD] = u;
-            const double wpp = wave_sum((double)pp), wuu = wave_sum((double)uu);
-            if ((tid & 63u) == 0) sh.pp[j + q][tid >> 6] = wpp, sh.uu[j + q][tid >> 6] = wuu;
           }
+        }
+        // two chunks' sums at a time, each as wave_sum adds it up; rows 0 .. 3: p^2 of chunk q, of q + 1, u^2 of chunk q, of q + 1
+#pragma unroll
+        for (uint32_t q = 0; q < B; q += 2) {
+          const double w = row_sum(add16(add32((double)pp[q], (double)uu[q]), add32((double)pp[q + 1], (double)uu[q + 1])));
+          if ((tid & 15u) == 0) ((tid & 32u) ? sh.uu : sh.pp)[j + q + ((tid >> 4) & 1u)][tid >> 6] = w;
         }
         loads_issued();
       }
@@ -1522,13 +1532,13 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
     if (tid < 2u * count) {  // the four wavefronts' sums in index order; all in wavefront 0
       const uint32_t j = tid >> 1;
       const double* w = (tid & 1u) ? sh.uu[j] : sh.pp[j];
-      __hip_atomic_store(&ls.sums[(uint64_t)(first + j) * 2u + (tid & 1u)], ((w[0] + w[1]) + w[2]) + w[3], __ATOMIC_RELAXED,
+      __hip_atomic_store(&ls.sums[(uint64_t)(first + j * S) * 2u + (tid & 1u)], ((w[0] + w[1]) + w[2]) + w[3], __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     }
   } else {
     for (uint32_t j = 0; j < count; ++j) {
-      lamb_moments_chunk<GDT, CLIP, WB, GNT, false, true>(read_entry(&ls.tab[first + j]), coef, k, sh.step.pp, sh.step.uu,
-                                                          ls.sums + (uint64_t)(first + j) * 2u);
+      lamb_moments_chunk<GDT, CLIP, WB, GNT, false, true>(read_entry(&ls.tab[first + j * S]), coef, k, sh.step.pp, sh.step.uu,
+                                                          ls.sums + (uint64_t)(first + j * S) * 2u);
       __syncthreads();  // sh.step.pp / uu are reused by the next chunk
     }
   }
@@ -1562,12 +1572,12 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
         f32x4 x;
 #pragma unroll
         for (int i = 0; i < 4; ++i) x[i] = __fmaf_rn(sc, u[i], P[j][i]);
-        stv<true>(pv + j * kBlock + tid, x);
+        stv<true>(pv + j * S * kBlock + tid, x);
       }
     }
   } else {
     // every thread reads back the elements that it has stored itself
-    for (uint32_t j = 0; j < count; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j]), sc, k);
+    for (uint32_t j = 0; j < count; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j * S]), sc, k);
   }
 }
 
@@ -1631,8 +1641,8 @@ __global__ __launch_bounds__(kBlock) void k_lamb_tail(StepState st, LambState ls
   const auto update = [&](uint32_t i, uint32_t from, uint32_t to) {  // chunks [from, to) of item i
     const LambItem* ip = &ls.items[i];
     const float sc = __uint_as_float((uint32_t)ls.ready[ip->tensor]);
-    const uint32_t first = ip->first, end = min(to, ip->count);
-    for (uint32_t j = from; j < end; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j]), sc, k);
+    const uint32_t first = ip->first, S = lamb_stride(ip->flags), end = min(to, ip->count);
+    for (uint32_t j = from; j < end; ++j) lamb_update_chunk(read_entry(&ls.tab[first + j * S]), sc, k);
   };
   const uint32_t back = w / kLambItemChunks, chunk = w % kLambItemChunks;
   if (back < ls.first_end - ls.first_large) update(ls.first_end - 1u - back, chunk, chunk + 1u);
