@@ -596,6 +596,7 @@ Launch make_launch(const bca_plan* p, uint32_t requested, uint32_t n_chunks, boo
   L.staged = (p->tune_flags & BCA_TUNE_STAGE_TABLE_LDS) != 0;
   L.g_keep = g_keep;
   L.lds = g_keep ? 0 : p->adam_lds_reserve;  // grouped sweeps read g from cache and are fastest at full occupancy
+  L.order = AdamOrder::kTable;
   return L;
 }
 
@@ -1159,8 +1160,9 @@ int adam_step(bca_plan* p, const bca_adam* hp, uint64_t step, void* stream) {
   if (int rc = enqueue_hyper(p, (hipStream_t)stream)) return rc;
   const Table& T = p->apply_tab;
   const uint32_t n = (uint32_t)T.chunks.size();
-  hipError_t e = launch_adam(p->grad_dtype, T.d_chunks, 0, n, nullptr, false, nullptr, k,
-                             make_launch(p, p->grid_apply, n, false), (hipStream_t)stream);
+  Launch L = make_launch(p, p->grid_apply, n, false);
+  if (T.chunk_elems == kDefaultChunkApply && n >= kXcdRunsFrom) L.order = AdamOrder::kXcdRuns;
+  hipError_t e = launch_adam(p->grad_dtype, T.d_chunks, 0, n, nullptr, false, nullptr, k, L, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(e, "launching the Adam kernel");
   return BCA_OK;
 }
@@ -1229,9 +1231,10 @@ int bucket_clip_adam(bca_plan* p, const float* thresholds, const bca_adam* hp, u
       e = launch_whole_coef(p->d_bucket_sq, p->n_buckets, thresholds, nm + p->n_buckets, cf, st, s);
     if (e != hipSuccess) return fail_hip(e, "launching the finalize kernel");
     if (ev) (void)hipEventRecord(*ev++, s);
+    Launch L = make_launch(p, p->grid_apply, na, keep);
+    if (n_groups == 1) L.order = AdamOrder::kBackwards;
     e = launch_adam(p->grad_dtype, TA.d_chunks, ca0, na, cf, (flags & BCA_WRITE_BACK_GRADS) != 0,
-                    (flags & BCA_SKIP_STEP_ON_NONFINITE) ? st : nullptr,
-                    k, make_launch(p, p->grid_apply, na, keep), s);
+                    (flags & BCA_SKIP_STEP_ON_NONFINITE) ? st : nullptr, k, L, s);
     if (e != hipSuccess) return fail_hip(e, "launching the Adam kernel");
     if (ev) (void)hipEventRecord(*ev++, s);
     first = false;

@@ -745,17 +745,28 @@ __device__ __forceinline__ void adam_chunk_early(const Entry& en, const AdamK& k
   if (WB && c != 1.f) G::template store4<false>(gv, tid, g);
 }
 
+// Which chunk the i-th workgroup of one per chunk takes (AdamOrder).
+__device__ __forceinline__ uint32_t adam_chunk_of(uint32_t i, uint32_t n, AdamOrder order) {
+  if (order == AdamOrder::kBackwards) return n - 1u - i;
+  const uint32_t at = i % (8u * kXcdRun), base = i - at;
+  if (order == AdamOrder::kXcdRuns && n - base >= 8u * kXcdRun) return base + (at % 8u) * kXcdRun + at / 8u;
+  return i;
+}
+
 template <int GDT, bool FUSED, bool WB, uint32_t U, bool GNT, bool STAGED>
 __global__ __launch_bounds__(kBlock) void k_adam(const Chunk* __restrict__ table, uint32_t c0, uint32_t n,
                                                   const float* __restrict__ coefs, const int32_t* skip_status,
-                                                  const AdamK ka) {
+                                                  const AdamK ka, AdamOrder order) {
   if (skip_status != nullptr && (*skip_status & BCA_STATUS_NONFINITE)) return;
   const AdamK k = resolve(ka);
-  for_each_chunk<STAGED>(table, c0, n, [&](const Entry& en, uint32_t) {
+  const auto sweep = [&](const Entry& en, uint32_t) {
     float coef = 1.f;
     if constexpr (FUSED) coef = coefs[en.bucket];
     adam_chunk<GDT, FUSED, WB, U, GNT>(en, coef, k);
-  });
+  };
+  if constexpr (STAGED) for_each_chunk<STAGED>(table, c0, n, sweep);
+  else if (gridDim.x == n) sweep(read_entry(&table[c0 + adam_chunk_of(blockIdx.x, n, order)]), 0);
+  else for_each_chunk<STAGED>(table, c0, n, sweep);
 }
 
 // ---- LAMB -------------------------------------------------------------------------
@@ -2033,16 +2044,16 @@ hipError_t launch_scale(int gdt, const Chunk* table, uint32_t c0, uint32_t n, co
 
 template <int GDT, uint32_t U, bool GNT, bool ST>
 static void launch_adam_t(const Chunk* table, uint32_t c0, uint32_t n, const float* coefs, bool write_back,
-                          const int32_t* skip_status, const AdamK& k, uint32_t grid, uint32_t lds, hipStream_t stream) {
+                          const int32_t* skip_status, const AdamK& k, const Launch& L, hipStream_t stream) {
   if (coefs == nullptr)
-    hipLaunchKernelGGL((k_adam<GDT, false, false, U, GNT, ST>), dim3(grid), dim3(kBlock), lds, stream, table, c0, n,
-                       coefs, skip_status, k);
+    hipLaunchKernelGGL((k_adam<GDT, false, false, U, GNT, ST>), dim3(L.grid), dim3(kBlock), L.lds, stream, table, c0, n,
+                       coefs, skip_status, k, L.order);
   else if (!write_back)
-    hipLaunchKernelGGL((k_adam<GDT, true, false, U, GNT, ST>), dim3(grid), dim3(kBlock), lds, stream, table, c0, n,
-                       coefs, skip_status, k);
+    hipLaunchKernelGGL((k_adam<GDT, true, false, U, GNT, ST>), dim3(L.grid), dim3(kBlock), L.lds, stream, table, c0, n,
+                       coefs, skip_status, k, L.order);
   else
-    hipLaunchKernelGGL((k_adam<GDT, true, true, U, GNT, ST>), dim3(grid), dim3(kBlock), lds, stream, table, c0, n,
-                       coefs, skip_status, k);
+    hipLaunchKernelGGL((k_adam<GDT, true, true, U, GNT, ST>), dim3(L.grid), dim3(kBlock), L.lds, stream, table, c0, n,
+                       coefs, skip_status, k, L.order);
 }
 
 hipError_t launch_adam(int gdt, const Chunk* table, uint32_t c0, uint32_t n, const float* coefs, bool write_back,
@@ -2053,8 +2064,7 @@ hipError_t launch_adam(int gdt, const Chunk* table, uint32_t c0, uint32_t n, con
     pick2(!L.g_keep, L.staged, [&](auto gnt, auto st) {
       constexpr bool GNT = decltype(gnt)::value, ST = decltype(st)::value;
       pick_gdt(gdt, [&](auto gd) {
-        launch_adam_t<decltype(gd)::value, U, GNT, ST>(table, c0, n, coefs, write_back, skip_status, k, L.grid, L.lds,
-                                                       stream);
+        launch_adam_t<decltype(gd)::value, U, GNT, ST>(table, c0, n, coefs, write_back, skip_status, k, L, stream);
       });
     });
   });
