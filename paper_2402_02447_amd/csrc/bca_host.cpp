@@ -679,6 +679,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
   }
   if (chunk_norm == 0) chunk_norm = kDefaultChunkNorm;
   build_table(&p->norm_tab, chunk_norm, n_buckets, bucket_seg_off, segments);
+  for (uint32_t b = 0; b < n_buckets; ++b) p->n_filled += p->norm_tab.bucket_off[b] != p->norm_tab.bucket_off[b + 1] ? 1u : 0u;
   if (p->norm_tab.chunks.size() >= (1ull << 28))
     return fail(BCA_ERR_RANGE, "too many squared-norm chunks; raise chunk_norm");
   build_table(&p->apply_tab, chunk_apply, n_buckets, bucket_seg_off, segments);
@@ -1220,17 +1221,23 @@ int bucket_clip_adam(bca_plan* p, const float* thresholds, const bca_adam* hp, u
     const Table& TA = p->apply_tab;
     const uint32_t cn0 = TN.bucket_off[b0], nn = TN.bucket_off[b1] - cn0;
     const uint32_t ca0 = TA.bucket_off[b0], na = TA.bucket_off[b1] - ca0;
-    // the first squared-norm launch of a call also clears the status word
-    hipError_t e = launch_sqnorm(p->grad_dtype, TN.d_chunks, cn0, nn, p->d_partials, first ? st : nullptr,
-                                 make_launch(p, norm_grid(p, nn), nn, keep), s);
-    if (e != hipSuccess) return fail_hip(e, "launching the squared-norm kernel");
-    if (ev) (void)hipEventRecord(*ev++, s);
-    e = launch_finalize(p->d_partials, TN.d_bucket_off, b0, b1, whole ? nullptr : thresholds, nm, cf, st,
-                        whole ? p->d_bucket_sq : nullptr, s);
-    if (e == hipSuccess && whole)
-      e = launch_whole_coef(p->d_bucket_sq, p->n_buckets, thresholds, nm + p->n_buckets, cf, st, s);
-    if (e != hipSuccess) return fail_hip(e, "launching the finalize kernel");
-    if (ev) (void)hipEventRecord(*ev++, s);
+    hipError_t e = hipSuccess;
+    if (skip && !multi && nn <= kOneLaunchNormChunks) {
+      e = launch_norms(p->grad_dtype, step_state(p), nn, p->n_buckets, p->n_filled, whole, thresholds, nm, cf, p->d_bucket_sq, st, s);
+      if (e != hipSuccess) return fail_hip(e, "launching the norms kernel");
+    } else {
+      // the first squared-norm launch of a call also clears the status word
+      e = launch_sqnorm(p->grad_dtype, TN.d_chunks, cn0, nn, p->d_partials, first ? st : nullptr,
+                        make_launch(p, norm_grid(p, nn), nn, keep), s);
+      if (e != hipSuccess) return fail_hip(e, "launching the squared-norm kernel");
+      if (ev) (void)hipEventRecord(*ev++, s);
+      e = launch_finalize(p->d_partials, TN.d_bucket_off, b0, b1, whole ? nullptr : thresholds, nm, cf, st,
+                          whole ? p->d_bucket_sq : nullptr, s);
+      if (e == hipSuccess && whole)
+        e = launch_whole_coef(p->d_bucket_sq, p->n_buckets, thresholds, nm + p->n_buckets, cf, st, s);
+      if (e != hipSuccess) return fail_hip(e, "launching the finalize kernel");
+      if (ev) (void)hipEventRecord(*ev++, s);
+    }
     Launch L = make_launch(p, p->grid_apply, na, keep);
     if (n_groups == 1) L.order = AdamOrder::kBackwards;
     e = launch_adam(p->grad_dtype, TA.d_chunks, ca0, na, cf, (flags & BCA_WRITE_BACK_GRADS) != 0,

@@ -118,6 +118,11 @@ enum class AdamOrder : uint32_t {
 constexpr uint32_t kXcdRun = 256, kXcdRunsFrom = 144u << 10;
 constexpr uint32_t kDefaultSpinLimit = 1u << 18;  // polls of a ready word before a waiting item gives up (about a second)
 
+// Squared-norm chunks (of 16 Ki elements) up to which a call that needs every norm first has them from one launch (k_norms).  It saves two
+// launches, which small calls wait for on the host; larger ones wait for the chain of exchanges inside instead.  Whole-gradient step, us, three
+// launches and the sweep / one and the sweep: 6 K to 130 K elements 15.0 / 9.5, 0.5 M 15.3 / 10.1, 0.4 M in one bucket 15.3 / 10.5, 1 M in one
+// 15.1 / 12.5, in four 15.0 / 12.8, 1.6 M (100 chunks) 15.4 / 15.4, 2 M 17.2 / 17.6, 2.4 M 19.7 / 20.3, BERT-Base 549 / 560.
+constexpr uint32_t kOneLaunchNormChunks = 64;
 // How a streaming kernel is launched.
 struct Launch {
   uint32_t grid;    // workgroups
@@ -153,7 +158,10 @@ enum : uint32_t {
   // k_step that finishes itself: workgroups whose item is decided, in kDoneSlots words and one that counts the full ones
   kCtlDone = kCtlLate + 96,
   kDoneSlots = 64,
-  kCtlWords = kCtlDone + 32 * (kDoneSlots + 1)
+  // k_norms: buckets that are done, and the status bits collected
+  kCtlNormsDone = kCtlDone + 32 * (kDoneSlots + 1),
+  kCtlNormsStatus = kCtlNormsDone + 32,
+  kCtlWords = kCtlNormsDone + 64
 };
 // Work items up to which the pipelined launch finishes itself instead of having k_finish behind it.  Measured, fused step, fp32
 // (k_finish / itself): 20 K elements 9.0 / 7.8 us, 1 M 13.3 / 12.8, 3 M 24.8 / 24.4, 8 M 51.1 / 50.9, 16 M 85.3 / 86.1.
@@ -294,6 +302,9 @@ hipError_t launch_sqnorm(int gdt, const Chunk* table, uint32_t c0, uint32_t n, d
 hipError_t launch_finalize(const double* partials, const uint32_t* bucket_chunk_off, uint32_t b0, uint32_t b1,
                            const float* thresholds, float* norms, float* coefs, int32_t* status, double* bucket_sq,
                            hipStream_t stream);
+// All norms and coefficients (whole: one coefficient for all buckets) of a plan of n squared-norm chunks in one launch.
+hipError_t launch_norms(int gdt, const StepState& st, uint32_t n, uint32_t n_buckets, uint32_t n_filled, bool whole, const float* thresholds,
+                        float* norms, float* coefs, double* bucket_sq, int32_t* status, hipStream_t stream);
 // One coefficient for all buckets from the whole-gradient norm and the single threshold *c.
 hipError_t launch_whole_coef(const double* bucket_sq, uint32_t n_buckets, const float* c, float* whole_norm,
                              float* coefs, int32_t* status, hipStream_t stream);
@@ -363,6 +374,7 @@ struct bca_plan {
   bca::AdamK* d_adamk = nullptr;  // the constants derived from them by k_hyper
   uint32_t tune_flags = 0;
   bool bound = false;
+  uint32_t n_filled = 0;  // buckets with elements
   std::vector<uint64_t> tensor_numel;
   bca::Table norm_tab, apply_tab;
   // LAMB: the fine cut again, tensor by tensor (chunks of tensor t are tensor_off[t] .. tensor_off[t+1]-1)

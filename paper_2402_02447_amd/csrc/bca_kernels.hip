@@ -1129,6 +1129,89 @@ __device__ __forceinline__ void store_partial(const StepState& st, uint32_t chun
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// All squared norms of a small plan in one launch, one workgroup per chunk, for calls that need every norm before any update (whole-gradient
+// clipping, the step that is skipped on Inf or NaN).  Partials are exchanged as norm_arrive does it, for its reasons; whichever workgroup
+// completes a bucket adds its partials up in k_finalize's order, and the one that completes the last bucket does what k_whole_coef does, hands
+// over the status bits and leaves the counters at zero.  Two launches fewer than k_sqnorm, k_finalize and k_whole_coef (one without
+// whole-gradient clipping), and the same bits; kOneLaunchNormChunks says where it pays.  n_filled: buckets with elements.
+template <int GDT>
+__global__ __launch_bounds__(kBlock) void k_norms(StepState st, uint32_t n, uint32_t n_buckets, uint32_t n_filled, bool whole,
+                                                   const float* __restrict__ thresholds, float* __restrict__ norms,
+                                                   float* __restrict__ coefs, double* __restrict__ bucket_sq, int32_t* status) {
+  __shared__ double s_w[kWaves];
+  __shared__ uint32_t s_last;
+  __shared__ float s_coef;
+  const uint32_t tid = threadIdx.x;
+  if (blockIdx.x == 0) {  // buckets without elements
+    int32_t bst = 0;
+    for (uint32_t b = tid; b < n_buckets; b += kBlock) {
+      if (st.norm_bucket_off[b] == st.norm_bucket_off[b + 1]) {
+        norms[b] = 0.f;
+        __hip_atomic_store(&bucket_sq[b], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!whole) coefs[b] = clip_coef(0.f, thresholds[b], bst);
+      }
+    }
+    if (bst != 0) ctl_or(&st.ctl[kCtlNormsStatus], (uint32_t)bst);
+  }
+  if (blockIdx.x < n) {
+    const Entry en = read_entry(&st.norm_tab[blockIdx.x]);
+    const uint32_t b = en.bucket, lo = st.norm_bucket_off[b], hi = st.norm_bucket_off[b + 1];
+    store_partial(st, blockIdx.x, sqnorm_chunk<GDT, true, 16>(en));
+    wait_vmem();      // the partials (and what has been stored above) have been acknowledged ...
+    __syncthreads();  // ... for every wavefront of the workgroup
+    if (tid == 0) {
+      const bool last = atomicAdd(&st.arrived[b], 1u) + 1u == hi - lo;
+      if (last) ctl_store(&st.arrived[b], 0u);  // left at zero for the next call
+      s_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last == 0u) return;
+    const double s = wave_sum(agent_partials(st, (uint64_t)lo * kWaves, (uint64_t)hi * kWaves));
+    if ((tid & 63u) == 0) s_w[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) {
+      const double tot = ((s_w[0] + s_w[1]) + s_w[2]) + s_w[3];
+      const float norm = (float)sqrt(tot);
+      int32_t bst = 0;
+      norms[b] = norm;
+      if (whole) __hip_atomic_store(&bucket_sq[b], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else coefs[b] = clip_coef(norm, thresholds[b], bst);
+      if (bst != 0) ctl_or(&st.ctl[kCtlNormsStatus], (uint32_t)bst);
+      wait_vmem();  // the sum and the bits have arrived before the bucket is counted
+      const bool last = atomicAdd(&st.ctl[kCtlNormsDone], 1u) + 1u == n_filled;
+      if (last) ctl_store(&st.ctl[kCtlNormsDone], 0u);
+      s_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last == 0u) return;
+  } else {  // a plan without elements: this is the only workgroup
+    wait_vmem();
+    __syncthreads();
+  }
+  if (whole) {
+    double s = 0.0;
+    for (uint32_t b = tid; b < n_buckets; b += kBlock)
+      s += __hip_atomic_load(&bucket_sq[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s = wave_sum(s);
+    if ((tid & 63u) == 0) s_w[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) {
+      const float norm = (float)sqrt(((s_w[0] + s_w[1]) + s_w[2]) + s_w[3]);
+      int32_t bst = 0;
+      s_coef = clip_coef(norm, thresholds[0], bst);
+      norms[n_buckets] = norm;
+      if (bst != 0) ctl_or(&st.ctl[kCtlNormsStatus], (uint32_t)bst);
+    }
+    __syncthreads();
+    for (uint32_t b = tid; b < n_buckets; b += kBlock) coefs[b] = s_coef;
+  }
+  if (tid == 0) {
+    wait_vmem();
+    *status = (int32_t)ctl_load(&st.ctl[kCtlNormsStatus]);
+    ctl_store(&st.ctl[kCtlNormsStatus], 0u);
+  }
+}
+
 // A squared-norm item of k_step: `count` consecutive chunks of the norm table (all of one bucket), first
 // chunk idx; or (kItemEmpty) the stand-in for bucket idx, which has no elements.  A chunk's partials are the
 // same whichever item it was part of.
@@ -2009,6 +2092,15 @@ hipError_t launch_finalize(const double* partials, const uint32_t* bucket_chunk_
   if (b1 <= b0) return hipSuccess;
   hipLaunchKernelGGL(k_finalize, dim3(b1 - b0), dim3(kBlock), 0, stream, partials, bucket_chunk_off, b0, thresholds,
                      norms, coefs, status, bucket_sq);
+  return hipGetLastError();
+}
+
+hipError_t launch_norms(int gdt, const StepState& st, uint32_t n, uint32_t n_buckets, uint32_t n_filled, bool whole, const float* thresholds,
+                        float* norms, float* coefs, double* bucket_sq, int32_t* status, hipStream_t stream) {
+  pick_gdt(gdt, [&](auto gd) {
+    hipLaunchKernelGGL((k_norms<decltype(gd)::value>), dim3(std::max(n, 1u)), dim3(kBlock), 0, stream, st, n, n_buckets, n_filled, whole,
+                       thresholds, norms, coefs, bucket_sq, status);
+  });
   return hipGetLastError();
 }
 
