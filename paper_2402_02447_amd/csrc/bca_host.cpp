@@ -1106,6 +1106,10 @@ int bucket_clip(bca_plan* p, uint32_t b0, uint32_t b1, const float* thresholds, 
   float* nm = norms ? norms : p->d_norms;
   float* cf = coefs ? coefs : p->d_coefs;
   int32_t* st = status ? status : p->d_status;
+  if (nn == 1 && b1 - b0 == 1 && !(p->tune_flags & BCA_TUNE_MULTI_LAUNCH)) {
+    const hipError_t e = launch_clip_one(p->grad_dtype, TN.d_chunks + cn0, 0, 0, thresholds + b0, nm + b0, cf + b0, st, s);
+    return e == hipSuccess ? (int)BCA_OK : fail_hip(e, "launching the clip kernel");
+  }
   uint32_t most = 0;  // chunks of the range's largest bucket
   for (uint32_t b = b0; b < b1; ++b) most = std::max(most, TN.bucket_off[b + 1] - TN.bucket_off[b]);
   // First launch: the squared-norm partials of the range's chunks (one workgroup per chunk: a single bucket has

@@ -328,6 +328,9 @@ hipError_t launch_step(int gdt, const StepState& st, const uint32_t* work, uint3
 hipError_t launch_clip_scale(int gdt, const Chunk* norm_tab, uint32_t cn0, uint32_t n, const uint32_t* bucket_chunk_off,
                              uint32_t b0, uint32_t b1, const double* partials, const float* thresholds, float* norms,
                              float* coefs, int32_t* status, hipStream_t stream);
+// bucket_clip of one bucket that is one squared-norm chunk: its table entry, or (tab == nullptr) n elements at g.
+hipError_t launch_clip_one(int gdt, const Chunk* tab, uint64_t g, uint32_t n, const float* threshold, float* norm, float* coef, int32_t* status,
+                           hipStream_t stream);
 hipError_t launch_copy(void* dst, const void* src, uint64_t nbytes, hipStream_t stream);
 
 // bucket_clip_flat: one contiguous bucket of n <= kFlatMaxElems elements at g, clipped in place with partial
