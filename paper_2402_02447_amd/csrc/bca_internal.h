@@ -100,7 +100,7 @@ constexpr uint64_t kLambGroupElems = 32ull << 20;
 // whole-gradient step 606 / 606 / 577 / 552 / 561 / 594; BERT-Large with three 1 618 and 1 669, with four 1 538 and 1 583.
 // The fused single-launch step does not gain from it (its items wait on each other) and does not use it.
 constexpr uint32_t kDefaultAdamLdsReserve = 36u << 10;
-// The order in which the workgroups of an Adam sweep, one per chunk, take the chunks.  Workgroups go round the eight XCDs.
+// The order in which an Adam sweep's workgroups take the chunks.  Workgroups, one per chunk, go round the eight XCDs.
 enum class AdamOrder : uint32_t {
   kTable,
   // Every XCD sweeps kXcdRun consecutive chunks (1 MiB of each array) of a run of eight times as many; what is left over in the table's
@@ -131,7 +131,7 @@ struct Launch {
   bool g_keep;      // gradients are loaded with the normal (cacheable) policy because they are read again soon
   uint32_t lds;     // Adam sweep (k_adam) only: bytes of LDS a workgroup reserves without using them, which caps
                     // how many workgroups a compute unit holds at once
-  AdamOrder order;  // Adam sweep with one workgroup per chunk only
+  AdamOrder order;  // Adam sweep without `staged`
 };
 
 // Device-side state of the pipelined launch (k_step, followed by its finish kernel).

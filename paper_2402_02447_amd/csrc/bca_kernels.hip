@@ -745,11 +745,12 @@ __device__ __forceinline__ void adam_chunk_early(const Entry& en, const AdamK& k
   if (WB && c != 1.f) G::template store4<false>(gv, tid, g);
 }
 
-// Which chunk the i-th workgroup of one per chunk takes (AdamOrder).
+// The chunk that comes i-th (AdamOrder).
 __device__ __forceinline__ uint32_t adam_chunk_of(uint32_t i, uint32_t n, AdamOrder order) {
+  if (order == AdamOrder::kTable) return i;
   if (order == AdamOrder::kBackwards) return n - 1u - i;
   const uint32_t at = i % (8u * kXcdRun), base = i - at;
-  if (order == AdamOrder::kXcdRuns && n - base >= 8u * kXcdRun) return base + (at % 8u) * kXcdRun + at / 8u;
+  if (n - base >= 8u * kXcdRun) return base + (at % 8u) * kXcdRun + at / 8u;
   return i;
 }
 
@@ -765,8 +766,8 @@ __global__ __launch_bounds__(kBlock) void k_adam(const Chunk* __restrict__ table
     adam_chunk<GDT, FUSED, WB, U, GNT>(en, coef, k);
   };
   if constexpr (STAGED) for_each_chunk<STAGED>(table, c0, n, sweep);
-  else if (gridDim.x == n) sweep(read_entry(&table[c0 + adam_chunk_of(blockIdx.x, n, order)]), 0);
-  else for_each_chunk<STAGED>(table, c0, n, sweep);
+  else
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) sweep(read_entry(&table[c0 + adam_chunk_of(i, n, order)]), 0);
 }
 
 // ---- LAMB -------------------------------------------------------------------------
