@@ -107,10 +107,10 @@ enum class AdamOrder : uint32_t {
   // order.  Pays in plans of kXcdRunsFrom chunks and more.  adam_step, us, table's order / runs, two cards, fp32: 20 M elements 84 / 89 and 84 / 89,
   // 57 M 258 / 263 and 257 / 262, 109 M 478 / 492 and 477 / 491, 135 M 587 / 596 and 588 / 600, 160 M 738 / 728 and 744 / 728, 200 M 944 / 875 and
   // 931 / 874, 250 M 1 202 / 1 132 and 1 196 / 1 130, 335 M 1 559 / 1 511 and 1 541 / 1 510; 160 M with packed gradients 744 / 720; fp16 135 M
-  // 557 / 566, 200 M 847 / 838; packed bf16 335 M 1 445 / 1 411.  Runs of 128, 320, 512 and 800 chunks instead of 256: 335 M 1 537, 1 533, 1 543,
-  // 1 548 (256: 1 520); of 16 to 64, in a probe, 15 % slower than the table's order.
+  // 557 / 566, 200 M 847 / 838; packed bf16 335 M 1 445 / 1 411.  Runs of 128, 512 and 800 chunks instead of 256: 335 M 1 537, 1 543, 1 548
+  // (256: 1 520); of 16 to 64, in a probe, 15 % slower than the table's order.
   kXcdRuns,
-  // Behind squared norms of everything: what was read last is the likeliest to be cached.  Whole-gradient step of BERT-Base, table's order /
+  // Behind squared norms of everything: what was read last is the likeliest to be cached.  Whole-gradient step of BERT-Base, three workgroups a compute unit, table's order /
   // backwards / runs of 256 / those backwards, us: 555 / 553 / 563 / 564, another card 570 / 558 / - / 561.  With four workgroups a compute unit,
   // against the table's order with three: 11 M elements 65.7 -> 63.9, 34 M 182 -> 179, BERT-Base 562 -> 544, BERT-Large 1 798 -> 1 753.
   kBackwards
