@@ -333,6 +333,12 @@ void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& 
     return kEnd;
   };
   for (uint32_t i = 0; i < p->lamb_items.size(); ++i) (void)part(i);
+  // A run that is swept in front and held at its end is dealt out in consecutive chunks: what an item has is held or not as it is listed.
+  for (uint32_t i = 0; i < p->lamb_items.size(); i += (p->lamb_items[i].flags & kLambSpread) ? kLambStride : 1u) {
+    LambItem* run = &p->lamb_items[i];
+    if (!(run->flags & kLambSpread) || part(i) == part(i + kLambStride - 1u)) continue;
+    for (uint32_t k = 0; k < kLambStride; ++k) run[k].first = run[0].first + k * kLambItemChunks, run[k].flags = 0u;
+  }
   std::vector<LambItem> sorted;
   std::vector<uint32_t> place(p->lamb_items.size());
   for (const int now : {kWhole, kSwept, kEnd}) {

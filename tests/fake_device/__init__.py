@@ -17,6 +17,7 @@ from paper_2402_02447_amd import lbs
 B.load_library()
 fake = ctypes.CDLL("libamdhip64.so.7")
 fake.fake_launch_name.restype = fake.fake_kernel_name.restype = ctypes.c_char_p
+fake.fake_launch_arg.restype = ctypes.c_void_p
 fake.fake_device_allocations.restype = fake.fake_device_frees.restype = ctypes.c_ulonglong
 
 def kernels():

@@ -19,6 +19,8 @@ std::map<const void*, std::string>& names() {
 struct Launch {
   const void* kernel;
   unsigned grid;
+  size_t lds;
+  std::vector<char> arg;
 };
 std::vector<Launch>& launches() {
   static std::vector<Launch> v;
@@ -26,6 +28,8 @@ std::vector<Launch>& launches() {
 }
 bool g_fail = false;
 unsigned long long g_mallocs = 0, g_frees = 0;
+std::string g_watched;  // kernels of whose argument number g_arg the first g_arg_bytes bytes are kept
+unsigned g_arg = 0, g_arg_bytes = 0;
 int g_cus = 256;
 size_t g_static_lds = 0;
 struct Config {
@@ -57,6 +61,9 @@ void fake_set_static_lds(unsigned n) { g_static_lds = n; }  // what every kernel
 unsigned fake_num_launches() { return (unsigned)launches().size(); }
 const char* fake_launch_name(unsigned i) { return names()[launches()[i].kernel].c_str(); }
 unsigned fake_launch_grid(unsigned i) { return launches()[i].grid; }
+unsigned fake_launch_lds(unsigned i) { return (unsigned)launches()[i].lds; }
+void fake_watch(const char* kernel, unsigned arg, unsigned n_bytes) { g_watched = kernel, g_arg = arg, g_arg_bytes = n_bytes; }
+const char* fake_launch_arg(unsigned i) { return launches()[i].arg.empty() ? nullptr : launches()[i].arg.data(); }
 unsigned fake_num_kernels() { return (unsigned)names().size(); }
 const char* fake_kernel_name(unsigned i) { return std::next(names().begin(), i)->second.c_str(); }  // every kernel the library has
 void fake_forget_launches() { launches().clear(); }
@@ -79,10 +86,12 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *grid = g_config.grid, *block = g_config.block, *lds = g_config.lds, *stream = g_config.stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t lds, hipStream_t) {
   const bool failing = g_fail;  // the note is the test's, not the library's
   g_fail = false;
-  launches().push_back({f, grid.x});
+  launches().push_back({f, grid.x, lds, {}});
+  if (g_arg_bytes != 0 && names()[f].find(g_watched) != std::string::npos)
+    launches().back().arg.assign((const char*)args[g_arg], (const char*)args[g_arg] + g_arg_bytes);
   g_fail = failing;
   return hipSuccess;
 }

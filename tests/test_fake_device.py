@@ -111,6 +111,47 @@ def test_lamb_goes_in_two_sweeps_where_slots_would_idle():
                     assert (seen == 1).all()
 
 
+def test_the_listed_items_of_lamb_are_those_of_the_kernel(device):
+    """k_lamb's own item table: every chunk is in it once and at its address, also where workgroups share a run of chunks, and the chunks that
+    wait on the chip are those that the plan lists as held.  Tensors that are held, and ones of which only the end is, which begins at an item's
+    distance from the last one, wherever that is in a run."""
+    fake_device.run(device, """
+SPREAD, HELD, ALONE, STATE = 32, 4, 16, np.dtype([("tab", "u8"), ("items", "u8"), ("rest", "u8", 6), ("n", "u4", 4)])
+ITEM = np.dtype([("at", "u8", 4), ("first", "u4"), ("count", "u4"), ("tensor", "u4"), ("bucket", "u4"), ("flags", "u4"), ("items", "u4"), ("chunks", "u4", 2)])
+fake.fake_watch(b"k_lambI", 1, STATE.itemsize)
+split = 0
+for sizes, cap in [([n] + [4 << 20] * 8, 1 << 40) for n in (22_050_000, 22_100_000, 22_150_000, 30_000_000)] + [
+        ([96 * 1024 * k + r for k in (1, 2, 11, 40) for r in (-1, 0, 1, 60_000)], 3 * 96 * 1024), ([1 << 20] * 20, 300_000)]:
+    lay = W.layout_flat_split(sizes, cap)
+    plan = B.Plan.from_layout(lay, B.BCA_GRAD_F32)
+    base = [[(k + 1 << 44) + (t << 32) for t in range(len(sizes))] for k in range(4)]
+    plan.bind(*base)
+    chunks = [plan.chunk_info(i, B.BCA_TABLE_LAMB) for i in range(plan.n_chunks(B.BCA_TABLE_LAMB))]
+    for clip in (False, True):
+        kernels()
+        plan.bucket_clip_lamb(64, B.AdamHyper(), 1, 0, 64, 64, 64, 64) if clip else plan.lamb_step(B.AdamHyper(), 1, 64)
+        st = np.frombuffer(ctypes.string_at(fake.fake_launch_arg(0), STATE.itemsize), STATE)[0]
+        items = np.frombuffer(ctypes.string_at(int(st["items"]), int(st["n"][0]) * ITEM.itemsize), ITEM)
+        held, listed = np.full(len(chunks), -1), np.full(len(chunks), -1)
+        for it in items:
+            stride = 8 if it["flags"] & SPREAD else 1
+            split += stride == 8
+            for j in range(it["count"]):
+                i = int(it["first"]) + j * stride
+                assert held[i] == -1 and chunks[i][0] == it["tensor"] and chunks[i][3] == it["bucket"]
+                held[i] = (it["flags"] & (HELD if clip else HELD | ALONE)) != 0
+            t, begin = chunks[it["first"]][:2]
+            assert [int(x) for x in it["at"]] == [base[k][t] + 4 * begin for k in range(4)]
+        for kind, first, count, tensor, h in plan.lamb_items(clip):
+            if kind == 1:
+                assert (listed[first:first + count] == -1).all()
+                listed[first:first + count] = h
+        assert (held >= 0).all() and (held == listed).all(), (sizes[0], clip, int((held != listed).sum()))
+    plan.close()
+assert split > 1000
+""")
+
+
 def test_lamb_in_one_pass_costs_a_plan_one_allocation(device):
     """Every plan of some size has its tables, also where only Adam is called: they are one block, given back with the plan."""
     fake_device.run(device, """

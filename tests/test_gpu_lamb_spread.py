@@ -35,3 +35,21 @@ def test_runs_that_end_with_the_tensor_and_with_the_bucket(dtype, gdt, clip, fla
         one.same(two)
     one.plan.close()
     two.plan.close()
+
+
+@pytest.mark.parametrize("clip,flags", [(False, 0), (True, 0), (True, B.BCA_WRITE_BACK_GRADS)])
+@pytest.mark.parametrize("large", [22_050_000, 30_000_001])
+def test_a_run_in_which_the_held_end_of_a_tensor_begins(clip, flags, large):
+    """A tensor of which the last 768 items are held, the first of them amid a run; its other items keep their moments cached, full ones and
+    those at the ends of its buckets."""
+    lay = W.layout_flat_split([large] + [4 << 20] * 8, 1 << 30 if large & 1 else 3 * RUN + 5)
+    one, two = Run(lay, *TYPES[0], 5), Run(lay, *TYPES[0], 5, **_two_sweeps(clip))
+    held = [h for kind, _, _, t, h in one.plan.lamb_items(clip) if kind == 1 and t == 0]
+    assert sum(held) == 768 and len(held) > 2 * 768 and two.plan.n_lamb_items(clip) == 0
+    for step in (3, 4):
+        one.go(clip, step, flags)
+        two.go(clip, step, flags)
+        torch.cuda.synchronize()
+        one.same(two)
+    one.plan.close()
+    two.plan.close()
