@@ -127,7 +127,8 @@ typedef struct bca_tuning {
   uint32_t adam_lds_reserve; /* adam_step (and any other Adam sweep that streams the gradients): bytes of LDS
                             each workgroup reserves without using them, which caps the workgroups resident
                             per compute unit (160 KiB each) -- the sweep streams fastest with few
-                            wavefronts in flight.  0: default (36 KiB); 1: none; at most 65536       */
+                            wavefronts in flight.  0: default (36 KiB; none where the chunks are one and an
+                            eighth to two rounds of the four workgroups that leaves a compute unit); 1: none; at most 65536 */
   uint32_t spin_limit;   /* pipelined calls (bucket_clip_adam, bucket_clip_lamb): polls of a bucket's
                             ready word after which a waiting work item gives up, is carried out at the end of the
                             call and BCA_STATUS_TIMEOUT is reported; 0: default (2^18, about a second).  LAMB in one

@@ -255,6 +255,13 @@ void mark_early(bca_plan* p, int n_cus) {
     if (p->work[w] >> 30 == kItemAdam) p->work[w] |= kItemEarly;
 }
 
+// Whether an Adam sweep over the whole plan, one workgroup a chunk, is done in two rounds of kAdamResidentPerCu workgroups a compute unit the
+// second of which is more than an eighth full: then all workgroups start at once instead (kDefaultAdamLdsReserve).
+bool in_two_rounds(const bca_plan* p, int n_cus) {
+  const uint64_t n = p->apply_tab.chunks.size(), slots = (uint64_t)std::max(n_cus, 1) * kAdamResidentPerCu;
+  return p->grid_apply == 0 && p->apply_tab.chunk_elems == kDefaultChunkApply && n > slots + slots / 8 && n <= 2 * slots;
+}
+
 // Items and work lists of LAMB in one pass (see k_lamb), for tables cut at kDefaultChunkApply.  `slots`: workgroups of
 // that kernel that are resident on the GPU at a time.
 //   An item is up to kLambItemChunks full chunks, or one short chunk; where a run is long enough its chunks are dealt to kLambStride items
@@ -730,6 +737,7 @@ static int plan_create(bca_plan** out, int device, uint32_t n_tensors, const uin
     const std::vector<uint32_t> a2l = apply_to_lamb_map(p);
     mark_early(p, prop.multiProcessorCount);
     lamb_items(prop.multiProcessorCount, a2l);
+    if (!(tuning && tuning->adam_lds_reserve) && in_two_rounds(p, prop.multiProcessorCount)) p->adam_lds_reserve = 0;
     // One block for LAMB in one pass, so that plans that never use it are set up about as fast as without (six allocations
     // and as many copies: 160 tensors of 64 K 620 us instead of 543).  Ready words and arrival counters lie on pages of their own:
     // polled and counted on one page they slow each other down (6.9 M elements 45.4 -> 51.3 us a step).

@@ -152,6 +152,30 @@ assert split > 1000
 """)
 
 
+def test_adam_sweeps_of_up_to_two_rounds_of_chunks_start_at_once(device):
+    """LDS that the sweeps of adam_step and of the whole-gradient step reserve: 36 KiB, four workgroups a compute unit, but none where the chunks
+    are one and an eighth to two rounds of those; what the caller asks for, always."""
+    fake_device.run(device, """
+def reserved(chunks, **tuning):
+    with B.Plan.from_layout(W.layout_flat_split([1024 * chunks - 5], 1 << 40), B.BCA_GRAD_F32, **tuning) as plan:
+        plan.bind(*[[k << 40] for k in (1, 2, 3, 4)])
+        kernels()
+        plan.adam_step(B.AdamHyper(), 1)
+        plan.bucket_clip_adam(64, B.AdamHyper(), 1, B.BCA_CLIP_WHOLE_GRADIENT, 64, 64, 64)
+        lds = [fake.fake_launch_lds(i) for i in range(fake.fake_num_launches()) if b"k_adam" in fake.fake_launch_name(i)]
+        assert len(lds) == 2 and lds[0] == lds[1], lds
+        return lds[0]
+for cus in (256, 64):
+    fake.fake_set_cus(cus)
+    for sixteenths, want in ((1, 36), (16, 36), (18, 36), (19, 0), (25, 0), (32, 0), (33, 36), (200, 36)):
+        assert reserved(cus * sixteenths // 4) == want << 10, (cus, sixteenths)
+    assert reserved(cus * 4 + cus // 2 + 1) == 0 and reserved(cus * 8 + 1) == 36 << 10
+    for asked, got in ((1, 0), (20 << 10, 20 << 10), (36 << 10, 36 << 10)):
+        assert reserved(cus * 6, adam_lds_reserve=asked) == got
+    assert reserved(cus * 6, grid_apply=cus) == 36 << 10 and reserved(cus * 3, chunk_apply=2048) == 36 << 10
+""")
+
+
 def test_lamb_in_one_pass_costs_a_plan_one_allocation(device):
     """Every plan of some size has its tables, also where only Adam is called: they are one block, given back with the plan."""
     fake_device.run(device, """
