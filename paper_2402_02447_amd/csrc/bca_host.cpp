@@ -1256,10 +1256,9 @@ int bucket_clip_adam(bca_plan* p, const float* thresholds, const bca_adam* hp, u
       if (e != hipSuccess) return fail_hip(e, "launching the finalize kernel");
       if (ev) (void)hipEventRecord(*ev++, s);
     }
-    Launch L = make_launch(p, p->grid_apply, na, keep);
-    if (n_groups == 1) L.order = AdamOrder::kBackwards;
     e = launch_adam(p->grad_dtype, TA.d_chunks, ca0, na, cf, (flags & BCA_WRITE_BACK_GRADS) != 0,
-                    (flags & BCA_SKIP_STEP_ON_NONFINITE) ? st : nullptr, k, L, s);
+                    (flags & BCA_SKIP_STEP_ON_NONFINITE) ? st : nullptr,
+                    k, make_launch(p, p->grid_apply, na, keep), s);
     if (e != hipSuccess) return fail_hip(e, "launching the Adam kernel");
     if (ev) (void)hipEventRecord(*ev++, s);
     first = false;

@@ -113,11 +113,7 @@ enum class AdamOrder : uint32_t {
   // 931 / 874, 250 M 1 202 / 1 132 and 1 196 / 1 130, 335 M 1 559 / 1 511 and 1 541 / 1 510; 160 M with packed gradients 744 / 720; fp16 135 M
   // 557 / 566, 200 M 847 / 838; packed bf16 335 M 1 445 / 1 411.  Runs of 128, 512 and 800 chunks instead of 256: 335 M 1 537, 1 543, 1 548
   // (256: 1 520); of 16 to 64, in a probe, 15 % slower than the table's order.
-  kXcdRuns,
-  // Behind squared norms of everything: what was read last is the likeliest to be cached.  Whole-gradient step of BERT-Base, three workgroups a compute unit, table's order /
-  // backwards / runs of 256 / those backwards, us: 555 / 553 / 563 / 564, another card 570 / 558 / - / 561.  With four workgroups a compute unit,
-  // against the table's order with three: 11 M elements 65.7 -> 63.9, 34 M 182 -> 179, BERT-Base 562 -> 544, BERT-Large 1 798 -> 1 753.
-  kBackwards
+  kXcdRuns
 };
 constexpr uint32_t kXcdRun = 256, kXcdRunsFrom = 144u << 10;
 constexpr uint32_t kDefaultSpinLimit = 1u << 18;  // polls of a ready word before a waiting item gives up (about a second)

@@ -748,7 +748,6 @@ __device__ __forceinline__ void adam_chunk_early(const Entry& en, const AdamK& k
 // The chunk that comes i-th (AdamOrder).
 __device__ __forceinline__ uint32_t adam_chunk_of(uint32_t i, uint32_t n, AdamOrder order) {
   if (order == AdamOrder::kTable) return i;
-  if (order == AdamOrder::kBackwards) return n - 1u - i;
   const uint32_t at = i % (8u * kXcdRun), base = i - at;
   if (n - base >= 8u * kXcdRun) return base + (at % 8u) * kXcdRun + at / 8u;
   return i;

@@ -1,5 +1,5 @@
-"""The Adam sweep's orders of the chunks: in the table's order and in runs by XCD (adam_step, by the size of the plan), and backwards behind
-the squared norms of everything; each against a plan whose sweep is a persistent grid, which takes the table's order, bit for bit."""
+"""The Adam sweep's orders of the chunks: the table's, and runs by XCD (adam_step, by the size of the plan); each against a plan whose sweep
+is a persistent grid, which takes the table's order, bit for bit."""
 import pytest
 import torch
 
