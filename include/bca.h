@@ -118,7 +118,8 @@ typedef struct bca_tuning {
                             multiple of 1024; 0: 16 Ki, what a workgroup fetches in one go                 */
   uint32_t chunk_apply;  /* largest chunk of the scale / Adam passes, elements, multiple of 1024 */
   uint32_t grid_norm;    /* workgroups of the squared-norm kernel (0: one per chunk)            */
-  uint32_t grid_apply;   /* workgroups of the scale / Adam kernels (0: one per chunk)           */
+  uint32_t grid_apply;   /* workgroups of the scale / Adam kernels (0: one per chunk); the chunks of a grid that
+                            is given are taken in the table's order                              */
   uint32_t unroll_apply; /* 128-bit accesses in flight per lane and array in scale / Adam: 1, 2, 4 */
   uint32_t flags;        /* BCA_TUNE_*                                                          */
   uint64_t group_bytes;  /* bucket_clip_adam walks the buckets in groups of at most this many

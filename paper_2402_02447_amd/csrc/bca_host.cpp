@@ -1180,7 +1180,7 @@ int adam_step(bca_plan* p, const bca_adam* hp, uint64_t step, void* stream) {
   const Table& T = p->apply_tab;
   const uint32_t n = (uint32_t)T.chunks.size();
   Launch L = make_launch(p, p->grid_apply, n, false);
-  if (T.chunk_elems == kDefaultChunkApply && n >= kXcdRunsFrom) L.order = AdamOrder::kXcdRuns;
+  if (T.chunk_elems == kDefaultChunkApply && n >= kXcdRunsFrom && p->grid_apply == 0) L.order = AdamOrder::kXcdRuns;
   hipError_t e = launch_adam(p->grad_dtype, T.d_chunks, 0, n, nullptr, false, nullptr, k, L, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(e, "launching the Adam kernel");
   return BCA_OK;

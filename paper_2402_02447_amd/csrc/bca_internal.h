@@ -104,15 +104,17 @@ constexpr uint64_t kLambGroupElems = 32ull << 20;
 // 2 300 11.4 / 11.8 and 11.1 / 11.5; whole-gradient step 1 300 15.5 / 14.7 and 14.5 / 13.7, 1 600 16.4 / 15.9 and 15.8 / 15.2.
 // The fused single-launch step does not gain from it (its items wait on each other) and does not use it.
 constexpr uint32_t kDefaultAdamLdsReserve = 36u << 10, kAdamResidentPerCu = 4;
-// The order in which an Adam sweep's workgroups take the chunks.  Workgroups, one per chunk, go round the eight XCDs.
+// The order in which an Adam sweep's workgroups take the chunks.
 enum class AdamOrder : uint32_t {
   kTable,
-  // Every XCD sweeps kXcdRun consecutive chunks (1 MiB of each array) of a run of eight times as many; what is left over in the table's
-  // order.  Pays in plans of kXcdRunsFrom chunks and more.  adam_step, us, table's order / runs, two cards, fp32: 20 M elements 84 / 89 and 84 / 89,
-  // 57 M 258 / 263 and 257 / 262, 109 M 478 / 492 and 477 / 491, 135 M 587 / 596 and 588 / 600, 160 M 738 / 728 and 744 / 728, 200 M 944 / 875 and
-  // 931 / 874, 250 M 1 202 / 1 132 and 1 196 / 1 130, 335 M 1 559 / 1 511 and 1 541 / 1 510; 160 M with packed gradients 744 / 720; fp16 135 M
-  // 557 / 566, 200 M 847 / 838; packed bf16 335 M 1 445 / 1 411.  Runs of 128, 512 and 800 chunks instead of 256: 335 M 1 537, 1 543, 1 548
-  // (256: 1 520); of 16 to 64, in a probe, 15 % slower than the table's order.
+  // Workgroups, one per chunk, go round the eight XCDs: every XCD sweeps kXcdRun consecutive chunks (1 MiB of each array) of a run of eight
+  // times as many; what is left over in the table's order.  For plans of kXcdRunsFrom chunks and more.  Where it pays depends on how the arrays lie:
+  // adam_step, us, table's order / runs, four workgroups a compute unit, several cards.  Arrays in arenas, tensor behind tensor, fp32: 20 M elements 84 / 89, 57 M
+  // 258 / 263, 109 M 478 / 492, 135 M 587 / 596, 160 M 738 / 728 and 762 / 717, 184 M 877 / 839, 234 M 1 093 / 1 059, 285 M 1 310 / 1 281, 335 M
+  // 1 559 / 1 511 and 1 565 / 1 510; bf16 184 M 788 / 778, 234 M 974 / 999, 335 M 1 442 / 1 440; all one element off 16 bytes, 335 M 1 697 / 1 619, bf16 1 571 / 1 520.
+  // Tensors in allocations of their own, as torch's allocator places them: fp32 184 M 819 / 824, 234 M 1 045 / 1 060, 285 M 1 271 / 1 296, 335 M 1 452 / 1 518 to
+  // 1 518 / 1 518; bf16 741 / 776, 951 / 993, 1 169 / 1 203, 1 371 / 1 416 (packed gradients the same).  Runs of 128, 512 and 800 chunks instead of 256: 335 M
+  // 1 537, 1 543, 1 548 (256: 1 520); of 16 to 64, in a probe, 15 % slower than the table's order.
   kXcdRuns
 };
 constexpr uint32_t kXcdRun = 256, kXcdRunsFrom = 144u << 10;

@@ -176,6 +176,29 @@ for cus in (256, 64):
 """)
 
 
+def test_runs_by_xcd_are_for_one_workgroup_a_chunk(device):
+    """The order that adam_step's sweep is given: runs in plans of 144 Ki chunks and more in the library's own cut; in smaller ones, on a grid
+    that the caller gives, and behind whole-gradient norms the table's."""
+    fake_device.run(device, """
+fake.fake_watch(b"k_adam", 6, 4)
+def order(chunks, whole=False, **tuning):
+    with B.Plan.from_layout(W.layout_flat_split([1024 * chunks - 5], 1 << 40), B.BCA_GRAD_F32, **tuning) as plan:
+        plan.bind(*[[k << 40] for k in (1, 2, 3, 4)])
+        kernels()
+        if whole:
+            plan.bucket_clip_adam(64, B.AdamHyper(), 1, B.BCA_CLIP_WHOLE_GRADIENT, 64, 64, 64)
+        else:
+            plan.adam_step(B.AdamHyper(), 1)
+        i = fake.fake_num_launches() - 1
+        assert b"k_adam" in fake.fake_launch_name(i)
+        return int.from_bytes(ctypes.string_at(fake.fake_launch_arg(i), 4), "little")
+RUNS = 144 << 10
+assert [order(n) for n in (1, RUNS - 1, RUNS, RUNS + 5)] == [0, 0, 1, 1]
+assert order(RUNS, grid_apply=512) == order(RUNS, grid_apply=500) == order(RUNS, chunk_apply=2048) == order(2 * RUNS, chunk_apply=2048) == 0
+assert order(RUNS, whole=True) == order(1, whole=True) == 0
+""")
+
+
 def test_lamb_in_one_pass_costs_a_plan_one_allocation(device):
     """Every plan of some size has its tables, also where only Adam is called: they are one block, given back with the plan."""
     fake_device.run(device, """
