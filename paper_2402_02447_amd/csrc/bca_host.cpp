@@ -1240,7 +1240,7 @@ int bucket_clip_adam(bca_plan* p, const float* thresholds, const bca_adam* hp, u
     const uint32_t cn0 = TN.bucket_off[b0], nn = TN.bucket_off[b1] - cn0;
     const uint32_t ca0 = TA.bucket_off[b0], na = TA.bucket_off[b1] - ca0;
     hipError_t e = hipSuccess;
-    if (skip && !multi && nn <= kOneLaunchNormChunks) {
+    if (skip && !multi && nn <= kOneLaunchNormChunks && p->n_buckets <= kOneLaunchNormBuckets) {
       e = launch_norms(p->grad_dtype, step_state(p), nn, p->n_buckets, p->n_filled, whole, thresholds, nm, cf, p->d_bucket_sq, st, s);
       if (e != hipSuccess) return fail_hip(e, "launching the norms kernel");
     } else {

@@ -121,10 +121,15 @@ constexpr uint32_t kXcdRun = 256, kXcdRunsFrom = 144u << 10;
 constexpr uint32_t kDefaultSpinLimit = 1u << 18;  // polls of a ready word before a waiting item gives up (about a second)
 
 // Squared-norm chunks (of 16 Ki elements) up to which a call that needs every norm first has them from one launch (k_norms).  It saves two
-// launches, which small calls wait for on the host; larger ones wait for the chain of exchanges inside instead.  Whole-gradient step, us, three
-// launches and the sweep / one and the sweep: 6 K to 130 K elements 15.0 / 9.5, 0.5 M 15.3 / 10.1, 0.4 M in one bucket 15.3 / 10.5, 1 M in one
-// 15.1 / 12.5, in four 15.0 / 12.8, 1.6 M (100 chunks) 15.4 / 15.4, 2 M 17.2 / 17.6, 2.4 M 19.7 / 20.3, BERT-Base 549 / 560.
+// launches (the skipped step without whole-gradient clipping one), which small calls wait for on the host; larger ones wait for the chain of exchanges
+// inside instead.  Whole-gradient step, us, three launches and the sweep / one and the sweep: 2 K to 130 K elements 13.9 / 9.7, 0.45 M in one bucket 13.7 / 9.5,
+// in 20 13.8 / 11.3, 0.7 M 13.8 / 12.0, 1 M in one (62 chunks) 15.1 / 12.5, 1.6 M (100 chunks) 15.4 / 15.4, 2 M 17.2 / 17.6, 2.4 M 19.7 / 20.3, BERT-Base 549 / 560.
+// The skipped step, two hosts: 2 K to 130 K 11.2 / 9.1 and 11.3 / 9.2, 0.45 M 11.1 / 10.5 and 11.2 / 10.1, 0.7 M 11.2 / 11.6 and 11.6 / 11.2.
 constexpr uint32_t kOneLaunchNormChunks = 64;
+// ... and buckets, all but those many of them without elements: one workgroup goes over them all.  50 chunks and k buckets without elements, two hosts,
+// whole-gradient step: k = 0 11.8 / 10.0 and 14.1 / 11.1, 500 11.7 / 10.6, 1 000 11.9 / 12.4 and 13.9 / 12.4, 5 000 16.7 / 20.9, 100 000 142 / 235; the skipped
+// step 1 000 9.1 / 11.1 and 11.3 / 11.6, 5 000 11.5 / 18.2, 100 000 34 / 213.
+constexpr uint32_t kOneLaunchNormBuckets = 1024;
 // How a streaming kernel is launched.
 struct Launch {
   uint32_t grid;    // workgroups

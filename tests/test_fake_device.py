@@ -199,6 +199,28 @@ assert order(RUNS, whole=True) == order(1, whole=True) == 0
 """)
 
 
+def test_norms_of_a_small_plan_in_one_launch(device):
+    """Up to 64 squared-norm chunks and 1 024 buckets, all but a few of them without elements."""
+    fake_device.run(device, """
+K = 16384
+def forms(lay):
+    out = []
+    with B.Plan.from_layout(lay, B.BCA_GRAD_F32) as plan:
+        plan.bind(*[[k << 40] * lay.n_tensors for k in (1, 2, 3, 4)])
+        for flags in (B.BCA_CLIP_WHOLE_GRADIENT, B.BCA_CLIP_WHOLE_GRADIENT | B.BCA_SKIP_STEP_ON_NONFINITE, B.BCA_SKIP_STEP_ON_NONFINITE):
+            kernels()
+            plan.bucket_clip_adam(64, B.AdamHyper(), 1, flags, 64, 64, 64)
+            names = [k for k, _ in kernels()]
+            assert names in (["k_norms", "k_adam"], ["k_sqnorm", "k_finalize"] + ["k_whole_coef"] * (flags != B.BCA_SKIP_STEP_ON_NONFINITE) + ["k_adam"]), names
+            out.append(int(names[0] == "k_norms"))
+    return out
+flat, each = W.layout_flat_split, W.layout_one_tensor_per_bucket
+for lay, want in ((flat([5], 10), 1), (flat([64 * K], 1 << 40), 1), (flat([64 * K + 1], 1 << 40), 0), (each([9000] * 32 + [0] * 992), 1),
+                  (each([9000] * 32 + [0] * 993), 0), (each([9000] * 50 + [0] * 20_000), 0)):
+    assert forms(lay) == [want] * 3, (lay.n_buckets, want, forms(lay))
+""")
+
+
 def test_lamb_in_one_pass_costs_a_plan_one_allocation(device):
     """Every plan of some size has its tables, also where only Adam is called: they are one block, given back with the plan."""
     fake_device.run(device, """

@@ -53,9 +53,10 @@ def test_same_bits_as_separate_launches(gdt, dtype, flags, sizes, cap):
 
 @pytest.mark.parametrize("flags", [WHOLE, SKIP])
 def test_buckets_and_plans_without_elements(flags):
-    lay = W.layout_one_tensor_per_bucket([0, 5, 0, 40_000, 0])
-    for a, b in zip(_run(lay, B.BCA_GRAD_F32, torch.float32, flags, False), _run(lay, B.BCA_GRAD_F32, torch.float32, flags, False, tune_flags=B.BCA_TUNE_MULTI_LAUNCH)):
-        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    for sizes in ([0, 5, 0, 40_000, 0], [0] * 511 + [9_000, 40_000] + [0] * 511, [0] * 511 + [9_000, 40_000] + [0] * 512):
+        lay = W.layout_one_tensor_per_bucket(sizes)
+        for a, b in zip(_run(lay, B.BCA_GRAD_F32, torch.float32, flags, False), _run(lay, B.BCA_GRAD_F32, torch.float32, flags, False, tune_flags=B.BCA_TUNE_MULTI_LAUNCH)):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     lay = W.layout_one_tensor_per_bucket([0, 0])
     norms, status = _run(lay, B.BCA_GRAD_F32, torch.float32, flags, False)[0:3:2]
     assert not norms.any() and int(status.item()) == 0
