@@ -41,7 +41,7 @@ def _run(lay, gdt, dtype, flags, spoil, **tuning):
     return seen + g + p + m + v
 
 
-@pytest.mark.parametrize("gdt,dtype", [(B.BCA_GRAD_F32, torch.float32), (B.BCA_GRAD_BF16, torch.bfloat16)])
+@pytest.mark.parametrize("gdt,dtype", [(B.BCA_GRAD_F32, torch.float32), (B.BCA_GRAD_F16, torch.float16), (B.BCA_GRAD_BF16, torch.bfloat16)])
 @pytest.mark.parametrize("flags", [WHOLE, SKIP, WHOLE | SKIP, WHOLE | WB])
 @pytest.mark.parametrize("sizes,cap", [([1], 10), ([0, 3], 10), ([5, 0, K, K + 1], 3000), ([64 * K], 1 << 30), ([63 * K, 7], 2 * K + 5), ([64 * K, 1], 1 << 30), ([300_000, 1], 1 << 30)])
 def test_same_bits_as_separate_launches(gdt, dtype, flags, sizes, cap):
