@@ -219,7 +219,7 @@ int bca_plan_work_item(const bca_plan* plan, uint32_t i, uint32_t* kind, uint32_
  * where the bound tensors lie.  Item i is kind 0 or 2 as above, or kind 1 = LAMB on `count` consecutive chunks of
  * BCA_TABLE_LAMB from `first` on, all of `tensor`; *held: 1 if they wait on the chip for that tensor's ratio, 0 if the
  * tensor is swept twice.  Eight items of twelve chunks side by side in one tensor and bucket are carried out
- * together: each workgroup takes every eighth of their 96 chunks.  Any out pointer may be NULL.  BCA_ERR_RANGE for i out of range. */
+ * together, all held or all swept twice: each workgroup takes every eighth of their 96 chunks.  Any out pointer may be NULL.  BCA_ERR_RANGE for i out of range. */
 uint32_t bca_plan_num_lamb_items(const bca_plan* plan, int clip);
 int bca_plan_lamb_item(const bca_plan* plan, int clip, uint32_t i, uint32_t* kind, uint32_t* first, uint32_t* count,
                        uint32_t* tensor, uint32_t* held);
@@ -248,8 +248,10 @@ int bucket_clip_apply(bca_plan* plan, uint32_t b0, uint32_t b1, const float* thr
 /* bucket_clip_norms followed by bucket_clip_apply on buckets [b0, b1) in one call, for the
  * paper's use of the method: a bucket is clipped as soon as backward has produced it,
  * before its all-reduce (Sec. 4.2, Alg. 1).  Same norms, coefficients and scaled
- * gradients, bit for bit.  Two launches: the squared-norm partials, then a kernel whose
- * workgroups each derive their bucket's coefficient from the partials and scale a chunk;
+ * gradients, bit for bit.  One launch for a range of one bucket of one squared-norm chunk (16 384
+ * elements unless tuned); else two: the squared-norm partials, then a kernel whose
+ * workgroups each derive their bucket's coefficient from the partials and scale a chunk
+ * (where a bucket has more than 1 024 chunks three: partials, coefficients, scaling);
  * no workgroup waits for another.  norms / coefs (DEVICE [B], entries b0..b1-1
  * written) and status (DEVICE int32, written: BCA_STATUS_NONFINITE, _BAD_THRESHOLD as in
  * bucket_clip_apply) may each be NULL. */
@@ -268,7 +270,7 @@ int bucket_clip(bca_plan* plan, uint32_t b0, uint32_t b1, const float* threshold
  * GPU share the array: calls that overlap in time on one GPU (different streams) race; calls in
  * stream order are fine, each call writes what it later reads and needs nothing cleared.
  * Results equal bucket_clip's on a one-tensor, one-bucket plan with chunk_norm = 16384, bit for
- * bit.  Only enqueues (two kernels; three beyond 16 Mi elements). */
+ * bit.  Only enqueues (one kernel for 1 to 16 384 elements, else two; three beyond 16 Mi elements). */
 int bucket_clip_flat(void* g /*DEVICE*/, uint64_t n, int grad_dtype, const float* threshold /*DEVICE*/,
                      float* norm /*DEVICE or NULL*/, float* coef /*DEVICE or NULL*/,
                      int32_t* status /*DEVICE or NULL*/, void* stream);

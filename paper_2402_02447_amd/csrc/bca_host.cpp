@@ -264,10 +264,9 @@ bool in_two_rounds(const bca_plan* p, int n_cus) {
 
 // Items and work lists of LAMB in one pass (see k_lamb), for tables cut at kDefaultChunkApply.  `slots`: workgroups of
 // that kernel that are resident on the GPU at a time.
-//   An item is up to kLambItemChunks full chunks, or one short chunk; where a run is long enough its chunks are dealt to kLambStride items
-// at a time (kLambSpread).  Items are made in the order of the apply table (bucket
-// by bucket, as the segments lie), which is also the order in which they are worked on, so that a tensor's items
-// follow one another.
+//   An item is up to kLambItemChunks full chunks, or one short chunk; where a run is long enough its chunks are dealt to
+// kLambStride items at a time (kLambSpread).  Items are made in the order of the apply table (bucket by bucket, as the
+// segments lie), which is also the order in which they are worked on, so that a tensor's items follow one another.
 void build_lamb_items(bca_plan* p, uint32_t slots, const std::vector<uint32_t>& apply_to_lamb) {
   const Table& A = p->apply_tab;
   const uint64_t most = (uint64_t)slots * kLambHeldNum / kLambHeldDen;  // items of a tensor, for it to be held

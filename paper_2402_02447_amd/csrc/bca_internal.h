@@ -203,8 +203,8 @@ struct StepState {
   uint32_t spin_limit;              // polls of a ready word before a waiting item gives up
 };
 
-// LAMB in one pass (k_lamb).  An item is up to kLambItemChunks consecutive chunks of the tensor-major table, all of one
-// tensor and one bucket.  Addresses and the kLambRegular bit are filled in by bca_plan_bind.
+// LAMB in one pass (k_lamb).  An item is up to kLambItemChunks chunks of the tensor-major table, all of one
+// tensor and one bucket: consecutive ones, or (kLambSpread) ones kLambStride apart.  Addresses and the kLambRegular bit are filled in by bca_plan_bind.
 constexpr uint32_t kLambItemChunks = 12;
 struct alignas(16) LambItem {
   uint64_t g, p, m, v;  // device byte addresses of the item's first element
@@ -224,7 +224,7 @@ constexpr uint32_t kLambHeldAlone = 16u;  // as kLambHeld, in lamb_step only
 // consecutive chunks read 4 to 16 KiB in a piece, from as many places as there are workgroups, and the memory system is slow at that.  Probe
 // of the held sweep (334 M elements, 4 reads and 3 writes, twelve chunks an item, four fetched at a time), ms by stride: 1 1.73, 2 1.67, 4 1.61,
 // 6 1.69, 8 1.55, 12 1.70, 16 1.58, 24 1.64, 32 1.69, 40 1.75, 64 1.71, 1024 2.0.  In runs of kLambStride * kLambItemChunks full
-// chunks; what is left of a tensor or bucket goes in items of consecutive chunks.
+// chunks; what is left of a tensor or bucket goes in items of consecutive chunks, and so does a run of which a part is held and a part is not.
 constexpr uint32_t kLambSpread = 32u, kLambStride = 8, kLambPlaceShift = 8;  // from that bit on: which of its run's items it is
 // Workgroups of k_lamb that are resident at a time on a compute unit: what __launch_bounds__ asks for (128 VGPRs), and four
 // times the 33 KiB of LDS fit in 160 KiB.

@@ -331,8 +331,9 @@ __device__ __forceinline__ uint32_t vector_head(uint32_t len, uint64_t p, uint64
 
 // Sums by butterfly, distances 32, 16, 8, 4, 2, 1.  Lanes meet by permlane swaps (32, 16) and by DPP rotations inside rows of 16:
 // with the value 8 lanes on already added, rotating by 4 brings the one 4 lanes across, and so on down.  Every one of these launches
-// ends in a chain of such sums, and a move is a vector instruction where a shuffle is a trip through LDS: three buckets of 17 K
-// elements 6.01 -> 5.88 us a fused step, LAMB on 335 M elements (two sums a chunk) 1 862 -> 1 850.
+// ends in a chain of such sums, and a move is a vector instruction where a shuffle is a trip through LDS: fused steps of 17 K and 0.5 M
+// elements, one plan called again and again, 7.2 -> 6.8 and 8.6 -> 8.2 us (five turns; where inputs change from pass to pass no difference:
+// 5.95 -> 5.94), LAMB on 335 M elements (two sums a chunk) 1 862 -> 1 850.
 __device__ __forceinline__ double join(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); }
 // Rows 2, 3 of a and rows 0, 1 of b change places, then the two are added: lanes 0 .. 31 hold the sums of a's lanes 32 apart, lanes
 // 32 .. 63 those of b's.  add16: the same with the odd rows of a, the even rows of b and lanes 16 apart.
@@ -1445,7 +1446,7 @@ __global__ __launch_bounds__(kBlock, EARLY ? 8 : 1) void k_step(StepState st, co
 // part of u in LDS 1.67; in tensors of 1 M: 1.58 and 1.64; two sweeps in runs 2.05).
 // An item's chunks lie kLambStride apart where the tensor is long enough, and four of them are fetched at a time: BERT-Large lamb_step
 // 1 748 us with items of consecutive chunks, two at a time; consecutive, four at a time 1 731; kLambStride apart, two 1 685, four 1 675;
-// BERT-Base, fp16, behind clipping 534, 533, 524 and 520.
+// BERT-Base, fp16, behind clipping (tensors in allocations of their own, as everywhere here) 534, 533, 524 and 520.
 //   BERT-Large, fp32: lamb_step 2085 us in two sweeps in runs, 1675 like this; BERT-Base, fp16, behind clipping 695 and 520.
 //
 // Sums are taken chunk by chunk and added in k_lamb_trust's order: results are those of the two sweeps bit for bit (where
@@ -1568,7 +1569,9 @@ __device__ __forceinline__ void lamb_item(const StepState& st, const LambState& 
     const bool keep = (flags & kLambKeep) != 0u && !held, wb = WB && coef != 1.f;
     // Whether the moments stay cached is decided out here, a sweep for each: with the two kinds of store in the arms of one branch the compiler
     // makes one store of them, without the streaming hint (BERT-Large lamb_step 1 848 us like that, 1 748 so; BERT-Base fp16 behind
-    // the clip 568 and 534).
+    // the clip 568 and 534).  A plan of 8 M to 40 M elements that is stepped again with nothing in between found its moments cached like that, and does not
+    // now: with all that has changed since, lamb_step fp32 11 M 61 -> 64 (in three tensors 62), 20 M 103 -> 108, 34 M 166 -> 180; with 1 GiB of other memory
+    // swept in between, as a training step does, 73 -> 70, 122 -> 113, 198 -> 184.
     const auto sweep = [&](auto full, auto kept) {
     constexpr bool FULL = decltype(full)::value, KEEP = decltype(kept)::value;
 #pragma unroll
