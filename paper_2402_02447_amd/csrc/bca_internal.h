@@ -97,7 +97,8 @@ constexpr uint64_t kLambGroupElems = 32ull << 20;
 // The stand-alone Adam sweep streams faster with four workgroups (sixteen wavefronts) a compute unit than with all eight: fewer requests
 // in flight suit the four-read / three-write mix.  36 KiB of the 160 KiB LDS reserved per workgroup give that.  us with eight / six / five /
 // four / three / two workgroups, two cards: BERT-Base 537 / 537 / 521 / 501 / 508 / 534 (without reserve 8; 20, 27, 32, 48, 56 KiB),
-// whole-gradient step 606 / 606 / 577 / 552 / 561 / 594; BERT-Large with three 1 618 and 1 669, with four 1 538 and 1 583.
+// whole-gradient step 606 / 606 / 577 / 552 / 561 / 594; BERT-Large in the table's order, three / four, arrays in arenas 1 591 / 1 565, tensors in allocations of
+// their own 1 505 / 1 473, bf16 1 571 / 1 442 and 1 477 / 1 371.
 // Not reserved where the chunks are one and an eighth to two rounds of those four: with eight a compute unit all of them start at once, instead of a round
 // and a part of one.  us, reserved / not, 256 compute units, fp32 and bf16: 1 050 chunks 5.8 / 6.4 and 5.3 / 5.7, 1 100 5.6 / 6.1 and 5.5 / 6.1,
 // 1 300 7.5 / 7.3 and 7.0 / 6.9, 1 500 8.6 / 7.9 and 8.0 / 7.7, 1 600 8.8 / 8.2 and 8.4 / 8.2, 1 700 8.8 / 8.5 and 9.1 / 8.8, 2 048 9.6 / 9.4 and 9.6 / 9.3,
